@@ -1,7 +1,8 @@
 // Static triangle enumeration in G_prec (Section 5 and the proof of Theorem 1): for every DAG
 // edge (u, v) and every w in N+(u), {u, v, w} is a triangle iff w is also in N+(v); u is then the
 // source vertex and u < v < w in the ordering.  The paper tests {v, w} with a hash lookup; here
-// one wavefront owns one source vertex u and stages N+(u) (at most degeneracy entries) in LDS.
+// one wavefront owns a source vertex u, or a pack of consecutive ones with short runs, and stages
+// N+(u) (at most degeneracy entries) in LDS.
 // For each v in N+(u) the two sorted runs N+(u) after v and N+(v) are intersected by walking the
 // shorter and binary-searching the longer (hub vertices late in the ordering have long N+(v)
 // runs reached from many u).  The candidates of all v are spread over the 64 lanes through a
@@ -33,19 +34,28 @@ constexpr unsigned kBlock = 256;
 constexpr unsigned kWaves = kBlock / 64;
 constexpr uint32_t kCap = 512;    // LDS entries of N+(u) (and of one N+(v)) per wavefront
 constexpr uint32_t kStage = 32;   // walks at least this long search an LDS copy of N+(v)
-// Work grabs of one counter, heaviest (highest-ranked) source vertices first: the first kSplitU
-// vertices are split into kParts tickets each (part p takes every kParts-th block of 64 flattened
-// candidates and every kParts-th staged neighbour), the next kSingles are one ticket each, and
-// later tickets are kChunk vertices each.  No wavefront serialises the dense core.
+// Work tickets, heaviest (highest-ranked) source vertices first: the first `split` vertices are
+// kParts tickets each (part p takes every kParts-th block of 64 flattened candidates and every
+// kParts-th staged neighbour), the next `singles` are one ticket each, and later tickets are `span`
+// vertices each (the first `quads` of them four), whose runs a wavefront packs into its LDS slice
+// and works on together.  No wavefront serialises the dense core, and one over short runs fills its
+// lanes: the runs of consecutive vertices are one stretch of DAG edges, so a pack is handled like
+// one vertex whose entries carry the ends of their own runs.
+struct Tickets {
+    uint32_t split, singles, quads, span, total;
+    uint32_t stride;   // 1: a wavefront's next ticket is the one `waves` further on; 0: the next of one counter
+};
 constexpr uint32_t kSplitU = 8192, kParts = 8;   // kSplitU 4096: +0.5 ms; 16384: +0.3 ms (61M-edge graph)
 constexpr uint32_t kSingles = 16384;
-constexpr uint32_t kChunk = 16;
-constexpr uint32_t kOut = 192;    // triangles a wavefront buffers in LDS before appending them
+constexpr uint32_t kSpan = 32;      // vertices of a pack ticket (8: +1.4 ms on that graph; 16: +0.2 ms)
+constexpr uint32_t kSpanMax = 63;   // (a ticket's run ends are held one per lane)
+constexpr uint32_t kLowOut = 64;    // graphs with no longer run: no splits, no bitmaps
+constexpr uint32_t kOut = 128;    // triangles a wavefront buffers in LDS before appending them
 // list positions a wavefront reserves at once (one atomic on the shared counter per kChunkTri
 // triangles instead of one per buffer: thousands of wavefronts meeting at one counter serialise)
 constexpr uint32_t kChunkTri = 2048;
 static_assert(kChunkTri >= kOut, "a buffer fits a fresh chunk");
-constexpr int kBatchBuild = 4;    // blocks of 64 flattened candidates a lane works on at once
+constexpr int kBatchBuild = 3;    // blocks of 64 flattened candidates a lane works on at once
 constexpr int kBatchFused = 1;    // (one in the one-shot pass: its counting holds the registers)
 constexpr uint32_t kBmMin = 16;      // heads of N+(v) at least for a bitmap
 constexpr uint32_t kBmWin = 32768;   // ranks a bitmap spans at most (1024 words)
@@ -196,27 +206,35 @@ struct TriSink {
     uint64_t cap;
     unsigned long long *total;
     const FusedArgs *fa;
-    unsigned long long *found_total;   // triangles found (stored pass)
     unsigned long long found = 0;   // triangles this wavefront found (counted, in the one-shot pass)
     unsigned long long cb = 0, ce = 0;   // the reserved positions [cb, ce) not yet used (stored pass)
     bool chunked = true;                 // stretches of kChunkTri positions, else one per buffer
-    int64_t acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    unsigned long long s3lo = 0, s3hi = 0;
+    // LDS sums of the wavefront (one-shot pass): the eight counts, then the multiplicity products'
+    // 32-bit limbs (kept here, not in registers: the walks between two flushes need those)
+    unsigned long long *sums = nullptr;
     // counts one triangle; false when it belongs to the medium or heavy paths (the rest list)
     __device__ __forceinline__ bool count_one(uint32_t a, uint32_t b, uint32_t c) {
         const FusedArgs &F = *fa;
         const uint32_t *eoff = F.eoff;
         const uint64_t s_uv = eoff[2 * a + 2] - eoff[2 * a], s_uw = eoff[2 * b + 2] - eoff[2 * b],
                        s_vw = eoff[2 * c + 2] - eoff[2 * c];
-        const unsigned __int128 p3 = (unsigned __int128)(s_uv * s_uw) * s_vw;
-        const unsigned long long lo = (unsigned long long)p3;
-        s3lo += lo;
-        s3hi += (unsigned long long)(p3 >> 64) + (s3lo < lo ? 1ull : 0ull);
-        if (F.unit_ok && s_uv == 1 && s_uw == 1 && s_vw == 1) {
+        const bool unit = s_uv == 1 && s_uw == 1 && s_vw == 1;
+        const uint64_t um = __ballot(unit);
+        if (unit) {
+            if (__ffsll((unsigned long long)um) - 1 == (int)(threadIdx.x & 63)) atomicAdd(&sums[8], (unsigned long long)__popcll(um));
+        } else {
+            const unsigned __int128 p3 = (unsigned __int128)(s_uv * s_uw) * s_vw;
+            const unsigned long long lo = (unsigned long long)p3, hi = (unsigned long long)(p3 >> 64);
+            atomicAdd(&sums[8], lo & 0xffffffffull);
+            if (lo >> 32) atomicAdd(&sums[9], lo >> 32);
+            if (hi) atomicAdd(&sums[10], hi);
+        }
+        if (F.unit_ok && unit) {
             uint32_t cc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
             cdev::unit_one<false>(cdev::unit_record(a, b, c, eoff, F.key, F.shift), F.u, cc, nullptr);
 #pragma unroll
-            for (int j = 0; j < 8; ++j) acc[j] += cc[j];
+            for (int j = 0; j < 8; ++j)
+                if (cc[j]) atomicAdd(&sums[j], (unsigned long long)cc[j]);
         } else if (s_uv * s_uw <= F.cap_l && s_vw <= cdev::kLightVw) {
             cdev::Acc<false> A;
             cdev::Lists L;
@@ -226,7 +244,8 @@ struct TriSink {
             cdev::light_pairs<1, 0>(F.key, L, F.q, A);
             cdev::light_pairs<1, 1>(F.key, L, F.q, A);
 #pragma unroll
-            for (int j = 0; j < 8; ++j) acc[j] += A.t[j];
+            for (int j = 0; j < 8; ++j)
+                if (A.t[j]) atomicAdd(&sums[j], (unsigned long long)A.t[j]);
         } else {
             return false;
         }
@@ -297,16 +316,10 @@ struct TriSink {
         cb = ce;
     }
 
-    // at the end: the buffer out, the rest of the stretch emptied, and the wavefront's triangles
-    // added up (to the found counter, or in the one-shot pass to the total)
+    // at the end: the buffer out and the rest of the stretch emptied
     __device__ __forceinline__ void finish(unsigned lane) {
         flush(lane);
-        if (FUSED) {
-            if (lane == 0 && found) atomicAdd(total, found);
-        } else {
-            fill_empty(lane);
-            if (lane == 0 && found) atomicAdd(found_total, found);
-        }
+        if (!FUSED) fill_empty(lane);
     }
 
     // the lanes with hit set hold one triangle each; mask = the wave's ballot of hit
@@ -325,72 +338,104 @@ struct TriSink {
     }
 };
 
+// Bound by the latency of each wavefront's chain (rows, heads, their rows, the owner search, the
+// lookup), not by bandwidth: packs give a chain 200-odd entries of work where one short run gave a
+// dozen.  Stored pass before and after packing: 9.0 -> 7.5 ms (61M edges, 1.3e9 candidates),
+// 2.05 -> 0.30 ms (10M edges, longest run 54), 0.75 -> 0.02 ms (60K edges).
 template <bool FUSED>
 __global__ void __launch_bounds__(kBlock, 4)   // four wavefronts per SIMD (the LDS allows four blocks per CU)
 k_tri(uint32_t n, const uint32_t *__restrict__ dag_row, const uint32_t *__restrict__ dag_col,
       uint32_t *__restrict__ tri, uint64_t cap, unsigned long long *__restrict__ total,
       unsigned int *__restrict__ next_u, unsigned long long *__restrict__ cand, FusedArgs fa,
       const uint4 *__restrict__ binfo, const uint64_t *__restrict__ bslots,
-      unsigned long long *__restrict__ found_total, int chunked) {
-    // per wavefront: N+(u), the run starts and (16-bit) lengths of each N+(v), and one slice that
-    // holds the prefix of walk lengths during the flattened walks and then a staged N+(v) copy
+      unsigned long long *__restrict__ found_total, int chunked, Tickets T) {
+    // per wavefront: the entries of the pack's runs N+(u), (16-bit) the end of each entry's run, the
+    // run starts and (16-bit) lengths of each N+(v), and one slice that holds the prefix of walk
+    // lengths during the flattened walks and then a staged N+(v) copy
     __shared__ uint32_t s_nbr[kWaves][kCap];
     __shared__ uint32_t s_pre[kWaves][kCap + 1];
     __shared__ uint32_t s_vb[kWaves][kCap];
     __shared__ uint16_t s_dv[kWaves][kCap];
+    __shared__ uint16_t s_re[kWaves][kCap];
     __shared__ uint32_t s_out[kWaves][3 * kOut];
     const unsigned wave = threadIdx.x / 64, lane = threadIdx.x & 63;
     uint32_t *nbr_lds = s_nbr[wave], *pre_lds = s_pre[wave], *vb_lds = s_vb[wave], *vn_lds = s_pre[wave];
-    uint16_t *dv_lds = s_dv[wave];
-    TriSink<FUSED> out{s_out[wave], 0, tri, cap, total, &fa, found_total};
+    uint16_t *dv_lds = s_dv[wave], *re_lds = s_re[wave];
+    TriSink<FUSED> out{s_out[wave], 0, tri, cap, total, &fa};
     out.chunked = chunked != 0;
+    if (FUSED) {
+        __shared__ unsigned long long s_acc[kWaves][11];
+        out.sums = s_acc[wave];
+        if (lane < 11) out.sums[lane] = 0;
+    }
     unsigned long long wave_cand = 0;   // candidates tested, added once per wave
-    for (;;) {
-        uint32_t ticket = 0;
-        if (lane == 0) ticket = atomicAdd(next_u, 1u);
-        ticket = __shfl(ticket, 0, 64);
-        uint64_t b64;
-        uint32_t span, part = 0, parts = 1;
-        if (ticket < kSplitU * kParts) {
-            b64 = ticket / kParts;
+    const uint32_t waves = gridDim.x * kWaves;
+    uint32_t ticket = blockIdx.x * kWaves + wave;   // the first one is the wavefront's own
+    while (ticket < T.total) {
+        uint32_t base, span, part = 0, parts = 1;
+        if (ticket < T.split * kParts) {
+            base = ticket / kParts;
             part = ticket % kParts;
             parts = kParts;
             span = 1;
-        } else if (ticket < kSplitU * kParts + kSingles) {
-            b64 = kSplitU + (ticket - kSplitU * kParts);
+        } else if (ticket < T.split * kParts + T.singles) {
+            base = T.split + (ticket - T.split * kParts);
             span = 1;
         } else {
-            b64 = kSplitU + kSingles + (uint64_t)(ticket - kSplitU * kParts - kSingles) * kChunk;
-            span = kChunk;
+            const uint32_t p = ticket - T.split * kParts - T.singles, q = p < T.quads ? p : T.quads;
+            base = T.split + T.singles + 4 * q + (p - q) * T.span;
+            span = p < T.quads ? 4 : T.span;
         }
-        if (b64 >= n) break;
-        const uint32_t base = (uint32_t)b64;
-        const uint32_t last = base + span < n ? base + span : n;
         // highest rank first: the dense core, with the longest N+ runs, comes last in the ordering
-        for (uint32_t ci = base; ci < last; ++ci) {
-        const uint32_t u = n - 1 - ci;
-        const uint32_t r0 = dag_row[u], du = dag_row[u + 1] - r0;
+        const uint32_t u_end = n - base, u_beg = u_end > span ? u_end - span : 0u;
+        // lane l: first DAG edge of vertex u_beg + l (and, past the last, the end of its run)
+        const uint32_t rows = u_beg + lane <= u_end ? dag_row[u_beg + lane] : 0xffffffffu;
+        for (uint32_t u = u_beg; u < u_end;) {
+        // the next vertices whose runs fit the LDS slice together, or one longer run
+        const uint32_t at = u - u_beg;
+        const uint32_t r0 = __shfl(rows, at, 64);
+        const uint32_t end_l = __shfl(rows, at + lane + 1 < 64 ? at + lane + 1 : 63, 64);
+        const uint32_t ends = u + lane < u_end ? end_l - r0 : 0xffffffffu;
+        const uint64_t fits = __ballot(ends <= kCap);
+        const bool in_lds = (fits & 1) != 0;
+        const uint32_t cnt = in_lds ? (uint32_t)__ffsll((unsigned long long)~fits) - 1 : 1u;
+        const uint32_t du = __shfl(ends, cnt - 1, 64);   // entries of the pack
+        u += cnt;
         if (du < 2) continue;
-        const bool in_lds = du <= kCap;
         const uint32_t *nbr = in_lds ? nbr_lds : dag_col + r0;
-        // stage N+(u), the run start and length of each N+(v), and the prefix of the walk lengths
-        // min(du - i - 1, d+(v)) (walks that search an LDS copy of N+(v) are taken later)
+        // stage the runs, the run start and length of each N+(v), and the prefix of the walk lengths
+        // min(entries after this one in its run, d+(v)) (walks that search an LDS copy of N+(v) are
+        // taken later)
         uint32_t carry = 0;
+        bool any_long = false;
         for (uint32_t b = 0; b < du; b += 64) {
             const uint32_t i = b + lane;
+            uint32_t re = du;
+            if (cnt > 1) {   // the run of entry i: the number of run ends at or before it
+                uint32_t r = 0;
+#pragma unroll
+                for (uint32_t s = 32; s > 0; s >>= 1) {
+                    const uint32_t e = __shfl(ends, (r + s - 1) & 63, 64);
+                    if (r + s <= cnt && e <= i) r += s;
+                }
+                re = __shfl(ends, r < cnt ? r : cnt - 1, 64);
+            }
             uint32_t dv = 0;
+            bool staged = false;
             if (i < du) {
                 const uint32_t v = dag_col[r0 + i];
                 const uint32_t vb = dag_row[v], outv = dag_row[v + 1] - vb;
-                const uint32_t after = du - i - 1;
+                const uint32_t after = re - i - 1;
                 if (in_lds) {
                     nbr_lds[i] = v;
                     vb_lds[i] = vb;
+                    re_lds[i] = (uint16_t)re;
                     dv_lds[i] = (uint16_t)(outv < 0xffffu ? outv : 0xffffu);
                 }
-                const bool staged = outv > after && after >= kStage && outv <= kCap;
+                staged = in_lds && outv > after && after >= kStage && outv <= kCap;
                 dv = in_lds ? (staged ? 0 : (outv < after ? outv : after)) : (i + 1 < du ? outv : 0);
             }
+            any_long |= __ballot(staged) != 0;
             uint32_t x = dv;   // inclusive wave scan
 #pragma unroll
             for (int s = 1; s < 64; s <<= 1) {
@@ -411,7 +456,7 @@ k_tri(uint32_t n, const uint32_t *__restrict__ dag_row, const uint32_t *__restri
             // instead of one
             constexpr int kBatch = FUSED ? kBatchFused : kBatchBuild;
             for (uint32_t b = part * 64; b < work; b += parts * 64 * kBatch) {
-                uint32_t ci[kBatch], cj[kBatch], cvb[kBatch], cov[kBatch], w[kBatch], lo[kBatch], len[kBatch];
+                uint32_t ci[kBatch], cj[kBatch], cvb[kBatch], cov[kBatch], cre[kBatch], w[kBatch], lo[kBatch], len[kBatch];
                 bool ok[kBatch], walk_v[kBatch];
 #pragma unroll
                 for (int x = 0; x < kBatch; ++x) {
@@ -420,20 +465,21 @@ k_tri(uint32_t n, const uint32_t *__restrict__ dag_row, const uint32_t *__restri
                     ci[x] = ok[x] ? owner(pre_lds, du, p) : 0u;
                     cj[x] = p - pre_lds[ci[x]];
                     cvb[x] = vb_lds[ci[x]];
+                    cre[x] = re_lds[ci[x]];
                     const uint32_t d16 = dv_lds[ci[x]];
                     cov[x] = d16 != 0xffffu ? d16 : (ok[x] ? dag_row[nbr_lds[ci[x]] + 1] - cvb[x] : 0u);
                     // walk N+(v) and search N+(u) after v in LDS, or walk N+(u) after v and search
                     // N+(v) in global memory
-                    walk_v[x] = cov[x] <= du - ci[x] - 1;
+                    walk_v[x] = cov[x] <= cre[x] - ci[x] - 1;
                 }
 #pragma unroll
                 for (int x = 0; x < kBatch; ++x)
                     w[x] = !ok[x] ? 0u : (walk_v[x] ? dag_col[cvb[x] + cj[x]] : nbr_lds[ci[x] + 1 + cj[x]]);
-                // searches in LDS (lower bound of w in nbr_lds[i + 1, du))
+                // searches in LDS (lower bound of w in u's run after v)
 #pragma unroll
                 for (int x = 0; x < kBatch; ++x) {
                     lo[x] = ci[x] + 1;
-                    len[x] = ok[x] && walk_v[x] ? du - ci[x] - 1 : 0u;
+                    len[x] = ok[x] && walk_v[x] ? cre[x] - ci[x] - 1 : 0u;
                 }
                 while (true) {
                     bool more = false;
@@ -461,7 +507,7 @@ k_tri(uint32_t n, const uint32_t *__restrict__ dag_row, const uint32_t *__restri
                     bmap[x] = false;
                     bhit[x] = false;
                     bpos[x] = 0;
-                    if (ok[x] && !walk_v[x]) {
+                    if (binfo && ok[x] && !walk_v[x]) {
                         const uint4 bi = binfo[nbr_lds[ci[x]]];
                         if (bi.y) {
                             bmap[x] = true;
@@ -494,7 +540,7 @@ k_tri(uint32_t n, const uint32_t *__restrict__ dag_row, const uint32_t *__restri
 #pragma unroll
                 for (int x = 0; x < kBatch; ++x) {
                     if (!ok[x]) at[x] = ~w[x];
-                    else if (walk_v[x]) at[x] = pos[x] < du ? nbr_lds[pos[x]] : ~w[x];
+                    else if (walk_v[x]) at[x] = pos[x] < cre[x] ? nbr_lds[pos[x]] : ~w[x];
                     else if (bmap[x]) at[x] = bhit[x] ? w[x] : ~w[x];
                     else at[x] = lo[x] < cvb[x] + cov[x] ? dag_col[lo[x]] : ~w[x];
                 }
@@ -509,19 +555,19 @@ k_tri(uint32_t n, const uint32_t *__restrict__ dag_row, const uint32_t *__restri
             // long walks into a long N+(v): 64 positions of N+(u) are tested at once and the
             // bitmap infos of those taken here loaded together; then each in turn searches its
             // N+(v) by bitmap lookups or on an LDS copy
-            for (uint32_t i0 = part; i0 + kStage < du; i0 += parts * 64) {
+            for (uint32_t i0 = part; any_long && i0 + kStage < du; i0 += parts * 64) {
                 const uint32_t il = i0 + lane * parts;
                 bool take = false;
                 uint4 bil = make_uint4(0, 0, 0, 0);
                 if (il + kStage < du) {
-                    const uint32_t after = du - il - 1, outv = dv_lds[il];   // 0xffff: longer than any stage
+                    const uint32_t after = re_lds[il] - il - 1, outv = dv_lds[il];   // 0xffff: longer than any stage
                     take = outv > after && after >= kStage && outv <= kCap;
-                    if (take) bil = binfo[nbr_lds[il]];
+                    if (take && binfo) bil = binfo[nbr_lds[il]];
                 }
                 for (uint64_t m = __ballot(take); m; m &= m - 1) {
                     const int src = __ffsll((unsigned long long)m) - 1;
                     const uint32_t i = i0 + (uint32_t)src * parts;
-                    const uint32_t after = du - i - 1, outv = dv_lds[i];
+                    const uint32_t after = re_lds[i] - i - 1, outv = dv_lds[i];
                     const uint32_t vb = vb_lds[i];
                     wave_cand += after;
                     const uint4 bi = make_uint4(__shfl(bil.x, src, 64), __shfl(bil.y, src, 64), __shfl(bil.z, src, 64),
@@ -576,27 +622,39 @@ k_tri(uint32_t n, const uint32_t *__restrict__ dag_row, const uint32_t *__restri
         }
         __builtin_amdgcn_wave_barrier();
         }
+        if (T.stride) {
+            ticket += waves;
+        } else {
+            if (lane == 0) ticket = waves + atomicAdd(next_u, 1u);
+            ticket = __shfl(ticket, 0, 64);
+        }
     }
     out.finish(lane);
-    if (lane == 0) atomicAdd(cand, wave_cand);
+    // triangles found and candidates tested: one atomic per workgroup each (into the triangle total
+    // in the one-shot pass)
+    __shared__ unsigned long long s_sum[2][kWaves];
+    if (lane == 0) {
+        s_sum[0][wave] = out.found;
+        s_sum[1][wave] = wave_cand;
+    }
+    __syncthreads();
+    if (threadIdx.x < 2) {
+        unsigned long long t = 0;
+#pragma unroll
+        for (unsigned w = 0; w < kWaves; ++w) t += s_sum[threadIdx.x][w];
+        if (t) atomicAdd(threadIdx.x ? cand : (FUSED ? total : found_total), t);
+    }
     if (FUSED) {
         // this wavefront's sums: its partial slot, and the 128-bit multiplicity sum with carry
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int64_t v = cdev::wave_sum((long long)out.acc[j]);
-            if (lane == 0) fa.part[8 * ((uint64_t)blockIdx.x * kWaves + wave) + j] = v;
-        }
-        unsigned long long lo = out.s3lo, hi = out.s3hi;
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            const unsigned long long lo2 = __shfl_xor(lo, o, 64), hi2 = __shfl_xor(hi, o, 64);
-            const unsigned long long sum = lo + lo2;
-            hi = hi + hi2 + (sum < lo ? 1ull : 0ull);
-            lo = sum;
-        }
+        if (lane < 8) fa.part[8 * ((uint64_t)blockIdx.x * kWaves + wave) + lane] = (int64_t)out.sums[lane];
         if (lane == 0) {
-            const unsigned long long old = atomicAdd(&fa.s3[0], lo);
-            atomicAdd(&fa.s3[1], hi + (old + lo < old ? 1ull : 0ull));
+            const unsigned __int128 t = (unsigned __int128)out.sums[8] + ((unsigned __int128)out.sums[9] << 32) +
+                                        ((unsigned __int128)out.sums[10] << 64);
+            const unsigned long long lo = (unsigned long long)t, hi = (unsigned long long)(t >> 64);
+            if (t) {
+                const unsigned long long old = atomicAdd(&fa.s3[0], lo);
+                atomicAdd(&fa.s3[1], hi + (old + lo < old ? 1ull : 0ull));
+            }
         }
     }
 }
@@ -607,6 +665,9 @@ int build_bitmaps(const dt_graph *g, DevMem &info, DevMem &slots) {
     dt_ctx *ctx = g->ctx;
     hipStream_t st = ctx->stream;
     const uint32_t n = g->n;
+    // runs of at most kLowOut heads: a search takes six steps at most, less than the passes that
+    // would make the bitmaps cost on such graphs
+    if (g->max_outdeg <= kLowOut) return DT_OK;
     DevMem words, base;
     DT_TRY(dev_alloc(ctx, info, (uint64_t)n * sizeof(uint4) + 16));
     DT_TRY(dev_alloc(ctx, words, ((uint64_t)n + 1) * 8));
@@ -633,6 +694,33 @@ int build_bitmaps(const dt_graph *g, DevMem &info, DevMem &slots) {
     return DT_OK;
 }
 
+// The tickets of an enumeration pass on a grid of at most four workgroups per CU (as many as are
+// resident), and the grid.  Graphs whose runs are all short have no dense core to spread: packs
+// only, as many vertices each as leave one ticket per wavefront, taken in strides, so that no
+// wavefront meets another at a counter (an atomic on one address takes about 15 ns, and with a
+// ticket per part of 8192 vertices the counter alone bounded the pass on small graphs).
+Tickets make_tickets(const dt_graph *g, unsigned *grid) {
+    const uint32_t n = g->n;
+    const uint32_t waves = (uint32_t)g->ctx->num_cus * 4 * kWaves;
+    Tickets T{0, 0, 0, kSpan, 0, 0};
+    if (g->max_outdeg > kLowOut) {
+        T.split = n < kSplitU ? n : kSplitU;
+        T.singles = n - T.split < kSingles ? n - T.split : kSingles;
+    } else {
+        // the densest vertices one by one, the next in fours, and the rest in one ticket a wavefront
+        T.singles = n < waves / 2 ? n : waves / 2;
+        T.quads = (n - T.singles) / 4 < waves / 4 ? (n - T.singles) / 4 : waves / 4;
+        T.span = (n - T.singles - 4 * T.quads + waves - 1) / waves;
+        T.span = T.span < 4 ? 4 : (T.span > kSpanMax ? kSpanMax : T.span);
+        T.stride = 1;
+    }
+    const uint32_t rest = n - T.split - T.singles - 4 * T.quads;
+    T.total = T.split * kParts + T.singles + T.quads + (rest + T.span - 1) / T.span;
+    const uint32_t blocks = (T.total + kWaves - 1) / kWaves;
+    *grid = blocks < (unsigned)g->ctx->num_cus * 4 ? blocks : (unsigned)g->ctx->num_cus * 4;
+    return T;
+}
+
 }  // namespace
 
 int enumerate_triangles(const dt_graph *g, DevMem &tri, uint64_t *ntri_out, uint64_t *cand_out,
@@ -654,7 +742,8 @@ int enumerate_triangles(const dt_graph *g, DevMem &tri, uint64_t *ntri_out, uint
     // they can leave: below kOut per stretch taken (at most one per kChunkTri - kOut triangles, and
     // one more per wavefront) and a last stretch per wavefront.
     uint64_t cap = std::max<uint64_t>(4ull * g->m_s, 1ull << 16);
-    const unsigned grid = (unsigned)ctx->num_cus * 8;
+    unsigned grid = 0;
+    const Tickets T = make_tickets(g, &grid);
     const uint64_t waves = (uint64_t)grid * kWaves;
     const int chunked = cap >= 4 * waves * kChunkTri ? 1 : 0;
     for (int attempt = 0; attempt < 2; ++attempt) {
@@ -664,7 +753,7 @@ int enumerate_triangles(const dt_graph *g, DevMem &tri, uint64_t *ntri_out, uint
         prof_begin(ctx, kProfTriFill, st);
         k_tri<false><<<grid, kBlock, 0, st>>>(n, g->dag_row.as<uint32_t>(), g->dag_col.as<uint32_t>(),
                                               tri.as<uint32_t>(), cap, c64, ctr.as<unsigned>(), c64 + 1, FusedArgs{},
-                                              binfo.as<uint4>(), bslots.as<uint64_t>(), c64 + 2, chunked);
+                                              binfo.as<uint4>(), bslots.as<uint64_t>(), c64 + 2, chunked, T);
         prof_end(ctx, kProfTriFill, st);
         DT_HIP(hipGetLastError());
         uint64_t *h = reinterpret_cast<uint64_t *>(ctx->pinned_stage);
@@ -687,7 +776,9 @@ int fused_count(dt_graph *g, const DQuery &q, int64_t *out8_dev, DevMem &rest, u
     hipStream_t st = ctx->stream;
     const uint32_t n = g->n;
     *n_rest = *ntri_out = *cand_out = 0;
-    const unsigned grid = (unsigned)ctx->num_cus * 8;
+    unsigned grid = 1;
+    const Tickets T = make_tickets(g, &grid);
+    if (grid == 0) grid = 1;
     const uint64_t n_part = (uint64_t)grid * kWaves;
     DevMem ctr, part, binfo, bslots;
     DT_TRY(dev_alloc(ctx, ctr, 256));
@@ -717,7 +808,7 @@ int fused_count(dt_graph *g, const DQuery &q, int64_t *out8_dev, DevMem &rest, u
         if (n)
             k_tri<true><<<grid, kBlock, 0, st>>>(n, g->dag_row.as<uint32_t>(), g->dag_col.as<uint32_t>(), nullptr, 0,
                                                  c64, ctr.as<unsigned>(), c64 + 1, fa, binfo.as<uint4>(),
-                                                 bslots.as<uint64_t>(), nullptr, 0);
+                                                 bslots.as<uint64_t>(), nullptr, 0, T);
         else
             DT_HIP(hipMemsetAsync(part.ptr, 0, n_part * 8 * sizeof(int64_t), st));
         prof_end(ctx, kProfTriFill, st);
