@@ -12,6 +12,8 @@
 // while it runs.  All edges at one source vertex u are then
 // one contiguous stretch of the store, which is exactly what the counting of all triangles with
 // source u walks (Section 5: only {u,v} and {u,w} are enumerated).
+#include <algorithm>
+
 #include "internal.h"
 
 namespace dt {
@@ -84,38 +86,43 @@ __device__ __forceinline__ void dag_edge(uint64_t d, uint4 r, uint32_t *__restri
     gsize[2 * d + 1] = r.w;
 }
 
-// Sort every run by head rank (heads are distinct).  Wavefronts take chunks of kTailChunk tails
-// from a work counter; runs that fit together in 64 lanes are loaded in one piece and sorted at
-// once: each entry placed at the number of (run, head) keys below its own, or, past 2^26
-// vertices, by a bitonic network on (run, head).  Longer runs are left to k_dag_sort_long.
+// Sort every run by head rank (heads are distinct).  Wavefronts take chunks of kTailChunk tails in
+// strides; runs that fit together in 64 lanes are loaded in one piece and sorted at once: each entry
+// placed at the number of (run, head) keys below its own, or, past 2^26 vertices, by a bitonic
+// network on (run, head).  Longer runs are left to k_dag_sort_long.
 constexpr uint32_t kTailChunk = 64;
 
 __global__ void __launch_bounds__(kBlock)
 k_dag_sort(uint32_t n, const uint32_t *__restrict__ dag_row, const uint4 *__restrict__ runs,
-           uint32_t *__restrict__ dag_col, uint32_t *__restrict__ dag_of, uint32_t *__restrict__ gsize,
-           unsigned *__restrict__ next_chunk) {
+           uint32_t *__restrict__ dag_col, uint32_t *__restrict__ dag_of, uint32_t *__restrict__ gsize) {
     const unsigned lane = threadIdx.x & 63;
-    for (;;) {
-        uint32_t t0 = 0;
-        if (lane == 0) t0 = atomicAdd(next_chunk, kTailChunk);
-        t0 = __shfl(t0, 0, 64);
-        if (t0 >= n) break;
+    const uint32_t chunks = (n + kTailChunk - 1) / kTailChunk, waves = gridDim.x * (kBlock / 64);
+    for (uint32_t c = blockIdx.x * (kBlock / 64) + threadIdx.x / 64; c < chunks; c += waves) {
+        const uint32_t t0 = c * kTailChunk;
         const uint32_t t1 = t0 + kTailChunk < n ? t0 + kTailChunk : n;
+        // lane l: first DAG edge of tail t0 + l; row_end: the end of the chunk's last run
+        const uint32_t rows = dag_row[t0 + lane < t1 ? t0 + lane : t1], row_end = dag_row[t1];
         uint32_t r = t0;
         while (r < t1) {
-            const uint32_t b = dag_row[r];
+            const uint32_t b = __builtin_amdgcn_readlane(rows, r - t0);
             // lane l: end of run r + l (relative to b) if that tail is in the chunk
-            const uint32_t endl = r + lane < t1 ? dag_row[r + lane + 1] - b : 0xffffffffu;
+            const uint32_t nx = r - t0 + lane + 1;
+            const uint32_t nrow = __shfl(rows, nx & 63, 64);
+            const uint32_t endl = r + lane < t1 ? (nx < 64 ? nrow : row_end) - b : 0xffffffffu;
             const uint64_t fits = __ballot(endl <= 64);
             const uint32_t cnt = fits == ~0ull ? 64u : (uint32_t)__ffsll((unsigned long long)~fits) - 1;
             if (cnt == 0) {   // run r alone exceeds 64: listed by k_long_runs, sorted by k_dag_sort_long
                 r += 1;
                 continue;
             }
-            const uint32_t len = __shfl(endl, cnt - 1, 64);
+            const uint32_t len = __builtin_amdgcn_readlane(endl, cnt - 1);
             // run of lane x: the number of runs ending at or before x
             uint32_t seg = 0;
-            for (uint32_t q = 0; q < cnt; ++q) seg += __shfl(endl, q, 64) <= lane ? 1u : 0u;
+#pragma unroll
+            for (uint32_t s = 64; s > 0; s >>= 1) {
+                const uint32_t e = __shfl(endl, (seg + s - 1) & 63, 64);
+                if (seg + s <= cnt && e <= lane) seg += s;
+            }
             uint4 rec = make_uint4(0xffffffffu, 0, 0, 0);
             uint64_t key = ~0ull;
             if (lane < len) {
@@ -127,7 +134,7 @@ k_dag_sort(uint32_t n, const uint32_t *__restrict__ dag_row, const uint4 *__rest
                 // of lanes with a smaller one
                 const uint32_t k32 = lane < len ? (seg << 26) | rec.x : 0xffffffffu;
                 uint32_t pos = 0;
-                for (uint32_t q = 0; q < len; ++q) pos += __shfl(k32, q, 64) < k32 ? 1u : 0u;
+                for (uint32_t q = 0; q < len; ++q) pos += (uint32_t)__builtin_amdgcn_readlane(k32, q) < k32 ? 1u : 0u;
                 if (lane < len) dag_edge(b + pos, rec, dag_col, dag_of, gsize);
                 r += cnt;
                 continue;
@@ -328,8 +335,10 @@ int orient(dt_graph *g, bool overlap) {
             g->dag_row.as<uint32_t>(), runs.as<uint4>(), g->dag_col.as<uint32_t>(), dag_of.as<uint32_t>(),
             gsize.as<uint32_t>());
         DT_HIP(hipGetLastError());
-        k_dag_sort<<<(unsigned)ctx->num_cus * 8, kBlock, 0, st>>>(n, g->dag_row.as<uint32_t>(), runs.as<uint4>(),
-            g->dag_col.as<uint32_t>(), dag_of.as<uint32_t>(), gsize.as<uint32_t>(), scal.as<unsigned>() + 8);
+        const unsigned sort_grid = std::min<unsigned>((unsigned)ctx->num_cus * 8,
+                                                      grid_for(n, kTailChunk * (kBlock / 64)));
+        k_dag_sort<<<sort_grid, kBlock, 0, st>>>(n, g->dag_row.as<uint32_t>(), runs.as<uint4>(),
+            g->dag_col.as<uint32_t>(), dag_of.as<uint32_t>(), gsize.as<uint32_t>());
         DT_HIP(hipGetLastError());
         if (ls != st) {
             DT_HIP(hipEventRecord(ctx->ev_relay[1], ls));

@@ -78,7 +78,7 @@ __device__ __forceinline__ int tri_class(uint64_t s_uv, uint64_t s_uw, uint64_t 
 }
 
 constexpr int kPartWords = 6;   // per block: sum_sigma3 lo, hi, bytes, light, medium, unit bytes
-constexpr unsigned kClsGrid = 4096;   // blocks of the classify and partition passes (grid-stride)
+constexpr unsigned kClsGrid = 4096;   // blocks of the classify and partition passes at most (grid-stride)
 constexpr int kTotWords = kClasses + kPartWords;   // class sizes, then the partial words
 
 // Per list entry its class (one byte; kClasses for an empty entry); per block the triangles of
@@ -607,7 +607,7 @@ int make_schedule(dt_graph *g, DevMem &tri) {
     R.cost_pct = g->cost_pct_used ? g->cost_pct_used : 100;
     // unit records hold 32-bit relative times
     R.unit_ok = g->span <= kUnitMaxSpan ? 1u : 0u;
-    const unsigned grid = kClsGrid;
+    const unsigned grid = std::min(kClsGrid, grid_for(nt, kBlock));
     DevMem cls, bcnt, part, base;
     DT_TRY(dev_alloc(ctx, cls, nt + 1));
     DT_TRY(dev_alloc(ctx, bcnt, (uint64_t)grid * kClasses * 4));
