@@ -245,7 +245,7 @@ struct dt_graph {
     // load products
     dt::DevMem sx, sy;          // uint32[m_s]: pair endpoints x < y
     dt::DevMem row;             // uint32[n + 1]: undirected CSR of G
-    dt::DevMem col, ceid;       // uint32[2 m_s]: neighbour, pair id
+    dt::DevMem col;             // uint32[2 m_s]: neighbours, by id
     dt::DevMem psid;            // uint32[m]: pair of each temporal edge (pair-major, key order)
     dt::DevMem pdir;            // uint8[m]: 0 if the edge goes x -> y
     dt::DevMem pkey;            // uint64[m]: key of each temporal edge (same order)
@@ -426,8 +426,8 @@ int count_batch(dt_ctx *ctx, uint64_t k, dt_graph *const *graphs, const dt_query
 // rocPRIM a nonzero begin_bit gave unsorted output for mid-size inputs (its merge-sort path).
 int sort_pairs_u64_u32(dt_ctx *ctx, const uint64_t *kin, uint64_t *kout, const uint32_t *vin,
                        uint32_t *vout, size_t n, int end_bit, hipStream_t s);
-int sort_pairs_u64_u64(dt_ctx *ctx, const uint64_t *kin, uint64_t *kout, const uint64_t *vin,
-                       uint64_t *vout, size_t n, int end_bit, hipStream_t s);
+int sort_pairs_u32_u32(dt_ctx *ctx, const uint32_t *kin, uint32_t *kout, const uint32_t *vin,
+                       uint32_t *vout, size_t n, int end_bit, hipStream_t s);
 // (16-bit key, 16-byte record) pairs; with `keep` the temporary storage is handed to the caller
 // instead of being released (and a foreign stream s is not waited for): for a sort left running on
 // a side stream, whose caller releases it after the join

@@ -24,7 +24,7 @@ namespace {
 
 // every device array of a graph, in a fixed order (the order of its host copies while swapped)
 std::vector<DevMem *> graph_arrays(dt_graph *g) {
-    return {&g->sx, &g->sy, &g->row, &g->col, &g->ceid, &g->psid, &g->pdir, &g->pkey,
+    return {&g->sx, &g->sy, &g->row, &g->col, &g->psid, &g->pdir, &g->pkey,
             &g->pstart, &g->c1, &g->core, &g->rank, &g->order, &g->dag_row, &g->dag_col,
             &g->eoff, &g->key, &g->sched.light, &g->sched.medium, &g->sched.mitems,
             &g->sched.light_w, &g->sched.medium_w, &g->sched.mitems_w, &g->sched.heavy,

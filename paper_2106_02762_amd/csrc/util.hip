@@ -158,8 +158,8 @@ int sort_pairs_u64_u32(dt_ctx *ctx, const uint64_t *kin, uint64_t *kout, const u
     return DT_OK;
 }
 
-int sort_pairs_u64_u64(dt_ctx *ctx, const uint64_t *kin, uint64_t *kout, const uint64_t *vin,
-                       uint64_t *vout, size_t n, int end_bit, hipStream_t s) {
+int sort_pairs_u32_u32(dt_ctx *ctx, const uint32_t *kin, uint32_t *kout, const uint32_t *vin,
+                       uint32_t *vout, size_t n, int end_bit, hipStream_t s) {
     if (n == 0) return DT_OK;
     size_t bytes = 0;
     DT_HIP(rocprim::radix_sort_pairs(nullptr, bytes, kin, kout, vin, vout, n, 0u,
@@ -168,8 +168,7 @@ int sort_pairs_u64_u64(dt_ctx *ctx, const uint64_t *kin, uint64_t *kout, const u
     DT_TRY(dev_alloc(ctx, tmp, bytes));
     DT_HIP(rocprim::radix_sort_pairs(tmp.ptr, bytes, kin, kout, vin, vout, n, 0u,
                                      (unsigned)end_bit, s));
-    // the temporary goes back to the context's cache, whose blocks are reused in stream order on
-    // the context's stream only: another stream must finish with it first
+    // (as above)
     if (s != ctx->stream) DT_HIP(hipStreamSynchronize(s));
     return DT_OK;
 }
