@@ -19,7 +19,8 @@
 // list wait for another round.  The first levels remove most of the graph and are bound by work,
 // the later ones by latency, and a barrier's cost grows with the number of blocks that meet at it:
 // the grid starts with one block of 1024 threads per CU and narrows to 128, 64, then 32 blocks
-// as vertices run out.  The barrier is a monotonic arrival counter that every block polls.  Counters
+// as vertices run out, and hands its last 65,536 vertices to a finish that takes no levels (below).  The
+// barrier is a monotonic arrival counter that every block polls.  Counters
 // that decide the next step (queue positions taken in a phase, survivors of a level scan) rotate
 // over three slots, so a fast block starting the next phase never changes what a slow block reads,
 // and every block takes the same branch.  A vertex is queued at most
@@ -30,6 +31,9 @@
 // it.  The queue index is also bounds-checked, and the host checks that exactly n vertices were
 // queued.  A barrier that waits far longer than any peel could take sets an error flag and lets its
 // block go, so that a fault in this logic ends the kernel instead of hanging it.
+#include <algorithm>
+#include <type_traits>
+
 #include "internal.h"
 
 namespace dt {
@@ -46,15 +50,10 @@ struct Width {
     unsigned blocks;
 };
 constexpr Width kWidths[4] = {{1000000, kGridWide}, {200000, 128}, {50000, 64}, {0, 32}};
-constexpr uint32_t kTail = kPeelTailMax;   // most vertices the one-workgroup finish takes (16-bit ids)
-// LDS of a peel block.  The one-workgroup finish keeps there the local CSR rows (kTail + 1
-// words), the degrees (16-bit, two per word), the removal queue and the list of vertices not yet
-// queued (16-bit local ids); on the grid the same words stage the vertices a block queues in one
-// round.
-constexpr uint32_t kRowWords = kTail + 1, kDegWords = kTail / 2, kQWords = kTail / 2, kLiveWords = kTail / 2;
-constexpr uint32_t kLdsWords = kRowWords + kDegWords + kQWords + kLiveWords;
-// on the grid the words hold two staging halves: the vertices a block is removing and those their
+constexpr uint32_t kTail = 65536;   // most vertices the finish takes (16-bit local ids and bounds)
+// LDS words of a peel block: two staging halves, the vertices the block is removing and those their
 // removal queues
+constexpr uint32_t kLdsWords = 40800;
 constexpr uint32_t kStage = kLdsWords / 2;
 constexpr uint32_t kUnset = 0xffffffffu;
 constexpr long kSpinLimit = 1l << 26;
@@ -70,7 +69,7 @@ struct PeelCtl {
     unsigned int error;      // a barrier gave up waiting, or a consistency check failed
     unsigned int rounds;     // removal rounds
     unsigned int kappa;      // largest level that removed a vertex
-    unsigned int nlvl;       // levels recorded by the one-workgroup finish
+    unsigned int fin[3];     // finish, per phase mod 3: a bound fell / a vertex was left over
     unsigned long long lres; // hand-over: local ids (low word) and adjacency entries (high word) given out
     unsigned int ho;         // 1: the grid handed its last vertices over (the state below is set)
     unsigned int ho_tail, ho_k, ho_rounds;   // queue positions taken, level and rounds at the hand-over
@@ -87,7 +86,8 @@ __device__ __forceinline__ int ld_relaxed(const int *p) {
 // Grid barrier.  Arrivals only ever increase, and every block passes the same barriers in the same
 // order with the same participants, so a barrier is complete once `target` arrivals (the running
 // sum of the participants of every barrier so far) have been counted: each block's first thread
-// publishes its block's writes, arrives, and polls the count; no block has to release the others.
+// publishes its block's writes, arrives, polls the count (an acquiring poll would throw away its
+// caches each time) and takes the others' writes; no block has to release the others.
 // A barrier that waits far longer than any peel could take sets an error flag and lets its block
 // go.
 __device__ void grid_barrier(PeelCtl *ctl, unsigned target) {
@@ -97,16 +97,15 @@ __device__ void grid_barrier(PeelCtl *ctl, unsigned target) {
         const unsigned a = atomicAdd(&ctl->arrived, 1u) + 1;
         if (a < target) {
             long spins = 0;
-            while (__hip_atomic_load(&ctl->arrived, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) < target) {
+            while (ld_relaxed(&ctl->arrived) < target) {
                 __builtin_amdgcn_s_sleep(1);
                 if (++spins > kSpinLimit) {
                     atomicOr(&ctl->error, 1u);
                     break;
                 }
             }
-        } else {
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
         }
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     }
     __syncthreads();
 }
@@ -169,180 +168,497 @@ __device__ __forceinline__ void remove_edges(uint32_t v, uint32_t first, uint32_
     remove_range(row[v], row[v + 1], first, stride, k, n, col, deg, level, ovc, ovf, err, s_stage, s_cnt);
 }
 
-// The last vertices: one workgroup finishes the peel on the subgraph they induce, with local
-// (16-bit) vertex ids.  The local CSR rows, the degrees, the removal queue and the list of vertices
-// not yet queued live in LDS, so a round touches global memory only to read adjacency (lcol);
-// workgroup barriers separate rounds.  rlist maps local ids to vertices.  A degree counts the
-// neighbours not yet removed (so it never falls below zero, and two 16-bit degrees share a word
-// safely) until the vertex is queued; queuing adds kMark - degree, which puts it at kMark, and
-// the at most kTail later decrements leave it at least kMark - kTail, above every level.  Each
-// wavefront keeps its own segment of the live list and compacts it in place at every level scan,
-// so a scan reads only the vertices still live, and takes one atomic per wavefront for the
-// survivors' count and smallest degree.  The queue positions (continuing from qbase) and the core
-// numbers are written at the end, from the queue and the level boundaries recorded in lvl (pairs:
-// first queue position, level).
-constexpr uint32_t kMark = 0xC000u, kMarked = 0x8000u;
-static_assert(kMark - kTail > kMarked && kMarked > kTail, "queued degrees stay above every level");
-__device__ void peel_tail(uint32_t R, uint32_t qbase, uint32_t k, uint32_t rounds,
-                          const uint32_t *__restrict__ rlist, const uint32_t *__restrict__ lrow,
-                          const uint16_t *__restrict__ lcol, uint32_t *__restrict__ lvl,
-                          uint32_t *__restrict__ level, uint32_t *__restrict__ queue, PeelCtl *ctl,
-                          uint32_t *s_mem) {
-    uint32_t *s_row = s_mem;                                              // kRowWords
-    uint32_t *s_deg = s_mem + kRowWords;                                  // kDegWords
-    uint16_t *s_q = reinterpret_cast<uint16_t *>(s_mem + kRowWords + kDegWords);               // kTail
-    uint16_t *s_live = reinterpret_cast<uint16_t *>(s_mem + kRowWords + kDegWords + kQWords);  // kTail
-    __shared__ unsigned s_qt, s_keep, s_min, s_nlvl;
-    const unsigned tid = threadIdx.x, lane = tid & 63, wave = tid / 64;
-    constexpr unsigned kWaves = kBlock / 64;
-    const uint64_t below = (1ull << lane) - 1;
-    for (uint32_t l = tid; l <= R; l += kBlock) s_row[l] = lrow[l];
-    for (uint32_t w = tid; w < kDegWords; w += kBlock) s_deg[w] = 0;
-    for (uint32_t l = tid; l < R; l += kBlock) s_live[l] = (uint16_t)l;
+// ------------------------------------------------------------------------------------------------
+// The finish: the last R vertices, on the subgraph they induce (local 16-bit ids; rows lrow, lcol).
+//
+// Level after level would take hundreds of levels of a few removal rounds each, bound by the latency
+// of every round.  Their core numbers come instead from bounds that fall: every vertex holds an upper
+// bound of its core number, first its degree, and replaces it by the largest t such that t neighbours
+// have bounds of at least t, until no bound falls (the last bounds are the core numbers).  Then every
+// shell is peeled at once: a vertex goes in the first round in which at most core(v) of its
+// neighbours of core >= core(v) are left, and vertices are ordered by (core, round).  A neighbour
+// placed after v has a larger core or went no earlier, so it was counted then: at most core(v) of
+// them.  Both parts run in phases over all R rows, 65 and 50 phases for the 61M-edge graph's last
+// 65,536 vertices where levels took 410 and 2,000 rounds (its peel 13.9 -> 8.4 ms, 2.9 of them here;
+// 10M edges: 1.9 -> 1.5 ms).  65,536 is what 16-bit ids and one workgroup's LDS hold; above it the level
+// peel is the faster one (a level of many vertices there costs less than their share of 65 phases).
+//
+// A wavefront owns consecutive local ids holding an even share of the entries.  Every phase each block
+// copies all bounds (128 KB at most) into LDS, where the gathers along the rows go; rows stream from
+// L2, short rows packed 64 entries at a time, rows of up to kRegRow entries held in registers
+// while their new bound is searched by ballots.  A phase may read bounds that others lower meanwhile:
+// any mix of old and new bounds is a set of upper bounds, and a phase in which none fell saw the final
+// ones.  In the rounds a vertex's value is 2 core + 1, less one once it is removed, so that a neighbour
+// counts for a vertex of core c when its value is at least 2 c + 1; a round reads the values left by the
+// rounds before it (two buffers).
+// ------------------------------------------------------------------------------------------------
+constexpr uint32_t kGroup = 32;      // vertices of a wavefront handled at once
+constexpr uint32_t kVertexCost = 32; // a vertex's share of the work, in entries, besides its row
+constexpr uint32_t kPerWave = 16;    // vertices per wavefront that a grid is sized for
+constexpr unsigned kBarGroup = 32;   // blocks that share a counter of the finish's barrier
+constexpr unsigned kBarLine = 32;    // words between counters
+constexpr uint32_t kPiece = 128;     // entries of a row a wavefront reads at once, two a lane
+constexpr uint32_t kRegPieces = 8;   // pieces of a row held in registers
+constexpr uint32_t kRegRow = kPiece * kRegPieces;
+constexpr uint32_t kFinSmall = 1024; // up to this many vertices one block finishes alone
+constexpr uint32_t kCoreLds = 4096;  // shells whose positions a block takes together
+
+struct FinArgs {
+    const uint32_t *rlist, *lrow;
+    const uint16_t *lcol;
+    uint16_t *val;        // R bounds; then, in the rounds, two buffers of R values
+    uint32_t *base;       // first position of each shell
+    uint32_t *cur;        // positions taken in each shell
+    uint32_t *pos;        // position of each vertex in its shell
+    uint32_t *level, *queue;
+    unsigned *bar;        // barrier counters: the root, then one per group of blocks, kBarLine apart
+    PeelCtl *ctl;
+};
+
+// Barrier `turn` (1, 2, ...) of the finish's nblk blocks: arrivals are counted per group of blocks, the
+// last of a group arrives at the root, and every block polls the root, or the only group's counter (an
+// atomic on one address takes about 15 ns, so 256 arrivals at one counter would take 4 us).  As in
+// grid_barrier, waiting far too long sets an error and lets the block go.
+// With `flag`, its value and the error state come back in s_flag, read once every block has arrived.
+__device__ void fin_barrier(const FinArgs &A, unsigned nblk, unsigned turn, const unsigned *flag = nullptr,
+                            unsigned *s_flag = nullptr) {
     __syncthreads();
-    for (uint32_t l = tid; l < R; l += kBlock)
-        atomicAdd(&s_deg[l >> 1], (s_row[l + 1] - s_row[l]) << ((l & 1) * 16));
-    if (tid == 0) {
-        s_qt = 0;
-        s_nlvl = 0;
+    if (threadIdx.x == 0 && nblk > 1) {
+        __threadfence();
+        const unsigned grp = blockIdx.x / kBarGroup, groups = (nblk + kBarGroup - 1) / kBarGroup;
+        const unsigned size = grp + 1 < groups ? kBarGroup : nblk - grp * kBarGroup;
+        unsigned *mine = &A.bar[(1 + grp) * kBarLine];
+        unsigned *poll = groups > 1 ? &A.bar[0] : mine;
+        const unsigned target = groups > 1 ? turn * groups : turn * size;
+        if (atomicAdd(mine, 1u) + 1 == turn * size && groups > 1) {
+            __threadfence();
+            atomicAdd(&A.bar[0], 1u);
+        }
+        long spins = 0;
+        while (ld_relaxed(poll) < target) {
+            __builtin_amdgcn_s_sleep(1);
+            ++spins;
+            // (a block that found an error has left)
+            if ((spins & 1023) == 0 && ld_relaxed(&A.ctl->error)) break;
+            if (spins > kSpinLimit) {
+                atomicOr(&A.ctl->error, 1u);
+                break;
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     }
-    // this wavefront's segment of the live list: [lb, lb + lc)
-    const uint32_t seg = (R + kWaves - 1) / kWaves;
-    const uint32_t lb = wave * seg < R ? wave * seg : R;
-    uint32_t lc = (lb + seg < R ? lb + seg : R) - lb;
-    uint32_t h = 0, t = 0;
-    auto deg_of = [&](uint32_t l) { return (s_deg[l >> 1] >> ((l & 1) * 16)) & 0xffffu; };
-    // queue y, whose degree is d (no decrement of y runs between reading d and this)
-    auto mark = [&](uint32_t y, uint32_t d) { atomicAdd(&s_deg[y >> 1], (kMark - d) << ((y & 1) * 16)); };
-    // remove one edge end at y; a degree taken from k + 1 to k queues y
-    auto dec = [&](uint32_t y, uint32_t kk) {
-        const uint32_t sh = (y & 1) * 16;
-        const uint32_t old = (atomicSub(&s_deg[y >> 1], 1u << sh) >> sh) & 0xffffu;
-        if (old == kk + 1) {
-            atomicAdd(&s_deg[y >> 1], (kMark - kk) << sh);
-            const uint32_t p = atomicAdd(&s_qt, 1u);
-            if (p < R) s_q[p] = (uint16_t)y;
+    if (threadIdx.x == 0 && flag) *s_flag = (ld_relaxed(flag) ? 1u : 0u) | (ld_relaxed(&A.ctl->error) ? 2u : 0u);
+    __syncthreads();
+}
+
+// f(I) for every piece I that begins before entry d: nested, so that one jump skips the rest
+template <uint32_t I = 0, class F> __device__ __forceinline__ void pieces(uint32_t d, F f) {
+    if constexpr (I < kRegPieces) {
+        if (I * kPiece < d) {
+            f(std::integral_constant<uint32_t, I>());
+            pieces<I + 1>(d, f);
         }
-    };
-    while (true) {
-        __syncthreads();
-        if (tid == 0) {
-            s_keep = 0;
-            s_min = 0xffffffffu;
+    }
+}
+// The first kRegRow of d entries at b, two a lane and piece (the last piece may read past the end, into
+// the next row or the list's padding), and their values in s_v: 0 past the end, below every threshold
+// asked of them.
+__device__ __forceinline__ void row_entries(const uint16_t *__restrict__ lcol, uint32_t b, uint32_t d, unsigned lane,
+                                            uint32_t (&c)[kRegPieces]) {
+    pieces(d, [&](auto i) { __builtin_memcpy(&c[i], lcol + b + i * kPiece + 2 * lane, 4); });
+}
+__device__ __forceinline__ void row_values(const uint16_t *s_v, const uint32_t (&c)[kRegPieces], uint32_t d, unsigned lane,
+                                           uint32_t (&v)[2 * kRegPieces]) {
+    pieces(d, [&](auto i) {
+        const uint32_t j = i * kPiece + 2 * lane;
+        const uint32_t x = s_v[c[i] & 0xffffu], y = s_v[c[i] >> 16];
+        v[2 * i] = j < d ? x : 0u;
+        v[2 * i + 1] = j + 1 < d ? y : 0u;
+    });
+}
+// values of at least t >= 1 among them
+__device__ __forceinline__ uint32_t count_at_least(const uint32_t (&v)[2 * kRegPieces], uint32_t d, uint32_t t) {
+    uint32_t n = 0;
+    pieces(d, [&](auto i) {
+        n += (uint32_t)__popcll(__ballot(v[2 * i] >= t)) + (uint32_t)__popcll(__ballot(v[2 * i + 1] >= t));
+    });
+    return n;
+}
+// f(values, entries left) for the first kRegRow entries of a row (in c), then the next ones, while f
+// says to go on; the entries of the next stretch are read while f works on one
+template <class F>
+__device__ __forceinline__ void row_stretches(const uint16_t *__restrict__ lcol, const uint16_t *s_v, uint32_t b, uint32_t d,
+                                              unsigned lane, const uint32_t (&first)[kRegPieces], F f) {
+    uint32_t c[kRegPieces];
+#pragma unroll
+    for (uint32_t i = 0; i < kRegPieces; ++i) c[i] = first[i];
+    for (uint32_t j0 = 0;; j0 += kRegRow) {
+        const uint32_t left = d - j0;
+        uint32_t nx[kRegPieces], v[2 * kRegPieces];
+        if (left > kRegRow) row_entries(lcol, b + j0 + kRegRow, left - kRegRow, lane, nx);
+        row_values(s_v, c, left, lane, v);
+        if (!f(v, left) || left <= kRegRow) return;
+#pragma unroll
+        for (uint32_t i = 0; i < kRegPieces; ++i) c[i] = nx[i];
+    }
+}
+
+// The rows of up to kGroup consecutive vertices.
+struct GroupRows {
+    uint32_t rows;      // lane l <= nv: first entry of vertex l (the end of the last at l = nv)
+    uint32_t nv;
+    __device__ __forceinline__ uint32_t begin(uint32_t x) const { return __builtin_amdgcn_readlane(rows, x); }
+    // lane l: end of the l-th row from x on, relative to the first (far past 64 beyond the group)
+    __device__ __forceinline__ uint32_t ends(uint32_t x, uint32_t b, unsigned lane) const {
+        const uint32_t e = __shfl(rows, (x + 1 + lane) & 63, 64);
+        return x + 1 + lane <= nv ? e - b : 0x7fffffffu;
+    }
+};
+
+// lane's row among the packed ones (ends per lane, cnt of them): how many end at or before it
+__device__ __forceinline__ uint32_t pack_row(uint32_t ends, uint32_t cnt, unsigned lane) {
+    uint32_t r = 0;
+#pragma unroll
+    for (uint32_t s = kGroup; s > 0; s >>= 1) {
+        const uint32_t e = __shfl(ends, (r + s - 1) & 63, 64);
+        if (r + s <= cnt && e <= lane) r += s;
+    }
+    return r;
+}
+
+__device__ __forceinline__ uint64_t bits_between(uint32_t a, uint32_t b) {   // bits [a, b), b <= 64
+    return (b < 64 ? (1ull << b) - 1 : ~0ull) & ~(a < 64 ? (1ull << a) - 1 : ~0ull);
+}
+
+// Walks the rows of a group: rows that fit 64 entries together by pack(x, cnt, b, ends), a longer one
+// by row(x, b, d, c) with its first entries in c; the entries of a long row are read while the one
+// before it is worked on.
+template <class Pack, class Row>
+__device__ __forceinline__ void walk_rows(const GroupRows &G, const uint16_t *__restrict__ lcol, unsigned lane, Pack pack,
+                                          Row row) {
+    uint32_t c[kRegPieces], x = 0;
+    bool have = false;
+    while (x < G.nv) {
+        const uint32_t b = G.begin(x), ends = G.ends(x, b, lane);
+        const uint64_t fits = __ballot(ends <= 64);
+        const uint32_t cnt = (uint32_t)__ffsll((unsigned long long)~fits) - 1;   // (lane 63 never fits)
+        if (cnt > 0) {
+            pack(x, cnt, b, ends);
+            x += cnt;
+            have = false;
+            continue;
         }
-        __syncthreads();
-        const uint32_t level_start = t;
-        // level scan over this wavefront's live vertices: queue those of degree <= k, keep the
-        // others (written back in place: a survivor's new slot is never after its old one, and
-        // the wavefront reads a chunk before it writes any of it)
-        {
-            uint32_t nk = 0;
-            unsigned md = 0xffffffffu;
-            for (uint32_t i0 = 0; i0 < lc; i0 += 64) {
-                const uint32_t i = i0 + lane;
-                uint32_t l = 0, d = kMark;
-                if (i < lc) {
-                    l = s_live[lb + i];
-                    d = deg_of(l);
+        const uint32_t d = __builtin_amdgcn_readlane(ends, 0);
+        if (!have) row_entries(lcol, b, d, lane, c);
+        uint32_t nx[kRegPieces];
+        have = x + 1 < G.nv;
+        if (have) {
+            const uint32_t nb = G.begin(x + 1), nd = G.begin(x + 2) - nb;
+            have = nd > 64;
+            if (have) row_entries(lcol, nb, nd, lane, nx);
+        }
+        row(x, b, d, c);
+#pragma unroll
+        for (uint32_t i = 0; i < kRegPieces; ++i) c[i] = nx[i];
+        x += 1;
+    }
+}
+
+// New bounds of a group's vertices (lane x < nv: vertex x; its present bound h comes in), at least k0.
+__device__ __forceinline__ uint32_t group_bounds(const GroupRows &G, const uint16_t *__restrict__ lcol,
+                                                 const uint16_t *s_h, uint32_t h, uint32_t k0, unsigned lane) {
+    walk_rows(
+        G, lcol, lane,
+        [&](uint32_t x, uint32_t cnt, uint32_t b, uint32_t ends) {
+            const uint32_t len = __builtin_amdgcn_readlane(ends, cnt - 1);
+            const uint32_t r = pack_row(ends, cnt, lane);
+            const uint32_t H = __shfl(h, (x + r) & 63, 64);
+            const uint32_t prev = __shfl(ends, (r - 1) & 63, 64), end = __shfl(ends, r & 63, 64);
+            const uint32_t beg = r ? prev : 0u;
+            const bool in = lane < len;
+            const uint32_t v = in ? s_h[lcol[b + lane]] : 0u;
+            const uint64_t mine = in ? bits_between(beg, end) : 0ull;
+            const uint32_t c = (uint32_t)__popcll(__ballot(in && v >= H) & mine);
+            uint32_t lo = H, hi = H;
+            if (in && c < H) {
+                lo = c > k0 ? c : k0;
+                hi = H - 1;
+                if (lo > hi) lo = hi;   // (a bound is never below k0)
+            }
+            while (__ballot(lo < hi)) {
+                const uint32_t mid = (lo + hi + 1) >> 1;
+                const uint32_t cm = (uint32_t)__popcll(__ballot(in && v >= mid) & mine);
+                if (lo < hi) {
+                    if (cm >= mid) lo = mid;
+                    else hi = mid - 1;
                 }
-                const bool tk = d <= k, kp = d > k && d < kMarked;
-                const uint64_t mt = __ballot(tk), mk = __ballot(kp);
-                if (mt) {
-                    uint32_t qb = 0;
-                    if (lane == 0) qb = atomicAdd(&s_qt, (unsigned)__popcll(mt));
-                    qb = __shfl(qb, 0, 64);
-                    if (tk) {
-                        const uint32_t p = qb + (uint32_t)__popcll(mt & below);
-                        mark(l, d);
-                        if (p < R) s_q[p] = (uint16_t)l;
+            }
+            // lane y of the group: the result of its row, when it has entries
+            const uint32_t y = lane - x;
+            const uint32_t yp = __shfl(ends, (y - 1) & 63, 64), ye = __shfl(ends, y & 63, 64);
+            const uint32_t yb = y ? yp : 0u;
+            const uint32_t nh = __shfl(lo, yb & 63, 64);
+            if (lane >= x && y < cnt && ye > yb) h = nh;
+        },
+        [&](uint32_t x, uint32_t b, uint32_t d, const uint32_t (&e)[kRegPieces]) {
+            const uint32_t H = __builtin_amdgcn_readlane(h, x);
+            uint32_t lo, hi = H - 1, c = 0;
+            if (d <= kRegRow) {
+                uint32_t v[2 * kRegPieces];
+                row_values(s_h, e, d, lane, v);
+                c = count_at_least(v, d, H);
+                if (c >= H) return;
+                lo = c > k0 ? c : k0;
+                if (lo > hi) lo = hi;
+                while (lo < hi) {
+                    const uint32_t mid = (lo + hi + 1) >> 1;
+                    if (count_at_least(v, d, mid) >= mid) lo = mid;
+                    else hi = mid - 1;
+                }
+            } else {
+                row_stretches(lcol, s_h, b, d, lane, e, [&](const uint32_t (&v)[2 * kRegPieces], uint32_t left) {
+                    c += count_at_least(v, left, H);
+                    return c < H;
+                });
+                if (c >= H) return;
+                // a longer row is read once more, for a few thresholds below H: its bound falls below the
+                // smallest one that it misses (an upper bound still; the next phases go on from there)
+                constexpr uint32_t kOff[8] = {1, 2, 4, 8, 16, 64, 256, 1024};
+                uint32_t n[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+                row_stretches(lcol, s_h, b, d, lane, e, [&](const uint32_t (&v)[2 * kRegPieces], uint32_t left) {
+#pragma unroll
+                    for (int q = 0; q < 8; ++q)
+                        if (H > kOff[q] && H - kOff[q] > k0) n[q] += count_at_least(v, left, H - kOff[q]);
+                    return true;
+                });
+                lo = H - 1;
+#pragma unroll
+                for (int q = 0; q < 8; ++q)
+                    if (H > kOff[q] && H - kOff[q] > k0 && n[q] < H - kOff[q]) lo = H - kOff[q] - 1;
+            }
+            if (lane == x) h = lo;
+        });
+    return h;
+}
+
+// Which of a group's vertices (lane x: core number C; `left` the ones not yet removed) have at most
+// core(v) neighbours of value at least 2 core(v) + 1.
+__device__ __forceinline__ uint32_t group_removable(const GroupRows &G, const uint16_t *__restrict__ lcol,
+                                                    const uint16_t *s_v, uint32_t C, uint32_t left, unsigned lane) {
+    uint32_t take = 0;
+    walk_rows(
+        G, lcol, lane,
+        [&](uint32_t x, uint32_t cnt, uint32_t b, uint32_t ends) {
+            if ((((uint64_t)left >> x) & ((1ull << cnt) - 1)) == 0) return;
+            const uint32_t len = __builtin_amdgcn_readlane(ends, cnt - 1);
+            const uint32_t r = pack_row(ends, cnt, lane);
+            const uint32_t t = 2 * __shfl(C, (x + r) & 63, 64) + 1;
+            const bool in = lane < len;
+            const uint64_t m = __ballot(in && s_v[lcol[b + (in ? lane : 0u)]] >= t);
+            // lane y of the group counts its own row
+            const uint32_t y = lane - x;
+            const uint32_t yp = __shfl(ends, (y - 1) & 63, 64), ye = __shfl(ends, y & 63, 64);
+            const uint32_t yb = y ? yp : 0u;
+            const bool ok = lane >= x && y < cnt && (uint32_t)__popcll(m & bits_between(yb, ye)) <= C;
+            take |= (uint32_t)__ballot(ok);
+        },
+        [&](uint32_t x, uint32_t b, uint32_t d, const uint32_t (&e)[kRegPieces]) {
+            if (((left >> x) & 1u) == 0) return;
+            const uint32_t c = __builtin_amdgcn_readlane(C, x);
+            uint32_t n = 0;
+            row_stretches(lcol, s_v, b, d, lane, e, [&](const uint32_t (&v)[2 * kRegPieces], uint32_t left) {
+                n += count_at_least(v, left, 2 * c + 1);
+                return n <= c;
+            });
+            if (n <= c) take |= 1u << x;
+        });
+    return take & left;
+}
+
+// the first vertex v <= R whose work before it, lrow[v] + kVertexCost * v, is at least x (64 probes at
+// a time)
+__device__ __forceinline__ uint32_t split_vertex(const uint32_t *__restrict__ lrow, uint32_t R, uint64_t x, unsigned lane) {
+    uint32_t lo = 0, len = R;   // the answer is in [lo, lo + len]
+    while (len > 0) {
+        const uint32_t step = (len + 63) / 64, i = lo + lane * step;
+        const bool below = lane * step < len && (uint64_t)lrow[i < R ? i : R] + (uint64_t)kVertexCost * i < x;
+        const uint32_t c = (uint32_t)__popcll(__ballot(below));   // (a prefix of the lanes)
+        if (c == 0) return lo;
+        const uint32_t nlo = lo + (c - 1) * step + 1, nend = lo + c * step < lo + len ? lo + c * step : lo + len;
+        lo = nlo;
+        len = nend - nlo;
+    }
+    return lo;
+}
+
+__global__ void __launch_bounds__(kBlock)
+k_peel_finish(FinArgs A) {
+    __shared__ __attribute__((aligned(16))) uint16_t s_v[kTail];
+    __shared__ uint32_t s_cnt[kCoreLds];
+    __shared__ unsigned s_any, s_more, s_scan[kBlock / 64];
+    PeelCtl *ctl = A.ctl;
+    if (!ctl->ho || ctl->error) return;
+    constexpr uint32_t kBW = kBlock / 64;
+    const uint32_t R = (uint32_t)ctl->lres, k0 = ctl->ho_k, qbase = ctl->ho_tail;
+    uint32_t nblk = R <= kFinSmall ? 1u : (R + kPerWave * kBW - 1) / (kPerWave * kBW);
+    if (nblk > gridDim.x) nblk = gridDim.x;
+    if (blockIdx.x >= nblk) return;
+    const unsigned tid = threadIdx.x, lane = tid & 63;
+    const uint32_t W = nblk * kBW, gw = blockIdx.x * kBW + tid / 64;
+    const uint32_t gtid = blockIdx.x * kBlock + tid, gsize = nblk * kBlock;
+    unsigned turn = 0;
+    // this wavefront's vertices
+    const uint64_t work = (uint64_t)A.lrow[R] + (uint64_t)kVertexCost * R;
+    const uint32_t va = split_vertex(A.lrow, R, work * gw / W, lane);
+    const uint32_t vb = gw + 1 < W ? split_vertex(A.lrow, R, work * (gw + 1) / W, lane) : R;
+    auto group_rows = [&](uint32_t v) {
+        GroupRows G;
+        G.nv = vb - v < kGroup ? vb - v : kGroup;
+        G.rows = A.lrow[v + (lane < G.nv ? lane : G.nv)];
+        return G;
+    };
+    const GroupRows G0 = group_rows(va < vb ? va : (vb < R ? vb : R));
+    // bounds: the degrees; no position taken
+    for (uint32_t v = gtid; v < R; v += gsize) A.val[v] = (uint16_t)(A.lrow[v + 1] - A.lrow[v]);
+    for (uint32_t c = gtid; c <= R; c += gsize) A.cur[c] = 0;
+    fin_barrier(A, nblk, ++turn);
+    auto load_values = [&](const uint16_t *from) {
+        const uint4 *src = reinterpret_cast<const uint4 *>(from);
+        uint4 *dst = reinterpret_cast<uint4 *>(s_v);
+        for (uint32_t i = tid; i < (R + 7) / 8; i += kBlock) dst[i] = src[i];
+        if (tid == 0) s_any = 0;
+    };
+    // every block learns whether any had something left to do (phase ph): bit 0; bit 1: an error
+    auto any_left = [&](bool mine, uint32_t ph) {
+        if (__ballot(mine) && lane == 0) s_any = 1;
+        __syncthreads();
+        if (tid == 0 && s_any)
+            __hip_atomic_store(&ctl->fin[ph % 3], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        fin_barrier(A, nblk, ++turn, &ctl->fin[ph % 3], &s_more);
+        const unsigned more = s_more;
+        // read by every block before the next barrier: cleared for the phase after next
+        if (gtid == 0)
+            __hip_atomic_store(&ctl->fin[(ph + 2) % 3], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return more;
+    };
+    // core numbers
+    uint32_t ph = 0;
+    for (;; ++ph) {
+        load_values(A.val);
+        __syncthreads();
+        bool fell = false;
+        for (uint32_t v0 = va; v0 < vb; v0 += kGroup) {
+            const GroupRows G = v0 == va ? G0 : group_rows(v0);
+            const uint32_t v = v0 + lane;
+            const uint32_t h = lane < G.nv ? s_v[v] : 0u;
+            const uint32_t nh = group_bounds(G, A.lcol, s_v, h, k0, lane);
+            if (lane < G.nv && nh != h) {
+                A.val[v] = (uint16_t)nh;
+                s_v[v] = (uint16_t)nh;
+                fell = true;
+            }
+        }
+        const unsigned more = any_left(fell, ph);
+        if (more & 2u) return;
+        if (!more) break;
+        if (ph > 2 * R + 64) {   // cannot happen: a phase settles at least one vertex
+            if (gtid == 0) atomicOr(&ctl->error, 16u);
+            return;
+        }
+    }
+    ++ph;
+    // shells: s_v holds the core numbers (nothing fell in the last phase)
+    {
+        uint16_t *first = A.val + kTail;
+        for (uint32_t v = va + lane; v < vb; v += 64) first[v] = (uint16_t)(2u * s_v[v] + 1u);
+    }
+    fin_barrier(A, nblk, ++turn);
+    uint32_t r = 0;
+    for (;; ++r, ++ph) {
+        const uint16_t *in = A.val + (r & 1 ? 0 : kTail);
+        uint16_t *out = A.val + (r & 1 ? kTail : 0);
+        load_values(in);
+        for (uint32_t c = tid; c < kCoreLds; c += kBlock) s_cnt[c] = 0;
+        __syncthreads();
+        bool rest = false, mine = false;   // mine: this lane's vertex of the first group goes now
+        uint32_t at = 0, core = 0;
+        for (uint32_t v0 = va; v0 < vb; v0 += kGroup) {
+            const GroupRows G = v0 == va ? G0 : group_rows(v0);
+            const uint32_t v = v0 + lane;
+            const uint32_t x = lane < G.nv ? s_v[v] : 0u, C = x >> 1;
+            const uint32_t left = (uint32_t)__ballot((x & 1u) != 0);
+            uint32_t take = 0;
+            if (left) {
+                take = group_removable(G, A.lcol, s_v, C, left, lane);
+                if (lane < G.nv && (take >> lane) & 1u) {
+                    if (v0 == va && C < kCoreLds) {
+                        mine = true;
+                        core = C;
+                        at = atomicAdd(&s_cnt[C], 1u);
+                    } else {
+                        A.pos[v] = atomicAdd(&A.cur[C], 1u);
                     }
                 }
-                if (kp) {
-                    s_live[lb + nk + (uint32_t)__popcll(mk & below)] = (uint16_t)l;
-                    md = d < md ? d : md;
-                }
-                nk += (uint32_t)__popcll(mk);
+                rest |= (left & ~take) != 0;
             }
-            lc = nk;
-            md = wave_min(md);
-            if (lane == 0 && nk) {
-                atomicAdd(&s_keep, nk);
-                atomicMin(&s_min, md);
-            }
+            if (lane < G.nv) out[v] = (uint16_t)(x - ((take >> lane) & 1u));
+        }
+        // positions: one atomic per block and shell
+        __syncthreads();
+        for (uint32_t c = tid; c < kCoreLds; c += kBlock) {
+            const uint32_t n = s_cnt[c];
+            if (n) s_cnt[c] = atomicAdd(&A.cur[c], n);
         }
         __syncthreads();
-        t = s_qt;
-        const uint32_t keep = s_keep, md = s_min;
-        if (keep == 0) h = t;   // every remaining vertex is queued: nothing left to update
-        // rounds: remove s_q[h, t)
-        while (h < t) {
-            const uint32_t f = t - h;
-            uint32_t i0, first, stride, step;
-            if (f >= kWaves) {
-                i0 = h + wave; first = lane; stride = 64; step = kWaves;
-            } else {
-                const uint32_t per = kWaves / f;
-                i0 = h + wave / per; first = (wave % per) * 64 + lane; stride = per * 64; step = f;
-                if (wave / per >= f) i0 = t;
-            }
-            for (uint32_t i = i0; i < t; i += step) {
-                const uint32_t x = s_q[i];
-                const uint32_t e = s_row[x + 1];
-                uint32_t j = s_row[x] + first;
-                for (; j + 3 * stride < e; j += 4 * stride) {
-                    const uint32_t y0 = lcol[j], y1 = lcol[j + stride], y2 = lcol[j + 2 * stride],
-                                   y3 = lcol[j + 3 * stride];
-                    dec(y0, k);
-                    dec(y1, k);
-                    dec(y2, k);
-                    dec(y3, k);
-                }
-                for (; j < e; j += stride) dec(lcol[j], k);
-            }
-            ++rounds;
-            __syncthreads();
-            h = t;
-            t = s_qt;
-            __syncthreads();
-        }
-        if (t > level_start && tid == 0) {   // this level removed s_q[level_start, t)
-            const uint32_t li = s_nlvl++;
-            lvl[2 * li] = level_start;
-            lvl[2 * li + 1] = k;
-        }
-        if (t >= R) break;
-        uint32_t next = k + 1;
-        if (t == level_start && md != 0xffffffffu && md > next) next = md;
-        k = next;
-        if (k > R + qbase + 1) {   // cannot happen, as in the grid loop
-            if (tid == 0) atomicOr(&ctl->error, 2u);
-            break;
+        if (mine) A.pos[va + lane] = s_cnt[core] + at;
+        const unsigned more = any_left(rest, ph);
+        if (more & 2u) return;
+        if (!more) break;
+        if (r > 2 * R + 64) {   // cannot happen: every shell loses a vertex in a round
+            if (gtid == 0) atomicOr(&ctl->error, 16u);
+            return;
         }
     }
+    // first position of every shell: every block writes the same ones, and reads its own back
+    uint32_t run = 0, top = 0;
+    for (uint32_t c0 = 0; c0 <= R && run < R; c0 += kBlock) {
+        const uint32_t c = c0 + tid, n = c <= R ? A.cur[c] : 0u;
+        uint32_t x = n;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t y = __shfl_up(x, o, 64);
+            if (lane >= (unsigned)o) x += y;
+        }
+        if (lane == 63) s_scan[tid / 64] = x;
+        __syncthreads();
+        uint32_t before = 0, total = 0;
+        for (uint32_t w = 0; w < kBW; ++w) {
+            before += w < tid / 64 ? s_scan[w] : 0u;
+            total += s_scan[w];
+        }
+        if (c <= R) A.base[c] = run + before + x - n;
+        if (n) top = c;
+        run += total;
+        __syncthreads();
+    }
+    if (tid == 0) s_any = 0;
     __syncthreads();
-    // queue positions and core numbers of the removed vertices, in removal order
-    const uint32_t nl = s_nlvl, nq = t < R ? t : R;
-    __threadfence_block();
-    for (uint32_t p = tid; p < nq; p += kBlock) {
-        const uint32_t v = rlist[s_q[p]];
-        queue[qbase + p] = v;
-        uint32_t lo = 0, len = nl;   // last boundary at or before p
-        while (len > 0) {
-            const uint32_t half = len >> 1;
-            if (lvl[2 * (lo + half)] <= p) {
-                lo += half + 1;
-                len -= half + 1;
-            } else {
-                len = half;
-            }
+    if (top) atomicMax(&s_any, top);
+    __syncthreads();
+    // positions and core numbers, each by the lane that took the position
+    for (uint32_t v0 = va; v0 < vb; v0 += kGroup) {
+        const uint32_t v = v0 + lane;
+        if (lane < kGroup && v < vb) {
+            const uint32_t c = s_v[v] >> 1, p = qbase + A.base[c] + A.pos[v], x = A.rlist[v];
+            if (p < qbase + R) A.queue[p] = x;
+            else atomicOr(&ctl->error, 16u);
+            A.level[x] = c;
         }
-        level[v] = lo > 0 ? lvl[2 * (lo - 1) + 1] : k;
     }
-    if (tid == 0) {
-        __hip_atomic_store(&ctl->qtail, qbase + nq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        ctl->kappa = k;
-        ctl->rounds = rounds;
-        ctl->nlvl = nl;
+    if (gtid == 0) {
+        ctl->kappa = s_any > k0 ? s_any : k0;
+        ctl->rounds = ctl->ho_rounds + r + 1;
+        __hip_atomic_store(&ctl->qtail, qbase + R, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 
@@ -350,8 +666,8 @@ __global__ void __launch_bounds__(kBlock)
 k_peel(uint32_t n, const uint32_t *__restrict__ row, const uint32_t *__restrict__ col,
        int *__restrict__ deg, uint32_t *__restrict__ level, uint32_t *__restrict__ queue,
        uint32_t *__restrict__ alive_a, uint32_t *__restrict__ alive_b, uint32_t *__restrict__ loc,
-       uint32_t *__restrict__ rlist, uint32_t *__restrict__ lrow, uint32_t *__restrict__ lvl,
-       uint16_t *__restrict__ lcol, uint64_t lcol_cap, uint32_t tail_cap, uint32_t *__restrict__ ovf0,
+       uint32_t *__restrict__ rlist, uint32_t *__restrict__ lrow, uint64_t lcol_cap, uint32_t tail_cap,
+       uint32_t *__restrict__ ovf0,
        uint32_t *__restrict__ ovf1, PeelCtl *__restrict__ ctl) {
     // the whole grid takes part while many vertices remain, then ever fewer of its first blocks
     unsigned nblk = gridDim.x;
@@ -630,7 +946,7 @@ k_peel(uint32_t n, const uint32_t *__restrict__ row, const uint32_t *__restrict_
         }
         return;
     }
-    // Hand over to one workgroup.  Every remaining vertex is in cur with its degree (the number
+    // Hand over to the finish.  Every remaining vertex is in cur with its degree (the number
     // of its remaining neighbours, since every queued vertex has been removed): give it a local
     // id and that many consecutive entries of the local adjacency (one 64-bit atomic per
     // wavefront reserves both, so rows follow local ids and lrow is a CSR row array), then write
@@ -714,17 +1030,6 @@ k_local_adj(const uint32_t *__restrict__ row, const uint32_t *__restrict__ col, 
     }
 }
 
-// the one-workgroup finish after a hand-over
-__global__ void __launch_bounds__(kBlock)
-k_peel_finish(const uint32_t *__restrict__ rlist, const uint32_t *__restrict__ lrow, const uint16_t *__restrict__ lcol,
-              uint32_t *__restrict__ lvl, uint32_t *__restrict__ level, uint32_t *__restrict__ queue,
-              PeelCtl *__restrict__ ctl) {
-    __shared__ __attribute__((aligned(16))) uint32_t s_mem[kLdsWords];
-    if (!ctl->ho || ctl->error) return;
-    peel_tail((uint32_t)ctl->lres, ctl->ho_tail, ctl->ho_k, ctl->ho_rounds, rlist, lrow, lcol, lvl, level, queue, ctl,
-              s_mem);
-}
-
 __global__ void k_finish(uint32_t n, const uint32_t *__restrict__ queue, uint32_t *__restrict__ rank) {
     uint32_t p = blockIdx.x * 256 + threadIdx.x;
     if (p < n) rank[queue[p]] = p;
@@ -736,7 +1041,7 @@ int peel(dt_graph *g) {
     dt_ctx *ctx = g->ctx;
     hipStream_t st = ctx->stream;
     const uint32_t n = g->n;
-    DevMem deg, alive, alive2, ctlm, loc, rlist, lrow, lvl, lcol, ovf0, ovf1;
+    DevMem deg, alive, alive2, ctlm, loc, rlist, lrow, lcol, ovf0, ovf1, fin;
     DT_TRY(dev_alloc(ctx, deg, (uint64_t)n * 4));
     DT_TRY(dev_alloc(ctx, alive, (uint64_t)n * 4));
     DT_TRY(dev_alloc(ctx, alive2, (uint64_t)n * 4));
@@ -745,16 +1050,24 @@ int peel(dt_graph *g) {
     DT_TRY(dev_alloc(ctx, g->core, (uint64_t)n * 4));
     DT_TRY(dev_alloc(ctx, g->order, (uint64_t)n * 4));
     DT_TRY(dev_alloc(ctx, g->rank, (uint64_t)n * 4));
-    DT_TRY(dev_alloc(ctx, ctlm, sizeof(PeelCtl)));
-    // the one-workgroup finish: at most tail_cap vertices, their adjacency within 2 m_static
-    // entries and below tail_cap (tail_cap - 1) as well
-    const uint32_t tail_cap = std::min<uint32_t>(g->tuning.peel_tail ? g->tuning.peel_tail : kTail, kTail);
+    // control block, then the finish's barrier counters (cleared together)
+    constexpr uint64_t kCtlBytes = 512, kBarBytes = (1 + 1024 / kBarGroup) * kBarLine * 4;
+    static_assert(sizeof(PeelCtl) <= kCtlBytes, "control block layout");
+    DT_TRY(dev_alloc(ctx, ctlm, kCtlBytes + kBarBytes));
+    // the finish: at most tail_cap vertices, their adjacency within 2 m_static entries and below
+    // tail_cap (tail_cap - 1) as well
+    // (twice a core number and one more fit 16 bits: of 32768 vertices always, of more while the pairs
+    // are too few for a core number of 2^15)
+    const uint32_t tail_max = g->m_s < (1ull << 28) ? kTail : kTail / 2;
+    const uint32_t tail_cap = std::min<uint32_t>(g->tuning.peel_tail ? g->tuning.peel_tail : tail_max, tail_max);
     const uint64_t lcol_cap = std::min<uint64_t>(2ull * g->m_s, (uint64_t)tail_cap * (tail_cap - 1));
     DT_TRY(dev_alloc(ctx, loc, (uint64_t)n * 4));
     DT_TRY(dev_alloc(ctx, rlist, (uint64_t)tail_cap * 4));
     DT_TRY(dev_alloc(ctx, lrow, ((uint64_t)tail_cap + 1) * 4));
-    DT_TRY(dev_alloc(ctx, lvl, (uint64_t)tail_cap * 8));
-    DT_TRY(dev_alloc(ctx, lcol, (lcol_cap + 1) * 2));
+    // its values (two buffers), shell starts and cursors, and positions
+    constexpr uint64_t kFinWords = kTail + 2ull * (kTail + 64) + kTail;
+    DT_TRY(dev_alloc(ctx, fin, kFinWords * 4));
+    DT_TRY(dev_alloc(ctx, lcol, (lcol_cap + kPiece) * 2));   // (the finish reads whole pieces)
     if (n == 0) {
         g->kappa = 0;
         g->peel_rounds = 0;
@@ -766,7 +1079,8 @@ int peel(dt_graph *g) {
     if (per_cu <= 0) return fail(DT_EDEVICE, "peel kernel cannot be resident");
     unsigned grid = kGridWide;
     if (grid > (unsigned)ctx->num_cus * (unsigned)per_cu) grid = (unsigned)ctx->num_cus * (unsigned)per_cu;
-    DT_HIP(hipMemsetAsync(ctlm.ptr, 0, sizeof(PeelCtl), st));
+    grid = std::min(grid, grid_for(n, kBlock));
+    DT_HIP(hipMemsetAsync(ctlm.ptr, 0, kCtlBytes + kBarBytes, st));
     uint32_t *level = g->core.as<uint32_t>();
     uint32_t *queue = g->order.as<uint32_t>();
     const uint32_t *row = g->row.as<uint32_t>(), *col = g->col.as<uint32_t>();
@@ -774,13 +1088,12 @@ int peel(dt_graph *g) {
     uint32_t *aa = alive.as<uint32_t>(), *ab = alive2.as<uint32_t>();
     PeelCtl *ctl = ctlm.as<PeelCtl>();
     uint32_t nn = n;
-    uint32_t *locp = loc.as<uint32_t>(), *rl = rlist.as<uint32_t>(), *lb = lrow.as<uint32_t>(),
-             *ld = lvl.as<uint32_t>();
+    uint32_t *locp = loc.as<uint32_t>(), *rl = rlist.as<uint32_t>(), *lb = lrow.as<uint32_t>();
     uint16_t *lc = lcol.as<uint16_t>();
     uint64_t lcap = lcol_cap;
     uint32_t tcap = tail_cap;
     uint32_t *o0 = ovf0.as<uint32_t>(), *o1 = ovf1.as<uint32_t>();
-    void *args[] = {&nn, &row, &col, &degp, &level, &queue, &aa, &ab, &locp, &rl, &lb, &ld, &lc, &lcap, &tcap,
+    void *args[] = {&nn, &row, &col, &degp, &level, &queue, &aa, &ab, &locp, &rl, &lb, &lcap, &tcap,
                     &o0, &o1, &ctl};
     prof_begin(ctx, kProfPeel, st);
     DT_HIP(hipLaunchCooperativeKernel((const void *)k_peel, dim3(grid), dim3(kBlock), args, 0, st));
@@ -790,10 +1103,26 @@ int peel(dt_graph *g) {
     prof_end(ctx, kProfPeelAdj, st);
     DT_HIP(hipGetLastError());
     prof_begin(ctx, kProfPeelTail, st);
-    k_peel_finish<<<1, kBlock, 0, st>>>(rl, lb, lc, ld, level, queue, ctl);
+    FinArgs fa;
+    fa.rlist = rl;
+    fa.lrow = lb;
+    fa.lcol = lc;
+    fa.base = fin.as<uint32_t>();
+    fa.cur = fa.base + kTail + 64;
+    fa.pos = fa.cur + kTail + 64;
+    fa.val = reinterpret_cast<uint16_t *>(fa.pos + kTail);
+    fa.level = level;
+    fa.queue = queue;
+    fa.bar = reinterpret_cast<unsigned *>(ctlm.as<uint8_t>() + kCtlBytes);
+    fa.ctl = ctl;
+    // as many blocks as the most vertices it can get fill (co-resident: one per CU)
+    const unsigned fgrid = std::min<unsigned>(std::min<unsigned>((unsigned)ctx->num_cus, 1024u),
+                                              grid_for(std::min(n, tail_cap), kPerWave * (kBlock / 64)));
+    void *fargs[] = {&fa};
+    DT_HIP(hipLaunchCooperativeKernel((const void *)k_peel_finish, dim3(fgrid), dim3(kBlock), fargs, 0, st));
     prof_end(ctx, kProfPeelTail, st);
     DT_HIP(hipGetLastError());
-    PeelCtl h{};
+    PeelCtl &h = *reinterpret_cast<PeelCtl *>(ctx->pinned_stage);
     DT_HIP(hipMemcpyAsync(&h, ctl, sizeof(h), hipMemcpyDeviceToHost, st));
     DT_HIP(hipStreamSynchronize(st));
     if (h.error & 1u) return fail(DT_EDEVICE, "core peel barrier timed out");

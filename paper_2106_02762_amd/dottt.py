@@ -233,7 +233,7 @@ def dt_graph_build(g):
 def dt_graph_set_tuning(g, light_pair_cap=0, heavy_chunk=0, medium_pair_cap=0, force_path=0,
                         peel_tail=0, order_method=0, medium_cost_pct=0, autotune=0):
     """force_path: 0 unit records and the split, 1 all light, 2 all heavy, 3 all medium.
-    peel_tail: vertices the level peel leaves to one workgroup (next build; 0 keeps the setting).
+    peel_tail: vertices the level peel leaves to its finish (next build; 0 keeps the setting).
     order_method: 0 the level-by-level peel, 1 h-index core numbers and shell rounds.
     medium_cost_pct: weight of the prefix procedures' cost in the medium / heavy split (percent).
     autotune: 0 tune per size class when not cached, 1 never, 2 tune again now."""
