@@ -93,43 +93,50 @@ k_batch(const BItem *__restrict__ items, const uint32_t *__restrict__ n_items_p,
     static_assert(kBB == 256, "a heavy count chunk is 256 source edges, one per thread");
     const uint32_t n_items = *n_items_p;
     const unsigned lane = threadIdx.x & 63, wave = threadIdx.x / 64;
+    __shared__ unsigned long long s_col[8 * kBB];
     for (uint32_t it = blockIdx.x; it < n_items; it += gridDim.x) {
         const BItem I = items[it];
         Acc<false> acc;
         if (I.kind == 2) {
             heavy_count_chunk(hqs[I.e], I.b, acc);
-            block_store<kBB>(acc.t, part + 8 * (uint64_t)it);
-            __syncthreads();
-            continue;
-        }
-        const BQuery Q = qs[I.q];
-        if (I.kind == 3) {
-            uint32_t c[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-            unit_run<false, kBB>(Q.unit, I.b, I.e, Q.u, c, nullptr);
-#pragma unroll
-            for (int j = 0; j < 8; ++j) acc.t[j] = c[j];
-        } else if (I.kind == 0) {
-            for (uint64_t i = I.b + threadIdx.x; i < I.e; i += kBB) light_tri(Q.light, i, Q.eoff, Q.key, Q.q, acc);
         } else {
-            for (uint64_t b = I.b + 64 * wave; b < I.e; b += kBB)
-                medium_lanes(Q.medium, Q.mitems, b + lane, b + lane < I.e, Q.eoff, Q.key, Q.q, acc, lane, Q.mlev);
+            const BQuery Q = qs[I.q];
+            if (I.kind == 3) {
+                uint32_t c[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+                unit_run<false, kBB>(Q.unit, I.b, I.e, Q.u, c, nullptr);
+#pragma unroll
+                for (int j = 0; j < 8; ++j) acc.t[j] = c[j];
+            } else {
+                AccLane<kBB, 1> pairs(s_col);
+                if (I.kind == 0) {
+                    for (uint64_t i = I.b + threadIdx.x; i < I.e; i += kBB)
+                        light_tri(Q.light[3 * i], Q.light[3 * i + 1], Q.light[3 * i + 2], Q.eoff, Q.key, Q.q, pairs);
+                } else {
+                    for (uint64_t b = I.b + 64 * wave; b < I.e; b += kBB)
+                        medium_lanes(Q.medium, Q.mitems, b + lane, b + lane < I.e, Q.eoff, Q.key, Q.q, pairs, lane, Q.mlev);
+                }
+                pairs.get(acc.t);
+            }
         }
         block_store<kBB>(acc.t, part + 8 * (uint64_t)it);
         __syncthreads();
     }
 }
 
-// out[i] = sum of the partials of query i's items [qfirst[i], qfirst[i+1])
+// out[i] = sum of the partials of query i's items [qfirst[i], qfirst[i+1]): a wavefront per query (four a block), lane
+// 8 o + j adding type j of every eighth item from the o-th on
 __global__ void k_batch_reduce(const uint32_t *__restrict__ nq_p, const uint32_t *__restrict__ qfirst,
                                const int64_t *__restrict__ part, int64_t *__restrict__ out) {
-    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    const uint64_t i = (uint64_t)blockIdx.x * 4 + threadIdx.x / 64;
+    const uint32_t lane = threadIdx.x & 63;
     if (i >= *nq_p) return;
-    int64_t t[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    for (uint32_t it = qfirst[i]; it < qfirst[i + 1]; ++it)
+    const uint32_t e = qfirst[i + 1];
+    int64_t t = 0;
+#pragma unroll 4
+    for (uint32_t it = qfirst[i] + lane / 8; it < e; it += 8) t += part[8 * (uint64_t)it + (lane & 7)];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) t[j] += part[8 * (uint64_t)it + j];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) out[8 * (uint64_t)i + j] = t[j];
+    for (int o = 8; o < 64; o <<= 1) t += __shfl_xor((long long)t, o, 64);
+    if (lane < 8) out[8 * i + lane] = t;
 }
 
 template <class T> int host_grow(T *&p, uint64_t &cap, uint64_t want) {
@@ -365,7 +372,7 @@ struct BatchRunner {
         k_bheavy_prefix<<<grid, kPrefixBlock, 0, stream>>>(d_hq.as<HeavyArgs>(), d_hpre.as<HItem>(), cnt + 3, 2);
         k_batch<<<grid, kBB, 0, stream>>>(d_items.as<BItem>(), cnt, d_q.as<BQuery>(), d_hq.as<HeavyArgs>(),
                                           d_part.as<int64_t>());
-        k_batch_reduce<<<grid_for(cap_q, 256), 256, 0, stream>>>(d_counts.as<uint32_t>() + 1, d_qfirst.as<uint32_t>(),
+        k_batch_reduce<<<grid_for(cap_q, 4), 256, 0, stream>>>(d_counts.as<uint32_t>() + 1, d_qfirst.as<uint32_t>(),
                                                                  d_part.as<int64_t>(), d_out.as<int64_t>());
         (void)hipMemcpyAsync(h_out, d_out.ptr, cap_q * 8 * sizeof(int64_t), hipMemcpyDeviceToHost, stream);
         hipError_t e = hipStreamEndCapture(stream, &graph);

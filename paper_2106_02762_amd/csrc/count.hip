@@ -45,25 +45,43 @@ namespace {
 // ACC: Acc<false> (int64 type counts), Acc<true> (the 48 cells by atomics, no partials) or AccW
 // (128-bit type counts, 16-word partial slots)
 template <class ACC> constexpr bool kCells = std::is_same<ACC, Acc<true>>::value;
+template <class ACC> constexpr int kAccWords = std::is_same<ACC, AccW>::value ? 2 : 1;
+
+// body(accumulator) of a pairwise kernel with accumulator ACC, then its block's partial slot
+template <class ACC, unsigned BLOCK, class BODY>
+__device__ __forceinline__ void with_pairwise(int64_t *__restrict__ partial, int64_t *__restrict__ cells, BODY &&body) {
+    if constexpr (kCells<ACC>) {
+        AccCells acc{cells};
+        body(acc);
+    } else {
+        __shared__ unsigned long long s_col[8 * kAccWords<ACC> * BLOCK];
+        AccLane<BLOCK, kAccWords<ACC>> acc(s_col);
+        body(acc);
+        ACC out;
+        acc.get(out.t);
+        acc_store<BLOCK>(out, partial, blockIdx.x);
+    }
+}
 
 template <class ACC, unsigned BLOCK>
 __global__ void __launch_bounds__(BLOCK)
 k_light(Ranges R, const uint32_t *__restrict__ tri, const uint32_t *__restrict__ eoff,
         const uint64_t *__restrict__ key, DQuery q, int64_t *__restrict__ partial,
         int64_t *__restrict__ cells, unsigned long long *__restrict__ visits) {
-    ACC acc;
-    acc.cells = cells;
-    const uint64_t n_tri = R.pre[R.n];
-    const uint32_t nblk = gridDim.x;
-    const uint32_t b = xcd_block(blockIdx.x, nblk);
-    const uint64_t per = (n_tri + nblk - 1) / nblk;
-    const uint64_t beg = (uint64_t)b * per;
-    const uint64_t end = beg + per < n_tri ? beg + per : n_tri;
-    uint32_t r = 0;
-    for (uint64_t i = beg + threadIdx.x; i < end; i += BLOCK)
-        light_tri(tri, range_at(R, r, i), eoff, key, q, acc);
-    add_visits(visits, acc.visits);
-    if (!kCells<ACC>) acc_store<BLOCK>(acc, partial, blockIdx.x);
+    with_pairwise<ACC, BLOCK>(partial, cells, [&](auto &acc) {
+        const uint64_t n_tri = R.pre[R.n];
+        const uint32_t nblk = gridDim.x;
+        const uint32_t b = xcd_block(blockIdx.x, nblk);
+        const uint64_t per = (n_tri + nblk - 1) / nblk;
+        const uint64_t beg = (uint64_t)b * per;
+        const uint64_t end = beg + per < n_tri ? beg + per : n_tri;
+        uint32_t r = 0;
+        for (uint64_t i = beg + threadIdx.x; i < end; i += BLOCK) {
+            const uint64_t t = range_at(R, r, i);
+            light_tri(tri[3 * t], tri[3 * t + 1], tri[3 * t + 2], eoff, key, q, acc);
+        }
+        add_visits(visits, acc.visits);
+    });
 }
 
 // medium path: wave w takes the 64 entries from 64 w on, then those from 64 (w + W) on, ...;
@@ -73,22 +91,21 @@ __global__ void __launch_bounds__(BLOCK)
 k_medium(Ranges R, const uint32_t *__restrict__ med, const uint32_t *__restrict__ ent,
          const uint8_t *__restrict__ lev, const uint32_t *__restrict__ eoff, const uint64_t *__restrict__ key,
          DQuery q, int64_t *__restrict__ partial, int64_t *__restrict__ cells, unsigned long long *__restrict__ visits) {
-    ACC acc;
-    acc.cells = cells;
-    const unsigned lane = threadIdx.x & 63;
-    const uint64_t n_ent = R.pre[R.n];
-    const uint64_t W = (uint64_t)gridDim.x * (BLOCK / 64);
-    uint32_t r = 0;
-    uint64_t vis = 0;
-    for (uint64_t b = ((uint64_t)blockIdx.x * (BLOCK / 64) + threadIdx.x / 64) * 64; b < n_ent; b += W * 64) {
-        const uint64_t j = b + lane;
-        const bool active = j < n_ent;
-        // one visit per outer edge, plus the wavefront's close pairs (counted by lane 0)
-        const uint32_t pairs = medium_lanes(med, ent, active ? range_at(R, r, j) : 0, active, eoff, key, q, acc, lane, lev);
-        vis += (active ? 1u : 0u) + (lane == 0 ? pairs : 0u);
-    }
-    add_visits(visits, vis);
-    if (!kCells<ACC>) acc_store<BLOCK>(acc, partial, blockIdx.x);
+    with_pairwise<ACC, BLOCK>(partial, cells, [&](auto &acc) {
+        const unsigned lane = threadIdx.x & 63;
+        const uint64_t n_ent = R.pre[R.n];
+        const uint64_t W = (uint64_t)gridDim.x * (BLOCK / 64);
+        uint32_t r = 0;
+        uint64_t vis = 0;
+        for (uint64_t b = ((uint64_t)blockIdx.x * (BLOCK / 64) + threadIdx.x / 64) * 64; b < n_ent; b += W * 64) {
+            const uint64_t j = b + lane;
+            const bool active = j < n_ent;
+            // one visit per outer edge, plus the wavefront's close pairs (counted by lane 0)
+            const uint32_t pairs = medium_lanes(med, ent, active ? range_at(R, r, j) : 0, active, eoff, key, q, acc, lane, lev);
+            vis += (active ? 1u : 0u) + (lane == 0 ? pairs : 0u);
+        }
+        add_visits(visits, vis);
+    });
 }
 
 // unit path: block b takes a contiguous run of the records [beg, end)
@@ -192,41 +209,15 @@ struct SweepQ {
     uint32_t qlev;    // its level: the pass's medium / heavy split
 };
 
-// adds a sweep's contributions to one triple's eight LDS counters (of this wavefront)
-struct AccSweep {
-    unsigned long long *s;
-    template <class CA, class CB> __device__ __forceinline__ void add2(bool first, int64_t v) {
-        if (v) atomicAdd(&s[first ? CA::type : CB::type], (unsigned long long)v);
-    }
-    template <class C> __device__ __forceinline__ void add(int64_t v) {
-        if (v) atomicAdd(&s[C::type], (unsigned long long)v);
-    }
-};
-
-// The (uv, uw) pairs of one light triangle's direction lists A, B, each tested against every
-// triple: the enumeration and the keys are shared, the searches that depend on the deltas are not.
-template <int A, int B>
-__device__ __forceinline__ void light_pairs_sweep(const uint64_t *__restrict__ key, const Lists &L, const SweepQ &Q,
-                                                  unsigned long long *sw) {
-    const uint32_t xb = L.lo[A], xe = L.hi[A], yb = L.lo[2 + B], ye = L.hi[2 + B];
-    const int shift = Q.q[0].shift;
-    for (uint32_t ix = xb; ix < xe; ++ix) {
-        const uint64_t kx = key[ix];
-        for (uint32_t iy = yb; iy < ye; ++iy) {
-            const uint64_t ky = key[iy];
-            const bool uv_first = kx < ky;
-            const uint64_t k_lo = uv_first ? kx : ky, k_hi = uv_first ? ky : kx;
-            const int64_t t_lo = (int64_t)(k_lo >> shift), t_hi = (int64_t)(k_hi >> shift);
-            const int64_t gap = t_hi - t_lo;
-            if (gap > Q.d13max) continue;
-            for (uint32_t j = 0; j < Q.k; ++j) {
-                const DQuery &q = Q.q[j];
-                if (gap > q.d13) continue;
-                AccSweep a{sw + 8 * j};
-                light_third<A, B, 0>(key, L, q, uv_first, k_lo, k_hi, t_lo, t_hi, gap, a);
-                light_third<A, B, 1>(key, L, q, uv_first, k_lo, k_hi, t_lo, t_hi, gap, a);
-            }
-        }
+// one (uv edge, uw edge) pair against every triple
+__device__ __forceinline__ void sweep_pair(const uint64_t *__restrict__ key, uint32_t z0, uint32_t z1, uint32_t z2,
+                                           const SweepQ &Q, uint32_t d_uv, uint32_t d_uw, uint64_t k_uv, uint64_t k_uw,
+                                           unsigned long long *sw) {
+    const int64_t t_uv = (int64_t)(k_uv >> Q.q[0].shift), t_uw = (int64_t)(k_uw >> Q.q[0].shift);
+    if ((t_uv < t_uw ? t_uw - t_uv : t_uv - t_uw) > Q.d13max) return;
+    for (uint32_t j = 0; j < Q.k; ++j) {
+        AccShared a{sw + 8 * j};
+        pair_thirds(key, z0, z1, z2, Q.q[j], d_uv, d_uw, k_uv, k_uw, a);
     }
 }
 
@@ -324,12 +315,13 @@ k_light_sweep(Ranges R, const uint32_t *__restrict__ tri, const uint32_t *__rest
     uint32_t r = 0;
     for (uint64_t i = beg + threadIdx.x; i < end; i += BLOCK) {
         const uint64_t t = range_at(R, r, i);
-        Lists L;
-        load_lists(eoff, tri[3 * t], tri[3 * t + 1], tri[3 * t + 2], key, Q.q[0], L);   // one window
-        light_pairs_sweep<0, 0>(key, L, Q, sw);
-        light_pairs_sweep<0, 1>(key, L, Q, sw);
-        light_pairs_sweep<1, 0>(key, L, Q, sw);
-        light_pairs_sweep<1, 1>(key, L, Q, sw);
+        const uint32_t e_vw = tri[3 * t + 2];
+        const uint32_t z0 = eoff[2 * e_vw], z1 = eoff[2 * e_vw + 1], z2 = eoff[2 * e_vw + 2];
+        // (one window for all)
+        light_pairs(eoff, tri[3 * t], tri[3 * t + 1], key, Q.q[0],
+                    [&](uint32_t d_uv, uint32_t d_uw, uint64_t k_uv, uint64_t k_uw) {
+                        sweep_pair(key, z0, z1, z2, Q, d_uv, d_uw, k_uv, k_uw, sw);
+                    });
     }
     sweep_flush<BLOCK>(s_sw, Q.k, part, slot0 + blockIdx.x);
 }
@@ -356,12 +348,8 @@ k_medium_sweep(Ranges R, const uint32_t *__restrict__ med, const uint32_t *__res
         const uint64_t x = b + lane;
         const bool active = x < n_ent;
         medium_lanes_eval(med, ent, active ? range_at(R, r, x) : 0, active, eoff, key, qr,
-                          [&](int combo, const Lists &L, uint64_t k_uv, uint64_t k_uw) {
-                              for (uint32_t j = 0; j < Q.k; ++j) {
-                                  AccSweep a{sw + 8 * j};
-                                  medium_pair_any(combo, key, L, Q.q[j], k_uv, k_uw, a);
-                              }
-                          },
+                          [&](uint32_t d_uv, uint32_t d_uw, uint32_t z0, uint32_t z1, uint32_t z2, uint64_t k_uv,
+                              uint64_t k_uw) { sweep_pair(key, z0, z1, z2, Q, d_uv, d_uw, k_uv, k_uw, sw); },
                           lane, lev);
     }
     sweep_flush<BLOCK>(s_sw, Q.k, part, slot0 + blockIdx.x);

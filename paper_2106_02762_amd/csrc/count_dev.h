@@ -78,6 +78,79 @@ struct AccW {
     template <class C> __device__ __forceinline__ void add(int64_t v) { t[C::type] += (uint64_t)v; }
 };
 
+// ---------------------------------------------------------------------------------------------
+// accumulators of the pairwise paths (light and medium), whose directions are known at run time:
+// acc.third(place, uv_first, dirs, n) adds n triangles whose {v,w} edge is first (place 0: pi5 | pi6),
+// in the middle (1: pi3 | pi4) or last (2: pi1 | pi2); the first of each when the uv edge precedes the
+// uw edge; dirs = d_uv << 2 | d_uw << 1 | d_vw.
+// ---------------------------------------------------------------------------------------------
+// the types (0-based) and cells (rho - 1) of an ordering by dirs, four bits each
+constexpr uint32_t type_row(int pi) {
+    uint32_t r = 0;
+    for (int d = 0; d < 8; ++d) r |= (uint32_t)(psi_of(pi, rho_of(d >> 2, (d >> 1) & 1, d & 1)) - 1) << (4 * d);
+    return r;
+}
+constexpr uint32_t rho_row() {
+    uint32_t r = 0;
+    for (int d = 0; d < 8; ++d) r |= (uint32_t)(rho_of(d >> 2, (d >> 1) & 1, d & 1) - 1) << (4 * d);
+    return r;
+}
+__device__ __forceinline__ uint32_t third_type(int place, bool uv_first, uint32_t dirs) {
+    constexpr uint32_t kRow[3][2] = {{type_row(5), type_row(6)}, {type_row(3), type_row(4)}, {type_row(1), type_row(2)}};
+    return ((uv_first ? kRow[place][0] : kRow[place][1]) >> (4 * dirs)) & 7u;
+}
+
+// A block's counters in LDS, eight per lane (a column each, so no two lanes meet): adding to a type
+// known at run time is one LDS operation, where eight counters in registers would be selected one by
+// one.  WORDS 1: int64 counts.  WORDS 2: 128-bit counts (low words, then high ones).
+template <unsigned BLOCK, int WORDS> struct AccLane {
+    unsigned long long *col;   // this lane's column: word w of type t at col[(w * 8 + t) * BLOCK]
+    uint64_t visits = 0;
+    __device__ __forceinline__ explicit AccLane(unsigned long long *s) : col(s + threadIdx.x) {
+#pragma unroll
+        for (int i = 0; i < 8 * WORDS; ++i) col[i * BLOCK] = 0;
+    }
+    __device__ __forceinline__ void add(uint32_t type, uint64_t n) {
+        if (WORDS == 1) {
+            (void)__hip_atomic_fetch_add(&col[type * BLOCK], (unsigned long long)n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        } else {
+            const unsigned long long sum = col[type * BLOCK] + n;
+            col[type * BLOCK] = sum;
+            if (sum < n) ++col[(8 + type) * BLOCK];
+        }
+    }
+    __device__ __forceinline__ void third(int place, bool uv_first, uint32_t dirs, uint64_t n) {
+        if (n) add(third_type(place, uv_first, dirs), n);
+    }
+    template <class T> __device__ __forceinline__ void get(T (&t)[8]) const {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            t[i] = (T)col[i * BLOCK];
+            if constexpr (WORDS == 2) t[i] += (T)col[(8 + i) * BLOCK] << 64;
+        }
+    }
+};
+
+// the 48 cells by global atomics (diagnostic)
+struct AccCells {
+    int64_t *cells;
+    uint64_t visits = 0;
+    __device__ __forceinline__ void third(int place, bool uv_first, uint32_t dirs, uint64_t n) {
+        if (!n) return;
+        const int pi = (place == 0 ? 5 : (place == 1 ? 3 : 1)) + (uv_first ? 0 : 1);
+        atomicAdd((unsigned long long *)(cells + (pi - 1) * 8 + ((rho_row() >> (4 * dirs)) & 15u)), (unsigned long long)n);
+    }
+};
+
+// eight counters in LDS that lanes share (a sweep's triple, the one-shot pass's wavefront)
+struct AccShared {
+    unsigned long long *s;
+    uint64_t visits = 0;
+    __device__ __forceinline__ void third(int place, bool uv_first, uint32_t dirs, uint64_t n) {
+        if (n) atomicAdd(&s[third_type(place, uv_first, dirs)], (unsigned long long)n);
+    }
+};
+
 // position of element j of the ranges R (j < R.pre[R.n]); the cursor r only moves forward, so a
 // thread walking increasing j finds each range once
 __device__ __forceinline__ uint64_t range_at(const Ranges &R, uint32_t &r, uint64_t j) {
@@ -139,86 +212,132 @@ __device__ __forceinline__ void load_lists(const uint32_t *__restrict__ eoff, ui
 }
 
 // ---------------------------------------------------------------------------------------------
-// light path: one lane per triangle, every (uv edge, uw edge) pair
+// the third edges of one (uv edge, uw edge) pair (the pairwise form of Lemma 1)
 // ---------------------------------------------------------------------------------------------
-template <int A, int B, int C, class ACC>
-__device__ __forceinline__ void light_third(const uint64_t *__restrict__ key, const Lists &L,
-                                            const DQuery &q, bool uv_first, uint64_t k_lo,
-                                            uint64_t k_hi, int64_t t_lo, int64_t t_hi, int64_t gap,
+// {v,w} lists of up to this many edges are read edge by edge, all at once; longer ones are searched
+constexpr uint32_t kScanVw = 8;
+
+// The triangles of the pair (k_uv, k_uw) for query q, with the {v,w} edges [z0, z1) (v -> w) and
+// [z1, z2) (w -> v), the whole lists: a third edge is first, in the middle or last when its key is in
+// [K1, k_lo), [M1, M2) or [k_hi, K4), which hold the query's limits and its window (k_uv and k_uw are
+// inside the window).  Bound by the chain of dependent loads: short lists take one round of loads, long
+// ones a search for the six bounds in lockstep.
+template <class ACC>
+__device__ __forceinline__ void pair_thirds(const uint64_t *__restrict__ key, uint32_t z0, uint32_t z1, uint32_t z2,
+                                            const DQuery &q, uint32_t d_uv, uint32_t d_uw, uint64_t k_uv, uint64_t k_uw,
                                             ACC &acc) {
-    const uint32_t zb = L.lo[4 + C], ze = L.hi[4 + C];
-    if (zb == ze) return;
-    const uint32_t below_lo = lower(key, zb, ze, k_lo);   // z with key < k_lo
-    const uint32_t below_hi = lower(key, below_lo, ze, k_hi);
-    // z first: e1 = z, e2 = earlier of x, y, e3 = later
+    const bool uv_first = k_uv < k_uw;
+    const uint64_t k_lo = uv_first ? k_uv : k_uw, k_hi = uv_first ? k_uw : k_uv;
+    const int64_t t_lo = (int64_t)(k_lo >> q.shift), t_hi = (int64_t)(k_hi >> q.shift);
+    const int64_t gap = t_hi - t_lo;
+    if (gap > q.d13 || z0 == z2) return;   // d12, d23 <= d13: no z completes the pair
+    // z first: t_z >= max(t_lo - d12, t_hi - d13), needs gap <= d23
+    uint64_t K1 = k_lo, K4 = k_hi;
     if (gap <= q.d23) {
-        int64_t from = t_lo - q.d12 > t_hi - q.d13 ? t_lo - q.d12 : t_hi - q.d13;
-        uint32_t s = lower(key, zb, below_lo, before_time(from, q));
-        acc.template add2<Cell<5, A, B, C>, Cell<6, A, B, C>>(uv_first, (int64_t)(below_lo - s));
+        const uint64_t k = before_time(t_lo - q.d12 > t_hi - q.d13 ? t_lo - q.d12 : t_hi - q.d13, q);
+        K1 = k > q.klo ? k : q.klo;
     }
-    // z in the middle: t_hi - d23 <= t_z <= t_lo + d12, key between k_lo and k_hi
-    {
-        uint32_t a = lower(key, below_lo, below_hi, before_time(t_hi - q.d23, q));
-        uint32_t b = lower(key, below_lo, below_hi, before_time(t_lo + q.d12 + 1, q));
-        if (b > a) acc.template add2<Cell<3, A, B, C>, Cell<4, A, B, C>>(uv_first, (int64_t)(b - a));
-    }
-    // z last: t_z <= min(t_hi + d23, t_lo + d13), key after k_hi
+    // z in the middle: t_hi - d23 <= t_z <= t_lo + d12
+    const uint64_t ma = before_time(t_hi - q.d23, q), mb = before_time(t_lo + q.d12 + 1, q);
+    const uint64_t M1 = ma > k_lo ? ma : k_lo, M2 = mb < k_hi ? mb : k_hi;
+    // z last: t_z <= min(t_hi + d23, t_lo + d13), needs gap <= d12
     if (gap <= q.d12) {
-        int64_t until = t_hi + q.d23 < t_lo + q.d13 ? t_hi + q.d23 : t_lo + q.d13;
-        uint32_t e = lower(key, below_hi, ze, before_time(until + 1, q));
-        acc.template add2<Cell<1, A, B, C>, Cell<2, A, B, C>>(uv_first, (int64_t)(e - below_hi));
+        const uint64_t k = before_time((t_hi + q.d23 < t_lo + q.d13 ? t_hi + q.d23 : t_lo + q.d13) + 1, q);
+        K4 = k < q.khi ? k : q.khi;
     }
+    uint32_t n[2][3] = {{0, 0, 0}, {0, 0, 0}};
+    if (z2 - z0 <= kScanVw) {
+        for (uint32_t z = z0; z < z2; z += 4) {
+            uint64_t kz[4];
+#pragma unroll
+            for (uint32_t i = 0; i < 4; ++i) kz[i] = z + i < z2 ? key[z + i] : ~0ull;   // (~0: in no range)
+#pragma unroll
+            for (uint32_t i = 0; i < 4; ++i) {
+                const bool back = z + i >= z1;
+                const uint32_t f = kz[i] >= K1 && kz[i] < k_lo, m = kz[i] >= M1 && kz[i] < M2,
+                               l = kz[i] >= k_hi && kz[i] < K4;
+                n[0][0] += back ? 0u : f;
+                n[0][1] += back ? 0u : m;
+                n[0][2] += back ? 0u : l;
+                n[1][0] += back ? f : 0u;
+                n[1][1] += back ? m : 0u;
+                n[1][2] += back ? l : 0u;
+            }
+        }
+    } else {
+        // ranks of K1, k_lo, M1, M2, k_hi, K4; bounds at the ends of all time, and M1 = k_lo and
+        // M2 = k_hi (long deltas), need no search
+        const uint64_t K[6] = {K1, k_lo, M1, M2, k_hi, K4};
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            const uint32_t b = c ? z1 : z0, e = c ? z2 : z1;
+            if (b == e) continue;
+            uint32_t lo[6], len[6];
+#pragma unroll
+            for (int i = 0; i < 6; ++i) {
+                const bool skip = K[i] == 0 || K[i] == ~0ull || (i == 2 && M1 == k_lo) || (i == 3 && M2 == k_hi);
+                lo[i] = K[i] == ~0ull ? e : b;
+                len[i] = skip ? 0u : e - b;
+            }
+            while (len[0] | len[1] | len[2] | len[3] | len[4] | len[5]) {
+                uint64_t v[6];
+#pragma unroll
+                for (int i = 0; i < 6; ++i) v[i] = len[i] ? key[lo[i] + (len[i] >> 1)] : 0ull;
+#pragma unroll
+                for (int i = 0; i < 6; ++i) {
+                    const uint32_t half = len[i] >> 1;
+                    const bool right = len[i] && v[i] < K[i];
+                    lo[i] += right ? half + 1 : 0u;
+                    len[i] = right ? len[i] - half - 1 : half;
+                }
+            }
+            if (M1 == k_lo) lo[2] = lo[1];
+            if (M2 == k_hi) lo[3] = lo[4];
+            n[c][0] = lo[1] - lo[0];
+            n[c][1] = lo[3] > lo[2] ? lo[3] - lo[2] : 0u;
+            n[c][2] = lo[5] - lo[4];
+        }
+    }
+#pragma unroll
+    for (uint32_t c = 0; c < 2; ++c)
+#pragma unroll
+        for (int p = 0; p < 3; ++p) acc.third(p, uv_first, d_uv << 2 | d_uw << 1 | c, n[c][p]);
 }
 
-template <int A, int B, class ACC>
-__device__ __forceinline__ void light_pairs(const uint64_t *__restrict__ key, const Lists &L,
-                                            const DQuery &q, ACC &acc) {
-    const uint32_t xb = L.lo[A], xe = L.hi[A], yb = L.lo[2 + B], ye = L.hi[2 + B];
-    acc.visits += (uint64_t)(xe - xb) * (ye - yb);
-    for (uint32_t ix = xb; ix < xe; ++ix) {
-        const uint64_t kx = key[ix];
-        for (uint32_t iy = yb; iy < ye; ++iy) {
-            const uint64_t ky = key[iy];
-            const bool uv_first = kx < ky;
-            const uint64_t k_lo = uv_first ? kx : ky, k_hi = uv_first ? ky : kx;
-            const int64_t t_lo = (int64_t)(k_lo >> q.shift), t_hi = (int64_t)(k_hi >> q.shift);
-            const int64_t gap = t_hi - t_lo;
-            if (gap > q.d13) continue;   // d12, d23 <= d13: no z completes this pair
-            light_third<A, B, 0>(key, L, q, uv_first, k_lo, k_hi, t_lo, t_hi, gap, acc);
-            light_third<A, B, 1>(key, L, q, uv_first, k_lo, k_hi, t_lo, t_hi, gap, acc);
+// ---------------------------------------------------------------------------------------------
+// light path: one lane per triangle, every (uv edge, uw edge) pair
+// ---------------------------------------------------------------------------------------------
+// eval(d_uv, d_uw, k_uv, k_uw) for every pair inside the query's window
+template <class EVAL>
+__device__ __forceinline__ void light_pairs(const uint32_t *__restrict__ eoff, uint32_t e_uv, uint32_t e_uw,
+                                            const uint64_t *__restrict__ key, const DQuery &q, EVAL &&eval) {
+    const uint32_t a0 = eoff[2 * e_uv], a1 = eoff[2 * e_uv + 1], a2 = eoff[2 * e_uv + 2];
+    const uint32_t b0 = eoff[2 * e_uw], b1 = eoff[2 * e_uw + 1], b2 = eoff[2 * e_uw + 2];
+    for (uint32_t x = a0; x < a2; ++x) {
+        const uint64_t kx = key[x];
+        if (kx < q.klo || kx >= q.khi) continue;
+        for (uint32_t y = b0; y < b2; ++y) {
+            const uint64_t ky = key[y];
+            if (ky < q.klo || ky >= q.khi) continue;
+            eval(x >= a1 ? 1u : 0u, y >= b1 ? 1u : 0u, kx, ky);
         }
     }
 }
 
-// one light triangle: every (uv edge, uw edge) pair by one lane
+// one light triangle by one lane
 template <class ACC>
-__device__ __forceinline__ void light_tri(const uint32_t *__restrict__ tri, uint64_t i,
-                                          const uint32_t *__restrict__ eoff,
-                                          const uint64_t *__restrict__ key, const DQuery &q,
-                                          ACC &acc) {
-    Lists L;
-    load_lists(eoff, tri[3 * i], tri[3 * i + 1], tri[3 * i + 2], key, q, L);
-    light_pairs<0, 0>(key, L, q, acc);
-    light_pairs<0, 1>(key, L, q, acc);
-    light_pairs<1, 0>(key, L, q, acc);
-    light_pairs<1, 1>(key, L, q, acc);
+__device__ __forceinline__ void light_tri(uint32_t e_uv, uint32_t e_uw, uint32_t e_vw, const uint32_t *__restrict__ eoff,
+                                          const uint64_t *__restrict__ key, const DQuery &q, ACC &acc) {
+    const uint32_t z0 = eoff[2 * e_vw], z1 = eoff[2 * e_vw + 1], z2 = eoff[2 * e_vw + 2];
+    light_pairs(eoff, e_uv, e_uw, key, q, [&](uint32_t d_uv, uint32_t d_uw, uint64_t k_uv, uint64_t k_uw) {
+        ++acc.visits;
+        pair_thirds(key, z0, z1, z2, q, d_uv, d_uw, k_uv, k_uw, acc);
+    });
 }
 
 // ---------------------------------------------------------------------------------------------
 // medium path: one lane per edge of a triangle's smaller source-incident pair
 // ---------------------------------------------------------------------------------------------
-template <int A, int B, class ACC>
-__device__ __forceinline__ void medium_pair(const uint64_t *__restrict__ key, const Lists &L,
-                                            const DQuery &q, uint64_t kx, uint64_t ky, ACC &acc) {
-    const bool uv_first = kx < ky;
-    const uint64_t k_lo = uv_first ? kx : ky, k_hi = uv_first ? ky : kx;
-    const int64_t t_lo = (int64_t)(k_lo >> q.shift), t_hi = (int64_t)(k_hi >> q.shift);
-    const int64_t gap = t_hi - t_lo;
-    if (gap > q.d13) return;
-    light_third<A, B, 0>(key, L, q, uv_first, k_lo, k_hi, t_lo, t_hi, gap, acc);
-    light_third<A, B, 1>(key, L, q, uv_first, k_lo, k_hi, t_lo, t_hi, gap, acc);
-}
-
 // the outer pair of a medium triangle: the source-incident pair with fewer temporal edges
 // (uv on a tie); the medium path has one entry per outer edge
 __host__ __device__ __forceinline__ bool medium_outer_is_uv(uint32_t s_uv, uint32_t s_uw) { return s_uv <= s_uw; }
@@ -262,7 +381,7 @@ __device__ __forceinline__ void lower2(const uint64_t *__restrict__ key, uint32_
 // those y form one key range (clipped to the window too), found by binary search.  The wavefront then spreads the (x, y) pairs of all its lanes evenly over the lanes
 // (pair j belongs to the last lane whose exclusive prefix of pair counts is <= j), so one outer edge
 // with many close partners does not stall the others.  Every lane of the wavefront must call this.
-// Each pair goes to eval(direction combination 2 d_uv + d_uw, its {v,w} lists, uv key, uw key);
+// Each pair goes to eval(d_uv, d_uw, its {v,w} lists' bounds z0, z1, z2 (unclipped), uv key, uw key);
 // q gives the window and the d13 of the closeness test.
 // With lev (the windowed copies), an entry whose triangle's level is below q.qlev is skipped: that
 // triangle is counted by the prefix procedures for this query.  Returns the pairs this wavefront
@@ -273,7 +392,7 @@ __device__ __forceinline__ uint32_t medium_lanes_eval(const uint32_t *__restrict
                                                       const uint64_t *__restrict__ key, const DQuery &q, EVAL &&eval,
                                                       unsigned lane, const uint8_t *__restrict__ lev = nullptr) {
     uint64_t kx = 0;
-    uint32_t lo0 = 0, c0 = 0, lo1 = 0, c1 = 0, zb0 = 0, ze0 = 0, zb1 = 0, ze1 = 0, flags = 0;
+    uint32_t lo0 = 0, c0 = 0, lo1 = 0, c1 = 0, z0 = 0, z1 = 0, z2 = 0, flags = 0;
     if (active && lev && lev[ent[2 * e]] < q.qlev) active = false;
     if (active) {
         const uint32_t t = ent[2 * e], jc = ent[2 * e + 1];
@@ -304,15 +423,10 @@ __device__ __forceinline__ uint32_t medium_lanes_eval(const uint32_t *__restrict
             lower2(key, r1b, r1e, klo, khi, lo1, hi1);
             c0 = hi0 - lo0;
             c1 = hi1 - lo1;
-            if (c0 + c1) {   // the {v,w} lists, clipped to the window
-                zb0 = eoff[2 * e_vw];
-                ze0 = eoff[2 * e_vw + 1];
-                ze1 = eoff[2 * e_vw + 2];
-                zb1 = ze0;
-                if (q.windowed) {
-                    lower2(key, zb0, ze0, q.klo, q.khi, zb0, ze0);
-                    lower2(key, zb1, ze1, q.klo, q.khi, zb1, ze1);
-                }
+            if (c0 + c1) {
+                z0 = eoff[2 * e_vw];
+                z1 = eoff[2 * e_vw + 1];
+                z2 = eoff[2 * e_vw + 2];
             }
         }
     }
@@ -339,11 +453,7 @@ __device__ __forceinline__ uint32_t medium_lanes_eval(const uint32_t *__restrict
         const uint32_t oc0 = __shfl(c0, l, 64), olo0 = __shfl(lo0, l, 64), olo1 = __shfl(lo1, l, 64);
         const uint32_t ofl = __shfl(flags, l, 64);
         const uint64_t okx = ((uint64_t)(uint32_t)__shfl(kx_hi, l, 64) << 32) | (uint32_t)__shfl(kx_lo, l, 64);
-        Lists L;
-        L.lo[4] = __shfl(zb0, l, 64);
-        L.hi[4] = __shfl(ze0, l, 64);
-        L.lo[5] = __shfl(zb1, l, 64);
-        L.hi[5] = __shfl(ze1, l, 64);
+        const uint32_t oz0 = __shfl(z0, l, 64), oz1 = __shfl(z1, l, 64), oz2 = __shfl(z2, l, 64);
         if (jp >= total) continue;
         const bool outer_uv = ofl & 1u;
         const uint32_t x_dir = (ofl >> 1) & 1u, y_dir = r < oc0 ? 0u : 1u;
@@ -351,21 +461,9 @@ __device__ __forceinline__ uint32_t medium_lanes_eval(const uint32_t *__restrict
         // (uv edge, uw edge) with their directions
         const uint64_t k_uv = outer_uv ? okx : ky, k_uw = outer_uv ? ky : okx;
         const uint32_t d_uv = outer_uv ? x_dir : y_dir, d_uw = outer_uv ? y_dir : x_dir;
-        eval(d_uv * 2 + d_uw, L, k_uv, k_uw);
+        eval(d_uv, d_uw, oz0, oz1, oz2, k_uv, k_uw);
     }
     return total;
-}
-
-// one (uv, uw) pair of given direction combination for query q
-template <class ACC>
-__device__ __forceinline__ void medium_pair_any(int combo, const uint64_t *__restrict__ key, const Lists &L,
-                                                const DQuery &q, uint64_t k_uv, uint64_t k_uw, ACC &acc) {
-    switch (combo) {
-        case 0: medium_pair<0, 0>(key, L, q, k_uv, k_uw, acc); break;
-        case 1: medium_pair<0, 1>(key, L, q, k_uv, k_uw, acc); break;
-        case 2: medium_pair<1, 0>(key, L, q, k_uv, k_uw, acc); break;
-        default: medium_pair<1, 1>(key, L, q, k_uv, k_uw, acc); break;
-    }
 }
 
 // the medium path for one query into accumulator acc; returns the pairs the wavefront evaluated
@@ -375,9 +473,8 @@ __device__ __forceinline__ uint32_t medium_lanes(const uint32_t *__restrict__ me
                                                  const uint64_t *__restrict__ key, const DQuery &q, ACC &acc,
                                                  unsigned lane, const uint8_t *__restrict__ lev = nullptr) {
     return medium_lanes_eval(med, ent, e, active, eoff, key, q,
-                             [&](int combo, const Lists &L, uint64_t k_uv, uint64_t k_uw) {
-                                 medium_pair_any(combo, key, L, q, k_uv, k_uw, acc);
-                             },
+                             [&](uint32_t d_uv, uint32_t d_uw, uint32_t z0, uint32_t z1, uint32_t z2, uint64_t k_uv,
+                                 uint64_t k_uw) { pair_thirds(key, z0, z1, z2, q, d_uv, d_uw, k_uv, k_uw, acc); },
                              lane, lev);
 }
 

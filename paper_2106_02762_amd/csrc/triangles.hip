@@ -236,16 +236,8 @@ struct TriSink {
             for (int j = 0; j < 8; ++j)
                 if (cc[j]) atomicAdd(&sums[j], (unsigned long long)cc[j]);
         } else if (s_uv * s_uw <= F.cap_l && s_vw <= cdev::kLightVw) {
-            cdev::Acc<false> A;
-            cdev::Lists L;
-            cdev::load_lists(eoff, a, b, c, F.key, F.q, L);
-            cdev::light_pairs<0, 0>(F.key, L, F.q, A);
-            cdev::light_pairs<0, 1>(F.key, L, F.q, A);
-            cdev::light_pairs<1, 0>(F.key, L, F.q, A);
-            cdev::light_pairs<1, 1>(F.key, L, F.q, A);
-#pragma unroll
-            for (int j = 0; j < 8; ++j)
-                if (A.t[j]) atomicAdd(&sums[j], (unsigned long long)A.t[j]);
+            cdev::AccShared A{sums};
+            cdev::light_tri(a, b, c, eoff, F.key, F.q, A);
         } else {
             return false;
         }
