@@ -403,10 +403,8 @@ int dt_count(dt_graph *g, const dt_query *q, int64_t out[8]) {
     dt_ctx *ctx = g->ctx;
     DeviceGuard dg(ctx->device);
     const bool wide = (g->sum_sigma3 >> 63) != 0;
-    const size_t words = wide ? 16 : 8;
-    DT_TRY(count_enqueue(g, dq, ctx->out8.as<int64_t>(), ctx->stream, false, nullptr, ctx->scratch));
-    DT_HIP(hipMemcpyAsync(ctx->pinned_out, ctx->out8.ptr, words * sizeof(int64_t), hipMemcpyDeviceToHost,
-                          ctx->stream));
+    // the reduction writes its words to pinned host memory itself
+    DT_TRY(count_enqueue(g, dq, ctx->pinned_out, ctx->stream, false, nullptr, ctx->scratch));
     DT_HIP(hipStreamSynchronize(ctx->stream));
     if (wide) return narrow_counts(ctx->pinned_out, nullptr, out);
     memcpy(out, ctx->pinned_out, 8 * sizeof(int64_t));
@@ -499,9 +497,7 @@ int dt_count_sweep(dt_graph *g, uint64_t k, const dt_query *queries, int64_t *ou
         }
         dt_ctx *ctx = g->ctx;
         DeviceGuard dg(ctx->device);
-        DT_TRY(count_sweep_enqueue(g, dq, kk, ctx->out8.as<int64_t>(), ctx->stream, ctx->scratch));
-        DT_HIP(hipMemcpyAsync(ctx->pinned_out, ctx->out8.ptr, 8 * kk * sizeof(int64_t), hipMemcpyDeviceToHost,
-                              ctx->stream));
+        DT_TRY(count_sweep_enqueue(g, dq, kk, ctx->pinned_out, ctx->stream, ctx->scratch));
         DT_HIP(hipStreamSynchronize(ctx->stream));
         memcpy(out + 8 * b, ctx->pinned_out, 8 * kk * sizeof(int64_t));
     }

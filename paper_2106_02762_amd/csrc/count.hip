@@ -44,13 +44,13 @@ namespace {
 
 // ACC: Acc<false> (int64 type counts), Acc<true> (the 48 cells by atomics, no partials) or AccW
 // (128-bit type counts, 16-word partial slots)
-template <class ACC> constexpr bool kCells = std::is_same<ACC, Acc<true>>::value;
+template <class ACC> constexpr bool kCellsAcc = std::is_same<ACC, Acc<true>>::value;
 template <class ACC> constexpr int kAccWords = std::is_same<ACC, AccW>::value ? 2 : 1;
 
 // body(accumulator) of a pairwise kernel with accumulator ACC, then its block's partial slot
 template <class ACC, unsigned BLOCK, class BODY>
 __device__ __forceinline__ void with_pairwise(int64_t *__restrict__ partial, int64_t *__restrict__ cells, BODY &&body) {
-    if constexpr (kCells<ACC>) {
+    if constexpr (kCellsAcc<ACC>) {
         AccCells acc{cells};
         body(acc);
     } else {
@@ -63,65 +63,85 @@ __device__ __forceinline__ void with_pairwise(int64_t *__restrict__ partial, int
     }
 }
 
+// light path: block b of nblk takes a contiguous run of the list's ranges
+template <unsigned BLOCK, class PACC>
+__device__ __forceinline__ void light_block(uint32_t b, uint32_t nblk, const Ranges &R, const uint32_t *__restrict__ tri,
+                                            const uint32_t *__restrict__ eoff, const uint64_t *__restrict__ key,
+                                            const DQuery &q, PACC &acc) {
+    const uint64_t n_tri = R.pre[R.n];
+    const uint64_t per = (n_tri + nblk - 1) / nblk;
+    const uint64_t beg = (uint64_t)xcd_block(b, nblk) * per;
+    const uint64_t end = beg + per < n_tri ? beg + per : n_tri;
+    uint32_t r = 0;
+    for (uint64_t i = beg + threadIdx.x; i < end; i += BLOCK) {
+        const uint64_t t = range_at(R, r, i);
+        light_tri(tri[3 * t], tri[3 * t + 1], tri[3 * t + 2], eoff, key, q, acc);
+    }
+}
+
+// medium path: wave w takes the 64 entries from 64 w on, then those from 64 (w + W) on, ...;
+// with lev (windowed copies) entries of triangles below the query's level are skipped
+template <unsigned BLOCK, class PACC>
+__device__ __forceinline__ void medium_block(uint32_t b, uint32_t nblk, const Ranges &R, const uint32_t *__restrict__ med,
+                                             const uint32_t *__restrict__ ent, const uint8_t *__restrict__ lev,
+                                             const uint32_t *__restrict__ eoff, const uint64_t *__restrict__ key,
+                                             const DQuery &q, PACC &acc) {
+    const unsigned lane = threadIdx.x & 63;
+    const uint64_t n_ent = R.pre[R.n];
+    const uint64_t W = (uint64_t)nblk * (BLOCK / 64);
+    uint32_t r = 0;
+    for (uint64_t e = ((uint64_t)b * (BLOCK / 64) + threadIdx.x / 64) * 64; e < n_ent; e += W * 64) {
+        const uint64_t j = e + lane;
+        const bool active = j < n_ent;
+        // one visit per outer edge, plus the wavefront's close pairs (counted by lane 0)
+        const uint32_t pairs = medium_lanes(med, ent, active ? range_at(R, r, j) : 0, active, eoff, key, q, acc, lane, lev);
+        acc.visits += (active ? 1u : 0u) + (lane == 0 ? pairs : 0u);
+    }
+}
+
+// unit path: block b of nblk takes a contiguous run of the records [beg, end); returns its length
+template <bool CELLS, unsigned BLOCK>
+__device__ __forceinline__ uint64_t unit_block(uint32_t b, uint32_t nblk, uint64_t beg, uint64_t end,
+                                               const uint4 *__restrict__ rec, const UQuery &u, uint32_t (&c)[8],
+                                               int64_t *__restrict__ cells) {
+    const uint64_t per = (end - beg + nblk - 1) / nblk;
+    const uint64_t rb = beg + (uint64_t)b * per;
+    const uint64_t re = rb + per < end ? rb + per : end;
+    if (rb >= re) return 0;
+    unit_run<CELLS, BLOCK>(rec, rb, re, u, c, cells);
+    return re - rb;
+}
+
 template <class ACC, unsigned BLOCK>
 __global__ void __launch_bounds__(BLOCK)
 k_light(Ranges R, const uint32_t *__restrict__ tri, const uint32_t *__restrict__ eoff,
         const uint64_t *__restrict__ key, DQuery q, int64_t *__restrict__ partial,
         int64_t *__restrict__ cells, unsigned long long *__restrict__ visits) {
     with_pairwise<ACC, BLOCK>(partial, cells, [&](auto &acc) {
-        const uint64_t n_tri = R.pre[R.n];
-        const uint32_t nblk = gridDim.x;
-        const uint32_t b = xcd_block(blockIdx.x, nblk);
-        const uint64_t per = (n_tri + nblk - 1) / nblk;
-        const uint64_t beg = (uint64_t)b * per;
-        const uint64_t end = beg + per < n_tri ? beg + per : n_tri;
-        uint32_t r = 0;
-        for (uint64_t i = beg + threadIdx.x; i < end; i += BLOCK) {
-            const uint64_t t = range_at(R, r, i);
-            light_tri(tri[3 * t], tri[3 * t + 1], tri[3 * t + 2], eoff, key, q, acc);
-        }
+        light_block<BLOCK>(blockIdx.x, gridDim.x, R, tri, eoff, key, q, acc);
         add_visits(visits, acc.visits);
     });
 }
 
-// medium path: wave w takes the 64 entries from 64 w on, then those from 64 (w + W) on, ...;
-// with lev (windowed copies) entries of triangles below the query's level are skipped
 template <class ACC, unsigned BLOCK>
 __global__ void __launch_bounds__(BLOCK)
 k_medium(Ranges R, const uint32_t *__restrict__ med, const uint32_t *__restrict__ ent,
          const uint8_t *__restrict__ lev, const uint32_t *__restrict__ eoff, const uint64_t *__restrict__ key,
          DQuery q, int64_t *__restrict__ partial, int64_t *__restrict__ cells, unsigned long long *__restrict__ visits) {
     with_pairwise<ACC, BLOCK>(partial, cells, [&](auto &acc) {
-        const unsigned lane = threadIdx.x & 63;
-        const uint64_t n_ent = R.pre[R.n];
-        const uint64_t W = (uint64_t)gridDim.x * (BLOCK / 64);
-        uint32_t r = 0;
-        uint64_t vis = 0;
-        for (uint64_t b = ((uint64_t)blockIdx.x * (BLOCK / 64) + threadIdx.x / 64) * 64; b < n_ent; b += W * 64) {
-            const uint64_t j = b + lane;
-            const bool active = j < n_ent;
-            // one visit per outer edge, plus the wavefront's close pairs (counted by lane 0)
-            const uint32_t pairs = medium_lanes(med, ent, active ? range_at(R, r, j) : 0, active, eoff, key, q, acc, lane, lev);
-            vis += (active ? 1u : 0u) + (lane == 0 ? pairs : 0u);
-        }
-        add_visits(visits, vis);
+        medium_block<BLOCK>(blockIdx.x, gridDim.x, R, med, ent, lev, eoff, key, q, acc);
+        add_visits(visits, acc.visits);
     });
 }
 
-// unit path: block b takes a contiguous run of the records [beg, end)
 template <class ACC, unsigned BLOCK>
 __global__ void __launch_bounds__(BLOCK)
 k_unit(uint64_t beg, uint64_t end, const uint4 *__restrict__ rec, UQuery u, int64_t *__restrict__ partial,
        int64_t *__restrict__ cells, unsigned long long *__restrict__ visits) {
-    constexpr bool CELLS = kCells<ACC>;
-    const uint64_t n = end - beg;
-    const uint64_t per = (n + gridDim.x - 1) / gridDim.x;
-    const uint64_t b = beg + (uint64_t)blockIdx.x * per;
-    const uint64_t e = b + per < end ? b + per : end;
     uint32_t c[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    if (b < e) unit_run<CELLS, BLOCK>(rec, b, e, u, c, cells);
-    if (visits && threadIdx.x == 0 && e > b) atomicAdd(visits, (unsigned long long)(e - b));
-    if (!CELLS) {
+    const uint64_t n = unit_block<kCellsAcc<ACC>, BLOCK>(blockIdx.x, gridDim.x, beg, end, rec, u, c, cells);
+    if (visits && threadIdx.x == 0 && n) atomicAdd(visits, (unsigned long long)n);
+    if (!kCellsAcc<ACC>) {
         ACC acc;
 #pragma unroll
         for (int j = 0; j < 8; ++j) acc.t[j] = c[j];
@@ -129,56 +149,121 @@ k_unit(uint64_t beg, uint64_t end, const uint4 *__restrict__ rec, UQuery u, int6
     }
 }
 
+// The three paths of one count in one launch: mg medium blocks (the longest chains first), then lg light
+// ones and ug unit ones, each with its own partial slot.
+struct SmallCount {
+    Ranges lr, mr;
+    const uint32_t *light, *medium, *mitems, *eoff;
+    const uint8_t *mlev;
+    const uint64_t *key;
+    const uint4 *unit;
+    uint64_t ub, ue;
+    DQuery q;
+    UQuery u;
+    uint32_t mg, lg, ug;
+};
+template <class ACC, unsigned BLOCK>
+__global__ void __launch_bounds__(BLOCK)
+k_small(SmallCount C, int64_t *__restrict__ partial) {
+    const uint32_t b = blockIdx.x;
+    if (b >= C.mg + C.lg) {
+        uint32_t c[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+        unit_block<false, BLOCK>(b - C.mg - C.lg, C.ug, C.ub, C.ue, C.unit, C.u, c, nullptr);
+        ACC acc;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) acc.t[j] = c[j];
+        acc_store<BLOCK>(acc, partial, b);
+        return;
+    }
+    with_pairwise<ACC, BLOCK>(partial, nullptr, [&](auto &acc) {
+        if (b < C.mg) medium_block<BLOCK>(b, C.mg, C.mr, C.medium, C.mitems, C.mlev, C.eoff, C.key, C.q, acc);
+        else light_block<BLOCK>(b - C.mg, C.lg, C.lr, C.light, C.eoff, C.key, C.q, acc);
+    });
+}
+
 // ---------------------------------------------------------------------------------------------
 // heavy path (the per-item bodies are in count_dev.h, shared with the batched kernel)
 // ---------------------------------------------------------------------------------------------
+// The heavy work of up to kSweepMax queries over the same triangles, each with its own scratch: block
+// row y of every kernel is query y.
+struct HeavySet {
+    HeavyArgs A[kSweepMax];
+};
+
 // window-clipped bounds of the six lists of every heavy triangle of the query
-__global__ void k_heavy_clip(HeavyArgs A, uint64_t n_q) {
+__global__ void k_heavy_clip(HeavySet S, uint64_t n_q) {
     const uint64_t h = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (h < n_q) heavy_clip_one(A, h);
+    if (h < n_q) heavy_clip_one(S.A[blockIdx.y], h);
 }
 
 // phase 1 of the prefix pass over prefix chunks [A.pb, pe)
 __global__ void __launch_bounds__(kPrefixBlock)
-k_heavy_prefix_local(HeavyArgs A, uint64_t pe, unsigned long long *__restrict__ visits) {
+k_heavy_prefix_local(HeavySet S, uint64_t pe, unsigned long long *__restrict__ visits) {
+    const HeavyArgs &A = S.A[blockIdx.y];
     uint64_t vis = 0;
     for (uint64_t c = A.pb + blockIdx.x; c < pe; c += gridDim.x) heavy_prefix_local_chunk(A, c, vis);
     add_visits(visits, vis);
 }
 
 // phase 2: the carries between the chunks of each list (a thread per chunk, the list's first works)
-__global__ void k_heavy_prefix_scan(HeavyArgs A, uint64_t pe) {
+__global__ void k_heavy_prefix_scan(HeavySet S, uint64_t pe) {
+    const HeavyArgs &A = S.A[blockIdx.y];
     const uint64_t c = A.pb + (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (c < pe) heavy_prefix_scan_list(A, c, pe);
 }
 
 // phase 3: every chunk adds its carry
 __global__ void __launch_bounds__(kPrefixBlock)
-k_heavy_prefix_add(HeavyArgs A, uint64_t pe) {
+k_heavy_prefix_add(HeavySet S, uint64_t pe) {
+    const HeavyArgs &A = S.A[blockIdx.y];
     for (uint64_t c = A.pb + blockIdx.x; c < pe; c += gridDim.x) heavy_prefix_add_chunk(A, c);
 }
 
 // the count pass: chunks [cb, ce) of 256 source edges (of the four lists in a row) each
 template <class ACC, unsigned BLOCK>
 __global__ void __launch_bounds__(BLOCK)
-k_heavy_count(HeavyArgs A, uint64_t cb, uint64_t ce, int64_t *__restrict__ partial, int64_t *__restrict__ cells,
+k_heavy_count(HeavySet S, uint64_t cb, uint64_t ce, int64_t *__restrict__ partial, int64_t *__restrict__ cells,
               unsigned long long *__restrict__ visits) {
+    const HeavyArgs &A = S.A[blockIdx.y];
     ACC acc;
     acc.cells = cells;
     for (uint64_t ch = cb + blockIdx.x; ch < ce; ch += gridDim.x) heavy_count_chunk(A, ch, acc);
     add_visits(visits, acc.visits);
-    if (!kCells<ACC>) acc_store<BLOCK>(acc, partial, blockIdx.x);
+    if (!kCellsAcc<ACC>) acc_store<BLOCK>(acc, partial, (uint64_t)blockIdx.y * gridDim.x + blockIdx.x);
 }
 
 // final reduction of the per-block partials into out8 (deterministic order)
-__global__ void __launch_bounds__(256)
-k_reduce(uint64_t n_part, const int64_t *__restrict__ partial, int64_t *__restrict__ out8) {
-    int64_t t[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    for (uint64_t i = threadIdx.x; i < n_part; i += 256) {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) t[j] += partial[8 * i + j];
+// (thread i adds word i, i + 1024, ... of the partials, all of type i % 8: 8192 slots 22 -> 8 us against
+// a slot per thread and 256 threads)
+constexpr unsigned kReduceBlock = 1024;
+__device__ __forceinline__ void reduce_words(uint64_t n_words, const int64_t *__restrict__ partial, int64_t &t) {
+    uint64_t i = threadIdx.x;
+    for (; i + 3 * kReduceBlock < n_words; i += 4 * kReduceBlock) {
+        const int64_t a = partial[i], b = partial[i + kReduceBlock], c = partial[i + 2 * kReduceBlock],
+                      d = partial[i + 3 * kReduceBlock];
+        t += a + b + c + d;
     }
-    block_store<256>(t, out8);
+    for (; i < n_words; i += kReduceBlock) t += partial[i];
+}
+// thread i's sum t (of type i % 8) over the block into out8
+__device__ __forceinline__ void reduce_store(int64_t t, int64_t *__restrict__ out8) {
+    __shared__ int64_t s[kReduceBlock / 64][8];
+#pragma unroll
+    for (int o = 8; o < 64; o <<= 1) t += __shfl_xor((long long)t, o, 64);
+    if ((threadIdx.x & 63) < 8) s[threadIdx.x / 64][threadIdx.x & 7] = t;
+    __syncthreads();
+    if (threadIdx.x < 8) {
+        int64_t v = 0;
+#pragma unroll
+        for (unsigned w = 0; w < kReduceBlock / 64; ++w) v += s[w][threadIdx.x];
+        out8[threadIdx.x] = v;
+    }
+}
+__global__ void __launch_bounds__(kReduceBlock)
+k_reduce(uint64_t n_part, const int64_t *__restrict__ partial, int64_t *__restrict__ out8) {
+    int64_t t = 0;
+    reduce_words(8 * n_part, partial, t);
+    reduce_store(t, out8);
 }
 
 // the 128-bit form: 16-word partials into 16 words (low, high per type)
@@ -355,26 +440,28 @@ k_medium_sweep(Ranges R, const uint32_t *__restrict__ med, const uint32_t *__res
     sweep_flush<BLOCK>(s_sw, Q.k, part, slot0 + blockIdx.x);
 }
 
-// out[8 j + i] (+)= sum over slots of part[8 (K slot + j) + i]; block j for query j
-__global__ void __launch_bounds__(256)
-k_reduce_sweep(uint64_t n_slot, uint32_t k, const int64_t *__restrict__ part, int64_t *__restrict__ out, int add) {
+// out[8 j + i] = sum over slots of part[8 (K slot + j) + i] and over x of heavy[8 (n_heavy j + x) + i];
+// block j for query j
+__global__ void __launch_bounds__(kReduceBlock)
+k_reduce_sweep(uint64_t n_slot, uint32_t k, const int64_t *__restrict__ part, uint64_t n_heavy,
+               const int64_t *__restrict__ heavy, int64_t *__restrict__ out) {
     const uint32_t j = blockIdx.x;
-    int64_t t[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    for (uint64_t i = threadIdx.x; i < n_slot; i += 256) {
-#pragma unroll
-        for (int x = 0; x < 8; ++x) t[x] += part[8 * (i * k + j) + x];
-    }
-    __shared__ int64_t s_prev[8];
-    if (threadIdx.x < 8) s_prev[threadIdx.x] = add ? out[8 * j + threadIdx.x] : 0;
-    __syncthreads();
-    block_store<256>(t, out + 8 * j);
-    __syncthreads();
-    if (threadIdx.x < 8) out[8 * j + threadIdx.x] += s_prev[threadIdx.x];
+    int64_t t = 0;
+    if (n_heavy) reduce_words(8 * n_heavy, heavy + 8 * n_heavy * j, t);
+#pragma unroll 4
+    for (uint64_t i = threadIdx.x / 8; i < n_slot; i += kReduceBlock / 8) t += part[8 * (i * k + j) + (threadIdx.x & 7)];
+    reduce_store(t, out + 8 * j);
 }
 
 constexpr unsigned kLightBlock = 256;
 constexpr unsigned kUnitBlock = 256;
 constexpr uint64_t kUnitPerBlock = 16384;   // records per workgroup at least (64 per thread)
+// Counts of up to this many light, medium and unit blocks per CU take them in one launch: they are all
+// resident at once, so the three kernels side by side would overlap no more, and the fork, the two joins
+// and two launches cost more than the work (10K edges: 72 -> 31 us).  Larger counts fork, where
+// each kernel's own registers leave more wavefronts in flight.
+constexpr unsigned kSmallPerCu = 4;
+constexpr uint64_t kSweepHeavyBytes = 1ull << 30;   // prefix arrays of a sweep's queries at a time
 
 }  // namespace
 
@@ -502,27 +589,67 @@ void count_plan(const dt_graph *g, const DQuery &q, unsigned parts, CountPlan &p
     p.heavy_bytes = p.hr.n ? p.hr.scratch_bytes : 0;
 }
 
-// The four paths' kernels of a planned count with accumulator ACC: the light and heavy ones on sl,
-// the medium one on sm, the unit one on s; partial slots of 8 words (16 for AccW) in the order
-// light, heavy, medium, unit.
+// The heavy kernels of k queries over the range hr on stream s: scratch of query j at scratch + j *
+// hr.scratch_bytes, partial slots of query j from j * hg on.
 template <class ACC>
-int launch_paths(dt_graph *g, const DQuery &q, const CountPlan &p, const ScratchView &sv, hipStream_t s,
+int launch_heavy(dt_graph *g, const DQuery *qs, uint32_t k, const HeavyRange &hr, unsigned hg, uint8_t *scratch,
+                 int64_t *part, hipStream_t s, int64_t *cells_dev, unsigned long long *visits) {
+    dt_ctx *ctx = g->ctx;
+    const Schedule &S = g->sched;
+    if (g->tuning.heavy_chunk != 256) return fail(DT_EINVAL, "heavy_chunk %u not compiled", g->tuning.heavy_chunk);
+    HeavySet H;
+    for (uint32_t j = 0; j < k; ++j) heavy_args(g, qs[j], hr, scratch + j * hr.scratch_bytes, H.A[j]);
+    const uint64_t npc = S.n_pchunks - hr.pb;
+    const unsigned pgrid = (unsigned)std::min<uint64_t>(npc, (uint64_t)ctx->num_cus * 16);
+    k_heavy_clip<<<dim3(grid_for(hr.n, 256), k), 256, 0, s>>>(H, hr.n);
+    DT_HIP(hipGetLastError());
+    prof_begin(ctx, kProfHeavyPrefix, s);
+    k_heavy_prefix_local<<<dim3(pgrid, k), kPrefixBlock, 0, s>>>(H, S.n_pchunks, visits);
+    DT_HIP(hipGetLastError());
+    k_heavy_prefix_scan<<<dim3(grid_for(npc, 256), k), 256, 0, s>>>(H, S.n_pchunks);
+    DT_HIP(hipGetLastError());
+    k_heavy_prefix_add<<<dim3(pgrid, k), kPrefixBlock, 0, s>>>(H, S.n_pchunks);
+    prof_end(ctx, kProfHeavyPrefix, s);
+    DT_HIP(hipGetLastError());
+    prof_begin(ctx, kProfHeavyCount, s);
+    k_heavy_count<ACC, 256><<<dim3(hg, k), 256, 0, s>>>(H, hr.cb, S.n_chunks, part, cells_dev, visits);
+    prof_end(ctx, kProfHeavyCount, s);
+    DT_HIP(hipGetLastError());
+    return DT_OK;
+}
+
+// The four paths' kernels of a planned count with accumulator ACC: the heavy ones on sl, and the light
+// ones before them on sl, the medium one on sm and the unit one on s, or, with `small`, these three in one
+// launch on s; partial slots of 8 words (16 for AccW): heavy, then medium, light, unit.
+template <class ACC>
+int launch_paths(dt_graph *g, const DQuery &q, const CountPlan &p, const ScratchView &sv, bool small, hipStream_t s,
                  hipStream_t sl, hipStream_t sm, int64_t *cells_dev, unsigned long long *visits) {
     dt_ctx *ctx = g->ctx;
     Schedule &S = g->sched;
     constexpr uint64_t W = std::is_same<ACC, AccW>::value ? 16 : 8;
     const unsigned lg = p.lg, hg = p.hg, mg = p.mg, ug = p.ug;
-    int64_t *part = sv.part;
+    int64_t *hp = sv.part, *mp = hp + W * hg, *lp = mp + W * mg, *up = lp + W * lg;
     const uint32_t *eoff = g->eoff.as<uint32_t>();
     const uint64_t *key = g->key.as<uint64_t>();
+    if constexpr (!kCellsAcc<ACC>) {
+        if (small) {
+            SmallCount C{p.lr, p.mr, p.light, p.medium, p.mitems, eoff, p.mlev, key, S.unit.as<uint4>(), p.ub, p.ue, q,
+                         unit_query(q), mg, lg, ug};
+            prof_begin(ctx, kProfMedium, s);
+            k_small<ACC, 256><<<mg + lg + ug, 256, 0, s>>>(C, mp);
+            prof_end(ctx, kProfMedium, s);
+            DT_HIP(hipGetLastError());
+            if (p.hr.n) DT_TRY(launch_heavy<ACC>(g, &q, 1, p.hr, hg, sv.heavy, hp, sl, nullptr, nullptr));
+            return DT_OK;
+        }
+    }
     if (lg) {
         prof_begin(ctx, kProfLight, sl);
-        k_light<ACC, kLightBlock><<<lg, kLightBlock, 0, sl>>>(p.lr, p.light, eoff, key, q, part, cells_dev, visits);
+        k_light<ACC, kLightBlock><<<lg, kLightBlock, 0, sl>>>(p.lr, p.light, eoff, key, q, lp, cells_dev, visits);
         prof_end(ctx, kProfLight, sl);
         DT_HIP(hipGetLastError());
     }
     if (mg) {
-        int64_t *mp = part + W * ((uint64_t)lg + hg);
         prof_begin(ctx, kProfMedium, sm);
         k_medium<ACC, 256><<<mg, 256, 0, sm>>>(p.mr, p.medium, p.mitems, p.mlev, eoff, key, q, mp, cells_dev, visits);
         prof_end(ctx, kProfMedium, sm);
@@ -530,36 +657,12 @@ int launch_paths(dt_graph *g, const DQuery &q, const CountPlan &p, const Scratch
     }
     if (ug) {
         const UQuery u = unit_query(q);
-        int64_t *up = part + W * ((uint64_t)lg + hg + mg);
         prof_begin(ctx, kProfUnit, s);
         k_unit<ACC, kUnitBlock><<<ug, kUnitBlock, 0, s>>>(p.ub, p.ue, S.unit.as<uint4>(), u, up, cells_dev, visits);
         prof_end(ctx, kProfUnit, s);
         DT_HIP(hipGetLastError());
     }
-    if (p.hr.n) {
-        const HeavyRange &hr = p.hr;
-        const uint64_t npc = S.n_pchunks - hr.pb;
-        HeavyArgs A;
-        heavy_args(g, q, hr, sv.heavy, A);
-        k_heavy_clip<<<grid_for(hr.n, 256), 256, 0, sl>>>(A, hr.n);
-        DT_HIP(hipGetLastError());
-        const unsigned pgrid = (unsigned)std::min<uint64_t>(npc, (uint64_t)ctx->num_cus * 16);
-        prof_begin(ctx, kProfHeavyPrefix, sl);
-        k_heavy_prefix_local<<<pgrid, kPrefixBlock, 0, sl>>>(A, S.n_pchunks, visits);
-        DT_HIP(hipGetLastError());
-        k_heavy_prefix_scan<<<grid_for(npc, 256), 256, 0, sl>>>(A, S.n_pchunks);
-        DT_HIP(hipGetLastError());
-        k_heavy_prefix_add<<<pgrid, kPrefixBlock, 0, sl>>>(A, S.n_pchunks);
-        prof_end(ctx, kProfHeavyPrefix, sl);
-        DT_HIP(hipGetLastError());
-        const unsigned cb = g->tuning.heavy_chunk;
-        if (cb != 256) return fail(DT_EINVAL, "heavy_chunk %u not compiled", cb);
-        int64_t *hp = part + W * (uint64_t)lg;
-        prof_begin(ctx, kProfHeavyCount, sl);
-        k_heavy_count<ACC, 256><<<hg, 256, 0, sl>>>(A, hr.cb, S.n_chunks, hp, cells_dev, visits);
-        prof_end(ctx, kProfHeavyCount, sl);
-        DT_HIP(hipGetLastError());
-    }
+    if (p.hr.n) DT_TRY(launch_heavy<ACC>(g, &q, 1, p.hr, hg, sv.heavy, hp, sl, cells_dev, visits));
     return DT_OK;
 }
 
@@ -583,41 +686,42 @@ int count_launch(dt_graph *g, const DQuery &q, const CountPlan &p, int64_t *out8
     // The paths are independent (each writes its own partial slots): when more than one has work,
     // the light and then the heavy kernels run on the context's first side stream and the medium
     // kernel on the second, forked from s here and joined back before the reduction, beside the
-    // unit kernel on s, so that their latency-bound tails overlap.
+    // unit kernel on s, so that their latency-bound tails overlap.  A small count takes the light,
+    // medium and unit blocks in one launch on s, and only the heavy kernels beside it.
+    const bool small = !cells && !visits && (lg || mg || ug) && (uint64_t)lg + mg + ug <= (uint64_t)ctx->num_cus * kSmallPerCu;
     hipStream_t sl = s, sm = s;
-    const bool fork = ctx->side[0] && ((lg || hg ? 1 : 0) + (mg ? 1 : 0) + (ug ? 1 : 0)) >= 2;
+    const bool fork = ctx->side[0] && (small ? hg != 0 : ((lg || hg ? 1 : 0) + (mg ? 1 : 0) + (ug ? 1 : 0)) >= 2);
+    const bool fork_l = fork && (hg || (!small && lg)), fork_m = fork && !small && mg;
     if (fork) {
         DT_HIP(hipEventRecord(ctx->ev_fork, s));
-        if (lg || hg) {
+        if (fork_l) {
             DT_HIP(hipStreamWaitEvent(ctx->side[0], ctx->ev_fork, 0));
             sl = ctx->side[0];
         }
-        if (mg) {
+        if (fork_m) {
             DT_HIP(hipStreamWaitEvent(ctx->side[1], ctx->ev_fork, 0));
             sm = ctx->side[1];
         }
     }
     if (cells) {
-        DT_TRY(launch_paths<Acc<true>>(g, q, p, sv, s, sl, sm, cells_dev, visits));
+        DT_TRY(launch_paths<Acc<true>>(g, q, p, sv, small, s, sl, sm, cells_dev, visits));
     } else if (p.wide) {
-        DT_TRY(launch_paths<AccW>(g, q, p, sv, s, sl, sm, nullptr, visits));
+        DT_TRY(launch_paths<AccW>(g, q, p, sv, small, s, sl, sm, nullptr, visits));
     } else {
-        DT_TRY(launch_paths<Acc<false>>(g, q, p, sv, s, sl, sm, nullptr, visits));
+        DT_TRY(launch_paths<Acc<false>>(g, q, p, sv, small, s, sl, sm, nullptr, visits));
     }
-    if (fork) {
-        if (lg || hg) {
-            DT_HIP(hipEventRecord(ctx->ev_join[0], sl));
-            DT_HIP(hipStreamWaitEvent(s, ctx->ev_join[0], 0));
-        }
-        if (mg) {
-            DT_HIP(hipEventRecord(ctx->ev_join[1], sm));
-            DT_HIP(hipStreamWaitEvent(s, ctx->ev_join[1], 0));
-        }
+    if (fork_l) {
+        DT_HIP(hipEventRecord(ctx->ev_join[0], sl));
+        DT_HIP(hipStreamWaitEvent(s, ctx->ev_join[0], 0));
+    }
+    if (fork_m) {
+        DT_HIP(hipEventRecord(ctx->ev_join[1], sm));
+        DT_HIP(hipStreamWaitEvent(s, ctx->ev_join[1], 0));
     }
     if (!cells) {
         prof_begin(ctx, kProfReduce, s);
         if (p.wide) k_reduce_w<<<1, 256, 0, s>>>(n_part, part, out8_dev);
-        else k_reduce<<<1, 256, 0, s>>>(n_part, part, out8_dev);
+        else k_reduce<<<1, kReduceBlock, 0, s>>>(n_part, part, out8_dev);
         prof_end(ctx, kProfReduce, s);
         DT_HIP(hipGetLastError());
     }
@@ -640,14 +744,15 @@ int count_enqueue(dt_graph *g, const DQuery &q, int64_t *out8_dev, hipStream_t s
 }
 
 void count_reduce(uint64_t n_part, const int64_t *part, int64_t *out8_dev, hipStream_t s) {
-    k_reduce<<<1, 256, 0, s>>>(n_part, part, out8_dev);
+    k_reduce<<<1, kReduceBlock, 0, s>>>(n_part, part, out8_dev);
 }
 
 // A sweep: k <= kSweepMax queries with one window.  The unit, light and medium kernels visit each
 // triangle's data once per pass and count it for every delta triple: records and lists are read
 // once, the light path enumerates each triangle's pairs once, the medium path finds each entry's
 // close pairs once (for the largest d13); only the delta-dependent searches repeat.  The rare heavy
-// triangles are counted per query first, and the reduction adds the rest to those sums.
+// triangles are counted for every query in one set of launches (61M edges, eight triples: 1.3 ms of 1.9
+// when each query took its own, one after the other).
 int count_sweep_enqueue(dt_graph *g, const DQuery *qs, uint32_t k, int64_t *out_dev, hipStream_t s, Scratch &sc) {
     dt_ctx *ctx = g->ctx;
     Schedule &S = g->sched;
@@ -665,18 +770,11 @@ int count_sweep_enqueue(dt_graph *g, const DQuery *qs, uint32_t k, int64_t *out_
     // finds close pairs at that distance for every triple)
     uint32_t qlm = 0;
     for (uint32_t j = 0; j < k; ++j) qlm = qs[j].qlev > qlm ? qs[j].qlev : qlm;
-    // heavy triangles: one count per query, written to out_dev
     DQuery qh = q0;
     qh.qlev = qlm;
     HeavyRange hr;
     heavy_range(g, qh, hr);
-    const bool heavy = hr.n > 0;
-    if (heavy)
-        for (uint32_t j = 0; j < k; ++j) {
-            DQuery qq = qs[j];
-            qq.qlev = qlm;
-            DT_TRY(count_enqueue(g, qq, out_dev + 8 * j, s, false, nullptr, sc, 4));
-        }
+    const unsigned hg = hr.n ? (unsigned)std::min<uint64_t>(S.n_chunks - hr.cb, (uint64_t)ctx->num_cus * 16) : 0;
     Q.qlev = qlm;
     Ranges lr, mr;
     const uint8_t *mlev = nullptr;
@@ -694,14 +792,29 @@ int count_sweep_enqueue(dt_graph *g, const DQuery *qs, uint32_t k, int64_t *out_
     const unsigned ug = ue > ub ? (unsigned)std::min<uint64_t>((ue - ub + kUnitPerBlock - 1) / kUnitPerBlock,
                                                                (uint64_t)ctx->num_cus * 8) : 0;
     const uint64_t n_slot = (uint64_t)ug + lgx + mg;
-    DT_TRY(ensure(ctx, sc.sweep_partials, (n_slot + 1) * k * 8 * sizeof(int64_t)));
-    int64_t *part = sc.sweep_partials.as<int64_t>();
-    // the light and medium passes run on the side streams, beside the unit pass (as in a count)
+    DT_TRY(ensure(ctx, sc.sweep_partials, (n_slot + hg + 1) * k * 8 * sizeof(int64_t)));
+    int64_t *part = sc.sweep_partials.as<int64_t>(), *hpart = part + 8 * n_slot * k;
+    // the heavy triangles of all k queries in one set of launches, when their scratch may be had: a
+    // query's prefix arrays each, at most kSweepHeavyBytes of them at a time, else one query after the
+    // other
+    uint32_t hk = 0;
+    if (hg) {
+        hk = (uint32_t)std::min<uint64_t>(k, std::max<uint64_t>(1, kSweepHeavyBytes / hr.scratch_bytes));
+        int rc = ensure(ctx, sc.heavy_vals, hk * hr.scratch_bytes);
+        if (rc == DT_ENOMEM && hk > 1) {
+            clear_error();
+            hk = 1;
+            rc = ensure(ctx, sc.heavy_vals, hr.scratch_bytes);
+        }
+        DT_TRY(rc);
+    }
+    // the light (then heavy) and medium passes run on the side streams, beside the unit pass (as in a
+    // count)
     hipStream_t sl = s, sm = s;
-    const bool fork = ctx->side[0] && ((ug ? 1 : 0) + (lgx ? 1 : 0) + (mg ? 1 : 0)) >= 2;
+    const bool fork = ctx->side[0] && ((ug ? 1 : 0) + (lgx || hg ? 1 : 0) + (mg ? 1 : 0)) >= 2;
     if (fork) {
         DT_HIP(hipEventRecord(ctx->ev_fork, s));
-        if (lgx) {
+        if (lgx || hg) {
             DT_HIP(hipStreamWaitEvent(ctx->side[0], ctx->ev_fork, 0));
             sl = ctx->side[0];
         }
@@ -723,6 +836,11 @@ int count_sweep_enqueue(dt_graph *g, const DQuery *qs, uint32_t k, int64_t *out_
         prof_end(ctx, kProfLight, sl);
         DT_HIP(hipGetLastError());
     }
+    for (uint32_t j = 0; hg && j < k; j += hk) {
+        const uint32_t kk = std::min(hk, k - j);
+        DT_TRY(launch_heavy<Acc<false>>(g, qs + j, kk, hr, hg, sc.heavy_vals.as<uint8_t>(), hpart + 8ull * hg * j, sl,
+                                        nullptr, nullptr));
+    }
     if (mg) {
         prof_begin(ctx, kProfMedium, sm);
         k_medium_sweep<256><<<mg, 256, 0, sm>>>(mr, medium, mitems, mlev, g->eoff.as<uint32_t>(), g->key.as<uint64_t>(),
@@ -731,7 +849,7 @@ int count_sweep_enqueue(dt_graph *g, const DQuery *qs, uint32_t k, int64_t *out_
         DT_HIP(hipGetLastError());
     }
     if (fork) {
-        if (lgx) {
+        if (lgx || hg) {
             DT_HIP(hipEventRecord(ctx->ev_join[0], sl));
             DT_HIP(hipStreamWaitEvent(s, ctx->ev_join[0], 0));
         }
@@ -741,7 +859,7 @@ int count_sweep_enqueue(dt_graph *g, const DQuery *qs, uint32_t k, int64_t *out_
         }
     }
     prof_begin(ctx, kProfReduce, s);
-    k_reduce_sweep<<<k, 256, 0, s>>>(n_slot, k, part, out_dev, heavy ? 1 : 0);
+    k_reduce_sweep<<<k, kReduceBlock, 0, s>>>(n_slot, k, part, hg, hpart, out_dev);
     prof_end(ctx, kProfReduce, s);
     DT_HIP(hipGetLastError());
     return DT_OK;
