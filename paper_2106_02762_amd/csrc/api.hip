@@ -266,8 +266,15 @@ int dt_graph_build(dt_graph *g) {
             dt_graph *g;
             ~Join() { (void)relayout_join(g); }
         } join{g};
-        DT_TRY(enumerate_triangles(g, tri, &ntri, &cand, &nlist));
+        int rc = enumerate_triangles(g, tri, &ntri, &cand, &nlist);
         DT_TRY(relayout_join(g));
+        if (rc == DT_ENOMEM && g->ukey.ptr) {   // without the unit keys (made again for the schedule)
+            clear_error();
+            DT_HIP(hipStreamSynchronize(g->ctx->stream));
+            g->ukey.reset();
+            rc = enumerate_triangles(g, tri, &ntri, &cand, &nlist);
+        }
+        DT_TRY(rc);
     }
     g->n_tri = ntri;
     g->n_tri_list = nlist;
@@ -275,7 +282,7 @@ int dt_graph_build(dt_graph *g) {
     g->alg_bytes_tri = 4 * (g->m_s + cand) + 12 * ntri;
     double t3 = now_ms();
     DT_TRY(resolve_split(g, &tri));
-    DT_TRY(make_schedule(g, tri));
+    DT_TRY(make_schedule(g, tri, true));
     double t4 = now_ms();
     g->ms_peel = t1 - t0;
     g->ms_orient = t2 - t1;
@@ -315,7 +322,7 @@ int dt_graph_set_tuning(dt_graph *g, const dt_tuning *tu) {
     if (ntri != g->n_tri) return fail(DT_EDEVICE, "triangle enumeration changed between passes");
     g->n_tri_list = nlist;
     DT_TRY(resolve_split(g, g->tuning.autotune == 2 ? &tri : nullptr));
-    return make_schedule(g, tri);
+    return make_schedule(g, tri, true);
 }
 
 int dt_graph_stats(const dt_graph *g, dt_stats *out) {
@@ -453,7 +460,7 @@ int dt_count_oneshot(dt_graph *g, const dt_query *q, int64_t out[8]) {
         // words at o + 8)
         g->n_tri = n_rest;
         g->n_tri_list = n_rest;
-        rc = make_schedule(g, rest);
+        rc = make_schedule(g, rest, true, false);
         if (rc == DT_OK) rc = count_enqueue(g, dq, o + 8, ctx->stream, false, nullptr, ctx->scratch);
     } else if (rc == DT_OK) {
         DT_HIP(hipMemsetAsync(o + 8, 0, 8 * sizeof(int64_t), ctx->stream));

@@ -260,6 +260,7 @@ struct dt_graph {
     dt::DevMem eoff;            // uint32[2 m_s + 1]: DAG edge d: tail->head edges [eoff[2d], eoff[2d+1]),
                                 //                    head->tail edges [eoff[2d+1], eoff[2d+2])
     dt::DevMem key;             // uint64[m]: keys in that layout
+    dt::DevMem ukey;            // uint64[m_s]: unit keys, until the schedule is made
     bool relay_pending = false; // key is still being written on the context's side[0] stream
     dt::DevMem relay_tmp[4];    // inputs and temporaries of that re-layout, held until it is joined
     uint64_t n_tri = 0;
@@ -306,8 +307,10 @@ constexpr uint32_t kNoEdge = 0xffffffffu;
 // every static triangle as (e_uv, e_uw, e_vw) DAG edge ids, in a list of *nlist entries of which
 // *ntri are triangles and the others empty; *cand: candidates tested
 int enumerate_triangles(const dt_graph *g, DevMem &tri, uint64_t *ntri, uint64_t *cand, uint64_t *nlist);
-// the schedule of g's count from its triangle list tri (g->n_tri_list entries, g->n_tri triangles)
-int make_schedule(dt_graph *g, DevMem &tri);
+// the schedule of g's count from its triangle list tri (g->n_tri_list entries, g->n_tri triangles);
+// last: tri is not read again and may be given back; with_units false: it holds no unit triangle
+void unit_keys(dt_graph *g, hipStream_t st);   // g->ukey (allocated) from the store
+int make_schedule(dt_graph *g, DevMem &tri, bool last, bool with_units = true);
 // orders the context's stream after a re-layout that orient(g, true) left running on side[0]
 // (no-op otherwise) and releases its temporaries; to be called before anything reads g->key
 int relayout_join(dt_graph *g);

@@ -359,6 +359,10 @@ int orient(dt_graph *g, bool overlap) {
         DT_HIP(hipEventRecord(ctx->ev_relay[0], st));
         DT_HIP(hipStreamWaitEvent(rs, ctx->ev_relay[0], 0));
     }
+    // the unit keys only for a build, whose schedule reads them, in the buffer of the (tail, head)
+    // pairs, which nothing reads any more
+    g->ukey.reset();
+    if (rs != st && g->span <= kUnitMaxSpan && g->tuning.force_path == 0) g->ukey = std::move(th);
     DevMem scan_tmp;
     DT_TRY(exclusive_scan_u32(ctx, gsize.as<uint32_t>(), g->eoff.as<uint32_t>(), ngroups + 1, rs,
                               rs != st ? &scan_tmp : nullptr));
@@ -369,6 +373,10 @@ int orient(dt_graph *g, bool overlap) {
             g->eoff.as<uint32_t>(), g->pkey.as<uint64_t>(), g->key.as<uint64_t>());
         prof_end(ctx, kProfRelayout, rs);
         DT_HIP(hipGetLastError());
+        if (g->ukey.ptr) {
+            unit_keys(g, rs);
+            DT_HIP(hipGetLastError());
+        }
         if (rs != st) {
             DT_HIP(hipEventRecord(ctx->ev_relay[1], rs));
             g->relay_tmp[0] = std::move(dag_of);

@@ -34,15 +34,15 @@ __device__ __forceinline__ uint32_t ceil_log2_1(uint32_t s) {   // ceil(log2(s +
     return s == 0 ? 0 : 32 - __clz(s);
 }
 
-enum : int { kClsLight = 0, kClsMedium = 1, kClsHeavy = 2, kClsUnit = 3, kClsContest = 4 };
-constexpr int kClasses = 5;
+enum : int { kClsLight = 0, kClsMedium = 1, kClsHeavy = 2, kClsContest = 3 };
+constexpr int kClasses = 4;
 // the medium path's per-lane counts are 32-bit sums over a wavefront: inner pairs stay below 2^25
 constexpr uint64_t kMediumMaxInner = 1ull << 25;
 constexpr uint32_t kCrossSample = 128;   // outer edges sampled by the level search
 
 struct SplitRule {
     uint64_t cap_l, cap_m;
-    uint32_t force, unit_ok, cost_pct;
+    uint32_t force, cost_pct;
 };
 
 // The pair budget of a triangle outside the light rule: how many (uv edge, uw edge) pairs the
@@ -62,10 +62,9 @@ __device__ __forceinline__ double pair_budget(uint64_t s_uv, uint64_t s_uw, uint
     return (heavy * cost_pct / 100.0 - outer) / (10.0 * lvw + 6.0);
 }
 
-// class of a triangle: unit, light, always medium, always heavy, or contested
+// class of a triangle that is no unit record: light, always medium, always heavy, or contested
 __device__ __forceinline__ int tri_class(uint64_t s_uv, uint64_t s_uw, uint64_t s_vw, const SplitRule &R) {
     const uint64_t P = s_uv * s_uw;
-    if (R.force == 0 && R.unit_ok && s_uv == 1 && s_uw == 1 && s_vw == 1) return kClsUnit;
     if (R.force == 1) return kClsLight;
     if (R.force == 2) return kClsHeavy;
     if (R.force == 3) return P < (1ull << 31) && s_uv < kMediumMaxInner && s_uw < kMediumMaxInner ? kClsMedium : kClsHeavy;
@@ -77,24 +76,25 @@ __device__ __forceinline__ int tri_class(uint64_t s_uv, uint64_t s_uw, uint64_t 
     return kClsContest;
 }
 
-constexpr int kPartWords = 6;   // per block: sum_sigma3 lo, hi, bytes, light, medium, unit bytes
+constexpr int kPartWords = 5;   // per block: sum_sigma3 lo, hi, bytes, light, medium bytes
 constexpr unsigned kClsGrid = 4096;   // blocks of the classify and partition passes at most (grid-stride)
 constexpr int kTotWords = kClasses + kPartWords;   // class sizes, then the partial words
 
 // Per list entry its class (one byte; kClasses for an empty entry); per block the triangles of
 // each class and the sum of sigma products (128-bit) and byte totals.  The partition pass walks the
 // entries in the same block / iteration order, so per-block class counts give every triangle its
-// place.
+// place.  The list has *n_p entries (at most n_max; null: n_max).
 __global__ void __launch_bounds__(kBlock)
-k_classify(uint64_t n_tri, const uint32_t *__restrict__ tri, const uint32_t *__restrict__ eoff, SplitRule R,
+k_classify(uint64_t n_max, const unsigned long long *__restrict__ n_p, const uint32_t *__restrict__ tri, const uint32_t *__restrict__ eoff, SplitRule R,
            uint8_t *__restrict__ cls, uint32_t *__restrict__ bcnt, uint64_t *__restrict__ part) {
     __shared__ unsigned long long s_w[kPartWords][kBlock / 64];
     __shared__ unsigned s_cnt[kClasses];
     if (threadIdx.x < kClasses) s_cnt[threadIdx.x] = 0;
     __syncthreads();
+    const uint64_t n_tri = n_p && *n_p < n_max ? *n_p : n_max;
     unsigned __int128 acc = 0;
-    unsigned long long bytes = 0, bytes_light = 0, bytes_medium = 0, bytes_unit = 0;
-    unsigned c[kClasses] = {0, 0, 0, 0, 0};
+    unsigned long long bytes = 0, bytes_light = 0, bytes_medium = 0;
+    unsigned c[kClasses] = {0, 0, 0, 0};
     for (uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x; i < n_tri; i += (uint64_t)gridDim.x * kBlock) {
         const uint32_t e_uv = tri[3 * i], e_uw = tri[3 * i + 1], e_vw = tri[3 * i + 2];
         if (e_uv == kNoEdge) {   // an empty entry: no class
@@ -109,17 +109,11 @@ k_classify(uint64_t n_tri, const uint32_t *__restrict__ tri, const uint32_t *__r
 #pragma unroll
         for (int x = 0; x < kClasses; ++x) c[x] += k == x;
         acc += (unsigned __int128)(s_uv * s_uw) * s_vw;
-        uint64_t b;
-        if (k == kClsUnit) {
-            b = sizeof(uint4);
-        } else {
-            const uint32_t probe = 2 * ceil_log2_1(s_vw);
-            b = 12 + 36 + 8 * (s_uv + s_uw) + 8 * (uint64_t)(s_vw < probe ? s_vw : probe);
-        }
+        const uint32_t probe = 2 * ceil_log2_1(s_vw);
+        const uint64_t b = 12 + 36 + 8 * (s_uv + s_uw) + 8 * (uint64_t)(s_vw < probe ? s_vw : probe);
         bytes += b;
         bytes_light += k == kClsLight ? b : 0;
         bytes_medium += (k == kClsMedium || k == kClsContest) ? b : 0;
-        bytes_unit += k == kClsUnit ? b : 0;
     }
 #pragma unroll
     for (int x = 0; x < kClasses; ++x)
@@ -127,7 +121,7 @@ k_classify(uint64_t n_tri, const uint32_t *__restrict__ tri, const uint32_t *__r
     // block sums: within each wavefront by shuffles (the 128-bit sum as two words with carry), then
     // over the wavefronts
     unsigned long long lo = (unsigned long long)acc, hi = (unsigned long long)(acc >> 64);
-    unsigned long long w[kPartWords - 2] = {bytes, bytes_light, bytes_medium, bytes_unit};
+    unsigned long long w[kPartWords - 2] = {bytes, bytes_light, bytes_medium};
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
         const unsigned long long lo2 = __shfl_xor(lo, o, 64), hi2 = __shfl_xor(hi, o, 64);
@@ -147,7 +141,7 @@ k_classify(uint64_t n_tri, const uint32_t *__restrict__ tri, const uint32_t *__r
     if (threadIdx.x < kClasses) bcnt[kClasses * blockIdx.x + threadIdx.x] = s_cnt[threadIdx.x];
     if (threadIdx.x == 0) {
         unsigned __int128 t = 0;
-        unsigned long long tw[kPartWords] = {0, 0, 0, 0, 0, 0};
+        unsigned long long tw[kPartWords] = {0, 0, 0, 0, 0};
         for (unsigned j = 0; j < kBlock / 64; ++j) {
             t += ((unsigned __int128)s_w[1][j] << 64) | s_w[0][j];
             for (int x = 2; x < kPartWords; ++x) tw[x] += s_w[x][j];
@@ -159,7 +153,7 @@ k_classify(uint64_t n_tri, const uint32_t *__restrict__ tri, const uint32_t *__r
 }
 
 // One workgroup: every classify block's first position in each class list (base, [block][class])
-// and the totals: tot[0..4] class sizes, tot[5..6] the 128-bit sum of sigma products, tot[7..10]
+// and the totals: tot[0..3] class sizes, tot[4..5] the 128-bit sum of sigma products, tot[6..8]
 // the byte totals.
 __global__ void __launch_bounds__(kBlock)
 k_cls_totals(unsigned nblk, const uint32_t *__restrict__ bcnt, const uint64_t *__restrict__ part,
@@ -190,7 +184,7 @@ k_cls_totals(unsigned nblk, const uint32_t *__restrict__ bcnt, const uint64_t *_
     }
     // the sums of the blocks' partial words, each thread over its blocks, then by shuffles
     unsigned __int128 t = 0;
-    unsigned long long w[kPartWords] = {0, 0, 0, 0, 0, 0};
+    unsigned long long w[kPartWords] = {0, 0, 0, 0, 0};
     for (unsigned b = b0; b < b1; ++b) {
         t += ((unsigned __int128)part[kPartWords * b + 1] << 64) | part[kPartWords * b];
         for (int x = 2; x < kPartWords; ++x) w[x] += part[kPartWords * b + x];
@@ -214,7 +208,7 @@ k_cls_totals(unsigned nblk, const uint32_t *__restrict__ bcnt, const uint64_t *_
     __syncthreads();
     if (tid == 0) {
         unsigned __int128 tt = 0;
-        unsigned long long tw[kPartWords] = {0, 0, 0, 0, 0, 0};
+        unsigned long long tw[kPartWords] = {0, 0, 0, 0, 0};
         for (unsigned j = 0; j < kBlock / 64; ++j) {
             tt += ((unsigned __int128)s_part[j][1] << 64) | s_part[j][0];
             for (int x = 2; x < kPartWords; ++x) tw[x] += s_part[j][x];
@@ -254,8 +248,7 @@ __device__ __forceinline__ uint16_t window_cell(uint32_t e_uv, uint32_t e_uw, ui
 
 // Per DAG edge with one temporal edge: that edge's key, with its direction (1: head -> tail) in
 // bit 63, which is free while unit records are built (spans below 2^31 and fewer than 2^31 edges
-// keep keys below 2^62); all ones for other edges.  The partition then builds a unit record from
-// three independent loads instead of three offset-then-key chains.
+// keep keys below 2^62); all ones for other edges.
 __global__ void k_unit_keys(uint64_t ms, const uint32_t *__restrict__ eoff, const uint64_t *__restrict__ key,
                             uint64_t *__restrict__ ukey) {
     const uint64_t e = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
@@ -264,20 +257,100 @@ __global__ void k_unit_keys(uint64_t ms, const uint32_t *__restrict__ eoff, cons
     ukey[e] = c - a == 1 ? key[a] | (uint64_t)(a == b ? 1u : 0u) << 63 : ~0ull;
 }
 
-// Every triangle to its class's list at base[class][block] + its rank in the block's walk: unit
-// triangles become records (in triangle order) with their t1 bucket as a sort key; light and
+// Unit triangles out of the list: the three unit keys of an entry say whether it is one and make its
+// record (with its t1 bucket as a sort key); the other triangles go to the rest list.  A workgroup
+// holds a tile of kSplitPer entries a thread, all their gathers in flight together, and takes the
+// tile's places in both outputs with one atomic each.  Bound by the list and the gathers of the third
+// edges' keys; one pass where classifying every entry and then moving it read both twice (classify,
+// partition of 67M entries: 1.0 + 1.9 ms, 1.0 so; the whole schedule 4.7 -> 3.0 ms).  Counters: ctr[0] unit
+// triangles, ctr[16] others (past unit_cap and rest_cap they are counted and not written).
+constexpr unsigned kSplitPer = 8;
+constexpr unsigned kSplitTile = kBlock * kSplitPer;
+__global__ void __launch_bounds__(kBlock)
+k_unit_split(uint64_t nt, const uint32_t *__restrict__ tri, const uint64_t *__restrict__ ukey, int shift, int bshift,
+             uint4 *__restrict__ urec, uint16_t *__restrict__ ubkt, uint64_t unit_cap,
+             uint32_t *__restrict__ rest, uint64_t rest_cap,
+             unsigned long long *__restrict__ ctr) {
+    __shared__ uint32_t s_cnt[2][kBlock / 64];
+    __shared__ unsigned long long s_base[2];
+    const unsigned lane = threadIdx.x & 63, wave = threadIdx.x / 64;
+    const uint64_t below = (1ull << lane) - 1;
+    for (uint64_t t0 = (uint64_t)blockIdx.x * kSplitTile; t0 < nt; t0 += (uint64_t)gridDim.x * kSplitTile) {
+        uint32_t e[kSplitPer][3];
+        uint64_t k[kSplitPer][3];
+#pragma unroll
+        for (unsigned j = 0; j < kSplitPer; ++j) {
+            const uint64_t i = t0 + j * kBlock + threadIdx.x;
+#pragma unroll
+            for (int x = 0; x < 3; ++x) e[j][x] = i < nt ? tri[3 * i + x] : kNoEdge;
+        }
+#pragma unroll
+        for (unsigned j = 0; j < kSplitPer; ++j)
+#pragma unroll
+            for (int x = 0; x < 3; ++x) k[j][x] = e[j][0] != kNoEdge ? ukey[e[j][x]] : ~0ull;
+        uint32_t nu = 0, nr = 0;   // of this wavefront
+#pragma unroll
+        for (unsigned j = 0; j < kSplitPer; ++j) {
+            const bool unit = k[j][0] != ~0ull && k[j][1] != ~0ull && k[j][2] != ~0ull;
+            nu += (uint32_t)__popcll(__ballot(unit));
+            nr += (uint32_t)__popcll(__ballot(!unit && e[j][0] != kNoEdge));
+        }
+        if (lane == 0) {
+            s_cnt[0][wave] = nu;
+            s_cnt[1][wave] = nr;
+        }
+        __syncthreads();
+        if (threadIdx.x < 2) {
+            uint32_t n = 0;
+            for (unsigned w = 0; w < kBlock / 64; ++w) {
+                const uint32_t c = s_cnt[threadIdx.x][w];
+                s_cnt[threadIdx.x][w] = n;
+                n += c;
+            }
+            s_base[threadIdx.x] = n ? atomicAdd(&ctr[16 * threadIdx.x], (unsigned long long)n) : 0ull;
+        }
+        __syncthreads();
+        uint64_t pu = s_base[0] + s_cnt[0][wave], pr = s_base[1] + s_cnt[1][wave];
+#pragma unroll
+        for (unsigned j = 0; j < kSplitPer; ++j) {
+            const bool unit = k[j][0] != ~0ull && k[j][1] != ~0ull && k[j][2] != ~0ull;
+            const bool other = !unit && e[j][0] != kNoEdge;
+            const uint64_t um = __ballot(unit), rm = __ballot(other);
+            if (unit) {
+                const uint64_t p = pu + (uint32_t)__popcll(um & below);
+                const uint64_t k3[3] = {k[j][0] & ~(1ull << 63), k[j][1] & ~(1ull << 63), k[j][2] & ~(1ull << 63)};
+                const int d3[3] = {(int)(k[j][0] >> 63), (int)(k[j][1] >> 63), (int)(k[j][2] >> 63)};
+                const uint4 r = cdev::unit_record_of(k3, d3, shift);
+                if (p < unit_cap) {
+                    urec[p] = r;
+                    ubkt[p] = (uint16_t)(r.x >> bshift);
+                }
+            }
+            if (other) {
+                const uint64_t p = pr + (uint32_t)__popcll(rm & below);
+                if (p < rest_cap) {
+                    rest[3 * p] = e[j][0];
+                    rest[3 * p + 1] = e[j][1];
+                    rest[3 * p + 2] = e[j][2];
+                }
+            }
+            pu += (uint32_t)__popcll(um);
+            pr += (uint32_t)__popcll(rm);
+        }
+    }
+}
+
+// Every triangle to its class's list at base[class][block] + its rank in the block's walk: light and
 // always-medium triangles also go, with their window cell as a sort key, to the windowed copies'
 // inputs; always-heavy ones go after the n_c contested ones in the heavy list; contested ones to
 // crec for the level search.
 __global__ void __launch_bounds__(kBlock)
 k_partition(uint64_t n_tri, const uint32_t *__restrict__ tri, const uint8_t *__restrict__ cls,
             const uint64_t *__restrict__ base, const uint32_t *__restrict__ eoff,
-            const uint64_t *__restrict__ key, const uint64_t *__restrict__ ukey, int shift, int bshift,
-            int cshift, uint64_t n_c,
+            const uint64_t *__restrict__ key, int shift, int cshift, uint64_t n_c,
             uint32_t *__restrict__ light, uint32_t *__restrict__ medium, uint32_t *__restrict__ heavy,
             uint4 *__restrict__ crec, uint4 *__restrict__ lrec, uint16_t *__restrict__ lkey,
-            uint4 *__restrict__ mrec, uint16_t *__restrict__ mkey, uint4 *__restrict__ urec,
-            uint16_t *__restrict__ ubkt) {
+            uint4 *__restrict__ mrec, uint16_t *__restrict__ mkey) {
     __shared__ unsigned long long s_wave[kBlock / 64];
     const unsigned lane = threadIdx.x & 63, wave = threadIdx.x / 64;
     uint64_t run[kClasses];
@@ -286,7 +359,7 @@ k_partition(uint64_t n_tri, const uint32_t *__restrict__ tri, const uint8_t *__r
     for (uint64_t b0 = (uint64_t)blockIdx.x * kBlock; b0 < n_tri; b0 += (uint64_t)gridDim.x * kBlock) {
         const uint64_t i = b0 + threadIdx.x;
         const int k = i < n_tri ? cls[i] : kClasses;
-        // five 12-bit class counters in one word (a block walks at most 256 triangles per step)
+        // 12-bit class counters in one word (a block walks at most 256 triangles per step)
         const unsigned long long f = k < kClasses ? 1ull << (12 * k) : 0ull;
         unsigned long long x = f;
 #pragma unroll
@@ -306,14 +379,7 @@ k_partition(uint64_t n_tri, const uint32_t *__restrict__ tri, const uint8_t *__r
         if (k < kClasses) {
             const uint64_t pos = run[k] + (((before + x - f) >> (12 * k)) & 0xfffull);
             const uint32_t e_uv = tri[3 * i], e_uw = tri[3 * i + 1], e_vw = tri[3 * i + 2];
-            if (k == kClsUnit) {
-                const uint64_t k3[3] = {ukey[e_uv] & ~(1ull << 63), ukey[e_uw] & ~(1ull << 63),
-                                        ukey[e_vw] & ~(1ull << 63)};
-                const int d3[3] = {(int)(ukey[e_uv] >> 63), (int)(ukey[e_uw] >> 63), (int)(ukey[e_vw] >> 63)};
-                const uint4 r = cdev::unit_record_of(k3, d3, shift);
-                urec[pos] = r;
-                ubkt[pos] = (uint16_t)(r.x >> bshift);
-            } else if (k == kClsContest) {
+            if (k == kClsContest) {
                 crec[pos] = make_uint4(e_uv, e_uw, e_vw, 0u);
             } else {
                 uint32_t *dst = (k == kClsLight ? light : (k == kClsMedium ? medium : heavy + 3 * n_c)) + 3 * pos;
@@ -592,9 +658,11 @@ int medium_fill(dt_ctx *ctx, uint64_t nm, DevMem &nch, DevMem &base, uint64_t ni
     return DT_OK;
 }
 
-}  // namespace
-
-int make_schedule(dt_graph *g, DevMem &tri) {
+// One attempt at the schedule.  The unit keys are g's, made here if the build left none.  lean: the
+// split's outputs are counted before they are allocated, and with last (nothing reads tri
+// afterwards) tri is given back once it is split, so that the attempt holds no more than the
+// schedule itself needs.
+int try_schedule(dt_graph *g, DevMem &tri, bool with_units, bool last, bool lean) {
     dt_ctx *ctx = g->ctx;
     hipStream_t st = ctx->stream;
     const uint64_t nt = g->n_tri_list;   // list entries (empty ones have no class)
@@ -606,55 +674,77 @@ int make_schedule(dt_graph *g, DevMem &tri) {
     R.force = g->tuning.force_path;
     R.cost_pct = g->cost_pct_used ? g->cost_pct_used : 100;
     // unit records hold 32-bit relative times
-    R.unit_ok = g->span <= kUnitMaxSpan ? 1u : 0u;
+    const bool unit_ok = g->span <= kUnitMaxSpan;
+    const bool units = with_units && R.force == 0 && unit_ok && g->m_s && g->n_tri;
     const unsigned grid = std::min(kClsGrid, grid_for(nt, kBlock));
-    DevMem cls, bcnt, part, base;
-    DT_TRY(dev_alloc(ctx, cls, nt + 1));
+    DevMem cls, bcnt, part, base, tot, rest, urec, ubkt;
     DT_TRY(dev_alloc(ctx, bcnt, (uint64_t)grid * kClasses * 4));
     DT_TRY(dev_alloc(ctx, part, (uint64_t)grid * kPartWords * 8));
     DT_TRY(dev_alloc(ctx, base, (uint64_t)grid * kClasses * 8));
-    // the per-edge unit keys (when unit records are allowed) on the first side stream, beside the
-    // classify pass; the partition pass waits for them
-    const bool units = R.force == 0 && R.unit_ok && g->m_s;
-    const hipStream_t ks = units && ctx->side[0] ? ctx->side[0] : st;
-    DevMem ukey;
-    DT_TRY(dev_alloc(ctx, ukey, (units ? g->m_s : 0) * 8));
-    struct KeyJoin {   // an early return must not release ukey while the side stream writes it
-        hipStream_t s, main;
-        ~KeyJoin() {
-            if (s != main) (void)hipStreamSynchronize(s);
-        }
-    } kjoin{ks, st};
-    if (units) {
-        if (ks != st) {
-            DT_HIP(hipEventRecord(ctx->ev_relay[0], st));
-            DT_HIP(hipStreamWaitEvent(ks, ctx->ev_relay[0], 0));
-        }
-        k_unit_keys<<<grid_for(g->m_s, kBlock), kBlock, 0, ks>>>(g->m_s, g->eoff.as<uint32_t>(), g->key.as<uint64_t>(),
-                                                                 ukey.as<uint64_t>());
+    DT_TRY(dev_alloc(ctx, tot, 512));
+    // t1 buckets of the unit records: at most 2^16, t1 >> unit_shift
+    int t_bits = 0;
+    while (t_bits < 31 && (1ll << t_bits) <= g->span) ++t_bits;
+    S.unit_shift = t_bits > 16 ? t_bits - 16 : 0;
+    const uint64_t nbk = unit_ok ? ((uint64_t)g->span >> S.unit_shift) + 1 : 1;
+    if (units && !g->ukey.ptr) {
+        DT_TRY(dev_alloc(ctx, g->ukey, g->m_s * 8));
+        unit_keys(g, st);
         DT_HIP(hipGetLastError());
-        if (ks != st) DT_HIP(hipEventRecord(ctx->ev_relay[1], ks));
     }
-    k_classify<<<grid, kBlock, 0, st>>>(nt, tri.as<uint32_t>(), g->eoff.as<uint32_t>(), R, cls.as<uint8_t>(),
-                                        bcnt.as<uint32_t>(), part.as<uint64_t>());
-    DT_HIP(hipGetLastError());
-    DevMem tot;
-    DT_TRY(dev_alloc(ctx, tot, 16 * 8));
-    k_cls_totals<<<1, kBlock, 0, st>>>(grid, bcnt.as<uint32_t>(), part.as<uint64_t>(), base.as<uint64_t>(),
-                                       tot.as<uint64_t>());
-    DT_HIP(hipGetLastError());
+    // room for unit records of every triangle and for other triangles of a quarter of them; the pass
+    // runs again at the counted sizes where that is too little
+    uint64_t unit_cap = lean ? 0 : g->n_tri, rest_cap = lean ? 0 : std::max<uint64_t>(g->n_tri / 4, 1ull << 16);
+    uint64_t n_rest = nt;
     uint64_t *hs = reinterpret_cast<uint64_t *>(ctx->pinned_stage);
-    DT_HIP(hipMemcpyAsync(hs, tot.ptr, kTotWords * 8, hipMemcpyDeviceToHost, st));
-    DT_HIP(hipStreamSynchronize(st));
+    unsigned long long *ctr = tot.as<unsigned long long>() + 16;   // (units at [0], others at [16])
+    for (int attempt = 0;; ++attempt) {
+        const uint32_t *list = tri.as<uint32_t>();
+        if (units) {
+            DT_TRY(dev_alloc(ctx, urec, unit_cap * sizeof(uint4)));
+            DT_TRY(dev_alloc(ctx, ubkt, unit_cap * 2));
+            DT_TRY(dev_alloc(ctx, rest, rest_cap * 12));
+            list = rest.as<uint32_t>();
+            DT_HIP(hipMemsetAsync(tot.ptr, 0, 512, st));
+            const unsigned sgrid = std::min<unsigned>(grid_for(nt, kSplitTile), (unsigned)ctx->num_cus * 16);
+            k_unit_split<<<sgrid, kBlock, 0, st>>>(nt, tri.as<uint32_t>(), g->ukey.as<uint64_t>(), g->shift, S.unit_shift,
+                                                   urec.as<uint4>(), ubkt.as<uint16_t>(), unit_cap, rest.as<uint32_t>(),
+                                                   rest_cap, ctr);
+            DT_HIP(hipGetLastError());
+        }
+        const uint64_t n_max = units ? rest_cap : nt;
+        DT_TRY(dev_alloc(ctx, cls, n_max + 1));
+        k_classify<<<grid, kBlock, 0, st>>>(n_max, units ? ctr + 16 : nullptr, list, g->eoff.as<uint32_t>(), R,
+                                            cls.as<uint8_t>(), bcnt.as<uint32_t>(), part.as<uint64_t>());
+        DT_HIP(hipGetLastError());
+        k_cls_totals<<<1, kBlock, 0, st>>>(grid, bcnt.as<uint32_t>(), part.as<uint64_t>(), base.as<uint64_t>(),
+                                           tot.as<uint64_t>());
+        DT_HIP(hipGetLastError());
+        DT_HIP(hipMemcpyAsync(hs, tot.ptr, 512, hipMemcpyDeviceToHost, st));
+        DT_HIP(hipStreamSynchronize(st));
+        if (!units) break;
+        n_rest = hs[32];
+        if (hs[16] + n_rest != g->n_tri) return fail(DT_EDEVICE, "unit and other triangles do not add up");
+        if (hs[16] <= unit_cap && n_rest <= rest_cap) break;
+        if (attempt) return fail(DT_EDEVICE, "triangle classes changed between passes");
+        unit_cap = hs[16];
+        rest_cap = n_rest;
+    }
+    if (units && lean && last) {
+        g->ukey.reset();
+        tri.reset();
+    }
+    const uint32_t *list = units ? rest.as<uint32_t>() : tri.as<uint32_t>();
+    const uint64_t nu = units ? hs[16] : 0;
     uint64_t ncls[kClasses];
     for (int c = 0; c < kClasses; ++c) ncls[c] = hs[c];
     const unsigned __int128 s3 = ((unsigned __int128)hs[kClasses + 1] << 64) | hs[kClasses];
-    g->sum_sigma3 = s3;
-    g->alg_bytes = hs[kClasses + 2];
+    g->sum_sigma3 = s3 + nu;
+    g->alg_bytes_unit = sizeof(uint4) * nu;
+    g->alg_bytes = hs[kClasses + 2] + g->alg_bytes_unit;
     g->alg_bytes_light = hs[kClasses + 3];
     g->alg_bytes_medium = hs[kClasses + 4];
-    g->alg_bytes_unit = hs[kClasses + 5];
-    const uint64_t na = ncls[kClsMedium], nh_always = ncls[kClsHeavy], nu = ncls[kClsUnit], nc = ncls[kClsContest];
+    const uint64_t na = ncls[kClsMedium], nh_always = ncls[kClsHeavy], nc = ncls[kClsContest];
     if (ncls[kClsLight] + na + nh_always + nu + nc != g->n_tri)
         return fail(DT_EDEVICE, "triangle classes do not add up");
     S.n_light = ncls[kClsLight];
@@ -668,33 +758,16 @@ int make_schedule(dt_graph *g, DevMem &tri) {
     DT_TRY(dev_alloc(ctx, S.light, S.n_light * 12));
     DT_TRY(dev_alloc(ctx, S.medium, nm * 12));
     DT_TRY(dev_alloc(ctx, S.heavy, nh * 12));
-    // t1 buckets of the unit records: at most 2^16, t1 >> unit_shift
-    int t_bits = 0;
-    while (t_bits < 31 && (1ll << t_bits) <= g->span) ++t_bits;
-    S.unit_shift = t_bits > 16 ? t_bits - 16 : 0;
-    const uint64_t nbk = R.unit_ok ? ((uint64_t)g->span >> S.unit_shift) + 1 : 1;
     // time slices of the window index: span >> cell_shift < kSlices
     S.cell_shift = 0;
     while (S.cell_shift < 62 && (g->span >> S.cell_shift) >= (int64_t)kSlices) ++S.cell_shift;
-    DevMem urec, ubkt, ubkt2, ustart, lrec, lkey, mrec, mkey, lstart, mstart, crec, ckey;
-    DT_TRY(dev_alloc(ctx, urec, nu * sizeof(uint4)));
-    DT_TRY(dev_alloc(ctx, ubkt, nu * 2));
+    DevMem ubkt2, ustart, lrec, lkey, mrec, mkey, lstart, mstart, crec, ckey;
     DT_TRY(dev_alloc(ctx, lrec, S.n_light * sizeof(uint4)));
     DT_TRY(dev_alloc(ctx, lkey, S.n_light * 2));
     DT_TRY(dev_alloc(ctx, mrec, nm * sizeof(uint4)));
     DT_TRY(dev_alloc(ctx, mkey, nm * 2));
     DT_TRY(dev_alloc(ctx, crec, nc * sizeof(uint4)));
     DT_TRY(dev_alloc(ctx, ckey, nc * 2));
-    if (units && ks != st) DT_HIP(hipStreamWaitEvent(st, ctx->ev_relay[1], 0));
-    if (nt) {
-        k_partition<<<grid, kBlock, 0, st>>>(nt, tri.as<uint32_t>(), cls.as<uint8_t>(), base.as<uint64_t>(),
-            g->eoff.as<uint32_t>(), g->key.as<uint64_t>(), ukey.as<uint64_t>(), g->shift, S.unit_shift, S.cell_shift, nc,
-            S.light.as<uint32_t>(), S.medium.as<uint32_t>(), S.heavy.as<uint32_t>(), crec.as<uint4>(), lrec.as<uint4>(),
-            lkey.as<uint16_t>(), mrec.as<uint4>(), mkey.as<uint16_t>(), urec.as<uint4>(), ubkt.as<uint16_t>());
-        DT_HIP(hipGetLastError());
-    }
-    cls.reset();
-    ukey.reset();
     // unit records ordered by t1 bucket (a stable two-pass radix sort on the 16-bit bucket) on the
     // first side stream, while this stream builds the other lists; the host keeps the bucket starts
     // (read back through the pinned staging buffer from byte kStageUnit; the cell starts, level
@@ -729,6 +802,14 @@ int make_schedule(dt_graph *g, DevMem &tri) {
         DT_HIP(hipMemcpyAsync(ctx->pinned_stage + kStageUnit, ustart.ptr, (nbk + 1) * 4, hipMemcpyDeviceToHost, us));
         if (us != st) DT_HIP(hipEventRecord(ctx->ev_relay[1], us));
     }
+    if (n_rest) {
+        k_partition<<<grid, kBlock, 0, st>>>(n_rest, list, cls.as<uint8_t>(), base.as<uint64_t>(),
+            g->eoff.as<uint32_t>(), g->key.as<uint64_t>(), g->shift, S.cell_shift, nc,
+            S.light.as<uint32_t>(), S.medium.as<uint32_t>(), S.heavy.as<uint32_t>(), crec.as<uint4>(), lrec.as<uint4>(),
+            lkey.as<uint16_t>(), mrec.as<uint4>(), mkey.as<uint16_t>());
+        DT_HIP(hipGetLastError());
+    }
+    cls.reset();
     // contested triangles: their levels, then descending level order after the always-medium
     // ones (medium list) and before the always-heavy ones (heavy list)
     DevMem kstart;
@@ -848,6 +929,31 @@ int make_schedule(dt_graph *g, DevMem &tri) {
     DT_HIP(hipStreamSynchronize(st));
     if (nu) memcpy(S.unit_index.data(), ctx->pinned_stage + kStageUnit, (nbk + 1) * 4);
     return DT_OK;
+}
+
+}  // namespace
+
+// A build makes the unit keys beside its enumeration; a schedule made again makes them first.
+void unit_keys(dt_graph *g, hipStream_t st) {
+    k_unit_keys<<<grid_for(g->m_s, kBlock), kBlock, 0, st>>>(g->m_s, g->eoff.as<uint32_t>(), g->key.as<uint64_t>(),
+                                                             g->ukey.as<uint64_t>());
+}
+
+// Where memory is short the attempt is made again with counted sizes and, if tri is needed again
+// (the trials of the split), at last without unit records: those are counted on the other paths.
+int make_schedule(dt_graph *g, DevMem &tri, bool last, bool with_units) {
+    int rc = try_schedule(g, tri, with_units, last, false);
+    if (rc == DT_ENOMEM && with_units) {
+        clear_error();
+        rc = try_schedule(g, tri, true, last, true);
+    }
+    if (rc == DT_ENOMEM && with_units && !last) {
+        clear_error();
+        rc = try_schedule(g, tri, false, last, true);
+    }
+    if (rc != DT_OK) g->sched = Schedule();
+    if (rc != DT_OK || last) g->ukey.reset();
+    return rc;
 }
 
 void cell_ranges(const std::vector<uint64_t> &ix, int cell_shift, const DQuery &q, Ranges &r) {

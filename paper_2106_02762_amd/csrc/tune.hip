@@ -98,7 +98,7 @@ int autotune_count(dt_graph *g, DevMem &tri, TunedCount *out) {
         for (uint32_t cp : pcts) {
             g->light_cap_used = lc;
             g->cost_pct_used = cp;
-            DT_TRY(make_schedule(g, tri));
+            DT_TRY(make_schedule(g, tri, false));
             float ms = 0.f;
             DT_TRY(time_counts(g, &ms));
             if (ms < best_ms - kMargin) {
@@ -109,7 +109,7 @@ int autotune_count(dt_graph *g, DevMem &tri, TunedCount *out) {
         }
     g->light_cap_used = best.light_cap;
     g->cost_pct_used = best.cost_pct;
-    DT_TRY(make_schedule(g, tri));
+    DT_TRY(make_schedule(g, tri, false));
     const uint32_t lbpc[3] = {16, 8, 32}, mbpc[3] = {8, 4, 16};
     best_ms = 1e30f;
     for (uint32_t l : lbpc)
