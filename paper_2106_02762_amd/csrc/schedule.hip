@@ -76,19 +76,31 @@ __device__ __forceinline__ int tri_class(uint64_t s_uv, uint64_t s_uw, uint64_t 
     return kClsContest;
 }
 
-constexpr int kPartWords = 5;   // per block: sum_sigma3 lo, hi, bytes, light, medium bytes
-constexpr unsigned kClsGrid = 4096;   // blocks of the classify and partition passes at most (grid-stride)
-constexpr int kTotWords = kClasses + kPartWords;   // class sizes, then the partial words
+constexpr int kSumWords = 5;   // sum_sigma3 lo, hi, bytes, light, medium bytes
+constexpr int kTotWords = kClasses + kSumWords;   // class sizes, then the sums
 
-// Per list entry its class (one byte; kClasses for an empty entry); per block the triangles of
-// each class and the sum of sigma products (128-bit) and byte totals.  The partition pass walks the
-// entries in the same block / iteration order, so per-block class counts give every triangle its
-// place.  The list has *n_p entries (at most n_max; null: n_max).
+// What the passes of a schedule count into, zeroed together.
+struct SchedCtr {
+    unsigned long long tot[kTotWords];         // k_classify's totals
+    unsigned long long units[16], rest[16];    // k_unit_split's counters (a line each, [0] used)
+    unsigned long long ticket[16];             // k_classify blocks done
+    unsigned long long cls_n[kClasses][16];    // k_partition's places
+    unsigned long long hist[2][kCells];        // light, medium triangles of each window cell
+    unsigned long long cur[2][kCells];         // and places taken in it
+    unsigned long long lev_hist[kLevels], lev_cur[kLevels];   // contested triangles of each level
+};
+
+// Per list entry its class (one byte; kClasses for an empty entry), and the totals: class sizes, the
+// sum of sigma products (128-bit) and byte totals.  The list has *n_p entries (at most n_max; null:
+// n_max).  A block adds its sums with one atomic each and the block that comes last writes the
+// totals and the split's counters to the host, so that no pass over per-block sums and no copy
+// follows.
 __global__ void __launch_bounds__(kBlock)
-k_classify(uint64_t n_max, const unsigned long long *__restrict__ n_p, const uint32_t *__restrict__ tri, const uint32_t *__restrict__ eoff, SplitRule R,
-           uint8_t *__restrict__ cls, uint32_t *__restrict__ bcnt, uint64_t *__restrict__ part) {
-    __shared__ unsigned long long s_w[kPartWords][kBlock / 64];
-    __shared__ unsigned s_cnt[kClasses];
+k_classify(uint64_t n_max, const unsigned long long *__restrict__ n_p, const uint32_t *__restrict__ tri,
+           const uint32_t *__restrict__ eoff, SplitRule R, uint8_t *__restrict__ cls, SchedCtr *__restrict__ ctr,
+           unsigned long long *__restrict__ host) {
+    __shared__ unsigned long long s_w[kSumWords][kBlock / 64];
+    __shared__ unsigned s_cnt[kClasses], s_last;
     if (threadIdx.x < kClasses) s_cnt[threadIdx.x] = 0;
     __syncthreads();
     const uint64_t n_tri = n_p && *n_p < n_max ? *n_p : n_max;
@@ -121,7 +133,7 @@ k_classify(uint64_t n_max, const unsigned long long *__restrict__ n_p, const uin
     // block sums: within each wavefront by shuffles (the 128-bit sum as two words with carry), then
     // over the wavefronts
     unsigned long long lo = (unsigned long long)acc, hi = (unsigned long long)(acc >> 64);
-    unsigned long long w[kPartWords - 2] = {bytes, bytes_light, bytes_medium};
+    unsigned long long w[kSumWords - 2] = {bytes, bytes_light, bytes_medium};
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
         const unsigned long long lo2 = __shfl_xor(lo, o, 64), hi2 = __shfl_xor(hi, o, 64);
@@ -129,93 +141,40 @@ k_classify(uint64_t n_max, const unsigned long long *__restrict__ n_p, const uin
         hi += hi2 + (s < lo ? 1ull : 0ull);
         lo = s;
 #pragma unroll
-        for (int x = 0; x < kPartWords - 2; ++x) w[x] += __shfl_xor(w[x], o, 64);
+        for (int x = 0; x < kSumWords - 2; ++x) w[x] += __shfl_xor(w[x], o, 64);
     }
     const unsigned wave = threadIdx.x / 64;
     if ((threadIdx.x & 63) == 0) {
         s_w[0][wave] = lo;
         s_w[1][wave] = hi;
-        for (int x = 2; x < kPartWords; ++x) s_w[x][wave] = w[x - 2];
+        for (int x = 2; x < kSumWords; ++x) s_w[x][wave] = w[x - 2];
     }
     __syncthreads();
-    if (threadIdx.x < kClasses) bcnt[kClasses * blockIdx.x + threadIdx.x] = s_cnt[threadIdx.x];
     if (threadIdx.x == 0) {
         unsigned __int128 t = 0;
-        unsigned long long tw[kPartWords] = {0, 0, 0, 0, 0};
+        unsigned long long tw[kSumWords] = {0, 0, 0, 0, 0};
         for (unsigned j = 0; j < kBlock / 64; ++j) {
             t += ((unsigned __int128)s_w[1][j] << 64) | s_w[0][j];
-            for (int x = 2; x < kPartWords; ++x) tw[x] += s_w[x][j];
+            for (int x = 2; x < kSumWords; ++x) tw[x] += s_w[x][j];
         }
-        part[kPartWords * blockIdx.x] = (uint64_t)t;
-        part[kPartWords * blockIdx.x + 1] = (uint64_t)(t >> 64);
-        for (int x = 2; x < kPartWords; ++x) part[kPartWords * blockIdx.x + x] = tw[x];
-    }
-}
-
-// One workgroup: every classify block's first position in each class list (base, [block][class])
-// and the totals: tot[0..3] class sizes, tot[4..5] the 128-bit sum of sigma products, tot[6..8]
-// the byte totals.
-__global__ void __launch_bounds__(kBlock)
-k_cls_totals(unsigned nblk, const uint32_t *__restrict__ bcnt, const uint64_t *__restrict__ part,
-             uint64_t *__restrict__ base, uint64_t *__restrict__ tot) {
-    __shared__ unsigned long long s_tot[kBlock];
-    const unsigned tid = threadIdx.x;
-    const unsigned per = (nblk + kBlock - 1) / kBlock;
-    const unsigned b0 = min(tid * per, nblk), b1 = min(b0 + per, nblk);
-    for (int c = 0; c < kClasses; ++c) {
-        unsigned long long mine = 0;
-        for (unsigned b = b0; b < b1; ++b) mine += bcnt[kClasses * b + c];
-        s_tot[tid] = mine;
-        __syncthreads();
-        // exclusive prefix over threads (Hillis-Steele on the LDS copy)
-        for (unsigned o = 1; o < kBlock; o <<= 1) {
-            const unsigned long long y = tid >= o ? s_tot[tid - o] : 0ull;
-            __syncthreads();
-            s_tot[tid] += y;
-            __syncthreads();
-        }
-        unsigned long long run = s_tot[tid] - mine;
-        for (unsigned b = b0; b < b1; ++b) {
-            base[kClasses * b + c] = run;
-            run += bcnt[kClasses * b + c];
-        }
-        if (tid == kBlock - 1) tot[c] = s_tot[tid];
-        __syncthreads();
-    }
-    // the sums of the blocks' partial words, each thread over its blocks, then by shuffles
-    unsigned __int128 t = 0;
-    unsigned long long w[kPartWords] = {0, 0, 0, 0, 0};
-    for (unsigned b = b0; b < b1; ++b) {
-        t += ((unsigned __int128)part[kPartWords * b + 1] << 64) | part[kPartWords * b];
-        for (int x = 2; x < kPartWords; ++x) w[x] += part[kPartWords * b + x];
-    }
-    unsigned long long lo = (unsigned long long)t, hi = (unsigned long long)(t >> 64);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const unsigned long long lo2 = __shfl_xor(lo, o, 64), hi2 = __shfl_xor(hi, o, 64);
-        const unsigned long long sum = lo + lo2;
-        hi += hi2 + (sum < lo ? 1ull : 0ull);
-        lo = sum;
-#pragma unroll
-        for (int x = 2; x < kPartWords; ++x) w[x] += __shfl_xor(w[x], o, 64);
-    }
-    __shared__ unsigned long long s_part[kBlock / 64][kPartWords];
-    if ((tid & 63) == 0) {
-        s_part[tid / 64][0] = lo;
-        s_part[tid / 64][1] = hi;
-        for (int x = 2; x < kPartWords; ++x) s_part[tid / 64][x] = w[x];
+        for (int x = 0; x < kClasses; ++x)
+            if (s_cnt[x]) atomicAdd(&ctr->tot[x], (unsigned long long)s_cnt[x]);
+        const unsigned long long t0 = (unsigned long long)t;
+        unsigned long long t1 = (unsigned long long)(t >> 64);
+        if (t0) t1 += atomicAdd(&ctr->tot[kClasses], t0) + t0 < t0 ? 1ull : 0ull;
+        if (t1) atomicAdd(&ctr->tot[kClasses + 1], t1);
+        for (int x = 2; x < kSumWords; ++x)
+            if (tw[x]) atomicAdd(&ctr->tot[kClasses + x], tw[x]);
+        __threadfence();
+        s_last = atomicAdd(&ctr->ticket[0], 1ull) == gridDim.x - 1;
     }
     __syncthreads();
-    if (tid == 0) {
-        unsigned __int128 tt = 0;
-        unsigned long long tw[kPartWords] = {0, 0, 0, 0, 0};
-        for (unsigned j = 0; j < kBlock / 64; ++j) {
-            tt += ((unsigned __int128)s_part[j][1] << 64) | s_part[j][0];
-            for (int x = 2; x < kPartWords; ++x) tw[x] += s_part[j][x];
-        }
-        tot[kClasses] = (uint64_t)tt;
-        tot[kClasses + 1] = (uint64_t)(tt >> 64);
-        for (int x = 2; x < kPartWords; ++x) tot[kClasses + x] = tw[x];
+    if (s_last) {
+        __threadfence();
+        if (threadIdx.x < kTotWords)
+            host[threadIdx.x] = __hip_atomic_load(&ctr->tot[threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        else if (threadIdx.x == kTotWords) host[kTotWords] = ctr->units[0];
+        else if (threadIdx.x == kTotWords + 1) host[kTotWords + 1] = ctr->rest[0];
     }
 }
 
@@ -262,15 +221,15 @@ __global__ void k_unit_keys(uint64_t ms, const uint32_t *__restrict__ eoff, cons
 // holds a tile of kSplitPer entries a thread, all their gathers in flight together, and takes the
 // tile's places in both outputs with one atomic each.  Bound by the list and the gathers of the third
 // edges' keys; one pass where classifying every entry and then moving it read both twice (classify,
-// partition of 67M entries: 1.0 + 1.9 ms, 1.0 so; the whole schedule 4.7 -> 3.0 ms).  Counters: ctr[0] unit
-// triangles, ctr[16] others (past unit_cap and rest_cap they are counted and not written).
+// partition of 67M entries: 1.0 + 1.9 ms, 1.0 so; the whole schedule 4.7 -> 3.0 ms).  Past unit_cap
+// and rest_cap triangles are counted and not written.
 constexpr unsigned kSplitPer = 8;
 constexpr unsigned kSplitTile = kBlock * kSplitPer;
 __global__ void __launch_bounds__(kBlock)
 k_unit_split(uint64_t nt, const uint32_t *__restrict__ tri, const uint64_t *__restrict__ ukey, int shift, int bshift,
              uint4 *__restrict__ urec, uint16_t *__restrict__ ubkt, uint64_t unit_cap,
              uint32_t *__restrict__ rest, uint64_t rest_cap,
-             unsigned long long *__restrict__ ctr) {
+             SchedCtr *__restrict__ ctr) {
     __shared__ uint32_t s_cnt[2][kBlock / 64];
     __shared__ unsigned long long s_base[2];
     const unsigned lane = threadIdx.x & 63, wave = threadIdx.x / 64;
@@ -307,7 +266,7 @@ k_unit_split(uint64_t nt, const uint32_t *__restrict__ tri, const uint64_t *__re
                 s_cnt[threadIdx.x][w] = n;
                 n += c;
             }
-            s_base[threadIdx.x] = n ? atomicAdd(&ctr[16 * threadIdx.x], (unsigned long long)n) : 0ull;
+            s_base[threadIdx.x] = n ? atomicAdd(threadIdx.x ? ctr->rest : ctr->units, (unsigned long long)n) : 0ull;
         }
         __syncthreads();
         uint64_t pu = s_base[0] + s_cnt[0][wave], pr = s_base[1] + s_cnt[1][wave];
@@ -340,63 +299,86 @@ k_unit_split(uint64_t nt, const uint32_t *__restrict__ tri, const uint64_t *__re
     }
 }
 
-// Every triangle to its class's list at base[class][block] + its rank in the block's walk: light and
-// always-medium triangles also go, with their window cell as a sort key, to the windowed copies'
-// inputs; always-heavy ones go after the n_c contested ones in the heavy list; contested ones to
-// crec for the level search.
+// Every triangle to its class's list: light and always-medium triangles with their window cells (mcell:
+// the always-medium ones first, then the n_c contested ones), which are counted too; always-heavy ones
+// after the n_c contested ones in the heavy list; contested ones to crec for the level search.  A
+// workgroup takes its tile's places in each list with one atomic a class.
+constexpr unsigned kPartPer = 4;
+constexpr unsigned kPartTile = kBlock * kPartPer;
 __global__ void __launch_bounds__(kBlock)
 k_partition(uint64_t n_tri, const uint32_t *__restrict__ tri, const uint8_t *__restrict__ cls,
-            const uint64_t *__restrict__ base, const uint32_t *__restrict__ eoff,
-            const uint64_t *__restrict__ key, int shift, int cshift, uint64_t n_c,
-            uint32_t *__restrict__ light, uint32_t *__restrict__ medium, uint32_t *__restrict__ heavy,
-            uint4 *__restrict__ crec, uint4 *__restrict__ lrec, uint16_t *__restrict__ lkey,
-            uint4 *__restrict__ mrec, uint16_t *__restrict__ mkey) {
-    __shared__ unsigned long long s_wave[kBlock / 64];
+            const uint32_t *__restrict__ eoff, const uint64_t *__restrict__ key, int shift, int cshift, uint64_t n_a,
+            uint64_t n_c, uint32_t *__restrict__ light, uint32_t *__restrict__ medium, uint32_t *__restrict__ heavy,
+            uint4 *__restrict__ crec, uint16_t *__restrict__ lcell, uint16_t *__restrict__ mcell,
+            SchedCtr *__restrict__ ctr) {
+    __shared__ uint32_t s_hist[2][kCells];
+    __shared__ uint32_t s_cnt[kClasses][kBlock / 64];
+    __shared__ unsigned long long s_base[kClasses];
     const unsigned lane = threadIdx.x & 63, wave = threadIdx.x / 64;
-    uint64_t run[kClasses];
+    const uint64_t below = (1ull << lane) - 1;
+    for (unsigned x = threadIdx.x; x < 2 * kCells; x += kBlock) s_hist[x / kCells][x % kCells] = 0;
+    for (uint64_t t0 = (uint64_t)blockIdx.x * kPartTile; t0 < n_tri; t0 += (uint64_t)gridDim.x * kPartTile) {
+        int k[kPartPer];
+        uint32_t mine[kClasses] = {0, 0, 0, 0};   // of this wavefront
 #pragma unroll
-    for (int c = 0; c < kClasses; ++c) run[c] = base[kClasses * blockIdx.x + c];
-    for (uint64_t b0 = (uint64_t)blockIdx.x * kBlock; b0 < n_tri; b0 += (uint64_t)gridDim.x * kBlock) {
-        const uint64_t i = b0 + threadIdx.x;
-        const int k = i < n_tri ? cls[i] : kClasses;
-        // 12-bit class counters in one word (a block walks at most 256 triangles per step)
-        const unsigned long long f = k < kClasses ? 1ull << (12 * k) : 0ull;
-        unsigned long long x = f;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const unsigned long long y = __shfl_up(x, o, 64);
-            if (lane >= (unsigned)o) x += y;
+        for (unsigned j = 0; j < kPartPer; ++j) {
+            const uint64_t i = t0 + j * kBlock + threadIdx.x;
+            k[j] = i < n_tri ? cls[i] : kClasses;
         }
-        if (lane == 63) s_wave[wave] = x;
-        __syncthreads();
-        unsigned long long before = 0, total = 0;
 #pragma unroll
-        for (unsigned w = 0; w < kBlock / 64; ++w) {
-            before += w < wave ? s_wave[w] : 0ull;
-            total += s_wave[w];
+        for (unsigned j = 0; j < kPartPer; ++j)
+#pragma unroll
+            for (int c = 0; c < kClasses; ++c) mine[c] += (uint32_t)__popcll(__ballot(k[j] == c));
+        __syncthreads();   // (s_hist zeroed; the last tile's places read)
+        if (lane == 0)
+            for (int c = 0; c < kClasses; ++c) s_cnt[c][wave] = mine[c];
+        __syncthreads();
+        if (threadIdx.x < kClasses) {
+            uint32_t n = 0;
+            for (unsigned w = 0; w < kBlock / 64; ++w) {
+                const uint32_t x = s_cnt[threadIdx.x][w];
+                s_cnt[threadIdx.x][w] = n;
+                n += x;
+            }
+            s_base[threadIdx.x] = n ? atomicAdd(&ctr->cls_n[threadIdx.x][0], (unsigned long long)n) : 0ull;
         }
         __syncthreads();
-        if (k < kClasses) {
-            const uint64_t pos = run[k] + (((before + x - f) >> (12 * k)) & 0xfffull);
-            const uint32_t e_uv = tri[3 * i], e_uw = tri[3 * i + 1], e_vw = tri[3 * i + 2];
-            if (k == kClsContest) {
-                crec[pos] = make_uint4(e_uv, e_uw, e_vw, 0u);
-            } else {
-                uint32_t *dst = (k == kClsLight ? light : (k == kClsMedium ? medium : heavy + 3 * n_c)) + 3 * pos;
-                dst[0] = e_uv;
-                dst[1] = e_uw;
-                dst[2] = e_vw;
-                if (k == kClsLight) {
-                    lrec[pos] = make_uint4(e_uv, e_uw, e_vw, 0u);
-                    lkey[pos] = window_cell(e_uv, e_uw, e_vw, eoff, key, shift, cshift);
-                } else if (k == kClsMedium) {
-                    mrec[pos] = make_uint4(e_uv, e_uw, e_vw, (uint32_t)kLevelAlways);
-                    mkey[pos] = window_cell(e_uv, e_uw, e_vw, eoff, key, shift, cshift);
+        uint64_t at[kClasses];
+#pragma unroll
+        for (int c = 0; c < kClasses; ++c) at[c] = s_base[c] + s_cnt[c][wave];
+#pragma unroll
+        for (unsigned j = 0; j < kPartPer; ++j) {
+            uint64_t pos = 0;
+#pragma unroll
+            for (int c = 0; c < kClasses; ++c) {
+                const uint64_t m = __ballot(k[j] == c);
+                if (k[j] == c) pos = at[c] + (uint32_t)__popcll(m & below);
+                at[c] += (uint32_t)__popcll(m);
+            }
+            if (k[j] < kClasses) {
+                const uint64_t i = t0 + j * kBlock + threadIdx.x;
+                const uint32_t e_uv = tri[3 * i], e_uw = tri[3 * i + 1], e_vw = tri[3 * i + 2];
+                if (k[j] == kClsContest) {
+                    crec[pos] = make_uint4(e_uv, e_uw, e_vw, 0u);
+                } else {
+                    uint32_t *dst = (k[j] == kClsLight ? light : (k[j] == kClsMedium ? medium : heavy + 3 * n_c)) + 3 * pos;
+                    dst[0] = e_uv;
+                    dst[1] = e_uw;
+                    dst[2] = e_vw;
+                }
+                if (k[j] != kClsHeavy) {
+                    const uint16_t cell = window_cell(e_uv, e_uw, e_vw, eoff, key, shift, cshift);
+                    if (k[j] == kClsLight) lcell[pos] = cell;
+                    else mcell[k[j] == kClsContest ? n_a + pos : pos] = cell;
+                    atomicAdd(&s_hist[k[j] == kClsLight ? 0 : 1][cell], 1u);
                 }
             }
         }
-#pragma unroll
-        for (int c = 0; c < kClasses; ++c) run[c] += (total >> (12 * c)) & 0xfffull;
+    }
+    __syncthreads();
+    for (unsigned x = threadIdx.x; x < 2 * kCells; x += kBlock) {
+        const uint32_t n = s_hist[x / kCells][x % kCells];
+        if (n) atomicAdd(&ctr->hist[x / kCells][x % kCells], (unsigned long long)n);
     }
 }
 
@@ -406,11 +388,14 @@ k_partition(uint64_t n_tri, const uint32_t *__restrict__ tri, const uint8_t *__r
 // The close pairs are counted exactly (two binary searches per outer edge and inner direction) on
 // up to kCrossSample outer edges spread evenly over the pair and scaled to all of them, stopping
 // once the budget is passed; the levels are found by binary search (close pairs grow with D).
-// Writes the level to crec[i].w and the sort key 255 - level (descending levels).  The level only
+// Writes the level to crec[i].w and counts the triangles of each level.  The level only
 // decides which exact method counts the triangle for a query.
 __global__ void __launch_bounds__(kBlock)
-k_crossover(uint64_t nc, uint4 *__restrict__ crec, uint16_t *__restrict__ ckey, const uint32_t *__restrict__ eoff,
-            const uint64_t *__restrict__ key, int shift, int64_t span, uint32_t cost_pct) {
+k_crossover(uint64_t nc, uint4 *__restrict__ crec, const uint32_t *__restrict__ eoff,
+            const uint64_t *__restrict__ key, int shift, int64_t span, uint32_t cost_pct, SchedCtr *__restrict__ ctr) {
+    __shared__ uint32_t s_lev[kLevels];
+    if (threadIdx.x < kLevels) s_lev[threadIdx.x] = 0;
+    __syncthreads();
     const unsigned lane = threadIdx.x & 63;
     const uint64_t nw = (uint64_t)gridDim.x * (kBlock / 64);
     for (uint64_t i = ((uint64_t)blockIdx.x * kBlock + threadIdx.x) / 64; i < nc; i += nw) {
@@ -454,30 +439,127 @@ k_crossover(uint64_t nc, uint4 *__restrict__ crec, uint16_t *__restrict__ ckey, 
         }
         if (lane == 0) {
             crec[i].w = lo;
-            ckey[i] = (uint16_t)(255u - lo);
+            atomicAdd(&s_lev[lo], 1u);
         }
+    }
+    __syncthreads();
+    if (threadIdx.x < kLevels && s_lev[threadIdx.x])
+        atomicAdd(&ctr->lev_hist[threadIdx.x], (unsigned long long)s_lev[threadIdx.x]);
+}
+
+// Exclusive sums over the workgroup of one value a thread, in thread order; the total to every thread.
+__device__ __forceinline__ unsigned long long block_scan(unsigned long long v, unsigned long long *s_wave,
+                                                         unsigned long long &total) {
+    const unsigned lane = threadIdx.x & 63, wave = threadIdx.x / 64;
+    unsigned long long x = v;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const unsigned long long y = __shfl_up(x, o, 64);
+        if (lane >= (unsigned)o) x += y;
+    }
+    __syncthreads();   // (the last call's s_wave read)
+    if (lane == 63) s_wave[wave] = x;
+    __syncthreads();
+    unsigned long long before = 0;
+    total = 0;
+    for (unsigned w = 0; w < blockDim.x / 64; ++w) {
+        before += w < wave ? s_wave[w] : 0ull;
+        total += s_wave[w];
+    }
+    return before + x - v;
+}
+
+// Starts of the window cells in a list, from its triangles of each cell.
+__device__ __forceinline__ void cell_starts(const unsigned long long *__restrict__ hist, unsigned long long *s_start,
+                                            unsigned long long *s_wave) {
+    constexpr unsigned per = kCells / kBlock;
+    static_assert(kCells % kBlock == 0, "cells a thread");
+    unsigned long long h[per], n = 0, total;
+#pragma unroll
+    for (unsigned x = 0; x < per; ++x) {
+        h[x] = hist[per * threadIdx.x + x];
+        n += h[x];
+    }
+    unsigned long long at = block_scan(n, s_wave, total);
+#pragma unroll
+    for (unsigned x = 0; x < per; ++x) {
+        s_start[per * threadIdx.x + x] = at;
+        at += h[x];
     }
 }
 
-// The contested triangles in descending level order (crec sorted): after the n_a always-medium
-// ones in the medium list (with their window cells and levels for the windowed copy) and first in
-// the heavy list.
-__global__ void k_contest_place(uint64_t nc, const uint4 *__restrict__ crec, uint64_t n_a,
-                                uint32_t *__restrict__ medium, uint32_t *__restrict__ heavy, uint4 *__restrict__ mrec,
-                                uint16_t *__restrict__ mkey, const uint32_t *__restrict__ eoff,
-                                const uint64_t *__restrict__ key, int shift, int cshift) {
-    const uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i >= nc) return;
-    const uint4 r = crec[i];
-    const uint64_t m = n_a + i;
-    medium[3 * m] = r.x;
-    medium[3 * m + 1] = r.y;
-    medium[3 * m + 2] = r.z;
-    heavy[3 * i] = r.x;
-    heavy[3 * i + 1] = r.y;
-    heavy[3 * i + 2] = r.z;
-    mrec[m] = r;
-    mkey[m] = window_cell(r.x, r.y, r.z, eoff, key, shift, cshift);
+// The windowed copies in window-cell order, and the contested triangles in descending level order:
+// after the n_a always-medium ones in the medium list and first in the heavy list.  Tiles of the light
+// list, of the always-medium list and of crec, one a workgroup: ranks within a tile by atomics in LDS,
+// the tile's places in a cell (and level) with one atomic each.  The order within a cell is of no
+// matter, so this takes the place of three sorts with their temporaries and the passes that packed and
+// unpacked their records (86 us for the lists of 61M edges).
+constexpr unsigned kPlacePer = 8;
+constexpr unsigned kPlaceTile = kBlock * kPlacePer;
+__global__ void __launch_bounds__(kBlock)
+k_place(uint64_t n_l, uint64_t n_a, uint64_t n_c, unsigned tiles_l, unsigned tiles_a, const uint32_t *__restrict__ light,
+        const uint16_t *__restrict__ lcell, uint32_t *__restrict__ medium, const uint16_t *__restrict__ mcell,
+        const uint4 *__restrict__ crec, uint32_t *__restrict__ heavy, uint32_t *__restrict__ light_w,
+        uint32_t *__restrict__ medium_w, uint8_t *__restrict__ mlev_w, SchedCtr *__restrict__ ctr) {
+    __shared__ unsigned long long s_at[kCells], s_lat[kLevels], s_wave[kBlock / 64];
+    __shared__ uint32_t s_cnt[kCells], s_lcnt[kLevels];
+    const int seg = blockIdx.x < tiles_l ? 0 : (blockIdx.x < tiles_l + tiles_a ? 1 : 2);
+    const uint64_t n = seg == 0 ? n_l : (seg == 1 ? n_a : n_c);
+    const uint64_t t0 = (uint64_t)(blockIdx.x - (seg == 0 ? 0u : (seg == 1 ? tiles_l : tiles_l + tiles_a))) * kPlaceTile;
+    const uint16_t *cells = seg == 0 ? lcell : (seg == 1 ? mcell : mcell + n_a);
+    const int list = seg == 0 ? 0 : 1;
+    for (unsigned x = threadIdx.x; x < kCells; x += kBlock) s_cnt[x] = 0;
+    if (threadIdx.x < kLevels) s_lcnt[threadIdx.x] = 0;
+    cell_starts(ctr->hist[list], s_at, s_wave);
+    __syncthreads();
+    uint32_t cell[kPlacePer], rank[kPlacePer], lrank[kPlacePer];
+    uint4 r[kPlacePer];
+#pragma unroll
+    for (unsigned j = 0; j < kPlacePer; ++j) {
+        const uint64_t i = t0 + j * kBlock + threadIdx.x;
+        cell[j] = kCells;
+        if (i < n) {
+            cell[j] = cells[i];
+            if (seg == 2) {
+                r[j] = crec[i];
+            } else {
+                const uint32_t *src = (seg == 0 ? light : medium) + 3 * i;
+                r[j] = make_uint4(src[0], src[1], src[2], (uint32_t)kLevelAlways);
+            }
+        }
+    }
+#pragma unroll
+    for (unsigned j = 0; j < kPlacePer; ++j)
+        if (cell[j] < kCells) {
+            rank[j] = atomicAdd(&s_cnt[cell[j]], 1u);
+            if (seg == 2) lrank[j] = atomicAdd(&s_lcnt[r[j].w], 1u);
+        }
+    __syncthreads();
+    for (unsigned x = threadIdx.x; x < kCells; x += kBlock)
+        if (s_cnt[x]) s_at[x] += atomicAdd(&ctr->cur[list][x], (unsigned long long)s_cnt[x]);
+    if (seg == 2 && threadIdx.x < kLevels && s_lcnt[threadIdx.x]) {
+        unsigned long long above = 0;   // contested triangles of higher levels
+        for (unsigned l = threadIdx.x + 1; l < kLevels; ++l) above += ctr->lev_hist[l];
+        s_lat[threadIdx.x] = above + atomicAdd(&ctr->lev_cur[threadIdx.x], (unsigned long long)s_lcnt[threadIdx.x]);
+    }
+    __syncthreads();
+#pragma unroll
+    for (unsigned j = 0; j < kPlacePer; ++j)
+        if (cell[j] < kCells) {
+            const uint64_t p = s_at[cell[j]] + rank[j];
+            uint32_t *dst = (seg == 0 ? light_w : medium_w) + 3 * p;
+            dst[0] = r[j].x;
+            dst[1] = r[j].y;
+            dst[2] = r[j].z;
+            if (seg != 0) mlev_w[p] = (uint8_t)r[j].w;
+            if (seg == 2) {
+                const uint64_t c = s_lat[r[j].w] + lrank[j];
+                uint32_t *m = medium + 3 * (n_a + c), *h = heavy + 3 * c;
+                m[0] = h[0] = r[j].x;
+                m[1] = h[1] = r[j].y;
+                m[2] = h[2] = r[j].z;
+            }
+        }
 }
 
 // bucket starts from the sorted bucket keys: start[x] for every x in (key[j - 1], key[j]] is j;
@@ -501,161 +583,190 @@ __global__ void k_unit_starts(uint64_t nu, uint32_t nbk, const uint16_t *__restr
     start[x] = (uint32_t)lo;
 }
 
-// first position of every key value 0..nk-1 in a sorted key array (nk + 1 entries, the last = n)
-__global__ void k_key_starts(uint64_t n, uint32_t nk, const uint16_t *__restrict__ ck, uint64_t *__restrict__ start) {
-    uint64_t j = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (j > n) return;
-    const int64_t cur = j < n ? (int64_t)ck[j] : (int64_t)nk;
-    const int64_t prev = j > 0 ? (int64_t)ck[j - 1] : -1;
-    for (int64_t x = prev + 1; x <= cur; ++x) start[x] = j;
-}
+constexpr uint32_t kChunk = 256;   // source edges per count chunk and per prefix chunk
 
-// (e_uv, e_uw, e_vw, level) records back to three words per triangle (and the levels to lev)
-__global__ void k_unpack3(uint64_t n, const uint4 *__restrict__ rec, uint32_t *__restrict__ out,
-                          uint8_t *__restrict__ lev) {
-    uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i >= n) return;
-    const uint4 r = rec[i];
-    out[3 * i] = r.x;
-    out[3 * i + 1] = r.y;
-    out[3 * i + 2] = r.z;
-    if (lev) lev[i] = (uint8_t)r.w;
-}
+// Work items of the medium and heavy lists, in three launches for all of them: sizes and their sums a
+// tile (k_sizes), the sums' prefix over the tiles (k_tile_sums), and in k_expand the prefix within the
+// tile and the items, which a tile writes in order, each thread finding its item's triangle in the
+// tile's prefix (one triangle a thread wrote them scattered: 60 us for both medium lists of the 10M-edge
+// graph, 27 us so with the heavy ones).  Five sequences: the medium entries of medium and of medium_w (one
+// per edge of the outer pair, the source-incident pair with fewer temporal edges, and chunk of the inner
+// pair), then of the heavy triangles the prefix slots (four arrays of length sigma + 1), count chunks and
+// prefix chunks (at least one per list, so that an empty list's total is written too).
+constexpr unsigned kItemPer = 4;
+constexpr unsigned kItemTile = kBlock * kItemPer;
+constexpr int kSeqs = 5;
+struct ItemArgs {
+    uint64_t nm, nh;
+    unsigned tiles_m, tiles_h;   // (each list + 1 entry, so that the last prefix is the total)
+    const uint32_t *eoff, *medium, *medium_w, *heavy;
+    unsigned long long *size[4];    // of medium, medium_w, slots, prefix chunks
+    unsigned long long *base[kSeqs];   // first item (n + 1 entries)
+    unsigned long long *tile;       // [kSeqs][max tiles]
+    unsigned tile_stride;
+    uint32_t *mitems, *mitems_w, *chunks, *pchunks;
+};
 
-// first medium item of every cell: the item base of the cell's first triangle
-__global__ void k_cell_items(const uint64_t *__restrict__ tstart, const uint64_t *__restrict__ ibase,
-                             uint64_t *__restrict__ istart) {
-    const uint32_t c = blockIdx.x * kBlock + threadIdx.x;
-    if (c <= kCells) istart[c] = ibase[tstart[c]];
-}
-
-// entries of the medium path: one per edge of the outer pair (the source-incident pair with fewer
-// temporal edges) and chunk of the inner pair
-__global__ void k_medium_sizes(uint64_t nm, const uint32_t *__restrict__ med, const uint32_t *__restrict__ eoff,
-                               uint64_t *__restrict__ nch) {
-    uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i >= nm) return;
+__device__ __forceinline__ uint64_t medium_size(const uint32_t *__restrict__ med, uint64_t i,
+                                                const uint32_t *__restrict__ eoff) {
     const uint32_t e_uv = med[3 * i], e_uw = med[3 * i + 1];
     const uint32_t s_uv = eoff[2 * e_uv + 2] - eoff[2 * e_uv], s_uw = eoff[2 * e_uw + 2] - eoff[2 * e_uw];
     const bool outer_uv = cdev::medium_outer_is_uv(s_uv, s_uw);
     const uint32_t s_out = outer_uv ? s_uv : s_uw, s_in = outer_uv ? s_uw : s_uv;
-    nch[i] = (uint64_t)s_out * cdev::medium_inner_chunks(s_out, s_in);
+    return (uint64_t)s_out * cdev::medium_inner_chunks(s_out, s_in);
 }
 
-__global__ void k_medium_fill(uint64_t nm, const uint64_t *__restrict__ nch, const uint64_t *__restrict__ base,
-                              uint32_t *__restrict__ items) {
-    uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i >= nm) return;
-    for (uint64_t j = 0; j < nch[i]; ++j) {
-        items[2 * (base[i] + j)] = (uint32_t)i;
-        items[2 * (base[i] + j) + 1] = (uint32_t)j;
-    }
-}
-
-constexpr uint32_t kChunk = 256;   // source edges per count chunk and per prefix chunk
-
-// prefix slots (four arrays of length sigma + 1), count chunks and prefix chunks (at least one per
-// list, so that an empty list's total is written too) of every heavy triangle
-__global__ void k_heavy_sizes(uint64_t n_heavy, const uint32_t *__restrict__ heavy,
-                              const uint32_t *__restrict__ eoff, uint64_t *__restrict__ slots,
-                              uint64_t *__restrict__ nch, uint64_t *__restrict__ npch) {
-    uint64_t h = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (h >= n_heavy) return;
+// lengths of a heavy triangle's four source lists: uv out, uv in, uw out, uw in
+__device__ __forceinline__ void heavy_lens(const uint32_t *__restrict__ heavy, uint64_t h,
+                                           const uint32_t *__restrict__ eoff, uint32_t len[4]) {
     const uint32_t e_uv = heavy[3 * h], e_uw = heavy[3 * h + 1];
-    const uint32_t len[4] = {eoff[2 * e_uv + 1] - eoff[2 * e_uv], eoff[2 * e_uv + 2] - eoff[2 * e_uv + 1],
-                             eoff[2 * e_uw + 1] - eoff[2 * e_uw], eoff[2 * e_uw + 2] - eoff[2 * e_uw + 1]};
-    const uint64_t src = (uint64_t)len[0] + len[1] + len[2] + len[3];
-    slots[h] = src + 4;
-    nch[h] = (src + kChunk - 1) / kChunk;
-    uint64_t p = 0;
-    for (int X = 0; X < 4; ++X) p += len[X] ? (len[X] + kChunk - 1) / kChunk : 1;
-    npch[h] = p;
+    len[0] = eoff[2 * e_uv + 1] - eoff[2 * e_uv];
+    len[1] = eoff[2 * e_uv + 2] - eoff[2 * e_uv + 1];
+    len[2] = eoff[2 * e_uw + 1] - eoff[2 * e_uw];
+    len[3] = eoff[2 * e_uw + 2] - eoff[2 * e_uw + 1];
 }
 
-__global__ void k_heavy_chunks(uint64_t n_heavy, const uint32_t *__restrict__ heavy, const uint32_t *__restrict__ eoff,
-                               const uint64_t *__restrict__ nch, const uint64_t *__restrict__ cbase,
-                               const uint64_t *__restrict__ pbase, uint32_t *__restrict__ chunks,
-                               uint32_t *__restrict__ pchunks) {
-    uint64_t h = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (h >= n_heavy) return;
-    for (uint64_t j = 0; j < nch[h]; ++j) {
-        chunks[2 * (cbase[h] + j)] = (uint32_t)h;
-        chunks[2 * (cbase[h] + j) + 1] = (uint32_t)(j * kChunk);
-    }
-    const uint32_t e_uv = heavy[3 * h], e_uw = heavy[3 * h + 1];
-    const uint32_t len[4] = {eoff[2 * e_uv + 1] - eoff[2 * e_uv], eoff[2 * e_uv + 2] - eoff[2 * e_uv + 1],
-                             eoff[2 * e_uw + 1] - eoff[2 * e_uw], eoff[2 * e_uw + 2] - eoff[2 * e_uw + 1]};
-    uint64_t p = pbase[h];
-    for (uint32_t X = 0; X < 4; ++X) {
-        const uint32_t nc = len[X] ? (len[X] + kChunk - 1) / kChunk : 1;
-        for (uint32_t c = 0; c < nc; ++c, ++p) {
-            pchunks[2 * p] = (uint32_t)h;
-            pchunks[2 * p + 1] = c * kChunk | X;
+__device__ __forceinline__ uint64_t list_chunks(uint32_t len) { return len ? ((uint64_t)len + kChunk - 1) / kChunk : 1; }
+
+__global__ void __launch_bounds__(kBlock) k_sizes(ItemArgs A) {
+    __shared__ unsigned long long s_sum[3];
+    if (threadIdx.x < 3) s_sum[threadIdx.x] = 0;
+    __syncthreads();
+    const bool med = blockIdx.x < A.tiles_m;
+    const unsigned tile = med ? blockIdx.x : blockIdx.x - A.tiles_m;
+    unsigned long long sum[3] = {0, 0, 0};
+    for (unsigned j = 0; j < kItemPer; ++j) {
+        const uint64_t i = (uint64_t)tile * kItemTile + j * kBlock + threadIdx.x;
+        if (med && i <= A.nm) {
+            const uint64_t x = i < A.nm ? medium_size(A.medium, i, A.eoff) : 0;
+            const uint64_t y = i < A.nm ? medium_size(A.medium_w, i, A.eoff) : 0;
+            A.size[0][i] = x;
+            A.size[1][i] = y;
+            sum[0] += x;
+            sum[1] += y;
+        } else if (!med && i <= A.nh) {
+            uint64_t slots = 0, p = 0;
+            if (i < A.nh) {
+                uint32_t len[4];
+                heavy_lens(A.heavy, i, A.eoff, len);
+                slots = (uint64_t)len[0] + len[1] + len[2] + len[3] + 4;
+                for (int X = 0; X < 4; ++X) p += list_chunks(len[X]);
+            }
+            A.size[2][i] = slots;
+            A.size[3][i] = p;
+            sum[0] += slots;
+            sum[1] += slots ? (slots - 4 + kChunk - 1) / kChunk : 0;
+            sum[2] += p;
         }
     }
+    for (int x = 0; x < 3; ++x) {
+        const unsigned long long t = cdev::wave_sum(sum[x]);
+        if ((threadIdx.x & 63) == 0 && t) atomicAdd(&s_sum[x], t);
+    }
+    __syncthreads();
+    if (threadIdx.x < (med ? 2u : 3u)) A.tile[(med ? 0 : 2) * A.tile_stride + threadIdx.x * A.tile_stride + tile] = s_sum[threadIdx.x];
 }
 
-// Per query level l = 1..kLevels, from the contested triangles' level starts (kstart over the
-// descending sort keys 255 - level): c = contested triangles of level >= l; the medium entries end
-// at ibase[n_a + c]; the heavy triangles, count chunks, prefix chunks and slots start at c.
-__global__ void k_level_tables(uint64_t n_a, const uint64_t *__restrict__ kstart, const uint64_t *__restrict__ ibase,
-                               const uint64_t *__restrict__ cbase, const uint64_t *__restrict__ pbase,
-                               const uint64_t *__restrict__ hslot, uint64_t *__restrict__ out) {
+// One workgroup: the tiles' sums to exclusive prefixes, the totals to the host.
+constexpr unsigned kTileBlock = 1024;
+__global__ void __launch_bounds__(kTileBlock) k_tile_sums(ItemArgs A, unsigned long long *__restrict__ host) {
+    __shared__ unsigned long long s_wave[kTileBlock / 64];
+    for (int x = 0; x < kSeqs; ++x) {
+        unsigned long long *t = A.tile + (uint64_t)x * A.tile_stride;
+        const unsigned n = x < 2 ? A.tiles_m : A.tiles_h;
+        unsigned long long run = 0;
+        for (unsigned b = 0; b < n; b += kTileBlock) {
+            const unsigned i = b + threadIdx.x;
+            const unsigned long long v = i < n ? t[i] : 0ull;
+            unsigned long long total;
+            const unsigned long long at = block_scan(v, s_wave, total);
+            if (i < n) t[i] = run + at;
+            run += total;
+        }
+        if (threadIdx.x == 0) host[x] = run;
+    }
+}
+
+// the tile's item p of s_pre (kItemTile + 1 prefixes): its entry
+__device__ __forceinline__ unsigned item_entry(const unsigned long long *s_pre, unsigned long long p) {
+    unsigned lo = 0, len = kItemTile;   // the last entry with prefix <= p
+    while (len > 1) {
+        const unsigned half = len / 2;
+        if (s_pre[lo + half] <= p) lo += half;
+        len -= half;
+    }
+    return lo;
+}
+
+__global__ void __launch_bounds__(kBlock) k_expand(ItemArgs A) {
+    __shared__ unsigned long long s_pre[kItemTile + 1], s_wave[kBlock / 64];
+    const bool med = blockIdx.x < A.tiles_m;
+    const unsigned tile = med ? blockIdx.x : blockIdx.x - A.tiles_m;
+    const uint64_t t0 = (uint64_t)tile * kItemTile, n = med ? A.nm : A.nh;
+    for (int x = med ? 0 : 2; x < (med ? 2 : kSeqs); ++x) {
+        const unsigned long long *size = A.size[x < 3 ? x : x - 1];
+        unsigned long long v[kItemPer], mine = 0, total;
+#pragma unroll
+        for (unsigned j = 0; j < kItemPer; ++j) {
+            const uint64_t i = t0 + kItemPer * threadIdx.x + j;
+            v[j] = i <= n ? size[i] : 0ull;
+            if (x == 3) v[j] = v[j] ? (v[j] - 4 + kChunk - 1) / kChunk : 0ull;   // count chunks, from the slots
+            mine += v[j];
+        }
+        unsigned long long at = block_scan(mine, s_wave, total);
+        const unsigned long long base = A.tile[(uint64_t)x * A.tile_stride + tile];
+#pragma unroll
+        for (unsigned j = 0; j < kItemPer; ++j) {
+            const uint64_t i = t0 + kItemPer * threadIdx.x + j;
+            s_pre[kItemPer * threadIdx.x + j] = at;
+            if (i <= n) A.base[x][i] = base + at;
+            at += v[j];
+        }
+        if (x == 2) continue;   // (the slots have no items)
+        if (threadIdx.x == 0) s_pre[kItemTile] = total;
+        __syncthreads();
+        uint2 *out = reinterpret_cast<uint2 *>(x == 0 ? A.mitems : (x == 1 ? A.mitems_w : (x == 3 ? A.chunks : A.pchunks)));
+        for (unsigned long long p = threadIdx.x; p < total; p += kBlock) {
+            const unsigned e = item_entry(s_pre, p);
+            uint32_t j = (uint32_t)(p - s_pre[e]);
+            if (x == 3) {
+                j *= kChunk;
+            } else if (x == 4) {
+                uint32_t len[4];
+                heavy_lens(A.heavy, t0 + e, A.eoff, len);
+                uint32_t X = 0;
+                while (X < 3 && j >= list_chunks(len[X])) j -= (uint32_t)list_chunks(len[X++]);
+                j = j * kChunk | X;
+            }
+            out[base + p] = make_uint2((uint32_t)(t0 + e), j);
+        }
+        __syncthreads();   // (s_pre read)
+    }
+}
+
+// One workgroup, to the host: the cell starts of the light list, the first medium item of every cell, and
+// per query level l = 1..kLevels, with c contested triangles of level >= l: the medium entries end at
+// those of n_a + c; the heavy triangles, count chunks, prefix chunks and slots start at c.
+__global__ void __launch_bounds__(kBlock)
+k_tables(uint64_t n_l, uint64_t n_a, ItemArgs A, const SchedCtr *__restrict__ ctr, unsigned long long *__restrict__ host) {
+    __shared__ unsigned long long s_at[kCells], s_wave[kBlock / 64];
+    cell_starts(ctr->hist[0], s_at, s_wave);
+    __syncthreads();
+    for (unsigned c = threadIdx.x; c <= kCells; c += kBlock) host[c] = c < kCells ? s_at[c] : n_l;
+    __syncthreads();
+    cell_starts(ctr->hist[1], s_at, s_wave);
+    __syncthreads();
+    for (unsigned c = threadIdx.x; c <= kCells; c += kBlock) host[kCells + 1 + c] = A.base[1][c < kCells ? s_at[c] : A.nm];
     const uint32_t l = threadIdx.x;
     if (l == 0 || l > kLevels) return;
-    const uint64_t c = kstart[256 - l];
-    out[0 * (kLevels + 1) + l] = ibase[n_a + c];
+    uint64_t c = 0;
+    for (uint32_t v = l; v < kLevels; ++v) c += ctr->lev_hist[v];
+    unsigned long long *out = host + 2 * (kCells + 1);
+    out[0 * (kLevels + 1) + l] = A.base[0][n_a + c];
     out[1 * (kLevels + 1) + l] = c;
-    out[2 * (kLevels + 1) + l] = cbase[c];
-    out[3 * (kLevels + 1) + l] = pbase[c];
-    out[4 * (kLevels + 1) + l] = hslot[c];
-}
-
-// Sort n (cell, record) pairs by cell, unpack the records to out (three words per triangle) and
-// write the cell starts (kCells + 1 entries) to start
-// (and, with lev, the records' levels to lev)
-int cell_order(dt_ctx *ctx, uint64_t n, DevMem &ckey, DevMem &rec, DevMem &out, DevMem &start, hipStream_t st,
-               uint8_t *lev = nullptr) {
-    DevMem k2, r2;
-    DT_TRY(dev_alloc(ctx, start, (uint64_t)(kCells + 1) * 8));
-    DT_TRY(dev_alloc(ctx, k2, n * 2));
-    DT_TRY(dev_alloc(ctx, r2, n * sizeof(uint4)));
-    DT_TRY(sort_pairs_u16_u4(ctx, ckey.as<uint16_t>(), k2.as<uint16_t>(), rec.as<uint4>(), r2.as<uint4>(), n, 16, st));
-    k_key_starts<<<grid_for(n + 1, kBlock), kBlock, 0, st>>>(n, kCells, k2.as<uint16_t>(), start.as<uint64_t>());
-    DT_HIP(hipGetLastError());
-    if (n) {
-        k_unpack3<<<grid_for(n, kBlock), kBlock, 0, st>>>(n, r2.as<uint4>(), out.as<uint32_t>(), lev);
-        DT_HIP(hipGetLastError());
-    }
-    return DT_OK;
-}
-
-// Work items of the medium list med (nm triangles): medium_sizes enqueues each triangle's item
-// count (nch) and first item (base, nm + 1 entries) and the total's read-back to *total (pinned
-// host memory, valid after the stream is synchronised); medium_fill then writes the items.
-int medium_sizes(dt_ctx *ctx, uint64_t nm, DevMem &med, DevMem &eoff, DevMem &nch, DevMem &base, uint64_t *total,
-                 hipStream_t st) {
-    DT_TRY(dev_alloc(ctx, nch, (nm + 1) * 8));
-    DT_TRY(dev_alloc(ctx, base, (nm + 1) * 8));
-    DT_HIP(hipMemsetAsync(nch.ptr, 0, (nm + 1) * 8, st));
-    if (nm) {
-        k_medium_sizes<<<grid_for(nm, kBlock), kBlock, 0, st>>>(nm, med.as<uint32_t>(), eoff.as<uint32_t>(),
-                                                                nch.as<uint64_t>());
-        DT_HIP(hipGetLastError());
-    }
-    DT_TRY(exclusive_scan_u64(ctx, nch.as<uint64_t>(), base.as<uint64_t>(), nm + 1, st));
-    DT_HIP(hipMemcpyAsync(total, base.as<uint64_t>() + nm, 8, hipMemcpyDeviceToHost, st));
-    return DT_OK;
-}
-
-int medium_fill(dt_ctx *ctx, uint64_t nm, DevMem &nch, DevMem &base, uint64_t ni, DevMem &items, hipStream_t st) {
-    DT_TRY(dev_alloc(ctx, items, ni * 8));
-    if (nm) {
-        k_medium_fill<<<grid_for(nm, kBlock), kBlock, 0, st>>>(nm, nch.as<uint64_t>(), base.as<uint64_t>(),
-                                                               items.as<uint32_t>());
-        DT_HIP(hipGetLastError());
-    }
-    return DT_OK;
+    out[2 * (kLevels + 1) + l] = A.base[3][c];
+    out[3 * (kLevels + 1) + l] = A.base[4][c];
+    out[4 * (kLevels + 1) + l] = A.base[2][c];
 }
 
 // One attempt at the schedule.  The unit keys are g's, made here if the build left none.  lean: the
@@ -676,12 +787,9 @@ int try_schedule(dt_graph *g, DevMem &tri, bool with_units, bool last, bool lean
     // unit records hold 32-bit relative times
     const bool unit_ok = g->span <= kUnitMaxSpan;
     const bool units = with_units && R.force == 0 && unit_ok && g->m_s && g->n_tri;
-    const unsigned grid = std::min(kClsGrid, grid_for(nt, kBlock));
-    DevMem cls, bcnt, part, base, tot, rest, urec, ubkt;
-    DT_TRY(dev_alloc(ctx, bcnt, (uint64_t)grid * kClasses * 4));
-    DT_TRY(dev_alloc(ctx, part, (uint64_t)grid * kPartWords * 8));
-    DT_TRY(dev_alloc(ctx, base, (uint64_t)grid * kClasses * 8));
-    DT_TRY(dev_alloc(ctx, tot, 512));
+    DevMem cls, zero, rest, urec, ubkt;
+    DT_TRY(dev_alloc(ctx, zero, sizeof(SchedCtr)));
+    SchedCtr *ctr = zero.as<SchedCtr>();
     // t1 buckets of the unit records: at most 2^16, t1 >> unit_shift
     int t_bits = 0;
     while (t_bits < 31 && (1ll << t_bits) <= g->span) ++t_bits;
@@ -692,12 +800,14 @@ int try_schedule(dt_graph *g, DevMem &tri, bool with_units, bool last, bool lean
         unit_keys(g, st);
         DT_HIP(hipGetLastError());
     }
-    // room for unit records of every triangle and for other triangles of a quarter of them; the pass
-    // runs again at the counted sizes where that is too little
-    uint64_t unit_cap = lean ? 0 : g->n_tri, rest_cap = lean ? 0 : std::max<uint64_t>(g->n_tri / 4, 1ull << 16);
+    // room for unit records of every triangle; for other triangles as many in lists up to 4M (48 MB;
+    // a second pass cost 60 us of the 10M-edge graph's build, whose triangles are nearly all others),
+    // a quarter of them in longer ones (a twelfth is needed at 61M edges).  The pass runs again at the
+    // counted sizes where that is too little.
+    uint64_t unit_cap = lean ? 0 : g->n_tri;
+    uint64_t rest_cap = lean ? 0 : std::max<uint64_t>(g->n_tri / 4, std::min<uint64_t>(g->n_tri, 1ull << 22));
     uint64_t n_rest = nt;
-    uint64_t *hs = reinterpret_cast<uint64_t *>(ctx->pinned_stage);
-    unsigned long long *ctr = tot.as<unsigned long long>() + 16;   // (units at [0], others at [16])
+    unsigned long long *hs = reinterpret_cast<unsigned long long *>(ctx->pinned_stage);
     for (int attempt = 0;; ++attempt) {
         const uint32_t *list = tri.as<uint32_t>();
         if (units) {
@@ -705,7 +815,9 @@ int try_schedule(dt_graph *g, DevMem &tri, bool with_units, bool last, bool lean
             DT_TRY(dev_alloc(ctx, ubkt, unit_cap * 2));
             DT_TRY(dev_alloc(ctx, rest, rest_cap * 12));
             list = rest.as<uint32_t>();
-            DT_HIP(hipMemsetAsync(tot.ptr, 0, 512, st));
+        }
+        DT_HIP(hipMemsetAsync(ctr, 0, sizeof(SchedCtr), st));
+        if (units) {
             const unsigned sgrid = std::min<unsigned>(grid_for(nt, kSplitTile), (unsigned)ctx->num_cus * 16);
             k_unit_split<<<sgrid, kBlock, 0, st>>>(nt, tri.as<uint32_t>(), g->ukey.as<uint64_t>(), g->shift, S.unit_shift,
                                                    urec.as<uint4>(), ubkt.as<uint16_t>(), unit_cap, rest.as<uint32_t>(),
@@ -714,20 +826,17 @@ int try_schedule(dt_graph *g, DevMem &tri, bool with_units, bool last, bool lean
         }
         const uint64_t n_max = units ? rest_cap : nt;
         DT_TRY(dev_alloc(ctx, cls, n_max + 1));
-        k_classify<<<grid, kBlock, 0, st>>>(n_max, units ? ctr + 16 : nullptr, list, g->eoff.as<uint32_t>(), R,
-                                            cls.as<uint8_t>(), bcnt.as<uint32_t>(), part.as<uint64_t>());
+        const unsigned grid = std::min(grid_for(n_max + 1, kBlock * 4), (unsigned)ctx->num_cus * 4);
+        k_classify<<<grid, kBlock, 0, st>>>(n_max, units ? ctr->rest : nullptr, list, g->eoff.as<uint32_t>(), R,
+                                            cls.as<uint8_t>(), ctr, hs);
         DT_HIP(hipGetLastError());
-        k_cls_totals<<<1, kBlock, 0, st>>>(grid, bcnt.as<uint32_t>(), part.as<uint64_t>(), base.as<uint64_t>(),
-                                           tot.as<uint64_t>());
-        DT_HIP(hipGetLastError());
-        DT_HIP(hipMemcpyAsync(hs, tot.ptr, 512, hipMemcpyDeviceToHost, st));
         DT_HIP(hipStreamSynchronize(st));
         if (!units) break;
-        n_rest = hs[32];
-        if (hs[16] + n_rest != g->n_tri) return fail(DT_EDEVICE, "unit and other triangles do not add up");
-        if (hs[16] <= unit_cap && n_rest <= rest_cap) break;
+        n_rest = hs[kTotWords + 1];
+        if (hs[kTotWords] + n_rest != g->n_tri) return fail(DT_EDEVICE, "unit and other triangles do not add up");
+        if (hs[kTotWords] <= unit_cap && n_rest <= rest_cap) break;
         if (attempt) return fail(DT_EDEVICE, "triangle classes changed between passes");
-        unit_cap = hs[16];
+        unit_cap = hs[kTotWords];
         rest_cap = n_rest;
     }
     if (units && lean && last) {
@@ -735,7 +844,7 @@ int try_schedule(dt_graph *g, DevMem &tri, bool with_units, bool last, bool lean
         tri.reset();
     }
     const uint32_t *list = units ? rest.as<uint32_t>() : tri.as<uint32_t>();
-    const uint64_t nu = units ? hs[16] : 0;
+    const uint64_t nu = units ? hs[kTotWords] : 0;
     uint64_t ncls[kClasses];
     for (int c = 0; c < kClasses; ++c) ncls[c] = hs[c];
     const unsigned __int128 s3 = ((unsigned __int128)hs[kClasses + 1] << 64) | hs[kClasses];
@@ -761,20 +870,16 @@ int try_schedule(dt_graph *g, DevMem &tri, bool with_units, bool last, bool lean
     // time slices of the window index: span >> cell_shift < kSlices
     S.cell_shift = 0;
     while (S.cell_shift < 62 && (g->span >> S.cell_shift) >= (int64_t)kSlices) ++S.cell_shift;
-    DevMem ubkt2, ustart, lrec, lkey, mrec, mkey, lstart, mstart, crec, ckey;
-    DT_TRY(dev_alloc(ctx, lrec, S.n_light * sizeof(uint4)));
-    DT_TRY(dev_alloc(ctx, lkey, S.n_light * 2));
-    DT_TRY(dev_alloc(ctx, mrec, nm * sizeof(uint4)));
-    DT_TRY(dev_alloc(ctx, mkey, nm * 2));
+    DevMem ubkt2, ustart, lcell, mcell, crec;
+    DT_TRY(dev_alloc(ctx, lcell, S.n_light * 2));
+    DT_TRY(dev_alloc(ctx, mcell, nm * 2));
     DT_TRY(dev_alloc(ctx, crec, nc * sizeof(uint4)));
-    DT_TRY(dev_alloc(ctx, ckey, nc * 2));
     // unit records ordered by t1 bucket (a stable two-pass radix sort on the 16-bit bucket) on the
     // first side stream, while this stream builds the other lists; the host keeps the bucket starts
     // (read back through the pinned staging buffer from byte kStageUnit; the cell starts, level
     // tables and other read-backs use the bytes before it)
-    constexpr size_t kStageUnit = 16384;
-    static_assert((kCells + 1) * 8 <= kStageUnit, "staging layout");
-    static_assert(5 * (kLevels + 1) * 8 + 16 <= kStageUnit, "staging layout");
+    constexpr size_t kStageUnit = 32768;
+    static_assert((2 * (kCells + 1) + 5 * (kLevels + 1)) * 8 <= kStageUnit, "staging layout");
     if (kStageUnit + (nbk + 1) * 4 > kPinnedStage) return fail(DT_EDEVICE, "unit bucket index exceeds staging");
     DevMem usort_tmp;
     const hipStream_t us = nu && ctx->side[0] ? ctx->side[0] : st;
@@ -785,14 +890,12 @@ int try_schedule(dt_graph *g, DevMem &tri, bool with_units, bool last, bool lean
             if (s != main) (void)hipStreamSynchronize(s);
         }
     } join{us, st};
-    if (nu) {
+    // (both are launched with the context's stream idle, after the classes were read)
+    auto unit_sort = [&]() -> int {
+        if (!nu) return DT_OK;
         DT_TRY(dev_alloc(ctx, ubkt2, nu * 2));
         DT_TRY(dev_alloc(ctx, S.unit, nu * sizeof(uint4)));
         DT_TRY(dev_alloc(ctx, ustart, (nbk + 1) * 4));
-        if (us != st) {
-            DT_HIP(hipEventRecord(ctx->ev_relay[0], st));
-            DT_HIP(hipStreamWaitEvent(us, ctx->ev_relay[0], 0));
-        }
         DT_TRY(sort_pairs_u16_u4(ctx, ubkt.as<uint16_t>(), ubkt2.as<uint16_t>(), urec.as<uint4>(), S.unit.as<uint4>(),
                                  nu, 16, us, us != st ? &usort_tmp : nullptr));
         k_unit_starts<<<grid_for(nbk + 1, kBlock), kBlock, 0, us>>>(nu, (uint32_t)nbk, ubkt2.as<uint16_t>(),
@@ -800,133 +903,105 @@ int try_schedule(dt_graph *g, DevMem &tri, bool with_units, bool last, bool lean
         DT_HIP(hipGetLastError());
         S.unit_index.resize(nbk + 1);
         DT_HIP(hipMemcpyAsync(ctx->pinned_stage + kStageUnit, ustart.ptr, (nbk + 1) * 4, hipMemcpyDeviceToHost, us));
-        if (us != st) DT_HIP(hipEventRecord(ctx->ev_relay[1], us));
-    }
-    if (n_rest) {
-        k_partition<<<grid, kBlock, 0, st>>>(n_rest, list, cls.as<uint8_t>(), base.as<uint64_t>(),
-            g->eoff.as<uint32_t>(), g->key.as<uint64_t>(), g->shift, S.cell_shift, nc,
-            S.light.as<uint32_t>(), S.medium.as<uint32_t>(), S.heavy.as<uint32_t>(), crec.as<uint4>(), lrec.as<uint4>(),
-            lkey.as<uint16_t>(), mrec.as<uint4>(), mkey.as<uint16_t>());
-        DT_HIP(hipGetLastError());
-    }
-    cls.reset();
-    // contested triangles: their levels, then descending level order after the always-medium
-    // ones (medium list) and before the always-heavy ones (heavy list)
-    DevMem kstart;
-    DT_TRY(dev_alloc(ctx, kstart, 257 * 8));
-    {
-        DevMem ckey2, crec2;
-        DT_TRY(dev_alloc(ctx, ckey2, nc * 2));
-        DT_TRY(dev_alloc(ctx, crec2, nc * sizeof(uint4)));
-        if (nc) {
-            k_crossover<<<(unsigned)std::min<uint64_t>((nc + kBlock / 64 - 1) / (kBlock / 64), (uint64_t)ctx->num_cus * 16),
-                          kBlock, 0, st>>>(nc, crec.as<uint4>(), ckey.as<uint16_t>(), g->eoff.as<uint32_t>(),
-                                           g->key.as<uint64_t>(), g->shift, g->span, R.cost_pct);
-            DT_HIP(hipGetLastError());
-            DT_TRY(sort_pairs_u16_u4(ctx, ckey.as<uint16_t>(), ckey2.as<uint16_t>(), crec.as<uint4>(), crec2.as<uint4>(),
-                                     nc, 16, st));
-            k_contest_place<<<grid_for(nc, kBlock), kBlock, 0, st>>>(nc, crec2.as<uint4>(), na, S.medium.as<uint32_t>(),
-                S.heavy.as<uint32_t>(), mrec.as<uint4>(), mkey.as<uint16_t>(), g->eoff.as<uint32_t>(),
-                g->key.as<uint64_t>(), g->shift, S.cell_shift);
-            DT_HIP(hipGetLastError());
-        }
-        k_key_starts<<<grid_for(nc + 1, kBlock), kBlock, 0, st>>>(nc, 256, ckey2.as<uint16_t>(), kstart.as<uint64_t>());
-        DT_HIP(hipGetLastError());
-    }
-    crec.reset();
-    ckey.reset();
-    // the windowed copies of the light and medium lists, in window-cell order
+        return DT_OK;
+    };
+    S.light_cells.assign(kCells + 1, 0);
+    S.mitem_cells.assign(kCells + 1, 0);
     DT_TRY(dev_alloc(ctx, S.light_w, S.n_light * 12));
     DT_TRY(dev_alloc(ctx, S.medium_w, nm * 12));
     DT_TRY(dev_alloc(ctx, S.mlev_w, nm + 1));
-    DT_TRY(cell_order(ctx, S.n_light, lkey, lrec, S.light_w, lstart, st));
-    DT_TRY(cell_order(ctx, nm, mkey, mrec, S.medium_w, mstart, st, S.mlev_w.as<uint8_t>()));
-    S.light_cells.resize(kCells + 1);
-    DT_HIP(hipMemcpyAsync(ctx->pinned_stage, lstart.ptr, (kCells + 1) * 8, hipMemcpyDeviceToHost, st));
-    DT_HIP(hipStreamSynchronize(st));
-    memcpy(S.light_cells.data(), ctx->pinned_stage, (kCells + 1) * 8);
-    // medium work items of both copies (the same totals: the same triangles in another order)
-    DevMem nch0, base0;
-    {
-        DevMem nch1, base;
-        uint64_t *ni2 = reinterpret_cast<uint64_t *>(ctx->pinned_stage);
-        DT_TRY(medium_sizes(ctx, nm, S.medium, g->eoff, nch0, base0, &ni2[0], st));
-        DT_TRY(medium_sizes(ctx, nm, S.medium_w, g->eoff, nch1, base, &ni2[1], st));
-        DT_HIP(hipStreamSynchronize(st));
-        const uint64_t ni = ni2[0], ni_w = ni2[1];
-        if (ni != ni_w) return fail(DT_EDEVICE, "medium work items of the two orders differ");
-        DT_TRY(medium_fill(ctx, nm, nch0, base0, ni, S.mitems, st));
-        DT_TRY(medium_fill(ctx, nm, nch1, base, ni_w, S.mitems_w, st));
-        S.n_mitems = ni;
-        DevMem istart;
-        DT_TRY(dev_alloc(ctx, istart, (uint64_t)(kCells + 1) * 8));
-        k_cell_items<<<grid_for(kCells + 1, kBlock), kBlock, 0, st>>>(mstart.as<uint64_t>(), base.as<uint64_t>(),
-                                                                      istart.as<uint64_t>());
-        DT_HIP(hipGetLastError());
-        S.mitem_cells.resize(kCells + 1);
-        DT_HIP(hipMemcpyAsync(ctx->pinned_stage, istart.ptr, (kCells + 1) * 8, hipMemcpyDeviceToHost, st));
-        DT_HIP(hipStreamSynchronize(st));
-        memcpy(S.mitem_cells.data(), ctx->pinned_stage, (kCells + 1) * 8);
-    }
-    // heavy slots, count chunks and prefix chunks
-    DevMem slots, nch, npch, cbase, pbase;
-    DT_TRY(dev_alloc(ctx, slots, (nh + 1) * 8));
-    DT_TRY(dev_alloc(ctx, nch, (nh + 1) * 8));
-    DT_TRY(dev_alloc(ctx, npch, (nh + 1) * 8));
-    DT_TRY(dev_alloc(ctx, cbase, (nh + 1) * 8));
-    DT_TRY(dev_alloc(ctx, pbase, (nh + 1) * 8));
     DT_TRY(dev_alloc(ctx, S.hslot, (nh + 1) * 8));
-    DT_HIP(hipMemsetAsync(slots.ptr, 0, (nh + 1) * 8, st));
-    DT_HIP(hipMemsetAsync(nch.ptr, 0, (nh + 1) * 8, st));
-    DT_HIP(hipMemsetAsync(npch.ptr, 0, (nh + 1) * 8, st));
-    if (nh) {
-        k_heavy_sizes<<<grid_for(nh, kBlock), kBlock, 0, st>>>(nh, S.heavy.as<uint32_t>(), g->eoff.as<uint32_t>(),
-                                                               slots.as<uint64_t>(), nch.as<uint64_t>(), npch.as<uint64_t>());
+    if (n_rest) {
+        k_partition<<<std::min(grid_for(n_rest, kPartTile), (unsigned)ctx->num_cus * 4), kBlock, 0, st>>>(n_rest, list,
+            cls.as<uint8_t>(), g->eoff.as<uint32_t>(), g->key.as<uint64_t>(), g->shift, S.cell_shift, na, nc,
+            S.light.as<uint32_t>(), S.medium.as<uint32_t>(), S.heavy.as<uint32_t>(), crec.as<uint4>(),
+            lcell.as<uint16_t>(), mcell.as<uint16_t>(), ctr);
         DT_HIP(hipGetLastError());
-    }
-    DT_TRY(exclusive_scan_u64(ctx, slots.as<uint64_t>(), S.hslot.as<uint64_t>(), nh + 1, st));
-    DT_TRY(exclusive_scan_u64(ctx, nch.as<uint64_t>(), cbase.as<uint64_t>(), nh + 1, st));
-    DT_TRY(exclusive_scan_u64(ctx, npch.as<uint64_t>(), pbase.as<uint64_t>(), nh + 1, st));
-    uint64_t *htot = reinterpret_cast<uint64_t *>(ctx->pinned_stage);
-    DT_HIP(hipMemcpyAsync(&htot[0], S.hslot.as<uint64_t>() + nh, 8, hipMemcpyDeviceToHost, st));
-    DT_HIP(hipMemcpyAsync(&htot[1], cbase.as<uint64_t>() + nh, 8, hipMemcpyDeviceToHost, st));
-    DT_HIP(hipMemcpyAsync(&htot[2], pbase.as<uint64_t>() + nh, 8, hipMemcpyDeviceToHost, st));
-    DT_HIP(hipStreamSynchronize(st));
-    S.n_slots = htot[0];
-    S.n_chunks = htot[1];
-    S.n_pchunks = htot[2];
-    if (S.n_chunks > 0xffffffffull || S.n_pchunks > 0xffffffffull || nh > 0xffffffffull)
-        return fail(DT_EOVERFLOW, "too many heavy work items (%llu)", (unsigned long long)S.n_chunks);
-    DT_TRY(dev_alloc(ctx, S.chunks, S.n_chunks * 8));
-    DT_TRY(dev_alloc(ctx, S.pchunks, S.n_pchunks * 8));
-    if (nh) {
-        k_heavy_chunks<<<grid_for(nh, kBlock), kBlock, 0, st>>>(nh, S.heavy.as<uint32_t>(), g->eoff.as<uint32_t>(),
-                                                                nch.as<uint64_t>(), cbase.as<uint64_t>(),
-                                                                pbase.as<uint64_t>(), S.chunks.as<uint32_t>(),
-                                                                S.pchunks.as<uint32_t>());
-        DT_HIP(hipGetLastError());
-    }
-    // the per-level bounds of the two lists
-    {
-        DevMem lt;
-        DT_TRY(dev_alloc(ctx, lt, 5 * (kLevels + 1) * 8));
-        DT_HIP(hipMemsetAsync(lt.ptr, 0, 5 * (kLevels + 1) * 8, st));
-        k_level_tables<<<1, 64, 0, st>>>(na, kstart.as<uint64_t>(), base0.as<uint64_t>(), cbase.as<uint64_t>(),
-                                         pbase.as<uint64_t>(), S.hslot.as<uint64_t>(), lt.as<uint64_t>());
-        DT_HIP(hipGetLastError());
-        DT_HIP(hipMemcpyAsync(htot, lt.ptr, 5 * (kLevels + 1) * 8, hipMemcpyDeviceToHost, st));
-        DT_HIP(hipStreamSynchronize(st));
-        for (uint32_t l = 1; l <= kLevels; ++l) {
-            S.med_item_at[l] = htot[0 * (kLevels + 1) + l];
-            S.heavy_tri_at[l] = htot[1 * (kLevels + 1) + l];
-            S.heavy_chunk_at[l] = htot[2 * (kLevels + 1) + l];
-            S.heavy_pchunk_at[l] = htot[3 * (kLevels + 1) + l];
-            S.heavy_slot_at[l] = htot[4 * (kLevels + 1) + l];
+        if (nc) {
+            k_crossover<<<(unsigned)std::min<uint64_t>((nc + kBlock / 64 - 1) / (kBlock / 64), (uint64_t)ctx->num_cus * 16),
+                          kBlock, 0, st>>>(nc, crec.as<uint4>(), g->eoff.as<uint32_t>(), g->key.as<uint64_t>(), g->shift,
+                                           g->span, R.cost_pct, ctr);
+            DT_HIP(hipGetLastError());
         }
+        const unsigned tiles_l = grid_for(S.n_light, kPlaceTile), tiles_a = grid_for(na, kPlaceTile),
+                       tiles_c = grid_for(nc, kPlaceTile);
+        if (tiles_l + tiles_a + tiles_c) {
+            k_place<<<tiles_l + tiles_a + tiles_c, kBlock, 0, st>>>(S.n_light, na, nc, tiles_l, tiles_a,
+                S.light.as<uint32_t>(), lcell.as<uint16_t>(), S.medium.as<uint32_t>(), mcell.as<uint16_t>(),
+                crec.as<uint4>(), S.heavy.as<uint32_t>(), S.light_w.as<uint32_t>(), S.medium_w.as<uint32_t>(),
+                S.mlev_w.as<uint8_t>(), ctr);
+            DT_HIP(hipGetLastError());
+        }
+        // work items: their sizes and totals, then the items and the tables the host keeps
+        DevMem sizes, bases, tiles;
+        ItemArgs A{};
+        A.nm = nm;
+        A.nh = nh;
+        A.tiles_m = grid_for(nm + 1, kItemTile);
+        A.tiles_h = grid_for(nh + 1, kItemTile);
+        A.eoff = g->eoff.as<uint32_t>();
+        A.medium = S.medium.as<uint32_t>();
+        A.medium_w = S.medium_w.as<uint32_t>();
+        A.heavy = S.heavy.as<uint32_t>();
+        A.tile_stride = std::max(A.tiles_m, A.tiles_h);
+        DT_TRY(dev_alloc(ctx, sizes, 2 * (nm + 1 + nh + 1) * 8));
+        DT_TRY(dev_alloc(ctx, bases, 2 * (nm + 1 + nh + 1) * 8));
+        DT_TRY(dev_alloc(ctx, tiles, (uint64_t)kSeqs * A.tile_stride * 8));
+        unsigned long long *sz = sizes.as<unsigned long long>(), *bs = bases.as<unsigned long long>();
+        A.size[0] = sz;
+        A.size[1] = sz + (nm + 1);
+        A.size[2] = sz + 2 * (nm + 1);
+        A.size[3] = sz + 2 * (nm + 1) + (nh + 1);
+        A.base[0] = bs;
+        A.base[1] = bs + (nm + 1);
+        A.base[2] = S.hslot.as<unsigned long long>();
+        A.base[3] = bs + 2 * (nm + 1);
+        A.base[4] = bs + 2 * (nm + 1) + (nh + 1);
+        A.tile = tiles.as<unsigned long long>();
+        k_sizes<<<A.tiles_m + A.tiles_h, kBlock, 0, st>>>(A);
+        DT_HIP(hipGetLastError());
+        k_tile_sums<<<1, kTileBlock, 0, st>>>(A, hs);
+        DT_HIP(hipGetLastError());
+        DT_TRY(unit_sort());
+        DT_HIP(hipStreamSynchronize(st));
+        if (hs[0] != hs[1]) return fail(DT_EDEVICE, "medium work items of the two orders differ");
+        S.n_mitems = hs[0];
+        S.n_slots = hs[2];
+        S.n_chunks = hs[3];
+        S.n_pchunks = hs[4];
+        if (S.n_chunks > 0xffffffffull || S.n_pchunks > 0xffffffffull || nh > 0xffffffffull)
+            return fail(DT_EOVERFLOW, "too many heavy work items (%llu)", (unsigned long long)S.n_chunks);
+        cls.reset();
+        crec.reset();
+        DT_TRY(dev_alloc(ctx, S.mitems, S.n_mitems * 8));
+        DT_TRY(dev_alloc(ctx, S.mitems_w, S.n_mitems * 8));
+        DT_TRY(dev_alloc(ctx, S.chunks, S.n_chunks * 8));
+        DT_TRY(dev_alloc(ctx, S.pchunks, S.n_pchunks * 8));
+        A.mitems = S.mitems.as<uint32_t>();
+        A.mitems_w = S.mitems_w.as<uint32_t>();
+        A.chunks = S.chunks.as<uint32_t>();
+        A.pchunks = S.pchunks.as<uint32_t>();
+        k_expand<<<A.tiles_m + A.tiles_h, kBlock, 0, st>>>(A);
+        DT_HIP(hipGetLastError());
+        k_tables<<<1, kBlock, 0, st>>>(S.n_light, na, A, ctr, hs);
+        DT_HIP(hipGetLastError());
+        DT_HIP(hipStreamSynchronize(st));
+        memcpy(S.light_cells.data(), hs, (kCells + 1) * 8);
+        memcpy(S.mitem_cells.data(), hs + (kCells + 1), (kCells + 1) * 8);
+        const unsigned long long *lt = hs + 2 * (kCells + 1);
+        for (uint32_t l = 1; l <= kLevels; ++l) {
+            S.med_item_at[l] = lt[0 * (kLevels + 1) + l];
+            S.heavy_tri_at[l] = lt[1 * (kLevels + 1) + l];
+            S.heavy_chunk_at[l] = lt[2 * (kLevels + 1) + l];
+            S.heavy_pchunk_at[l] = lt[3 * (kLevels + 1) + l];
+            S.heavy_slot_at[l] = lt[4 * (kLevels + 1) + l];
+        }
+    } else {
+        DT_TRY(unit_sort());
+        for (DevMem *m : {&S.mitems, &S.mitems_w, &S.chunks, &S.pchunks}) DT_TRY(dev_alloc(ctx, *m, 0));
     }
     // join the unit-record sort
-    if (nu && us != st) DT_HIP(hipStreamWaitEvent(st, ctx->ev_relay[1], 0));
-    DT_HIP(hipStreamSynchronize(st));
+    DT_HIP(hipStreamSynchronize(us));
     if (nu) memcpy(S.unit_index.data(), ctx->pinned_stage + kStageUnit, (nbk + 1) * 4);
     return DT_OK;
 }
