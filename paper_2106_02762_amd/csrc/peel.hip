@@ -174,23 +174,21 @@ __device__ __forceinline__ void remove_edges(uint32_t v, uint32_t first, uint32_
 // Level after level would take hundreds of levels of a few removal rounds each, bound by the latency
 // of every round.  Their core numbers come instead from bounds that fall: every vertex holds an upper
 // bound of its core number, first its degree, and replaces it by the largest t such that t neighbours
-// have bounds of at least t, until no bound falls (the last bounds are the core numbers).  Then every
-// shell is peeled at once: a vertex goes in the first round in which at most core(v) of its
-// neighbours of core >= core(v) are left, and vertices are ordered by (core, round).  A neighbour
-// placed after v has a larger core or went no earlier, so it was counted then: at most core(v) of
-// them.  Both parts run in phases over all R rows, 65 and 50 phases for the 61M-edge graph's last
-// 65,536 vertices where levels took 410 and 2,000 rounds (its peel 13.9 -> 8.4 ms, 2.9 of them here;
-// 10M edges: 1.9 -> 1.5 ms).  65,536 is what 16-bit ids and one workgroup's LDS hold; above it the level
-// peel is the faster one (a level of many vertices there costs less than their share of 65 phases).
+// have bounds of at least t, until no bound falls (the last bounds are the core numbers).  A phase reads
+// the bounds that the phase before left, so the phase in which a bound takes its last value orders its
+// shell: when v's bound fell to core(v), at most core(v) of its neighbours had larger ones, and those of
+// v's shell that fell to their core numbers in the same phase or later, like all of larger cores, were
+// among them.  Vertices ordered by (core, phase) are therefore in degeneracy order, and no vertex need be
+// removed from the others' counts.  65 phases for the 61M-edge graph's last 65,536 vertices where levels
+// took 410 and 2,000 rounds (its peel 13.9 -> 7.8 ms, 2.2 of them here; 2.8 with a second part of 50 phases
+// that removed the shells' vertices in rounds, at 1.3M edges 0.36 against 0.26 ms).  65,536 is what 16-bit
+// ids and one workgroup's LDS hold; above it the level peel is the faster one (a level of many vertices
+// there costs less than their share of 65 phases).
 //
 // A wavefront owns consecutive local ids holding an even share of the entries.  Every phase each block
 // copies all bounds (128 KB at most) into LDS, where the gathers along the rows go; rows stream from
 // L2, short rows packed 64 entries at a time, rows of up to kRegRow entries held in registers
-// while their new bound is searched by ballots.  A phase may read bounds that others lower meanwhile:
-// any mix of old and new bounds is a set of upper bounds, and a phase in which none fell saw the final
-// ones.  In the rounds a vertex's value is 2 core + 1, less one once it is removed, so that a neighbour
-// counts for a vertex of core c when its value is at least 2 c + 1; a round reads the values left by the
-// rounds before it (two buffers).
+// while their new bound is searched by ballots.  Bounds have two buffers, one read and one written.
 // ------------------------------------------------------------------------------------------------
 constexpr uint32_t kGroup = 32;      // vertices of a wavefront handled at once
 constexpr uint32_t kVertexCost = 32; // a vertex's share of the work, in entries, besides its row
@@ -201,15 +199,17 @@ constexpr uint32_t kPiece = 128;     // entries of a row a wavefront reads at on
 constexpr uint32_t kRegPieces = 8;   // pieces of a row held in registers
 constexpr uint32_t kRegRow = kPiece * kRegPieces;
 constexpr uint32_t kFinSmall = 1024; // up to this many vertices one block finishes alone
-constexpr uint32_t kCoreLds = 4096;  // shells whose positions a block takes together
+constexpr uint32_t kSlots = 2048;    // places a block takes together
+constexpr uint32_t kCellMost = 1u << 18;   // (core, phase) places counted in memory
 
 struct FinArgs {
     const uint32_t *rlist, *lrow;
     const uint16_t *lcol;
-    uint16_t *val;        // R bounds; then, in the rounds, two buffers of R values
-    uint32_t *base;       // first position of each shell
-    uint32_t *cur;        // positions taken in each shell
-    uint32_t *pos;        // position of each vertex in its shell
+    uint16_t *val;        // two buffers of R bounds
+    uint32_t *base;       // first position of each (core, phase)
+    uint32_t *cur;        // positions taken in each
+    uint32_t *when;       // the last phase in which each vertex's bound fell, and one; 0: in none
+    uint32_t *pos;        // position of each vertex among those of its (core, phase)
     uint32_t *level, *queue;
     unsigned *bar;        // barrier counters: the root, then one per group of blocks, kBarLine apart
     PeelCtl *ctl;
@@ -441,40 +441,6 @@ __device__ __forceinline__ uint32_t group_bounds(const GroupRows &G, const uint1
     return h;
 }
 
-// Which of a group's vertices (lane x: core number C; `left` the ones not yet removed) have at most
-// core(v) neighbours of value at least 2 core(v) + 1.
-__device__ __forceinline__ uint32_t group_removable(const GroupRows &G, const uint16_t *__restrict__ lcol,
-                                                    const uint16_t *s_v, uint32_t C, uint32_t left, unsigned lane) {
-    uint32_t take = 0;
-    walk_rows(
-        G, lcol, lane,
-        [&](uint32_t x, uint32_t cnt, uint32_t b, uint32_t ends) {
-            if ((((uint64_t)left >> x) & ((1ull << cnt) - 1)) == 0) return;
-            const uint32_t len = __builtin_amdgcn_readlane(ends, cnt - 1);
-            const uint32_t r = pack_row(ends, cnt, lane);
-            const uint32_t t = 2 * __shfl(C, (x + r) & 63, 64) + 1;
-            const bool in = lane < len;
-            const uint64_t m = __ballot(in && s_v[lcol[b + (in ? lane : 0u)]] >= t);
-            // lane y of the group counts its own row
-            const uint32_t y = lane - x;
-            const uint32_t yp = __shfl(ends, (y - 1) & 63, 64), ye = __shfl(ends, y & 63, 64);
-            const uint32_t yb = y ? yp : 0u;
-            const bool ok = lane >= x && y < cnt && (uint32_t)__popcll(m & bits_between(yb, ye)) <= C;
-            take |= (uint32_t)__ballot(ok);
-        },
-        [&](uint32_t x, uint32_t b, uint32_t d, const uint32_t (&e)[kRegPieces]) {
-            if (((left >> x) & 1u) == 0) return;
-            const uint32_t c = __builtin_amdgcn_readlane(C, x);
-            uint32_t n = 0;
-            row_stretches(lcol, s_v, b, d, lane, e, [&](const uint32_t (&v)[2 * kRegPieces], uint32_t left) {
-                n += count_at_least(v, left, 2 * c + 1);
-                return n <= c;
-            });
-            if (n <= c) take |= 1u << x;
-        });
-    return take & left;
-}
-
 // the first vertex v <= R whose work before it, lrow[v] + kVertexCost * v, is at least x (64 probes at
 // a time)
 __device__ __forceinline__ uint32_t split_vertex(const uint32_t *__restrict__ lrow, uint32_t R, uint64_t x, unsigned lane) {
@@ -494,7 +460,7 @@ __device__ __forceinline__ uint32_t split_vertex(const uint32_t *__restrict__ lr
 __global__ void __launch_bounds__(kBlock)
 k_peel_finish(FinArgs A) {
     __shared__ __attribute__((aligned(16))) uint16_t s_v[kTail];
-    __shared__ uint32_t s_cnt[kCoreLds];
+    __shared__ uint32_t s_key[kSlots], s_cnt[kSlots];
     __shared__ unsigned s_any, s_more, s_scan[kBlock / 64];
     PeelCtl *ctl = A.ctl;
     if (!ctl->ho || ctl->error) return;
@@ -519,8 +485,12 @@ k_peel_finish(FinArgs A) {
     };
     const GroupRows G0 = group_rows(va < vb ? va : (vb < R ? vb : R));
     // bounds: the degrees; no position taken
-    for (uint32_t v = gtid; v < R; v += gsize) A.val[v] = (uint16_t)(A.lrow[v + 1] - A.lrow[v]);
-    for (uint32_t c = gtid; c <= R; c += gsize) A.cur[c] = 0;
+    const uint32_t cell_cap = R < kCellMost / 32 ? 32 * R + 1024 : kCellMost;
+    for (uint32_t v = gtid; v < R; v += gsize) {
+        A.val[v] = (uint16_t)(A.lrow[v + 1] - A.lrow[v]);
+        A.when[v] = 0;
+    }
+    for (uint32_t c = gtid; c < cell_cap; c += gsize) A.cur[c] = 0;
     fin_barrier(A, nblk, ++turn);
     auto load_values = [&](const uint16_t *from) {
         const uint4 *src = reinterpret_cast<const uint4 *>(from);
@@ -544,18 +514,21 @@ k_peel_finish(FinArgs A) {
     // core numbers
     uint32_t ph = 0;
     for (;; ++ph) {
-        load_values(A.val);
+        load_values(A.val + (ph & 1 ? kTail : 0));
         __syncthreads();
+        uint16_t *out = A.val + (ph & 1 ? 0 : kTail);
         bool fell = false;
         for (uint32_t v0 = va; v0 < vb; v0 += kGroup) {
             const GroupRows G = v0 == va ? G0 : group_rows(v0);
             const uint32_t v = v0 + lane;
             const uint32_t h = lane < G.nv ? s_v[v] : 0u;
             const uint32_t nh = group_bounds(G, A.lcol, s_v, h, k0, lane);
-            if (lane < G.nv && nh != h) {
-                A.val[v] = (uint16_t)nh;
-                s_v[v] = (uint16_t)nh;
-                fell = true;
+            if (lane < G.nv) {
+                out[v] = (uint16_t)nh;
+                if (nh != h) {
+                    A.when[v] = ph + 1;
+                    fell = true;
+                }
             }
         }
         const unsigned more = any_left(fell, ph);
@@ -566,64 +539,64 @@ k_peel_finish(FinArgs A) {
             return;
         }
     }
-    ++ph;
-    // shells: s_v holds the core numbers (nothing fell in the last phase)
-    {
-        uint16_t *first = A.val + kTail;
-        for (uint32_t v = va + lane; v < vb; v += 64) first[v] = (uint16_t)(2u * s_v[v] + 1u);
-    }
-    fin_barrier(A, nblk, ++turn);
-    uint32_t r = 0;
-    for (;; ++r, ++ph) {
-        const uint16_t *in = A.val + (r & 1 ? 0 : kTail);
-        uint16_t *out = A.val + (r & 1 ? kTail : 0);
-        load_values(in);
-        for (uint32_t c = tid; c < kCoreLds; c += kBlock) s_cnt[c] = 0;
-        __syncthreads();
-        bool rest = false, mine = false;   // mine: this lane's vertex of the first group goes now
-        uint32_t at = 0, core = 0;
-        for (uint32_t v0 = va; v0 < vb; v0 += kGroup) {
-            const GroupRows G = v0 == va ? G0 : group_rows(v0);
-            const uint32_t v = v0 + lane;
-            const uint32_t x = lane < G.nv ? s_v[v] : 0u, C = x >> 1;
-            const uint32_t left = (uint32_t)__ballot((x & 1u) != 0);
-            uint32_t take = 0;
-            if (left) {
-                take = group_removable(G, A.lcol, s_v, C, left, lane);
-                if (lane < G.nv && (take >> lane) & 1u) {
-                    if (v0 == va && C < kCoreLds) {
-                        mine = true;
-                        core = C;
-                        at = atomicAdd(&s_cnt[C], 1u);
-                    } else {
-                        A.pos[v] = atomicAdd(&A.cur[C], 1u);
-                    }
-                }
-                rest |= (left & ~take) != 0;
+    // s_v holds the core numbers (nothing fell in this last phase ph); the largest of them
+    if (tid == 0) s_any = 0;
+    __syncthreads();
+    uint32_t top = 0;
+    for (uint32_t v = tid; v < R; v += kBlock) top = s_v[v] > top ? s_v[v] : top;
+    if (top) atomicMax(&s_any, top);
+    __syncthreads();
+    const uint32_t kmax = s_any;
+    const uint32_t T = ph + 1, shells = kmax >= k0 ? kmax - k0 + 1 : 1;
+    const bool wide = (uint64_t)shells * T > cell_cap;   // (core, phase) pairs beyond the room for them
+    const uint32_t cells = wide ? (shells < cell_cap ? shells : cell_cap) : shells * T;
+    // this block's vertices, one a thread and chunk: their places among those of their cell, taken with
+    // one atomic a block, chunk and cell where the cell's slot in LDS is free for it.  Beyond the room the
+    // cells are the shells, and the phases take their places one after the other.
+    const uint32_t ba = blockIdx.x, first = split_vertex(A.lrow, R, work * (ba * kBW) / W, lane);
+    const uint32_t last = ba + 1 < nblk ? split_vertex(A.lrow, R, work * ((ba + 1) * kBW) / W, lane) : R;
+    auto cell_of = [&](uint32_t v) {
+        const uint32_t c = s_v[v] > k0 ? s_v[v] - k0 : 0u;
+        return wide ? c : c * T + A.when[v];
+    };
+    for (uint32_t t = 0; t < (wide ? T : 1u); ++t) {
+        for (uint32_t v0 = first; v0 < last; v0 += kBlock) {
+            for (uint32_t x = tid; x < kSlots; x += kBlock) {
+                s_key[x] = ~0u;
+                s_cnt[x] = 0;
             }
-            if (lane < G.nv) out[v] = (uint16_t)(x - ((take >> lane) & 1u));
+            __syncthreads();
+            const uint32_t v = v0 + tid;
+            const bool in = v < last && (!wide || A.when[v] == t);
+            const uint32_t cell = in ? cell_of(v) : 0u, slot = cell % kSlots;
+            uint32_t at = 0;
+            bool held = false;
+            if (in) {
+                const uint32_t was = atomicCAS(&s_key[slot], ~0u, cell);
+                held = was == ~0u || was == cell;
+                at = held ? atomicAdd(&s_cnt[slot], 1u) : atomicAdd(&A.cur[cell], 1u);
+            }
+            __syncthreads();
+            for (uint32_t x = tid; x < kSlots; x += kBlock)
+                if (s_cnt[x]) s_cnt[x] = atomicAdd(&A.cur[s_key[x]], s_cnt[x]);
+            __syncthreads();
+            if (in) A.pos[v] = held ? s_cnt[slot] + at : at;
+            __syncthreads();
         }
-        // positions: one atomic per block and shell
-        __syncthreads();
-        for (uint32_t c = tid; c < kCoreLds; c += kBlock) {
-            const uint32_t n = s_cnt[c];
-            if (n) s_cnt[c] = atomicAdd(&A.cur[c], n);
-        }
-        __syncthreads();
-        if (mine) A.pos[va + lane] = s_cnt[core] + at;
-        const unsigned more = any_left(rest, ph);
-        if (more & 2u) return;
-        if (!more) break;
-        if (r > 2 * R + 64) {   // cannot happen: every shell loses a vertex in a round
-            if (gtid == 0) atomicOr(&ctl->error, 16u);
-            return;
-        }
+        fin_barrier(A, nblk, ++turn, &ctl->fin[0], &s_more);
+        if (s_more & 2u) return;
     }
-    // first position of every shell: every block writes the same ones, and reads its own back
-    uint32_t run = 0, top = 0;
-    for (uint32_t c0 = 0; c0 <= R && run < R; c0 += kBlock) {
-        const uint32_t c = c0 + tid, n = c <= R ? A.cur[c] : 0u;
-        uint32_t x = n;
+    // first position of every cell: every block writes the same ones, and reads its own back
+    uint32_t run = 0;
+    for (uint32_t c0 = 0; c0 < cells && run < R; c0 += 4 * kBlock) {
+        const uint32_t c = c0 + 4 * tid;
+        uint32_t n[4], mine = 0;
+#pragma unroll
+        for (uint32_t j = 0; j < 4; ++j) {
+            n[j] = c + j < cells ? A.cur[c + j] : 0u;
+            mine += n[j];
+        }
+        uint32_t x = mine;
 #pragma unroll
         for (int o = 1; o < 64; o <<= 1) {
             const uint32_t y = __shfl_up(x, o, 64);
@@ -636,28 +609,28 @@ k_peel_finish(FinArgs A) {
             before += w < tid / 64 ? s_scan[w] : 0u;
             total += s_scan[w];
         }
-        if (c <= R) A.base[c] = run + before + x - n;
-        if (n) top = c;
+        uint32_t at = run + before + x - mine;
+#pragma unroll
+        for (uint32_t j = 0; j < 4; ++j) {
+            if (c + j < cells) A.base[c + j] = at;
+            at += n[j];
+        }
         run += total;
         __syncthreads();
     }
-    if (tid == 0) s_any = 0;
-    __syncthreads();
-    if (top) atomicMax(&s_any, top);
-    __syncthreads();
     // positions and core numbers, each by the lane that took the position
-    for (uint32_t v0 = va; v0 < vb; v0 += kGroup) {
-        const uint32_t v = v0 + lane;
-        if (lane < kGroup && v < vb) {
-            const uint32_t c = s_v[v] >> 1, p = qbase + A.base[c] + A.pos[v], x = A.rlist[v];
+    for (uint32_t v0 = first; v0 < last; v0 += kBlock) {
+        const uint32_t v = v0 + tid;
+        if (v < last) {
+            const uint32_t p = qbase + A.base[cell_of(v)] + A.pos[v], x = A.rlist[v];
             if (p < qbase + R) A.queue[p] = x;
             else atomicOr(&ctl->error, 16u);
-            A.level[x] = c;
+            A.level[x] = s_v[v];
         }
     }
     if (gtid == 0) {
-        ctl->kappa = s_any > k0 ? s_any : k0;
-        ctl->rounds = ctl->ho_rounds + r + 1;
+        ctl->kappa = kmax > k0 ? kmax : k0;
+        ctl->rounds = ctl->ho_rounds + T;
         __hip_atomic_store(&ctl->qtail, qbase + R, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
@@ -1064,8 +1037,8 @@ int peel(dt_graph *g) {
     DT_TRY(dev_alloc(ctx, loc, (uint64_t)n * 4));
     DT_TRY(dev_alloc(ctx, rlist, (uint64_t)tail_cap * 4));
     DT_TRY(dev_alloc(ctx, lrow, ((uint64_t)tail_cap + 1) * 4));
-    // its values (two buffers), shell starts and cursors, and positions
-    constexpr uint64_t kFinWords = kTail + 2ull * (kTail + 64) + kTail;
+    // its bounds (two buffers), cell starts and cursors, phases and positions
+    constexpr uint64_t kFinWords = kTail + 2ull * kCellMost + 2ull * kTail;
     DT_TRY(dev_alloc(ctx, fin, kFinWords * 4));
     DT_TRY(dev_alloc(ctx, lcol, (lcol_cap + kPiece) * 2));   // (the finish reads whole pieces)
     if (n == 0) {
@@ -1108,8 +1081,9 @@ int peel(dt_graph *g) {
     fa.lrow = lb;
     fa.lcol = lc;
     fa.base = fin.as<uint32_t>();
-    fa.cur = fa.base + kTail + 64;
-    fa.pos = fa.cur + kTail + 64;
+    fa.cur = fa.base + kCellMost;
+    fa.when = fa.cur + kCellMost;
+    fa.pos = fa.when + kTail;
     fa.val = reinterpret_cast<uint16_t *>(fa.pos + kTail);
     fa.level = level;
     fa.queue = queue;
