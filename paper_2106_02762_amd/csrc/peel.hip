@@ -42,14 +42,16 @@ namespace {
 
 constexpr unsigned kBlock = 1024;
 constexpr unsigned kGridWide = 256;    // blocks of the first levels
-// the grid narrows as vertices run out: blocks while at least `from` vertices remain (timed per
-// phase on the 61M-edge graph: one width for all of them below 200,000 vertices, 16 or 8 blocks
-// there, and 256 blocks down to 16,000 vertices were all slower)
+// The grid narrows as vertices run out (blocks while at least `from` remain), where a level removes fewer
+// than kBusy of them: its rounds then wait for each other more than they work, and fewer blocks meet
+// sooner (61M edges, whose levels grow small: 3.9 ms so, 4.3 with 256 blocks throughout; 10M edges, a few
+// large levels: 0.50 ms so, 0.61 narrowing by the vertices left alone).
 struct Width {
     uint32_t from;
     unsigned blocks;
 };
-constexpr Width kWidths[4] = {{1000000, kGridWide}, {200000, 128}, {50000, 64}, {0, 32}};
+constexpr Width kWidths[3] = {{400000, kGridWide}, {50000, 128}, {0, 64}};
+constexpr uint32_t kBusy = 32768;
 constexpr uint32_t kTail = 65536;   // most vertices the finish takes (16-bit local ids and bounds)
 // LDS words of a peel block: two staging halves, the vertices the block is removing and those their
 // removal queues
@@ -65,7 +67,6 @@ struct PeelCtl {
     unsigned int qtail;      // vertices queued in all (written at the end)
     unsigned int qc[3];      // per grid phase mod 3: queue positions taken in that phase
     unsigned int ovc[3];     // per grid phase mod 3: vertices that phase queued past a full stage
-    unsigned int arrived;    // barrier arrivals (only ever increases)
     unsigned int error;      // a barrier gave up waiting, or a consistency check failed
     unsigned int rounds;     // removal rounds
     unsigned int kappa;      // largest level that removed a vertex
@@ -83,26 +84,47 @@ __device__ __forceinline__ int ld_relaxed(const int *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Grid barrier.  Arrivals only ever increase, and every block passes the same barriers in the same
-// order with the same participants, so a barrier is complete once `target` arrivals (the running
-// sum of the participants of every barrier so far) have been counted: each block's first thread
-// publishes its block's writes, arrives, polls the count (an acquiring poll would throw away its
-// caches each time) and takes the others' writes; no block has to release the others.
-// A barrier that waits far longer than any peel could take sets an error flag and lets its block
-// go.
-__device__ void grid_barrier(PeelCtl *ctl, unsigned target) {
+// Grid barrier.  Arrivals are counted per group of kBarGroup blocks, the last of a group arrives at the
+// root, and every block polls the root, or the only group's counter: an atomic on one address takes
+// about 15 ns, so 256 arrivals at one counter, which the pollers read meanwhile, took 4 us and more
+// (the level peel of 61M edges with one counter 5.0 ms, 3.9 so).
+// Counters only ever increase, and every block passes the same barriers in the same order with the same
+// participants (the grid narrows by whole groups), so a barrier is complete once its counter holds the
+// running sum of its arrivals: a block's first thread publishes its block's writes, arrives, polls (an
+// acquiring poll would throw away its caches each time) and takes the others' writes; no block has to
+// release the others.  A barrier that waits far longer than any peel could take sets an error flag and
+// lets its block go.
+constexpr unsigned kBarGroup = 32;   // blocks that share a counter
+constexpr unsigned kBarLine = 32;    // words between counters
+constexpr unsigned kBarWords = (1 + 1024 / kBarGroup) * kBarLine;   // the root, then one per group
+struct BarTurn {
+    unsigned turn = 0, root = 0;   // barriers passed, arrivals at the root so far
+};
+__device__ void group_barrier(unsigned *bar, unsigned *error, unsigned nblk, BarTurn &b) {
+    const unsigned groups = (nblk + kBarGroup - 1) / kBarGroup;
+    ++b.turn;
+    b.root += groups > 1 ? groups : 0u;
     __syncthreads();
-    if (threadIdx.x == 0) {
+    if (threadIdx.x == 0 && nblk > 1) {
         __threadfence();
-        const unsigned a = atomicAdd(&ctl->arrived, 1u) + 1;
-        if (a < target) {
-            long spins = 0;
-            while (ld_relaxed(&ctl->arrived) < target) {
-                __builtin_amdgcn_s_sleep(1);
-                if (++spins > kSpinLimit) {
-                    atomicOr(&ctl->error, 1u);
-                    break;
-                }
+        const unsigned grp = blockIdx.x / kBarGroup;
+        const unsigned size = grp + 1 < groups ? kBarGroup : nblk - grp * kBarGroup;
+        unsigned *mine = &bar[(1 + grp) * kBarLine];
+        unsigned *poll = groups > 1 ? &bar[0] : mine;
+        const unsigned target = groups > 1 ? b.root : b.turn * size;
+        if (atomicAdd(mine, 1u) + 1 == b.turn * size && groups > 1) {
+            __threadfence();
+            atomicAdd(&bar[0], 1u);
+        }
+        long spins = 0;
+        while (ld_relaxed(poll) < target) {
+            __builtin_amdgcn_s_sleep(1);
+            ++spins;
+            // (a block that found an error has left)
+            if ((spins & 1023) == 0 && ld_relaxed(error)) break;
+            if (spins > kSpinLimit) {
+                atomicOr(error, 1u);
+                break;
             }
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
@@ -193,8 +215,6 @@ __device__ __forceinline__ void remove_edges(uint32_t v, uint32_t first, uint32_
 constexpr uint32_t kGroup = 32;      // vertices of a wavefront handled at once
 constexpr uint32_t kVertexCost = 32; // a vertex's share of the work, in entries, besides its row
 constexpr uint32_t kPerWave = 16;    // vertices per wavefront that a grid is sized for
-constexpr unsigned kBarGroup = 32;   // blocks that share a counter of the finish's barrier
-constexpr unsigned kBarLine = 32;    // words between counters
 constexpr uint32_t kPiece = 128;     // entries of a row a wavefront reads at once, two a lane
 constexpr uint32_t kRegPieces = 8;   // pieces of a row held in registers
 constexpr uint32_t kRegRow = kPiece * kRegPieces;
@@ -211,44 +231,19 @@ struct FinArgs {
     uint32_t *when;       // the last phase in which each vertex's bound fell, and one; 0: in none
     uint32_t *pos;        // position of each vertex among those of its (core, phase)
     uint32_t *level, *queue;
-    unsigned *bar;        // barrier counters: the root, then one per group of blocks, kBarLine apart
+    unsigned *bar;        // barrier counters (kBarWords)
     PeelCtl *ctl;
 };
 
-// Barrier `turn` (1, 2, ...) of the finish's nblk blocks: arrivals are counted per group of blocks, the
-// last of a group arrives at the root, and every block polls the root, or the only group's counter (an
-// atomic on one address takes about 15 ns, so 256 arrivals at one counter would take 4 us).  As in
-// grid_barrier, waiting far too long sets an error and lets the block go.
-// With `flag`, its value and the error state come back in s_flag, read once every block has arrived.
-__device__ void fin_barrier(const FinArgs &A, unsigned nblk, unsigned turn, const unsigned *flag = nullptr,
+// Barrier of the finish's nblk blocks.  With `flag`, its value and the error state come back in s_flag,
+// read once every block has arrived.
+__device__ void fin_barrier(const FinArgs &A, unsigned nblk, BarTurn &turn, const unsigned *flag = nullptr,
                             unsigned *s_flag = nullptr) {
-    __syncthreads();
-    if (threadIdx.x == 0 && nblk > 1) {
-        __threadfence();
-        const unsigned grp = blockIdx.x / kBarGroup, groups = (nblk + kBarGroup - 1) / kBarGroup;
-        const unsigned size = grp + 1 < groups ? kBarGroup : nblk - grp * kBarGroup;
-        unsigned *mine = &A.bar[(1 + grp) * kBarLine];
-        unsigned *poll = groups > 1 ? &A.bar[0] : mine;
-        const unsigned target = groups > 1 ? turn * groups : turn * size;
-        if (atomicAdd(mine, 1u) + 1 == turn * size && groups > 1) {
-            __threadfence();
-            atomicAdd(&A.bar[0], 1u);
-        }
-        long spins = 0;
-        while (ld_relaxed(poll) < target) {
-            __builtin_amdgcn_s_sleep(1);
-            ++spins;
-            // (a block that found an error has left)
-            if ((spins & 1023) == 0 && ld_relaxed(&A.ctl->error)) break;
-            if (spins > kSpinLimit) {
-                atomicOr(&A.ctl->error, 1u);
-                break;
-            }
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    group_barrier(A.bar, &A.ctl->error, nblk, turn);
+    if (flag) {
+        if (threadIdx.x == 0) *s_flag = (ld_relaxed(flag) ? 1u : 0u) | (ld_relaxed(&A.ctl->error) ? 2u : 0u);
+        __syncthreads();
     }
-    if (threadIdx.x == 0 && flag) *s_flag = (ld_relaxed(flag) ? 1u : 0u) | (ld_relaxed(&A.ctl->error) ? 2u : 0u);
-    __syncthreads();
 }
 
 // f(I) for every piece I that begins before entry d: nested, so that one jump skips the rest
@@ -472,7 +467,7 @@ k_peel_finish(FinArgs A) {
     const unsigned tid = threadIdx.x, lane = tid & 63;
     const uint32_t W = nblk * kBW, gw = blockIdx.x * kBW + tid / 64;
     const uint32_t gtid = blockIdx.x * kBlock + tid, gsize = nblk * kBlock;
-    unsigned turn = 0;
+    BarTurn turn;
     // this wavefront's vertices
     const uint64_t work = (uint64_t)A.lrow[R] + (uint64_t)kVertexCost * R;
     const uint32_t va = split_vertex(A.lrow, R, work * gw / W, lane);
@@ -491,7 +486,7 @@ k_peel_finish(FinArgs A) {
         A.when[v] = 0;
     }
     for (uint32_t c = gtid; c < cell_cap; c += gsize) A.cur[c] = 0;
-    fin_barrier(A, nblk, ++turn);
+    fin_barrier(A, nblk, turn);
     auto load_values = [&](const uint16_t *from) {
         const uint4 *src = reinterpret_cast<const uint4 *>(from);
         uint4 *dst = reinterpret_cast<uint4 *>(s_v);
@@ -504,7 +499,7 @@ k_peel_finish(FinArgs A) {
         __syncthreads();
         if (tid == 0 && s_any)
             __hip_atomic_store(&ctl->fin[ph % 3], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        fin_barrier(A, nblk, ++turn, &ctl->fin[ph % 3], &s_more);
+        fin_barrier(A, nblk, turn, &ctl->fin[ph % 3], &s_more);
         const unsigned more = s_more;
         // read by every block before the next barrier: cleared for the phase after next
         if (gtid == 0)
@@ -583,7 +578,7 @@ k_peel_finish(FinArgs A) {
             if (in) A.pos[v] = held ? s_cnt[slot] + at : at;
             __syncthreads();
         }
-        fin_barrier(A, nblk, ++turn, &ctl->fin[0], &s_more);
+        fin_barrier(A, nblk, turn, &ctl->fin[0], &s_more);
         if (s_more & 2u) return;
     }
     // first position of every cell: every block writes the same ones, and reads its own back
@@ -641,7 +636,7 @@ k_peel(uint32_t n, const uint32_t *__restrict__ row, const uint32_t *__restrict_
        uint32_t *__restrict__ alive_a, uint32_t *__restrict__ alive_b, uint32_t *__restrict__ loc,
        uint32_t *__restrict__ rlist, uint32_t *__restrict__ lrow, uint64_t lcol_cap, uint32_t tail_cap,
        uint32_t *__restrict__ ovf0,
-       uint32_t *__restrict__ ovf1, PeelCtl *__restrict__ ctl) {
+       uint32_t *__restrict__ ovf1, PeelCtl *__restrict__ ctl, unsigned *__restrict__ bar) {
     // the whole grid takes part while many vertices remain, then ever fewer of its first blocks
     unsigned nblk = gridDim.x;
     const uint32_t gtid = blockIdx.x * kBlock + threadIdx.x;
@@ -649,7 +644,7 @@ k_peel(uint32_t n, const uint32_t *__restrict__ row, const uint32_t *__restrict_
     const uint32_t gwave = gtid / 64, lane = threadIdx.x & 63;
     uint32_t nwaves = gsize / 64;
     const uint64_t below = (1ull << lane) - 1;
-    unsigned btarget = 0;   // arrivals that complete the next barrier, less its participants
+    BarTurn turn;
     __shared__ __attribute__((aligned(16))) uint32_t s_mem[kLdsWords];
     __shared__ unsigned s_cnt, s_base;
     __shared__ unsigned s_wct[kBlock / 64], s_wck[kBlock / 64], s_wmd[kBlock / 64], s_bq, s_bk;
@@ -663,7 +658,7 @@ k_peel(uint32_t n, const uint32_t *__restrict__ row, const uint32_t *__restrict_
     }
     if (gtid == 0)
         for (int x = 0; x < 3; ++x) ctl->scan[x][1] = 0xffffffffu;
-    grid_barrier(ctl, btarget += nblk);
+    group_barrier(bar, &ctl->error, nblk, turn);
 
     // tail: vertices queued before the current grid phase (a scan or a round); phase ph takes its
     // queue positions tail + [0, qc[ph % 3]) and every block adds the final count after the phase's
@@ -764,7 +759,7 @@ k_peel(uint32_t n, const uint32_t *__restrict__ row, const uint32_t *__restrict_
                 }
             }
         }
-        grid_barrier(ctl, btarget += nblk);
+        group_barrier(bar, &ctl->error, nblk, turn);
         tail += ld_relaxed(&ctl->qc[ph % 3]);
         const uint32_t na2 = ld_relaxed(&ctl->scan[lv % 3][0]), md = ld_relaxed(&ctl->scan[lv % 3][1]);
         // the counters of the previous level were read by every block before this barrier: clear
@@ -780,9 +775,9 @@ k_peel(uint32_t n, const uint32_t *__restrict__ row, const uint32_t *__restrict_
         // few vertices left: the later levels are latency-bound, and a barrier costs more the
         // more blocks meet at it, so the grid narrows in steps (only ever narrows)
         {
-            unsigned want = kWidths[3].blocks;
+            unsigned want = kWidths[2].blocks;
             for (const Width &w : kWidths)
-                if (na2 >= w.from) {
+                if (na2 >= w.from || n_alive - na2 >= kBusy) {
                     want = w.blocks;
                     break;
                 }
@@ -874,7 +869,7 @@ k_peel(uint32_t n, const uint32_t *__restrict__ row, const uint32_t *__restrict_
                     }
                 }
                 ++rounds;
-                grid_barrier(ctl, btarget += nblk);
+                group_barrier(bar, &ctl->error, nblk, turn);
                 tail = qbase + ld_relaxed(&ctl->qc[ph % 3]);
                 head = tail;
                 nf = ld_relaxed(ovc);
@@ -958,7 +953,7 @@ k_peel(uint32_t n, const uint32_t *__restrict__ row, const uint32_t *__restrict_
             }
         }
     }
-    grid_barrier(ctl, btarget += nblk);
+    group_barrier(bar, &ctl->error, nblk, turn);
     const unsigned long long lres = __hip_atomic_load(&ctl->lres, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const uint32_t R = (uint32_t)lres, total = (uint32_t)(lres >> 32);
     if (R != n - tail || R > kTail || total > lcol_cap || ld_relaxed(&ctl->error)) {
@@ -1023,10 +1018,10 @@ int peel(dt_graph *g) {
     DT_TRY(dev_alloc(ctx, g->core, (uint64_t)n * 4));
     DT_TRY(dev_alloc(ctx, g->order, (uint64_t)n * 4));
     DT_TRY(dev_alloc(ctx, g->rank, (uint64_t)n * 4));
-    // control block, then the finish's barrier counters (cleared together)
-    constexpr uint64_t kCtlBytes = 512, kBarBytes = (1 + 1024 / kBarGroup) * kBarLine * 4;
+    // control block, then the barrier counters of the levels and of the finish (cleared together)
+    constexpr uint64_t kCtlBytes = 512, kBarBytes = kBarWords * 4;
     static_assert(sizeof(PeelCtl) <= kCtlBytes, "control block layout");
-    DT_TRY(dev_alloc(ctx, ctlm, kCtlBytes + kBarBytes));
+    DT_TRY(dev_alloc(ctx, ctlm, kCtlBytes + 2 * kBarBytes));
     // the finish: at most tail_cap vertices, their adjacency within 2 m_static entries and below
     // tail_cap (tail_cap - 1) as well
     // (twice a core number and one more fit 16 bits: of 32768 vertices always, of more while the pairs
@@ -1053,7 +1048,7 @@ int peel(dt_graph *g) {
     unsigned grid = kGridWide;
     if (grid > (unsigned)ctx->num_cus * (unsigned)per_cu) grid = (unsigned)ctx->num_cus * (unsigned)per_cu;
     grid = std::min(grid, grid_for(n, kBlock));
-    DT_HIP(hipMemsetAsync(ctlm.ptr, 0, kCtlBytes + kBarBytes, st));
+    DT_HIP(hipMemsetAsync(ctlm.ptr, 0, kCtlBytes + 2 * kBarBytes, st));
     uint32_t *level = g->core.as<uint32_t>();
     uint32_t *queue = g->order.as<uint32_t>();
     const uint32_t *row = g->row.as<uint32_t>(), *col = g->col.as<uint32_t>();
@@ -1065,9 +1060,10 @@ int peel(dt_graph *g) {
     uint16_t *lc = lcol.as<uint16_t>();
     uint64_t lcap = lcol_cap;
     uint32_t tcap = tail_cap;
+    unsigned *lbar = reinterpret_cast<unsigned *>(ctlm.as<uint8_t>() + kCtlBytes);
     uint32_t *o0 = ovf0.as<uint32_t>(), *o1 = ovf1.as<uint32_t>();
     void *args[] = {&nn, &row, &col, &degp, &level, &queue, &aa, &ab, &locp, &rl, &lb, &lcap, &tcap,
-                    &o0, &o1, &ctl};
+                    &o0, &o1, &ctl, &lbar};
     prof_begin(ctx, kProfPeel, st);
     DT_HIP(hipLaunchCooperativeKernel((const void *)k_peel, dim3(grid), dim3(kBlock), args, 0, st));
     prof_end(ctx, kProfPeel, st);
@@ -1087,7 +1083,7 @@ int peel(dt_graph *g) {
     fa.val = reinterpret_cast<uint16_t *>(fa.pos + kTail);
     fa.level = level;
     fa.queue = queue;
-    fa.bar = reinterpret_cast<unsigned *>(ctlm.as<uint8_t>() + kCtlBytes);
+    fa.bar = lbar + kBarWords;
     fa.ctl = ctl;
     // as many blocks as the most vertices it can get fill (co-resident: one per CU)
     const unsigned fgrid = std::min<unsigned>(std::min<unsigned>((unsigned)ctx->num_cus, 1024u),
