@@ -99,6 +99,61 @@ __device__ __forceinline__ void medium_block(uint32_t b, uint32_t nblk, const Ra
     }
 }
 
+// The same with the pairs of the wavefronts' largest groups of 64 entries shared by the block: at large
+// deltas a group holds up to a hundred thousand pairs where the mean is ten thousand, and the last
+// wavefronts ran alone for most of the kernel (61M edges without deltas: count 2.4 -> 1.7 ms; 100K edges
+// 0.36 -> 0.16).  A wavefront keeps the largest group of more than kShareMin pairs that
+// it meets for the end, in LDS; the block then evaluates its kept groups together.  Consecutive groups,
+// which often are of one large triangle, go to different blocks.
+constexpr uint32_t kShareMin = 512;
+constexpr unsigned kShareWords = 10;
+template <unsigned BLOCK, class PACC>
+__device__ __forceinline__ void medium_shared(uint32_t b, uint32_t nblk, const Ranges &R, const uint32_t *__restrict__ med,
+                                              const uint32_t *__restrict__ ent, const uint8_t *__restrict__ lev,
+                                              const uint32_t *__restrict__ eoff, const uint64_t *__restrict__ key,
+                                              const DQuery &q, PACC &acc) {
+    constexpr unsigned kWaves = BLOCK / 64;
+    __shared__ uint32_t s_kept[kWaves][kShareWords][64];
+    __shared__ uint32_t s_total[kWaves];
+    const unsigned lane = threadIdx.x & 63, wave = threadIdx.x / 64;
+    auto keep = [&](const MediumLanes &M) {
+        const uint32_t w[kShareWords] = {M.excl, M.c0, M.lo0, M.lo1, M.flags, M.kx_lo, M.kx_hi, M.z0, M.z1, M.z2};
+#pragma unroll
+        for (unsigned x = 0; x < kShareWords; ++x) s_kept[wave][x][lane] = w[x];
+    };
+    auto kept = [&](unsigned g, uint32_t total) {
+        uint32_t w[kShareWords];
+#pragma unroll
+        for (unsigned x = 0; x < kShareWords; ++x) w[x] = s_kept[g][x][lane];
+        return MediumLanes{w[0], w[1], w[2], w[3], w[4], w[5], w[6], w[7], w[8], w[9], total};
+    };
+    auto eval = [&](uint32_t d_uv, uint32_t d_uw, uint32_t z0, uint32_t z1, uint32_t z2, uint64_t k_uv, uint64_t k_uw) {
+        pair_thirds(key, z0, z1, z2, q, d_uv, d_uw, k_uv, k_uw, acc);
+    };
+    const uint64_t n_ent = R.pre[R.n];
+    const uint64_t W = (uint64_t)nblk * kWaves;
+    uint32_t r = 0, held = 0;
+    for (uint64_t e = ((uint64_t)wave * nblk + b) * 64; e < n_ent; e += W * 64) {
+        const uint64_t j = e + lane;
+        const bool active = j < n_ent;
+        MediumLanes M = medium_find(med, ent, active ? range_at(R, r, j) : 0, active, eoff, key, q, lane, lev);
+        acc.visits += (active ? 1u : 0u) + (lane == 0 ? M.total : 0u);
+        if (M.total > kShareMin && M.total > held) {
+            const MediumLanes old = kept(wave, held);
+            keep(M);
+            held = M.total;
+            M = old;
+        }
+        medium_spread(M, 0, 64, key, eval, lane);
+    }
+    if (lane == 0) s_total[wave] = held;
+    __syncthreads();
+    for (unsigned g = 0; g < kWaves; ++g) {
+        const uint32_t total = s_total[g];
+        if (total) medium_spread(kept(g, total), wave * 64, BLOCK, key, eval, lane);
+    }
+}
+
 // unit path: block b of nblk takes a contiguous run of the records [beg, end); returns its length
 template <bool CELLS, unsigned BLOCK>
 __device__ __forceinline__ uint64_t unit_block(uint32_t b, uint32_t nblk, uint64_t beg, uint64_t end,
@@ -121,6 +176,20 @@ k_light(Ranges R, const uint32_t *__restrict__ tri, const uint32_t *__restrict__
         light_block<BLOCK>(blockIdx.x, gridDim.x, R, tri, eoff, key, q, acc);
         add_visits(visits, acc.visits);
     });
+}
+
+// (the shared form has at most as many blocks as partial slots, and at least half as many: its blocks
+// zero the others)
+template <unsigned BLOCK>
+__global__ void __launch_bounds__(BLOCK)
+k_medium_shared(Ranges R, const uint32_t *__restrict__ med, const uint32_t *__restrict__ ent,
+                const uint8_t *__restrict__ lev, const uint32_t *__restrict__ eoff, const uint64_t *__restrict__ key,
+                DQuery q, int64_t *__restrict__ partial, unsigned slots, unsigned long long *__restrict__ visits) {
+    with_pairwise<Acc<false>, BLOCK>(partial, nullptr, [&](auto &acc) {
+        medium_shared<BLOCK>(blockIdx.x, gridDim.x, R, med, ent, lev, eoff, key, q, acc);
+        add_visits(visits, acc.visits);
+    });
+    if (threadIdx.x < 8 && gridDim.x + blockIdx.x < slots) partial[8 * (uint64_t)(gridDim.x + blockIdx.x) + threadIdx.x] = 0;
 }
 
 template <class ACC, unsigned BLOCK>
@@ -176,7 +245,7 @@ k_small(SmallCount C, int64_t *__restrict__ partial) {
         return;
     }
     with_pairwise<ACC, BLOCK>(partial, nullptr, [&](auto &acc) {
-        if (b < C.mg) medium_block<BLOCK>(b, C.mg, C.mr, C.medium, C.mitems, C.mlev, C.eoff, C.key, C.q, acc);
+        if (b < C.mg) medium_shared<BLOCK>(b, C.mg, C.mr, C.medium, C.mitems, C.mlev, C.eoff, C.key, C.q, acc);
         else light_block<BLOCK>(b - C.mg, C.lg, C.lr, C.light, C.eoff, C.key, C.q, acc);
     });
 }
@@ -651,7 +720,16 @@ int launch_paths(dt_graph *g, const DQuery &q, const CountPlan &p, const Scratch
     }
     if (mg) {
         prof_begin(ctx, kProfMedium, sm);
-        k_medium<ACC, 256><<<mg, 256, 0, sm>>>(p.mr, p.medium, p.mitems, p.mlev, eoff, key, q, mp, cells_dev, visits);
+        // shared where a triangle's close pairs are a fair part of all its pairs: deltas from 1/128 of the
+        // span on (61M edges: 1/240 of it 545 us with either, 1/2800 418 shared and 410 not, none 1700 and
+        // 2400); not for 128-bit sums, whose LDS would leave one block a compute unit
+        bool shared = false;
+        if constexpr (std::is_same<ACC, Acc<false>>::value) shared = q.d13 >= g->span / 128;
+        if (shared)
+            k_medium_shared<512><<<std::min(mg, grid_for(p.mr.pre[p.mr.n], 512)), 512, 0, sm>>>(
+                p.mr, p.medium, p.mitems, p.mlev, eoff, key, q, mp, mg, visits);
+        else
+            k_medium<ACC, 256><<<mg, 256, 0, sm>>>(p.mr, p.medium, p.mitems, p.mlev, eoff, key, q, mp, cells_dev, visits);
         prof_end(ctx, kProfMedium, sm);
         DT_HIP(hipGetLastError());
     }

@@ -384,13 +384,19 @@ __device__ __forceinline__ void lower2(const uint64_t *__restrict__ key, uint32_
 // Each pair goes to eval(d_uv, d_uw, its {v,w} lists' bounds z0, z1, z2 (unclipped), uv key, uw key);
 // q gives the window and the d13 of the closeness test.
 // With lev (the windowed copies), an entry whose triangle's level is below q.qlev is skipped: that
-// triangle is counted by the prefix procedures for this query.  Returns the pairs this wavefront
-// evaluated (its share of the visits).
-template <class EVAL>
-__device__ __forceinline__ uint32_t medium_lanes_eval(const uint32_t *__restrict__ med, const uint32_t *__restrict__ ent,
-                                                      uint64_t e, bool active, const uint32_t *__restrict__ eoff,
-                                                      const uint64_t *__restrict__ key, const DQuery &q, EVAL &&eval,
-                                                      unsigned lane, const uint8_t *__restrict__ lev = nullptr) {
+// triangle is counted by the prefix procedures for this query.  medium_lanes_eval returns the pairs this
+// wavefront evaluated (its share of the visits).
+// The two halves: medium_find gives a wavefront's entries with their close pairs, medium_spread evaluates
+// the pairs first + lane, first + stride + lane, ... of them.
+struct MediumLanes {
+    uint32_t excl, c0, lo0, lo1, flags, kx_lo, kx_hi, z0, z1, z2;   // of this lane's entry
+    uint32_t total;                                                 // pairs of the wavefront's entries
+};
+
+__device__ __forceinline__ MediumLanes medium_find(const uint32_t *__restrict__ med, const uint32_t *__restrict__ ent,
+                                                   uint64_t e, bool active, const uint32_t *__restrict__ eoff,
+                                                   const uint64_t *__restrict__ key, const DQuery &q, unsigned lane,
+                                                   const uint8_t *__restrict__ lev) {
     uint64_t kx = 0;
     uint32_t lo0 = 0, c0 = 0, lo1 = 0, c1 = 0, z0 = 0, z1 = 0, z2 = 0, flags = 0;
     if (active && lev && lev[ent[2 * e]] < q.qlev) active = false;
@@ -438,22 +444,26 @@ __device__ __forceinline__ uint32_t medium_lanes_eval(const uint32_t *__restrict
         const uint32_t y = __shfl_up(incl, o, 64);
         if (lane >= (unsigned)o) incl += y;
     }
-    const uint32_t excl = incl - c;
-    const uint32_t total = __shfl(incl, 63, 64);
-    if (total == 0) return 0;
-    const uint32_t kx_lo = (uint32_t)kx, kx_hi = (uint32_t)(kx >> 32);
-    for (uint32_t base = 0; base < total; base += 64) {
-        const uint32_t jp = base + lane;
+    return {incl - c, c0, lo0, lo1, flags, (uint32_t)kx, (uint32_t)(kx >> 32), z0, z1, z2,
+            (uint32_t)__shfl(incl, 63, 64)};
+}
+
+template <class EVAL>
+__device__ __forceinline__ void medium_spread(const MediumLanes &M, uint32_t first, uint32_t stride,
+                                              const uint64_t *__restrict__ key, EVAL &&eval, unsigned lane) {
+    const uint32_t total = M.total;
+    for (uint64_t base = first; base < total; base += stride) {
+        const uint32_t jp = (uint32_t)base + lane;
         const uint32_t jj = jp < total ? jp : total - 1;
         uint32_t l = 0;   // owner lane of pair jj
 #pragma unroll
         for (uint32_t step = 32; step > 0; step >>= 1)
-            if (__shfl(excl, l + step, 64) <= jj) l += step;
-        const uint32_t r = jj - __shfl(excl, l, 64);
-        const uint32_t oc0 = __shfl(c0, l, 64), olo0 = __shfl(lo0, l, 64), olo1 = __shfl(lo1, l, 64);
-        const uint32_t ofl = __shfl(flags, l, 64);
-        const uint64_t okx = ((uint64_t)(uint32_t)__shfl(kx_hi, l, 64) << 32) | (uint32_t)__shfl(kx_lo, l, 64);
-        const uint32_t oz0 = __shfl(z0, l, 64), oz1 = __shfl(z1, l, 64), oz2 = __shfl(z2, l, 64);
+            if (__shfl(M.excl, l + step, 64) <= jj) l += step;
+        const uint32_t r = jj - __shfl(M.excl, l, 64);
+        const uint32_t oc0 = __shfl(M.c0, l, 64), olo0 = __shfl(M.lo0, l, 64), olo1 = __shfl(M.lo1, l, 64);
+        const uint32_t ofl = __shfl(M.flags, l, 64);
+        const uint64_t okx = ((uint64_t)(uint32_t)__shfl(M.kx_hi, l, 64) << 32) | (uint32_t)__shfl(M.kx_lo, l, 64);
+        const uint32_t oz0 = __shfl(M.z0, l, 64), oz1 = __shfl(M.z1, l, 64), oz2 = __shfl(M.z2, l, 64);
         if (jp >= total) continue;
         const bool outer_uv = ofl & 1u;
         const uint32_t x_dir = (ofl >> 1) & 1u, y_dir = r < oc0 ? 0u : 1u;
@@ -463,7 +473,16 @@ __device__ __forceinline__ uint32_t medium_lanes_eval(const uint32_t *__restrict
         const uint32_t d_uv = outer_uv ? x_dir : y_dir, d_uw = outer_uv ? y_dir : x_dir;
         eval(d_uv, d_uw, oz0, oz1, oz2, k_uv, k_uw);
     }
-    return total;
+}
+
+template <class EVAL>
+__device__ __forceinline__ uint32_t medium_lanes_eval(const uint32_t *__restrict__ med, const uint32_t *__restrict__ ent,
+                                                      uint64_t e, bool active, const uint32_t *__restrict__ eoff,
+                                                      const uint64_t *__restrict__ key, const DQuery &q, EVAL &&eval,
+                                                      unsigned lane, const uint8_t *__restrict__ lev = nullptr) {
+    const MediumLanes M = medium_find(med, ent, e, active, eoff, key, q, lane, lev);
+    medium_spread(M, 0, 64, key, eval, lane);
+    return M.total;
 }
 
 // the medium path for one query into accumulator acc; returns the pairs the wavefront evaluated
