@@ -13,6 +13,7 @@
 // one contiguous stretch of the store, which is exactly what the counting of all triangles with
 // source u walks (Section 5: only {u,v} and {u,w} are enumerated).
 #include <algorithm>
+#include <cstring>
 
 #include "internal.h"
 
@@ -89,8 +90,11 @@ __device__ __forceinline__ void dag_edge(uint64_t d, uint4 r, uint32_t *__restri
 // Sort every run by head rank (heads are distinct).  Wavefronts take chunks of kTailChunk tails in
 // strides; runs that fit together in 64 lanes are loaded in one piece and sorted at once: each entry
 // placed at the number of (run, head) keys below its own, or, past 2^26 vertices, by a bitonic
-// network on (run, head).  Longer runs are left to k_dag_sort_long.
-constexpr uint32_t kTailChunk = 64;
+// network on (run, head).  Longer runs are left to k_dag_sort_long.  A chunk is short because the last
+// tails, whose runs nearly fill a piece each, are a chain of a microsecond a piece for their wavefront
+// (64 tails a chunk: 69 us of the 1.3M-edge graph's build and 161 of the 10M-edge one's; 18 and 54 so; at
+// 61M edges, where every wavefront has hundreds of chunks, 0.62 ms with either).
+constexpr uint32_t kTailChunk = 8;
 
 __global__ void __launch_bounds__(kBlock)
 k_dag_sort(uint32_t n, const uint32_t *__restrict__ dag_row, const uint4 *__restrict__ runs,
@@ -160,18 +164,31 @@ k_dag_sort(uint32_t n, const uint32_t *__restrict__ dag_row, const uint4 *__rest
     }
 }
 
-// the tails whose runs are longer than 64 (one atomic per wavefront)
-__global__ void k_long_runs(uint32_t n, const uint32_t *__restrict__ dag_row, unsigned *__restrict__ n_long,
-                            uint32_t *__restrict__ longs) {
-    const uint32_t t = blockIdx.x * kBlock + threadIdx.x;
+// The tails whose runs are longer than 64 (one atomic per wavefront), and the longest run (few blocks, as
+// each brings its own to one address).
+__global__ void __launch_bounds__(kBlock)
+k_long_runs(uint32_t n, const uint32_t *__restrict__ dag_row, unsigned *__restrict__ n_long,
+            uint32_t *__restrict__ longs, unsigned *__restrict__ longest) {
+    __shared__ unsigned s_max;
+    if (threadIdx.x == 0) s_max = 0;
+    __syncthreads();
     const unsigned lane = threadIdx.x & 63;
-    const bool is_long = t < n && dag_row[t + 1] - dag_row[t] > 64;
-    const uint64_t m = __ballot(is_long);
-    if (!m) return;
-    unsigned base = 0;
-    if (lane == 0) base = atomicAdd(n_long, (unsigned)__popcll(m));
-    base = __shfl(base, 0, 64);
-    if (is_long) longs[base + (unsigned)__popcll(m & ((1ull << lane) - 1))] = t;
+    unsigned mx = 0;
+    for (uint64_t t0 = (uint64_t)blockIdx.x * kBlock; t0 < n; t0 += (uint64_t)gridDim.x * kBlock) {
+        const uint64_t t = t0 + threadIdx.x;
+        const unsigned len = t < n ? dag_row[t + 1] - dag_row[t] : 0u;
+        mx = len > mx ? len : mx;
+        const bool is_long = len > 64;
+        const uint64_t m = __ballot(is_long);
+        if (!m) continue;
+        unsigned base = 0;
+        if (lane == 0) base = atomicAdd(n_long, (unsigned)__popcll(m));
+        base = __shfl(base, 0, 64);
+        if (is_long) longs[base + (unsigned)__popcll(m & ((1ull << lane) - 1))] = (uint32_t)t;
+    }
+    if (mx) atomicMax(&s_max, mx);
+    __syncthreads();
+    if (threadIdx.x == 0 && s_max) atomicMax(longest, s_max);
 }
 
 // Runs longer than 64: one workgroup per run.  Heads within a run are distinct, so an entry's place
@@ -239,23 +256,6 @@ k_dag_sort_long(const unsigned *__restrict__ n_long_p, const uint32_t *__restric
     }
 }
 
-// largest out-degree: max of row[i + 1] - row[i] over i < n
-__global__ void k_max_u32(uint64_t n, const uint32_t *__restrict__ row, unsigned *__restrict__ out) {
-    __shared__ unsigned s[kBlock];
-    unsigned mx = 0;
-    for (uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (uint64_t)gridDim.x * kBlock) {
-        const unsigned dg = row[i + 1] - row[i];
-        mx = dg > mx ? dg : mx;
-    }
-    s[threadIdx.x] = mx;
-    __syncthreads();
-    for (unsigned w = kBlock / 2; w > 0; w >>= 1) {
-        if (threadIdx.x < w) s[threadIdx.x] = max(s[threadIdx.x], s[threadIdx.x + w]);
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) atomicMax(out, s[0]);
-}
-
 // Move every temporal edge (pair-major, key order within the pair) to its place in the DAG-edge
 // layout: group 2d + direction, at its rank among the pair's edges of that direction.  Ranks come
 // from the running count c1 of head->tail flags, so each group stays in key order.
@@ -291,10 +291,13 @@ int orient(dt_graph *g, bool overlap) {
     hipStream_t st = ctx->stream;
     const uint64_t ms = g->m_s, m = g->m;
     const uint32_t n = g->n;
-    DevMem outdeg, cursor, th, runs, longs, dag_of, sflip, gsize, scal;
+    DevMem zero, th, runs, longs, dag_of, sflip, gsize;
     const uint64_t ngroups = 2 * ms;
-    DT_TRY(dev_alloc(ctx, outdeg, ((uint64_t)n + 1) * 4));
-    DT_TRY(dev_alloc(ctx, cursor, ((uint64_t)n + 1) * 4));
+    // cleared together: the longest run and (16 words on) the number of long ones, then each tail's runs
+    // and those placed
+    DT_TRY(dev_alloc(ctx, zero, 256 + 2 * ((uint64_t)n + 1) * 4));
+    unsigned *scal = zero.as<unsigned>();
+    uint32_t *outdeg = scal + 64, *cursor = outdeg + (n + 1);
     DT_TRY(dev_alloc(ctx, th, ms * 8));
     DT_TRY(dev_alloc(ctx, runs, ms * 16));
     DT_TRY(dev_alloc(ctx, longs, ((uint64_t)n + 1) * 4));
@@ -305,33 +308,30 @@ int orient(dt_graph *g, bool overlap) {
     DT_TRY(dev_alloc(ctx, g->dag_row, ((uint64_t)n + 1) * 4));
     DT_TRY(dev_alloc(ctx, g->eoff, (ngroups + 1) * 4));
     DT_TRY(dev_alloc(ctx, g->key, m * 8));
-    DT_TRY(dev_alloc(ctx, scal, 256));
-    DT_HIP(hipMemsetAsync(outdeg.ptr, 0, ((uint64_t)n + 1) * 4, st));
-    DT_HIP(hipMemsetAsync(cursor.ptr, 0, ((uint64_t)n + 1) * 4, st));
-    DT_HIP(hipMemsetAsync(gsize.ptr, 0, (ngroups + 1) * 4, st));
-    DT_HIP(hipMemsetAsync(scal.ptr, 0, 256, st));
+    // (every group's size is written, and the scan leaves out the entry past them)
+    DT_HIP(hipMemsetAsync(zero.ptr, 0, 256 + 2 * ((uint64_t)n + 1) * 4, st));
     if (ms) {
         k_dag_count<<<grid_for(ms, kBlock), kBlock, 0, st>>>(ms, g->sx.as<uint32_t>(), g->sy.as<uint32_t>(),
-            g->rank.as<uint32_t>(), outdeg.as<uint32_t>(), th.as<uint2>(), sflip.as<uint8_t>());
+            g->rank.as<uint32_t>(), outdeg, th.as<uint2>(), sflip.as<uint8_t>());
         DT_HIP(hipGetLastError());
     }
-    DT_TRY(exclusive_scan_u32(ctx, outdeg.as<uint32_t>(), g->dag_row.as<uint32_t>(), (uint64_t)n + 1, st));
+    DT_TRY(exclusive_scan_u32(ctx, outdeg, g->dag_row.as<uint32_t>(), (uint64_t)n + 1, st));
     if (ms) {
         k_dag_place<<<grid_for(ms, kBlock), kBlock, 0, st>>>(ms, th.as<uint2>(), sflip.as<uint8_t>(),
-            g->pstart.as<uint32_t>(), g->c1.as<uint32_t>(), g->dag_row.as<uint32_t>(), cursor.as<uint32_t>(),
+            g->pstart.as<uint32_t>(), g->c1.as<uint32_t>(), g->dag_row.as<uint32_t>(), cursor,
             runs.as<uint4>());
         DT_HIP(hipGetLastError());
         // runs of at most 64 on this stream, the longer ones beside them on side[1] (the two write
         // disjoint DAG edges; every buffer they use lives until this function returns, after the join)
-        k_long_runs<<<grid_for(n, kBlock), kBlock, 0, st>>>(n, g->dag_row.as<uint32_t>(), scal.as<unsigned>() + 16,
-                                                            longs.as<uint32_t>());
+        k_long_runs<<<std::min(grid_for(n, kBlock), 512u), kBlock, 0, st>>>(n, g->dag_row.as<uint32_t>(),
+            scal + 16, longs.as<uint32_t>(), scal);
         DT_HIP(hipGetLastError());
         hipStream_t ls = ctx->side[1] ? ctx->side[1] : st;
         if (ls != st) {
             DT_HIP(hipEventRecord(ctx->ev_relay[0], st));
             DT_HIP(hipStreamWaitEvent(ls, ctx->ev_relay[0], 0));
         }
-        k_dag_sort_long<<<(unsigned)ctx->num_cus * 4, kBlock, 0, ls>>>(scal.as<unsigned>() + 16, longs.as<uint32_t>(),
+        k_dag_sort_long<<<(unsigned)ctx->num_cus * 4, kBlock, 0, ls>>>(scal + 16, longs.as<uint32_t>(),
             g->dag_row.as<uint32_t>(), runs.as<uint4>(), g->dag_col.as<uint32_t>(), dag_of.as<uint32_t>(),
             gsize.as<uint32_t>());
         DT_HIP(hipGetLastError());
@@ -344,12 +344,6 @@ int orient(dt_graph *g, bool overlap) {
             DT_HIP(hipEventRecord(ctx->ev_relay[1], ls));
             DT_HIP(hipStreamWaitEvent(st, ctx->ev_relay[1], 0));
         }
-    }
-    if (n) {
-        unsigned grid = grid_for(n, kBlock);
-        if (grid > 2048) grid = 2048;
-        k_max_u32<<<grid, kBlock, 0, st>>>(n, g->dag_row.as<uint32_t>(), scal.as<unsigned>());
-        DT_HIP(hipGetLastError());
     }
     // with overlap the store offsets' scan and the re-layout go to side[0] and keep their inputs
     // and temporaries alive until relayout_join; nothing on the context's stream reads g->eoff or
@@ -386,10 +380,9 @@ int orient(dt_graph *g, bool overlap) {
             g->relay_pending = true;
         }
     }
-    unsigned mo = 0;
-    DT_HIP(hipMemcpyAsync(&mo, scal.ptr, 4, hipMemcpyDeviceToHost, st));
+    DT_HIP(hipMemcpyAsync(ctx->pinned_stage, scal, 4, hipMemcpyDeviceToHost, st));
     DT_HIP(hipStreamSynchronize(st));
-    g->max_outdeg = mo;
+    memcpy(&g->max_outdeg, ctx->pinned_stage, 4);
     return DT_OK;
 }
 
