@@ -18,10 +18,9 @@
 // barriers only), so a grid round usually ends a level; only vertices queued past a full staging
 // list wait for another round.  The first levels remove most of the graph and are bound by work,
 // the later ones by latency, and a barrier's cost grows with the number of blocks that meet at it:
-// the grid starts with one block of 1024 threads per CU and narrows to 128, 64, then 32 blocks
-// as vertices run out, and hands its last 65,536 vertices to a finish that takes no levels (below).  The
-// barrier is a monotonic arrival counter that every block polls.  Counters
-// that decide the next step (queue positions taken in a phase, survivors of a level scan) rotate
+// the grid starts with one block of 1024 threads per CU and narrows to 128, then 64 blocks as vertices
+// run out and levels grow small, and hands its last 65,536 vertices to a finish that takes no levels
+// (below).  The barrier counts arrivals in groups of blocks.  Counters that decide the next step (queue positions taken in a phase, survivors of a level scan) rotate
 // over three slots, so a fast block starting the next phase never changes what a slow block reads,
 // and every block takes the same branch.  A vertex is queued at most
 // once: by the level scan when its degree is <= k (no decrement runs during a scan), or by the
@@ -202,10 +201,10 @@ __device__ __forceinline__ void remove_edges(uint32_t v, uint32_t first, uint32_
 // v's shell that fell to their core numbers in the same phase or later, like all of larger cores, were
 // among them.  Vertices ordered by (core, phase) are therefore in degeneracy order, and no vertex need be
 // removed from the others' counts.  65 phases for the 61M-edge graph's last 65,536 vertices where levels
-// took 410 and 2,000 rounds (its peel 13.9 -> 7.8 ms, 2.2 of them here; 2.8 with a second part of 50 phases
-// that removed the shells' vertices in rounds, at 1.3M edges 0.36 against 0.26 ms).  65,536 is what 16-bit
-// ids and one workgroup's LDS hold; above it the level peel is the faster one (a level of many vertices
-// there costs less than their share of 65 phases).
+// took 410 and 2,000 rounds (its peel then 13.9 ms, now 6.7, 2.2 of them here; 2.8 with a second part of
+// 50 phases that removed the shells' vertices in rounds, at 1.3M edges 0.36 against 0.26 ms).  65,536 is
+// what 16-bit ids and one workgroup's LDS hold; above it the level peel is the faster one (a level of many
+// vertices there costs less than their share of 65 phases).
 //
 // A wavefront owns consecutive local ids holding an even share of the entries.  Every phase each block
 // copies all bounds (128 KB at most) into LDS, where the gathers along the rows go; rows stream from

@@ -220,9 +220,9 @@ __global__ void k_unit_keys(uint64_t ms, const uint32_t *__restrict__ eoff, cons
 // record (with its t1 bucket as a sort key); the other triangles go to the rest list.  A workgroup
 // holds a tile of kSplitPer entries a thread, all their gathers in flight together, and takes the
 // tile's places in both outputs with one atomic each.  Bound by the list and the gathers of the third
-// edges' keys; one pass where classifying every entry and then moving it read both twice (classify,
-// partition of 67M entries: 1.0 + 1.9 ms, 1.0 so; the whole schedule 4.7 -> 3.0 ms).  Past unit_cap
-// and rest_cap triangles are counted and not written.
+// edges' keys; one pass where classifying every entry and then moving it read both twice (67M entries:
+// classify 1.0 and partition 1.9 ms, this pass 1.0; the whole schedule 4.7 -> 2.9 ms).  Past unit_cap and
+// rest_cap triangles are counted and not written.
 constexpr unsigned kSplitPer = 8;
 constexpr unsigned kSplitTile = kBlock * kSplitPer;
 __global__ void __launch_bounds__(kBlock)
