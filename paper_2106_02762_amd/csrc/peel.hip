@@ -27,12 +27,14 @@
 // single decrement that takes its degree from k + 1 to k (degrees only fall, and a queued vertex
 // already has degree <= k, so no later decrement can see k + 1 again); a vertex queued by a
 // decrement also gets a large negative degree, so that the next scans, which still list it, skip
-// it.  The queue index is also bounds-checked, and the host checks that exactly n vertices were
-// queued.  A barrier that waits far longer than any peel could take sets an error flag and lets its
-// block go, so that a fault in this logic ends the kernel instead of hanging it.
+// it.  The queue index is also bounds-checked, the host checks that exactly n vertices were queued, and
+// the pass that takes the ranks from the queue that every place of it was taken.  A barrier that waits
+// far longer than any peel could take sets an error flag and lets its block go, so that a fault in this
+// logic ends the kernel instead of hanging it.
 #include <algorithm>
 #include <type_traits>
 
+#include "finish_room.h"
 #include "internal.h"
 
 namespace dt {
@@ -51,7 +53,6 @@ struct Width {
 };
 constexpr Width kWidths[3] = {{400000, kGridWide}, {50000, 128}, {0, 64}};
 constexpr uint32_t kBusy = 32768;
-constexpr uint32_t kTail = 65536;   // most vertices the finish takes (16-bit local ids and bounds)
 // LDS words of a peel block: two staging halves, the vertices the block is removing and those their
 // removal queues
 constexpr uint32_t kLdsWords = 40800;
@@ -219,7 +220,6 @@ constexpr uint32_t kRegPieces = 8;   // pieces of a row held in registers
 constexpr uint32_t kRegRow = kPiece * kRegPieces;
 constexpr uint32_t kFinSmall = 1024; // up to this many vertices one block finishes alone
 constexpr uint32_t kSlots = 2048;    // places a block takes together
-constexpr uint32_t kCellMost = 1u << 18;   // (core, phase) places counted in memory
 
 struct FinArgs {
     const uint32_t *rlist, *lrow;
@@ -479,7 +479,7 @@ k_peel_finish(FinArgs A) {
     };
     const GroupRows G0 = group_rows(va < vb ? va : (vb < R ? vb : R));
     // bounds: the degrees; no position taken
-    const uint32_t cell_cap = R < kCellMost / 32 ? 32 * R + 1024 : kCellMost;
+    const uint32_t cell_cap = FinishRoom::cells(R);
     for (uint32_t v = gtid; v < R; v += gsize) {
         A.val[v] = (uint16_t)(A.lrow[v + 1] - A.lrow[v]);
         A.when[v] = 0;
@@ -654,6 +654,7 @@ k_peel(uint32_t n, const uint32_t *__restrict__ row, const uint32_t *__restrict_
         level[v] = kUnset;
         alive_a[v] = v;
         loc[v] = kUnset;
+        queue[v] = kUnset;   // (a place that nothing takes is found with the ranks)
     }
     if (gtid == 0)
         for (int x = 0; x < 3; ++x) ctl->scan[x][1] = 0xffffffffu;
@@ -997,9 +998,14 @@ k_local_adj(const uint32_t *__restrict__ row, const uint32_t *__restrict__ col, 
     }
 }
 
-__global__ void k_finish(uint32_t n, const uint32_t *__restrict__ queue, uint32_t *__restrict__ rank) {
-    uint32_t p = blockIdx.x * 256 + threadIdx.x;
-    if (p < n) rank[queue[p]] = p;
+// the ranks; an id that is no vertex (a place of the queue that nothing took) is an error
+__global__ void k_finish(uint32_t n, const uint32_t *__restrict__ queue, uint32_t *__restrict__ rank,
+                         PeelCtl *__restrict__ ctl) {
+    const uint32_t p = blockIdx.x * 256 + threadIdx.x;
+    if (p >= n) return;
+    const uint32_t v = queue[p];
+    if (v < n) rank[v] = p;
+    else atomicOr(&ctl->error, 32u);
 }
 
 }  // namespace
@@ -1031,9 +1037,7 @@ int peel(dt_graph *g) {
     DT_TRY(dev_alloc(ctx, loc, (uint64_t)n * 4));
     DT_TRY(dev_alloc(ctx, rlist, (uint64_t)tail_cap * 4));
     DT_TRY(dev_alloc(ctx, lrow, ((uint64_t)tail_cap + 1) * 4));
-    // its bounds (two buffers), cell starts and cursors, phases and positions
-    constexpr uint64_t kFinWords = kTail + 2ull * kCellMost + 2ull * kTail;
-    DT_TRY(dev_alloc(ctx, fin, kFinWords * 4));
+    DT_TRY(dev_alloc(ctx, fin, FinishRoom::kWords * 4));
     DT_TRY(dev_alloc(ctx, lcol, (lcol_cap + kPiece) * 2));   // (the finish reads whole pieces)
     if (n == 0) {
         g->kappa = 0;
@@ -1075,11 +1079,11 @@ int peel(dt_graph *g) {
     fa.rlist = rl;
     fa.lrow = lb;
     fa.lcol = lc;
-    fa.base = fin.as<uint32_t>();
-    fa.cur = fa.base + kCellMost;
-    fa.when = fa.cur + kCellMost;
-    fa.pos = fa.when + kTail;
-    fa.val = reinterpret_cast<uint16_t *>(fa.pos + kTail);
+    fa.base = fin.as<uint32_t>() + FinishRoom::kBase;
+    fa.cur = fin.as<uint32_t>() + FinishRoom::kCur;
+    fa.when = fin.as<uint32_t>() + FinishRoom::kWhen;
+    fa.pos = fin.as<uint32_t>() + FinishRoom::kPos;
+    fa.val = reinterpret_cast<uint16_t *>(fin.as<uint32_t>() + FinishRoom::kVal);
     fa.level = level;
     fa.queue = queue;
     fa.bar = lbar + kBarWords;
@@ -1091,6 +1095,9 @@ int peel(dt_graph *g) {
     DT_HIP(hipLaunchCooperativeKernel((const void *)k_peel_finish, dim3(fgrid), dim3(kBlock), fargs, 0, st));
     prof_end(ctx, kProfPeelTail, st);
     DT_HIP(hipGetLastError());
+    // the ranks (what the orientation reads next), whose check of the queue the read-back takes along
+    k_finish<<<grid_for(n, 256), 256, 0, st>>>(n, queue, g->rank.as<uint32_t>(), ctl);
+    DT_HIP(hipGetLastError());
     PeelCtl &h = *reinterpret_cast<PeelCtl *>(ctx->pinned_stage);
     DT_HIP(hipMemcpyAsync(&h, ctl, sizeof(h), hipMemcpyDeviceToHost, st));
     DT_HIP(hipStreamSynchronize(st));
@@ -1100,10 +1107,6 @@ int peel(dt_graph *g) {
     g->kappa = h.kappa;
     g->peel_rounds = h.rounds;
     g->alg_bytes_peel = 16ull * n + 16ull * g->m_s;
-    // the ranks (what the orientation reads next, on the same stream); the temporaries released on
-    // return were last used by kernels the read-back above waited for
-    k_finish<<<grid_for(n, 256), 256, 0, st>>>(n, queue, g->rank.as<uint32_t>());
-    DT_HIP(hipGetLastError());
     return DT_OK;
 }
 
