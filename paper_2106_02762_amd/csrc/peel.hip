@@ -20,8 +20,9 @@
 // the later ones by latency, and a barrier's cost grows with the number of blocks that meet at it:
 // the grid starts with one block of 1024 threads per CU and narrows to 128, then 64 blocks as vertices
 // run out and levels grow small, and hands its last 65,536 vertices to a finish that takes no levels
-// (below).  The barrier counts arrivals in groups of blocks.  Counters that decide the next step (queue positions taken in a phase, survivors of a level scan) rotate
-// over three slots, so a fast block starting the next phase never changes what a slow block reads,
+// (below), or back to the levels where that is the slower way.  The barrier counts arrivals in groups of
+// blocks.  Counters that decide the next step (queue positions taken in a phase, survivors of a level scan)
+// rotate over three slots, so a fast block starting the next phase never changes what a slow block reads,
 // and every block takes the same branch.  A vertex is queued at most
 // once: by the level scan when its degree is <= k (no decrement runs during a scan), or by the
 // single decrement that takes its degree from k + 1 to k (degrees only fall, and a queued vertex
@@ -70,7 +71,8 @@ struct PeelCtl {
     unsigned int error;      // a barrier gave up waiting, or a consistency check failed
     unsigned int rounds;     // removal rounds
     unsigned int kappa;      // largest level that removed a vertex
-    unsigned int fin[3];     // finish, per phase mod 3: a bound fell / a vertex was left over
+    unsigned int fin[3];     // finish, per phase mod 3: bounds that fell (or kManyFell and more)
+    unsigned int left;       // the finish left its vertices to the level peel
     unsigned long long lres; // hand-over: local ids (low word) and adjacency entries (high word) given out
     unsigned int ho;         // 1: the grid handed its last vertices over (the state below is set)
     unsigned int ho_tail, ho_k, ho_rounds;   // queue positions taken, level and rounds at the hand-over
@@ -203,7 +205,8 @@ __device__ __forceinline__ void remove_edges(uint32_t v, uint32_t first, uint32_
 // among them.  Vertices ordered by (core, phase) are therefore in degeneracy order, and no vertex need be
 // removed from the others' counts.  65 phases for the 61M-edge graph's last 65,536 vertices where levels
 // took 410 and 2,000 rounds (its peel then 13.9 ms, now 6.7, 2.2 of them here; 2.8 with a second part of
-// 50 phases that removed the shells' vertices in rounds, at 1.3M edges 0.36 against 0.26 ms).  65,536 is
+// 50 phases that removed the shells' vertices in rounds, at 1.3M edges 0.36 against 0.26 ms).  A finish whose
+// falls do not die down leaves its vertices to the levels (kSlowPhase below).  65,536 is
 // what 16-bit ids and one workgroup's LDS hold; above it the level peel is the faster one (a level of many
 // vertices there costs less than their share of 65 phases).
 //
@@ -219,6 +222,16 @@ constexpr uint32_t kPiece = 128;     // entries of a row a wavefront reads at on
 constexpr uint32_t kRegPieces = 8;   // pieces of a row held in registers
 constexpr uint32_t kRegRow = kPiece * kRegPieces;
 constexpr uint32_t kFinSmall = 1024; // up to this many vertices one block finishes alone
+// When the finish leaves its vertices to the levels: after phase kSlowPhase if more than a quarter as many
+// bounds still fall as in the first, after kFewPhases phases in a row of at most kFewFell falls, and after
+// kPhaseMost phases.  Where degrees are spread, falls are a fifteenth of the first ones by then (61M edges;
+// random graphs, preferential attachment, small worlds, points in a plane: 1/9 to 1/1700), few for at most
+// 18 phases before the end, and the phases at most 65; on a chain or a lattice they go on as they began (a
+// path of 60,000 vertices: 2 a phase for 30,000 phases, 373 ms by them all, 42 ms left to the levels; a
+// 1,000-vertex path beside a 40,000-vertex power law: 15.4 and 4.3 ms; a lattice of 250 x 250: 4.2 and
+// 1.9), so that the phases tried cost little beside the levels.
+constexpr uint32_t kSlowPhase = 8, kFewFell = 64, kFewPhases = 24, kPhaseMost = 128;
+constexpr uint32_t kManyFell = 1u << 24;
 constexpr uint32_t kSlots = 2048;    // places a block takes together
 
 struct FinArgs {
@@ -240,7 +253,10 @@ __device__ void fin_barrier(const FinArgs &A, unsigned nblk, BarTurn &turn, cons
                             unsigned *s_flag = nullptr) {
     group_barrier(A.bar, &A.ctl->error, nblk, turn);
     if (flag) {
-        if (threadIdx.x == 0) *s_flag = (ld_relaxed(flag) ? 1u : 0u) | (ld_relaxed(&A.ctl->error) ? 2u : 0u);
+        if (threadIdx.x == 0) {
+            s_flag[0] = ld_relaxed(flag);
+            s_flag[1] = ld_relaxed(&A.ctl->error);
+        }
         __syncthreads();
     }
 }
@@ -455,7 +471,7 @@ __global__ void __launch_bounds__(kBlock)
 k_peel_finish(FinArgs A) {
     __shared__ __attribute__((aligned(16))) uint16_t s_v[kTail];
     __shared__ uint32_t s_key[kSlots], s_cnt[kSlots];
-    __shared__ unsigned s_any, s_more, s_scan[kBlock / 64];
+    __shared__ unsigned s_any, s_more[2], s_scan[kBlock / 64];
     PeelCtl *ctl = A.ctl;
     if (!ctl->ho || ctl->error) return;
     constexpr uint32_t kBW = kBlock / 64;
@@ -492,26 +508,28 @@ k_peel_finish(FinArgs A) {
         for (uint32_t i = tid; i < (R + 7) / 8; i += kBlock) dst[i] = src[i];
         if (tid == 0) s_any = 0;
     };
-    // every block learns whether any had something left to do (phase ph): bit 0; bit 1: an error
-    auto any_left = [&](bool mine, uint32_t ph) {
-        if (__ballot(mine) && lane == 0) s_any = 1;
+    // every block learns how many bounds fell in phase ph (kManyFell and more: many); s_more[1]: an error
+    auto any_left = [&](uint32_t fell, uint32_t ph) {
+        if (fell && lane == 0) atomicAdd(&s_any, fell);
         __syncthreads();
-        if (tid == 0 && s_any)
-            __hip_atomic_store(&ctl->fin[ph % 3], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        fin_barrier(A, nblk, turn, &ctl->fin[ph % 3], &s_more);
-        const unsigned more = s_more;
+        if (tid == 0 && s_any) {
+            if (s_any <= kFewFell / 4 || ph == 0 || ph == kSlowPhase) atomicAdd(&ctl->fin[ph % 3], s_any);
+            else __hip_atomic_store(&ctl->fin[ph % 3], kManyFell, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        fin_barrier(A, nblk, turn, &ctl->fin[ph % 3], s_more);
+        const unsigned more = s_more[0];
         // read by every block before the next barrier: cleared for the phase after next
         if (gtid == 0)
             __hip_atomic_store(&ctl->fin[(ph + 2) % 3], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return more;
     };
     // core numbers
-    uint32_t ph = 0;
+    uint32_t ph = 0, first_fell = 0, few = 0;
     for (;; ++ph) {
         load_values(A.val + (ph & 1 ? kTail : 0));
         __syncthreads();
         uint16_t *out = A.val + (ph & 1 ? 0 : kTail);
-        bool fell = false;
+        uint32_t fell = 0;   // of this wavefront
         for (uint32_t v0 = va; v0 < vb; v0 += kGroup) {
             const GroupRows G = v0 == va ? G0 : group_rows(v0);
             const uint32_t v = v0 + lane;
@@ -519,17 +537,17 @@ k_peel_finish(FinArgs A) {
             const uint32_t nh = group_bounds(G, A.lcol, s_v, h, k0, lane);
             if (lane < G.nv) {
                 out[v] = (uint16_t)nh;
-                if (nh != h) {
-                    A.when[v] = ph + 1;
-                    fell = true;
-                }
+                if (nh != h) A.when[v] = ph + 1;
             }
+            fell += (uint32_t)__popcll(__ballot(lane < G.nv && nh != h));
         }
-        const unsigned more = any_left(fell, ph);
-        if (more & 2u) return;
+        const uint32_t more = any_left(fell, ph);
+        if (s_more[1]) return;
         if (!more) break;
-        if (ph > 2 * R + 64) {   // cannot happen: a phase settles at least one vertex
-            if (gtid == 0) atomicOr(&ctl->error, 16u);
+        if (ph == 0) first_fell = more;
+        few = more <= kFewFell ? few + 1 : 0;
+        if ((ph == kSlowPhase && 4 * more > first_fell) || few >= kFewPhases || ph + 1 >= kPhaseMost) {
+            if (gtid == 0) ctl->left = 1;   // (every block sees the same counts, and leaves)
             return;
         }
     }
@@ -577,8 +595,8 @@ k_peel_finish(FinArgs A) {
             if (in) A.pos[v] = held ? s_cnt[slot] + at : at;
             __syncthreads();
         }
-        fin_barrier(A, nblk, turn, &ctl->fin[0], &s_more);
-        if (s_more & 2u) return;
+        fin_barrier(A, nblk, turn, &ctl->fin[0], s_more);
+        if (s_more[1]) return;
     }
     // first position of every cell: every block writes the same ones, and reads its own back
     uint32_t run = 0;
@@ -629,8 +647,201 @@ k_peel_finish(FinArgs A) {
     }
 }
 
+// ------------------------------------------------------------------------------------------------
+// The levels of the vertices that the finish leaves: where a fall travels one vertex a phase (long chains,
+// lattices), a phase a hop, each with a grid barrier and every row, costs far more than a removal round of
+// a workgroup.  One workgroup takes the last vertices, level by level, on the subgraph they induce, with
+// local (16-bit) vertex ids.  The local CSR rows, the degrees, the removal queue and the list of vertices
+// not yet queued live in LDS, so a round touches global memory only to read adjacency (lcol);
+// workgroup barriers separate rounds.  rlist maps local ids to vertices.  A degree counts the
+// neighbours not yet removed (so it never falls below zero, and two 16-bit degrees share a word
+// safely) until the vertex is queued; queuing adds kMark - degree, which puts it at kMark, and
+// the at most kLevelTail later decrements leave it at least kMark - kLevelTail, above every level.  Each
+// wavefront keeps its own segment of the live list and compacts it in place at every level scan,
+// so a scan reads only the vertices still live, and takes one atomic per wavefront for the
+// survivors' count and smallest degree.  The queue positions (continuing from qbase) and the core
+// numbers are written at the end, from the queue and the level boundaries recorded in lvl (pairs:
+// first queue position, level).  A path of 16,000 vertices: 46.7 ms by phases, 6.1 so.
+// ------------------------------------------------------------------------------------------------
+constexpr uint32_t kLevelTail = kPeelTailMax;   // most vertices of it: what one workgroup's LDS holds
+constexpr uint32_t kRowWords = kLevelTail + 1, kDegWords = kLevelTail / 2, kQWords = kLevelTail / 2,
+                   kLiveWords = kLevelTail / 2;
+constexpr uint32_t kMark = 0xC000u, kMarked = 0x8000u;
+static_assert(kMark - kLevelTail > kMarked && kMarked > kLevelTail, "queued degrees stay above every level");
 __global__ void __launch_bounds__(kBlock)
-k_peel(uint32_t n, const uint32_t *__restrict__ row, const uint32_t *__restrict__ col,
+k_peel_levels(const uint32_t *__restrict__ rlist, const uint32_t *__restrict__ lrow, const uint16_t *__restrict__ lcol,
+              uint32_t *__restrict__ lvl, uint32_t *__restrict__ level, uint32_t *__restrict__ queue,
+              PeelCtl *__restrict__ ctl) {
+    __shared__ __attribute__((aligned(16))) uint32_t s_mem[kRowWords + kDegWords + kQWords + kLiveWords];
+    if (!ctl->ho || ctl->error) return;
+    const uint32_t R = (uint32_t)ctl->lres, qbase = ctl->ho_tail;
+    uint32_t k = ctl->ho_k, rounds = ctl->ho_rounds;
+    uint32_t *s_row = s_mem;                                              // kRowWords
+    uint32_t *s_deg = s_mem + kRowWords;                                  // kDegWords
+    uint16_t *s_q = reinterpret_cast<uint16_t *>(s_mem + kRowWords + kDegWords);               // kLevelTail
+    uint16_t *s_live = reinterpret_cast<uint16_t *>(s_mem + kRowWords + kDegWords + kQWords);  // kLevelTail
+    __shared__ unsigned s_qt, s_keep, s_min, s_nlvl;
+    const unsigned tid = threadIdx.x, lane = tid & 63, wave = tid / 64;
+    constexpr unsigned kWaves = kBlock / 64;
+    const uint64_t below = (1ull << lane) - 1;
+    for (uint32_t l = tid; l <= R; l += kBlock) s_row[l] = lrow[l];
+    for (uint32_t w = tid; w < kDegWords; w += kBlock) s_deg[w] = 0;
+    for (uint32_t l = tid; l < R; l += kBlock) s_live[l] = (uint16_t)l;
+    __syncthreads();
+    for (uint32_t l = tid; l < R; l += kBlock)
+        atomicAdd(&s_deg[l >> 1], (s_row[l + 1] - s_row[l]) << ((l & 1) * 16));
+    if (tid == 0) {
+        s_qt = 0;
+        s_nlvl = 0;
+    }
+    // this wavefront's segment of the live list: [lb, lb + lc)
+    const uint32_t seg = (R + kWaves - 1) / kWaves;
+    const uint32_t lb = wave * seg < R ? wave * seg : R;
+    uint32_t lc = (lb + seg < R ? lb + seg : R) - lb;
+    uint32_t h = 0, t = 0;
+    auto deg_of = [&](uint32_t l) { return (s_deg[l >> 1] >> ((l & 1) * 16)) & 0xffffu; };
+    // queue y, whose degree is d (no decrement of y runs between reading d and this)
+    auto mark = [&](uint32_t y, uint32_t d) { atomicAdd(&s_deg[y >> 1], (kMark - d) << ((y & 1) * 16)); };
+    // remove one edge end at y; a degree taken from k + 1 to k queues y
+    auto dec = [&](uint32_t y, uint32_t kk) {
+        const uint32_t sh = (y & 1) * 16;
+        const uint32_t old = (atomicSub(&s_deg[y >> 1], 1u << sh) >> sh) & 0xffffu;
+        if (old == kk + 1) {
+            atomicAdd(&s_deg[y >> 1], (kMark - kk) << sh);
+            const uint32_t p = atomicAdd(&s_qt, 1u);
+            if (p < R) s_q[p] = (uint16_t)y;
+        }
+    };
+    while (true) {
+        __syncthreads();
+        if (tid == 0) {
+            s_keep = 0;
+            s_min = 0xffffffffu;
+        }
+        __syncthreads();
+        const uint32_t level_start = t;
+        // level scan over this wavefront's live vertices: queue those of degree <= k, keep the
+        // others (written back in place: a survivor's new slot is never after its old one, and
+        // the wavefront reads a chunk before it writes any of it)
+        {
+            uint32_t nk = 0;
+            unsigned md = 0xffffffffu;
+            for (uint32_t i0 = 0; i0 < lc; i0 += 64) {
+                const uint32_t i = i0 + lane;
+                uint32_t l = 0, d = kMark;
+                if (i < lc) {
+                    l = s_live[lb + i];
+                    d = deg_of(l);
+                }
+                const bool tk = d <= k, kp = d > k && d < kMarked;
+                const uint64_t mt = __ballot(tk), mk = __ballot(kp);
+                if (mt) {
+                    uint32_t qb = 0;
+                    if (lane == 0) qb = atomicAdd(&s_qt, (unsigned)__popcll(mt));
+                    qb = __shfl(qb, 0, 64);
+                    if (tk) {
+                        const uint32_t p = qb + (uint32_t)__popcll(mt & below);
+                        mark(l, d);
+                        if (p < R) s_q[p] = (uint16_t)l;
+                    }
+                }
+                if (kp) {
+                    s_live[lb + nk + (uint32_t)__popcll(mk & below)] = (uint16_t)l;
+                    md = d < md ? d : md;
+                }
+                nk += (uint32_t)__popcll(mk);
+            }
+            lc = nk;
+            md = wave_min(md);
+            if (lane == 0 && nk) {
+                atomicAdd(&s_keep, nk);
+                atomicMin(&s_min, md);
+            }
+        }
+        __syncthreads();
+        t = s_qt;
+        const uint32_t keep = s_keep, md = s_min;
+        if (keep == 0) h = t;   // every remaining vertex is queued: nothing left to update
+        // rounds: remove s_q[h, t)
+        while (h < t) {
+            const uint32_t f = t - h;
+            uint32_t i0, first, stride, step;
+            if (f >= kWaves) {
+                i0 = h + wave; first = lane; stride = 64; step = kWaves;
+            } else {
+                const uint32_t per = kWaves / f;
+                i0 = h + wave / per; first = (wave % per) * 64 + lane; stride = per * 64; step = f;
+                if (wave / per >= f) i0 = t;
+            }
+            for (uint32_t i = i0; i < t; i += step) {
+                const uint32_t x = s_q[i];
+                const uint32_t e = s_row[x + 1];
+                uint32_t j = s_row[x] + first;
+                for (; j + 3 * stride < e; j += 4 * stride) {
+                    const uint32_t y0 = lcol[j], y1 = lcol[j + stride], y2 = lcol[j + 2 * stride],
+                                   y3 = lcol[j + 3 * stride];
+                    dec(y0, k);
+                    dec(y1, k);
+                    dec(y2, k);
+                    dec(y3, k);
+                }
+                for (; j < e; j += stride) dec(lcol[j], k);
+            }
+            ++rounds;
+            __syncthreads();
+            h = t;
+            t = s_qt;
+            __syncthreads();
+        }
+        if (t > level_start && tid == 0) {   // this level removed s_q[level_start, t)
+            const uint32_t li = s_nlvl++;
+            lvl[2 * li] = level_start;
+            lvl[2 * li + 1] = k;
+        }
+        if (t >= R) break;
+        uint32_t next = k + 1;
+        if (t == level_start && md != 0xffffffffu && md > next) next = md;
+        k = next;
+        if (k > R + qbase + 1) {   // cannot happen, as in the grid loop
+            if (tid == 0) atomicOr(&ctl->error, 2u);
+            break;
+        }
+    }
+    __syncthreads();
+    // queue positions and core numbers of the removed vertices, in removal order
+    const uint32_t nl = s_nlvl, nq = t < R ? t : R;
+    __threadfence_block();
+    for (uint32_t p = tid; p < nq; p += kBlock) {
+        const uint32_t v = rlist[s_q[p]];
+        queue[qbase + p] = v;
+        uint32_t lo = 0, len = nl;   // last boundary at or before p
+        while (len > 0) {
+            const uint32_t half = len >> 1;
+            if (lvl[2 * (lo + half)] <= p) {
+                lo += half + 1;
+                len -= half + 1;
+            } else {
+                len = half;
+            }
+        }
+        level[v] = lo > 0 ? lvl[2 * (lo - 1) + 1] : k;
+    }
+    if (tid == 0) {
+        __hip_atomic_store(&ctl->qtail, qbase + nq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        ctl->kappa = k;
+        ctl->rounds = rounds;
+        ctl->left = 0;
+    }
+}
+
+// Where the level peel begins: with the whole graph, or (left > 0) with the vertices rlist[0, left) that
+// the finish left to it, at level k, with `tail` positions taken.
+struct PeelStart {
+    uint32_t left, k, tail, rounds;
+};
+
+__global__ void __launch_bounds__(kBlock)
+k_peel(PeelStart from, uint32_t n, const uint32_t *__restrict__ row, const uint32_t *__restrict__ col,
        int *__restrict__ deg, uint32_t *__restrict__ level, uint32_t *__restrict__ queue,
        uint32_t *__restrict__ alive_a, uint32_t *__restrict__ alive_b, uint32_t *__restrict__ loc,
        uint32_t *__restrict__ rlist, uint32_t *__restrict__ lrow, uint64_t lcol_cap, uint32_t tail_cap,
@@ -649,7 +860,12 @@ k_peel(uint32_t n, const uint32_t *__restrict__ row, const uint32_t *__restrict_
     __shared__ unsigned s_wct[kBlock / 64], s_wck[kBlock / 64], s_wmd[kBlock / 64], s_bq, s_bk;
 
     // the host cleared the control block; initialise per-vertex state
-    for (uint32_t v = gtid; v < n; v += gsize) {
+    for (uint32_t i = gtid; i < from.left; i += gsize) {
+        const uint32_t v = rlist[i];
+        alive_a[i] = v;
+        loc[v] = kUnset;
+    }
+    for (uint32_t v = gtid; !from.left && v < n; v += gsize) {
         deg[v] = (int)(row[v + 1] - row[v]);
         level[v] = kUnset;
         alive_a[v] = v;
@@ -663,7 +879,8 @@ k_peel(uint32_t n, const uint32_t *__restrict__ row, const uint32_t *__restrict_
     // tail: vertices queued before the current grid phase (a scan or a round); phase ph takes its
     // queue positions tail + [0, qc[ph % 3]) and every block adds the final count after the phase's
     // barrier, so all blocks agree on tail although a fast block may already be in the next phase
-    uint32_t k = 0, head = 0, tail = 0, n_alive = n, prev_tail = 0, rounds = 0, lv = 0, ph = 0;
+    uint32_t k = from.k, head = from.tail, tail = from.tail, n_alive = from.left ? from.left : n, prev_tail = from.tail,
+             rounds = from.rounds, lv = 0, ph = 0;
     uint32_t *cur = alive_a, *nxt = alive_b;
     bool done = false;
     // here every queued vertex has been removed: n - tail vertices remain
@@ -1004,6 +1221,7 @@ __global__ void k_finish(uint32_t n, const uint32_t *__restrict__ queue, uint32_
     const uint32_t p = blockIdx.x * 256 + threadIdx.x;
     if (p >= n) return;
     const uint32_t v = queue[p];
+    if (ctl->left) return;   // (not all of them ordered yet)
     if (v < n) rank[v] = p;
     else atomicOr(&ctl->error, 32u);
 }
@@ -1050,30 +1268,45 @@ int peel(dt_graph *g) {
     if (per_cu <= 0) return fail(DT_EDEVICE, "peel kernel cannot be resident");
     unsigned grid = kGridWide;
     if (grid > (unsigned)ctx->num_cus * (unsigned)per_cu) grid = (unsigned)ctx->num_cus * (unsigned)per_cu;
-    grid = std::min(grid, grid_for(n, kBlock));
-    DT_HIP(hipMemsetAsync(ctlm.ptr, 0, kCtlBytes + 2 * kBarBytes, st));
     uint32_t *level = g->core.as<uint32_t>();
     uint32_t *queue = g->order.as<uint32_t>();
     const uint32_t *row = g->row.as<uint32_t>(), *col = g->col.as<uint32_t>();
     int *degp = deg.as<int>();
     uint32_t *aa = alive.as<uint32_t>(), *ab = alive2.as<uint32_t>();
     PeelCtl *ctl = ctlm.as<PeelCtl>();
-    uint32_t nn = n;
     uint32_t *locp = loc.as<uint32_t>(), *rl = rlist.as<uint32_t>(), *lb = lrow.as<uint32_t>();
     uint16_t *lc = lcol.as<uint16_t>();
-    uint64_t lcap = lcol_cap;
-    uint32_t tcap = tail_cap;
     unsigned *lbar = reinterpret_cast<unsigned *>(ctlm.as<uint8_t>() + kCtlBytes);
     uint32_t *o0 = ovf0.as<uint32_t>(), *o1 = ovf1.as<uint32_t>();
-    void *args[] = {&nn, &row, &col, &degp, &level, &queue, &aa, &ab, &locp, &rl, &lb, &lcap, &tcap,
-                    &o0, &o1, &ctl, &lbar};
-    prof_begin(ctx, kProfPeel, st);
-    DT_HIP(hipLaunchCooperativeKernel((const void *)k_peel, dim3(grid), dim3(kBlock), args, 0, st));
-    prof_end(ctx, kProfPeel, st);
-    prof_begin(ctx, kProfPeelAdj, st);
-    k_local_adj<<<(unsigned)ctx->num_cus * 8, 256, 0, st>>>(row, col, degp, locp, rl, lb, lc, ctl);
-    prof_end(ctx, kProfPeelAdj, st);
-    DT_HIP(hipGetLastError());
+    PeelCtl &h = *reinterpret_cast<PeelCtl *>(ctx->pinned_stage);
+    // the levels on the grid from `from` on, until at most tcap vertices remain, and these vertices' local
+    // adjacency
+    auto grid_levels = [&](PeelStart from, uint32_t tcap) -> int {
+        DT_HIP(hipMemsetAsync(ctlm.ptr, 0, kCtlBytes + 2 * kBarBytes, st));
+        uint32_t nn = n;
+        uint64_t lcap = lcol_cap;
+        const unsigned blocks = std::min(grid, grid_for(from.left ? from.left : n, kBlock));
+        void *args[] = {&from, &nn, &row, &col, &degp, &level, &queue, &aa, &ab, &locp, &rl, &lb, &lcap, &tcap,
+                        &o0, &o1, &ctl, &lbar};
+        const bool mark = !from.left;   // (levels after the finish belong to its time)
+        if (mark) prof_begin(ctx, kProfPeel, st);
+        DT_HIP(hipLaunchCooperativeKernel((const void *)k_peel, dim3(blocks), dim3(kBlock), args, 0, st));
+        if (mark) prof_end(ctx, kProfPeel, st);
+        if (mark) prof_begin(ctx, kProfPeelAdj, st);
+        k_local_adj<<<(unsigned)ctx->num_cus * 8, 256, 0, st>>>(row, col, degp, locp, rl, lb, lc, ctl);
+        if (mark) prof_end(ctx, kProfPeelAdj, st);
+        DT_HIP(hipGetLastError());
+        return DT_OK;
+    };
+    // the ranks (what the orientation reads next), whose check of the queue the read-back takes along
+    auto ranks = [&]() -> int {
+        k_finish<<<grid_for(n, 256), 256, 0, st>>>(n, queue, g->rank.as<uint32_t>(), ctl);
+        DT_HIP(hipGetLastError());
+        DT_HIP(hipMemcpyAsync(&h, ctl, sizeof(h), hipMemcpyDeviceToHost, st));
+        DT_HIP(hipStreamSynchronize(st));
+        return DT_OK;
+    };
+    DT_TRY(grid_levels(PeelStart{}, tail_cap));
     prof_begin(ctx, kProfPeelTail, st);
     FinArgs fa;
     fa.rlist = rl;
@@ -1094,13 +1327,16 @@ int peel(dt_graph *g) {
     void *fargs[] = {&fa};
     DT_HIP(hipLaunchCooperativeKernel((const void *)k_peel_finish, dim3(fgrid), dim3(kBlock), fargs, 0, st));
     prof_end(ctx, kProfPeelTail, st);
-    DT_HIP(hipGetLastError());
-    // the ranks (what the orientation reads next), whose check of the queue the read-back takes along
-    k_finish<<<grid_for(n, 256), 256, 0, st>>>(n, queue, g->rank.as<uint32_t>(), ctl);
-    DT_HIP(hipGetLastError());
-    PeelCtl &h = *reinterpret_cast<PeelCtl *>(ctx->pinned_stage);
-    DT_HIP(hipMemcpyAsync(&h, ctl, sizeof(h), hipMemcpyDeviceToHost, st));
-    DT_HIP(hipStreamSynchronize(st));
+    DT_TRY(ranks());
+    if (h.left && !h.error) {   // it left them: level by level, the last ones in one workgroup
+        const PeelStart from{(uint32_t)h.lres, h.ho_k, h.ho_tail, h.ho_rounds};
+        static_assert(FinishRoom::kCells >= 2 * kLevelTail, "level boundaries fit the cells' room");
+        if (from.left > kLevelTail) DT_TRY(grid_levels(from, kLevelTail));
+        k_peel_levels<<<1, kBlock, 0, st>>>(rl, lb, lc, fa.base, level, queue, ctl);
+        prof_end(ctx, kProfPeelTail, st);
+        DT_HIP(hipGetLastError());
+        DT_TRY(ranks());
+    }
     if (h.error & 1u) return fail(DT_EDEVICE, "core peel barrier timed out");
     if (h.error) return fail(DT_EDEVICE, "core peel failed its consistency checks (code %u)", h.error);
     if (h.qtail != n) return fail(DT_EDEVICE, "core peel queued %u of %u vertices", h.qtail, n);
