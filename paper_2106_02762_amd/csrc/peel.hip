@@ -232,6 +232,7 @@ constexpr uint32_t kFinSmall = 1024; // up to this many vertices one block finis
 // 1.9), so that the phases tried cost little beside the levels.
 constexpr uint32_t kSlowPhase = 8, kFewFell = 64, kFewPhases = 24, kPhaseMost = 128;
 constexpr uint32_t kManyFell = 1u << 24;
+constexpr uint32_t kSharedRows = 16; // rows at most that a block's wavefronts walk together
 constexpr uint32_t kSlots = 2048;    // places a block takes together
 
 struct FinArgs {
@@ -375,8 +376,10 @@ __device__ __forceinline__ void walk_rows(const GroupRows &G, const uint16_t *__
 }
 
 // New bounds of a group's vertices (lane x < nv: vertex x; its present bound h comes in), at least k0.
+// Rows of `shared` entries and more keep theirs (the block walks those together).
 __device__ __forceinline__ uint32_t group_bounds(const GroupRows &G, const uint16_t *__restrict__ lcol,
-                                                 const uint16_t *s_h, uint32_t h, uint32_t k0, unsigned lane) {
+                                                 const uint16_t *s_h, uint32_t h, uint32_t k0, uint32_t shared,
+                                                 unsigned lane) {
     walk_rows(
         G, lcol, lane,
         [&](uint32_t x, uint32_t cnt, uint32_t b, uint32_t ends) {
@@ -411,6 +414,7 @@ __device__ __forceinline__ uint32_t group_bounds(const GroupRows &G, const uint1
             if (lane >= x && y < cnt && ye > yb) h = nh;
         },
         [&](uint32_t x, uint32_t b, uint32_t d, const uint32_t (&e)[kRegPieces]) {
+            if (d >= shared) return;
             const uint32_t H = __builtin_amdgcn_readlane(h, x);
             uint32_t lo, hi = H - 1, c = 0;
             if (d <= kRegRow) {
@@ -472,6 +476,7 @@ k_peel_finish(FinArgs A) {
     __shared__ __attribute__((aligned(16))) uint16_t s_v[kTail];
     __shared__ uint32_t s_key[kSlots], s_cnt[kSlots];
     __shared__ unsigned s_any, s_more[2], s_scan[kBlock / 64];
+    __shared__ uint32_t s_row[kSharedRows], s_rows, s_ge[kSharedRows], s_at[3][8];
     PeelCtl *ctl = A.ctl;
     if (!ctl->ho || ctl->error) return;
     constexpr uint32_t kBW = kBlock / 64;
@@ -496,6 +501,19 @@ k_peel_finish(FinArgs A) {
     const GroupRows G0 = group_rows(va < vb ? va : (vb < R ? vb : R));
     // bounds: the degrees; no position taken
     const uint32_t cell_cap = FinishRoom::cells(R);
+    // rows of twice a wavefront's share and more, which one wavefront would hold the others up with
+    // (fewer than nine can begin in a block's share)
+    const uint64_t share = work / nblk;
+    const uint32_t shared = share / 8 > 2 * kRegRow ? (uint32_t)(share / 8) : 2 * kRegRow;
+    if (tid == 0) s_rows = 0;
+    if (tid < 24) s_at[tid / 8][tid % 8] = 0;
+    __syncthreads();
+    for (uint32_t v = va + lane; v < vb; v += 64)
+        if (A.lrow[v + 1] - A.lrow[v] >= shared) {
+            const uint32_t x = atomicAdd(&s_rows, 1u);
+            if (x < kSharedRows) s_row[x] = v;
+            else atomicOr(&ctl->error, 64u);
+        }
     for (uint32_t v = gtid; v < R; v += gsize) {
         A.val[v] = (uint16_t)(A.lrow[v + 1] - A.lrow[v]);
         A.when[v] = 0;
@@ -507,6 +525,76 @@ k_peel_finish(FinArgs A) {
         uint4 *dst = reinterpret_cast<uint4 *>(s_v);
         for (uint32_t i = tid; i < (R + 7) / 8; i += kBlock) dst[i] = src[i];
         if (tid == 0) s_any = 0;
+        if (tid < kSharedRows) s_ge[tid] = 0;
+    };
+    // the block's rows that its wavefronts walk together: f(values, entries left) for this wavefront's
+    // stretches of the row at b, the first of them the one after `at` others
+    auto shared_stretches = [&](uint32_t b, uint32_t d, uint32_t at, auto f) {
+        for (uint32_t j = ((tid / 64 - at) % kBW) * kRegRow; j < d; j += kBW * kRegRow) {
+            uint32_t c[kRegPieces], v[2 * kRegPieces];
+            row_entries(A.lcol, b + j, d - j, lane, c);
+            row_values(s_v, c, d - j, lane, v);
+            f(v, d - j);
+        }
+    };
+    // New bounds of those rows, exact ones: the values of at least the present bound for all of them at
+    // once, then eight thresholds a pass for those that fall.  Returns how many did (to the first
+    // wavefront).  A wavefront a row, some thresholds a phase, took 130 us a phase beside a row of 46,544
+    // entries (200,000 vertices, 2M pairs: the peel 9.5 ms in 66 phases, 3.3 in 49 so).
+    uint32_t pass = 0;
+    auto shared_rows = [&](uint16_t *out, uint32_t ph) {
+        const uint32_t n_rows = s_rows;
+        uint32_t fell = 0, at = 0;
+        for (uint32_t x = 0; x < n_rows; ++x) {
+            const uint32_t v = s_row[x], b = A.lrow[v], d = A.lrow[v + 1] - b, H = s_v[v];
+            uint32_t n = 0;
+            shared_stretches(b, d, at, [&](const uint32_t (&w)[2 * kRegPieces], uint32_t left) {
+                n += count_at_least(w, left, H);
+            });
+            if (lane == 0 && n) atomicAdd(&s_ge[x], n);
+            at += (d + kRegRow - 1) / kRegRow;
+        }
+        __syncthreads();
+        for (uint32_t x = 0; x < n_rows; ++x) {
+            const uint32_t v = s_row[x], b = A.lrow[v], d = A.lrow[v + 1] - b, H = s_v[v], c = s_ge[x];
+            if (c >= H) continue;
+            uint32_t hi = H - 1, lo = c > k0 ? c : k0;
+            if (lo > hi) lo = hi;
+            while (lo < hi) {
+                uint32_t t[8], n[8];
+#pragma unroll
+                for (uint32_t q = 0; q < 8; ++q) {
+                    t[q] = lo + ((hi - lo) * (q + 1) + 7) / 8;
+                    n[q] = 0;
+                }
+                shared_stretches(b, d, 0, [&](const uint32_t (&w)[2 * kRegPieces], uint32_t left) {
+#pragma unroll
+                    for (uint32_t q = 0; q < 8; ++q) n[q] += count_at_least(w, left, t[q]);
+                });
+#pragma unroll
+                for (uint32_t q = 0; q < 8; ++q)
+                    if (lane == 0 && n[q]) atomicAdd(&s_at[pass % 3][q], n[q]);
+                __syncthreads();
+#pragma unroll
+                for (uint32_t q = 0; q < 8; ++q) {   // (t and the counts against it: true, then false)
+                    if (s_at[pass % 3][q] >= t[q]) {
+                        lo = t[q];
+                    } else {
+                        hi = t[q] - 1;
+                        break;
+                    }
+                }
+                // (for the pass after next: every thread has read it, and adds to it after a barrier)
+                if (tid < 8) s_at[(pass + 2) % 3][tid] = 0;
+                ++pass;
+            }
+            if (tid == 0) {
+                out[v] = (uint16_t)lo;
+                A.when[v] = ph + 1;
+            }
+            ++fell;
+        }
+        return tid / 64 ? 0u : fell;
     };
     // every block learns how many bounds fell in phase ph (kManyFell and more: many); s_more[1]: an error
     auto any_left = [&](uint32_t fell, uint32_t ph) {
@@ -534,12 +622,16 @@ k_peel_finish(FinArgs A) {
             const GroupRows G = v0 == va ? G0 : group_rows(v0);
             const uint32_t v = v0 + lane;
             const uint32_t h = lane < G.nv ? s_v[v] : 0u;
-            const uint32_t nh = group_bounds(G, A.lcol, s_v, h, k0, lane);
+            const uint32_t nh = group_bounds(G, A.lcol, s_v, h, k0, shared, lane);
             if (lane < G.nv) {
                 out[v] = (uint16_t)nh;
                 if (nh != h) A.when[v] = ph + 1;
             }
             fell += (uint32_t)__popcll(__ballot(lane < G.nv && nh != h));
+        }
+        if (s_rows) {
+            __syncthreads();   // (the wavefronts' own bounds written)
+            fell += shared_rows(out, ph);
         }
         const uint32_t more = any_left(fell, ph);
         if (s_more[1]) return;

@@ -1,7 +1,7 @@
 """Graphs whose core bounds fall one vertex a phase -- paths, thick chains, lattices, alone, beside a
 power-law part and behind leaves that the levels take first -- which the level peel's finish leaves to the
-levels, on the grid and in one workgroup.  Core numbers equal the oracle's, no vertex has more than core(v)
-neighbours after it, and a chain's phases end."""
+levels, on the grid and in one workgroup; and rows that a block's wavefronts walk together.  Core numbers
+equal the oracle's, no vertex has more than core(v) neighbours after it, and a chain's phases end."""
 import numpy as np
 import pytest
 
@@ -40,6 +40,14 @@ def _power(n, m, seed=1):
     return tuple(np.searchsorted(c, rng.random(m) * c[-1]) for _ in range(2))
 
 
+def _hubs(n, sizes, extra, seed=2):
+    rng = np.random.default_rng(seed)
+    u = np.concatenate([np.full(d, i) for i, d in enumerate(sizes)] + [rng.integers(0, n, extra)])
+    v = np.concatenate([rng.choice(n - len(sizes), d, replace=False) + len(sizes) for d in sizes] +
+                       [rng.integers(0, n, extra)])
+    return u, v
+
+
 def _graph(n, *parts):
     u, v = np.concatenate([p[0] for p in parts]), np.concatenate([p[1] for p in parts])
     ok = u != v
@@ -60,6 +68,8 @@ GRAPHS = {
     "behind leaves": lambda: _graph(90000, _chain(60000, 4), (60000 + np.arange(30000), np.arange(30000) * 2)),
     "behind leaves, both": lambda: _graph(91000, _power(30000, 300000), _chain(31000, 3, 29999),
                                           (60999 + np.arange(30001), np.arange(30001))),
+    "shared rows": lambda: _graph(40000, _hubs(40000, [2047, 2048, 2049, 3000, 17000, 30000], 50000)),
+    "many shared rows": lambda: _graph(65536, _hubs(65536, [2100] * 30 + [9000] * 12 + [60000] * 2, 100000)),
 }
 
 
@@ -84,3 +94,31 @@ def test_phases_of_a_chain_end(ctx, name):
     rounds = dt.dt_graph_stats(h)["peel_rounds"]
     dt.dt_graph_free(h)
     assert rounds < 900 and (name != "lattice" or rounds < 150), rounds
+
+
+def _phases(g, pairs):
+    """Phases of bounds that fall at once to the largest t such that t neighbours have bounds of at least t."""
+    u = np.concatenate(pairs)
+    v = np.concatenate(pairs[::-1])
+    start = np.concatenate([[0], np.cumsum(np.bincount(u, minlength=g.n))])
+    h, n = np.diff(start), 0
+    while True:
+        order = np.lexsort((-h[v], u))           # every vertex's neighbours by falling bound
+        w = u[order]
+        new = np.bincount(w, h[v][order] >= np.arange(w.shape[0]) - start[w] + 1, minlength=g.n).astype(np.int64)
+        new, n = np.minimum(new, h), n + 1
+        if (new == h).all():
+            return n
+        h = new
+
+
+def test_shared_rows_are_exact(ctx):
+    """Every row of more than 1,024 entries is walked by a whole block, whose new bounds are exact: as many
+    phases as bounds that fall all the way at once need."""
+    g = GRAPHS["shared rows"]()
+    say("rounds", g.name)
+    h = dt.dt_graph_load(ctx, g.n, g.src, g.dst, g.t)
+    dt.dt_graph_build(h)
+    rounds = dt.dt_graph_stats(h)["peel_rounds"]
+    dt.dt_graph_free(h)
+    assert rounds == _phases(g, _static_pairs(g))
