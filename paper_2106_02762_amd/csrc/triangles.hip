@@ -51,10 +51,18 @@ constexpr uint32_t kSpan = 32;      // vertices of a pack ticket (8: +1.4 ms on 
 constexpr uint32_t kSpanMax = 63;   // (a ticket's run ends are held one per lane)
 constexpr uint32_t kLowOut = 64;    // graphs with no longer run: no splits, no bitmaps
 constexpr uint32_t kOut = 128;    // triangles a wavefront buffers in LDS before appending them
-// list positions a wavefront reserves at once (one atomic on the shared counter per kChunkTri
-// triangles instead of one per buffer: thousands of wavefronts meeting at one counter serialise)
+// List positions a wavefront reserves at once, at most: one atomic on the shared counter per stretch
+// instead of one per buffer, since thousands of wavefronts meeting at one counter serialise (36M triangles
+// on 2M pairs, whose first pass has no room for stretches of 2,048: 10.6 ms with an atomic a buffer, 4.3
+// with the stretches of that room).
 constexpr uint32_t kChunkTri = 2048;
-static_assert(kChunkTri >= kOut, "a buffer fits a fresh chunk");
+// The stretches of a pass: `size` positions while the last one taken ended below `until`; above it exactly
+// a buffer's (so that what the last ones leave empty takes no triangle's place), and kChunkTri past the
+// list, where positions are only counted.
+struct Stretch {
+    uint32_t size;
+    uint64_t until;
+};
 constexpr int kBatchBuild = 3;    // blocks of 64 flattened candidates a lane works on at once
 constexpr int kBatchFused = 1;    // (one in the one-shot pass: its counting holds the registers)
 constexpr uint32_t kBmMin = 16;      // heads of N+(v) at least for a bitmap
@@ -188,11 +196,10 @@ struct FusedArgs {
 };
 
 // Buffered output: a wavefront collects its triangles in LDS and copies each full buffer into a
-// stretch of list positions it reserved with one atomic per kChunkTri positions; when the stretch
-// lacks room for a buffer, its rest is filled with empty triangles (all three ids kNoEdge) and a new
-// stretch is taken, and at the end the unused rest of the last one is filled the same way.  The
-// list therefore holds every triangle once and some empty entries, which the schedule skips; the
-// wavefronts also add up the triangles they found.  Positions past `cap` are counted but not
+// stretch of list positions it reserved with one atomic; what the stretch has no room for goes to the
+// next one, and at the end the unused rest of the last one is filled with empty triangles (all three ids
+// kNoEdge).  The list therefore holds every triangle once and some empty entries, which the schedule
+// skips; the wavefronts also add up the triangles they found.  Positions past `cap` are counted but not
 // written.  In the one-shot
 // pass (FUSED) a full buffer is counted instead: each lane takes every 64th buffered triangle;
 // one with a single temporal edge per pair is tested as a unit record, a light one is counted
@@ -208,7 +215,7 @@ struct TriSink {
     const FusedArgs *fa;
     unsigned long long found = 0;   // triangles this wavefront found (counted, in the one-shot pass)
     unsigned long long cb = 0, ce = 0;   // the reserved positions [cb, ce) not yet used (stored pass)
-    bool chunked = true;                 // stretches of kChunkTri positions, else one per buffer
+    Stretch stretch{};
     // LDS sums of the wavefront (one-shot pass): the eight counts, then the multiplicity products'
     // 32-bit limbs (kept here, not in registers: the walks between two flushes need those)
     unsigned long long *sums = nullptr;
@@ -278,20 +285,25 @@ struct TriSink {
             }
         } else {
             found += n;
-            if (ce - cb < n) {
-                // a new stretch: kChunkTri positions, or exactly this buffer's (chunked = false)
-                fill_empty(lane);
-                const unsigned long long want = chunked ? kChunkTri : n;
-                unsigned long long b = 0;
-                if (lane == 0) b = atomicAdd(total, want);
-                b = __shfl(b, 0, 64);
-                cb = b;
-                ce = b + want;
-            }
+            // the first `here` triangles to the stretch at hand, the others to a new one
             const unsigned long long base = cb;
-            cb += n;
-            for (uint32_t x = lane; x < 3 * n; x += 64)
-                if (base + x / 3 < cap) tri[3 * base + x] = buf[x];
+            unsigned long long next = 0;
+            const uint32_t here = ce - cb < n ? (uint32_t)(ce - cb) : n;
+            cb += here;
+            if (here < n) {
+                const uint32_t more = n - here;
+                const uint32_t size = ce < stretch.until ? stretch.size : (ce < cap ? 0u : kChunkTri);
+                const unsigned long long want = size > more ? size : more;
+                if (lane == 0) next = atomicAdd(total, want);
+                next = __shfl(next, 0, 64);
+                cb = next + more;
+                ce = next + want;
+            }
+            for (uint32_t x = lane; x < 3 * n; x += 64) {
+                const uint32_t t = x / 3;
+                const unsigned long long at = t < here ? base + t : next + (t - here);
+                if (at < cap) tri[3 * at + (x - 3 * t)] = buf[x];
+            }
         }
         __builtin_amdgcn_wave_barrier();
         n = 0;
@@ -340,7 +352,7 @@ k_tri(uint32_t n, const uint32_t *__restrict__ dag_row, const uint32_t *__restri
       uint32_t *__restrict__ tri, uint64_t cap, unsigned long long *__restrict__ total,
       unsigned int *__restrict__ next_u, unsigned long long *__restrict__ cand, FusedArgs fa,
       const uint4 *__restrict__ binfo, const uint64_t *__restrict__ bslots,
-      unsigned long long *__restrict__ found_total, int chunked, Tickets T) {
+      unsigned long long *__restrict__ found_total, Stretch stretch, Tickets T) {
     // per wavefront: the entries of the pack's runs N+(u), (16-bit) the end of each entry's run, the
     // run starts and (16-bit) lengths of each N+(v), and one slice that holds the prefix of walk
     // lengths during the flattened walks and then a staged N+(v) copy
@@ -354,7 +366,7 @@ k_tri(uint32_t n, const uint32_t *__restrict__ dag_row, const uint32_t *__restri
     uint32_t *nbr_lds = s_nbr[wave], *pre_lds = s_pre[wave], *vb_lds = s_vb[wave], *vn_lds = s_pre[wave];
     uint16_t *dv_lds = s_dv[wave], *re_lds = s_re[wave];
     TriSink<FUSED> out{s_out[wave], 0, tri, cap, total, &fa};
-    out.chunked = chunked != 0;
+    out.stretch = stretch;
     if (FUSED) {
         __shared__ unsigned long long s_acc[kWaves][11];
         out.sums = s_acc[wave];
@@ -727,25 +739,33 @@ int enumerate_triangles(const dt_graph *g, DevMem &tri, uint64_t *ntri_out, uint
     DevMem ctr, binfo, bslots;
     DT_TRY(dev_alloc(ctx, ctr, 256));
     DT_TRY(build_bitmaps(g, binfo, bslots));
-    // room for 4 triangles per static pair.  Wavefronts reserve stretches of kChunkTri positions
-    // when that room is at least four times what the last stretches of all wavefronts can leave
-    // empty, else exactly each buffer's positions (no empty entries).  A graph with more triangles
-    // runs the pass again, with room for its triangles and, with stretches, the most empty entries
-    // they can leave: below kOut per stretch taken (at most one per kChunkTri - kOut triangles, and
-    // one more per wavefront) and a last stretch per wavefront.
+    // Room for 4 triangles per static pair.  The stretches that wavefronts reserve leave at most an eighth
+    // of it empty.  A graph with more triangles runs the pass again, with room for its triangles and for
+    // what its stretches can leave empty, or, where memory is short, for its triangles only (a buffer's
+    // positions at a time).
     uint64_t cap = std::max<uint64_t>(4ull * g->m_s, 1ull << 16);
     unsigned grid = 0;
     const Tickets T = make_tickets(g, &grid);
     const uint64_t waves = (uint64_t)grid * kWaves;
-    const int chunked = cap >= 4 * waves * kChunkTri ? 1 : 0;
+    auto stretches = [&](uint64_t room) {
+        return (uint32_t)std::min<uint64_t>(kChunkTri, room / (8 * waves));
+    };
+    Stretch stretch{stretches(cap), cap / 2};
     for (int attempt = 0; attempt < 2; ++attempt) {
-        DT_TRY(dev_alloc(ctx, tri, cap * 12));
+        int rc = dev_alloc(ctx, tri, cap * 12);
+        if (rc == DT_ENOMEM && attempt) {
+            clear_error();
+            cap = *ntri_out;
+            stretch = Stretch{0, 0};
+            rc = dev_alloc(ctx, tri, cap * 12);
+        }
+        DT_TRY(rc);
         DT_HIP(hipMemsetAsync(ctr.ptr, 0, 40, st));
         unsigned long long *c64 = reinterpret_cast<unsigned long long *>(ctr.as<uint8_t>() + 8);
         prof_begin(ctx, kProfTriFill, st);
         k_tri<false><<<grid, kBlock, 0, st>>>(n, g->dag_row.as<uint32_t>(), g->dag_col.as<uint32_t>(),
                                               tri.as<uint32_t>(), cap, c64, ctr.as<unsigned>(), c64 + 1, FusedArgs{},
-                                              binfo.as<uint4>(), bslots.as<uint64_t>(), c64 + 2, chunked, T);
+                                              binfo.as<uint4>(), bslots.as<uint64_t>(), c64 + 2, stretch, T);
         prof_end(ctx, kProfTriFill, st);
         DT_HIP(hipGetLastError());
         uint64_t *h = reinterpret_cast<uint64_t *>(ctx->pinned_stage);
@@ -755,8 +775,9 @@ int enumerate_triangles(const dt_graph *g, DevMem &tri, uint64_t *ntri_out, uint
         *cand_out = h[1];
         *ntri_out = h[2];
         if (h[0] <= cap) return DT_OK;
-        const uint64_t stretches = h[2] / (kChunkTri - kOut) + 2 * waves;
-        cap = chunked ? h[2] + stretches * kOut + waves * kChunkTri : h[2];
+        stretch.size = stretches(h[2]);
+        cap = h[2] + waves * stretch.size;
+        stretch.until = cap;
         tri.reset();
     }
     return fail(DT_EDEVICE, "triangle enumeration changed between passes");
@@ -800,7 +821,7 @@ int fused_count(dt_graph *g, const DQuery &q, int64_t *out8_dev, DevMem &rest, u
         if (n)
             k_tri<true><<<grid, kBlock, 0, st>>>(n, g->dag_row.as<uint32_t>(), g->dag_col.as<uint32_t>(), nullptr, 0,
                                                  c64, ctr.as<unsigned>(), c64 + 1, fa, binfo.as<uint4>(),
-                                                 bslots.as<uint64_t>(), nullptr, 0, T);
+                                                 bslots.as<uint64_t>(), nullptr, Stretch{}, T);
         else
             DT_HIP(hipMemsetAsync(part.ptr, 0, n_part * 8 * sizeof(int64_t), st));
         prof_end(ctx, kProfTriFill, st);
