@@ -180,6 +180,22 @@ __device__ __forceinline__ uint32_t lower(const uint64_t *__restrict__ key, uint
     return lo;
 }
 
+// first indices in [lo, hi) whose keys are >= K1 and >= K2 (two searches in one loop)
+__device__ __forceinline__ void lower2(const uint64_t *__restrict__ key, uint32_t lo, uint32_t hi, uint64_t K1,
+                                       uint64_t K2, uint32_t &r1, uint32_t &r2) {
+    uint32_t l1 = lo, l2 = lo, len1 = hi - lo, len2 = hi - lo;
+    while (len1 | len2) {
+        const uint32_t h1 = len1 >> 1, h2 = len2 >> 1;
+        const bool go1 = len1 && key[l1 + h1] < K1, go2 = len2 && key[l2 + h2] < K2;
+        l1 += go1 ? h1 + 1 : 0;
+        len1 = go1 ? len1 - h1 - 1 : h1;
+        l2 += go2 ? h2 + 1 : 0;
+        len2 = go2 ? len2 - h2 - 1 : h2;
+    }
+    r1 = l1;
+    r2 = l2;
+}
+
 // key bound of "t < x" for a relative time x
 __device__ __forceinline__ uint64_t before_time(int64_t x, const DQuery &q) {
     return x <= 0 ? 0ull : (x > q.span ? ~0ull : ((uint64_t)x << q.shift));
@@ -307,19 +323,37 @@ __device__ __forceinline__ void pair_thirds(const uint64_t *__restrict__ key, ui
 // ---------------------------------------------------------------------------------------------
 // light path: one lane per triangle, every (uv edge, uw edge) pair
 // ---------------------------------------------------------------------------------------------
-// eval(d_uv, d_uw, k_uv, k_uw) for every pair inside the query's window
+// eval(d_uv, d_uw, k_uv, k_uw) for every pair inside the query's window.  Long lists, as raised light caps
+// and forced light triangles have, are clipped to a window first (10M edges, caps of 10,000 pairs, a window
+// of a thousandth of the span: 38 us, 468 with every edge read and tested); the short ones of the
+// default cap are read and tested.
+constexpr uint32_t kLightClip = 8;
 template <class EVAL>
 __device__ __forceinline__ void light_pairs(const uint32_t *__restrict__ eoff, uint32_t e_uv, uint32_t e_uw,
                                             const uint64_t *__restrict__ key, const DQuery &q, EVAL &&eval) {
-    const uint32_t a0 = eoff[2 * e_uv], a1 = eoff[2 * e_uv + 1], a2 = eoff[2 * e_uv + 2];
-    const uint32_t b0 = eoff[2 * e_uw], b1 = eoff[2 * e_uw + 1], b2 = eoff[2 * e_uw + 2];
-    for (uint32_t x = a0; x < a2; ++x) {
-        const uint64_t kx = key[x];
-        if (kx < q.klo || kx >= q.khi) continue;
-        for (uint32_t y = b0; y < b2; ++y) {
-            const uint64_t ky = key[y];
-            if (ky < q.klo || ky >= q.khi) continue;
-            eval(x >= a1 ? 1u : 0u, y >= b1 ? 1u : 0u, kx, ky);
+    // each pair's edges by direction: [x0, x0 + nx0) and [x1, x1 + nx1 - nx0), nx1 in all
+    uint32_t x0 = eoff[2 * e_uv], x1 = eoff[2 * e_uv + 1], nx0 = x1 - x0, nx1 = eoff[2 * e_uv + 2] - x0;
+    uint32_t y0 = eoff[2 * e_uw], y1 = eoff[2 * e_uw + 1], ny0 = y1 - y0, ny1 = eoff[2 * e_uw + 2] - y0;
+    bool test = q.windowed;
+    if (q.windowed && (nx1 > kLightClip || ny1 > kLightClip)) {
+        auto clip = [&](uint32_t &p0, uint32_t &p1, uint32_t &n0, uint32_t &n1) {
+            uint32_t h0, h1;
+            lower2(key, p0, p0 + n0, q.klo, q.khi, p0, h0);
+            lower2(key, p1, p1 + (n1 - n0), q.klo, q.khi, p1, h1);
+            n0 = h0 - p0;
+            n1 = n0 + (h1 - p1);
+        };
+        clip(x0, x1, nx0, nx1);
+        clip(y0, y1, ny0, ny1);
+        test = false;
+    }
+    for (uint32_t i = 0; i < nx1; ++i) {
+        const uint64_t kx = key[i < nx0 ? x0 + i : x1 + (i - nx0)];
+        if (test && (kx < q.klo || kx >= q.khi)) continue;
+        for (uint32_t j = 0; j < ny1; ++j) {
+            const uint64_t ky = key[j < ny0 ? y0 + j : y1 + (j - ny0)];
+            if (test && (ky < q.klo || ky >= q.khi)) continue;
+            eval(i >= nx0 ? 1u : 0u, j >= ny0 ? 1u : 0u, kx, ky);
         }
     }
 }
@@ -355,22 +389,6 @@ __host__ __device__ __forceinline__ uint32_t medium_inner_chunks(uint32_t s_oute
     return s_inner > kInnerChunk && (uint64_t)s_outer * s_inner <= kChunkMaxPairs
                ? (s_inner + kInnerChunk - 1) / kInnerChunk
                : 1u;
-}
-
-// first indices in [lo, hi) whose keys are >= K1 and >= K2 (two searches in one loop)
-__device__ __forceinline__ void lower2(const uint64_t *__restrict__ key, uint32_t lo, uint32_t hi, uint64_t K1,
-                                       uint64_t K2, uint32_t &r1, uint32_t &r2) {
-    uint32_t l1 = lo, l2 = lo, len1 = hi - lo, len2 = hi - lo;
-    while (len1 | len2) {
-        const uint32_t h1 = len1 >> 1, h2 = len2 >> 1;
-        const bool go1 = len1 && key[l1 + h1] < K1, go2 = len2 && key[l2 + h2] < K2;
-        l1 += go1 ? h1 + 1 : 0;
-        len1 = go1 ? len1 - h1 - 1 : h1;
-        l2 += go2 ? h2 + 1 : 0;
-        len2 = go2 ? len2 - h2 - 1 : h2;
-    }
-    r1 = l1;
-    r2 = l2;
 }
 
 // Medium entries: entry e = (triangle index into med, outer edge and inner chunk, as in
