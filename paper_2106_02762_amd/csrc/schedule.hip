@@ -589,13 +589,16 @@ constexpr uint32_t kChunk = 256;   // source edges per count chunk and per prefi
 // tile (k_sizes), the sums' prefix over the tiles (k_tile_sums), and in k_expand the prefix within the
 // tile and the items, which a tile writes in order, each thread finding its item's triangle in the
 // tile's prefix (one triangle a thread wrote them scattered: 60 us for both medium lists of the 10M-edge
-// graph, 27 us so with the heavy ones).  Five sequences: the medium entries of medium and of medium_w (one
+// graph, 27 us so with the heavy ones).  A tile of many items is shared by several workgroups, as few
+// tiles otherwise leave most of the chip idle (34,220 triangles of 300 items each: schedule 490 us, 1,450
+// with a workgroup a tile).  Five sequences: the medium entries of medium and of medium_w (one
 // per edge of the outer pair, the source-incident pair with fewer temporal edges, and chunk of the inner
 // pair), then of the heavy triangles the prefix slots (four arrays of length sigma + 1), count chunks and
 // prefix chunks (at least one per list, so that an empty list's total is written too).
 constexpr unsigned kItemPer = 4;
 constexpr unsigned kItemTile = kBlock * kItemPer;
 constexpr int kSeqs = 5;
+constexpr uint64_t kItemsPerBlock = 8192;
 struct ItemArgs {
     uint64_t nm, nh;
     unsigned tiles_m, tiles_h;   // (each list + 1 entry, so that the last prefix is the total)
@@ -667,10 +670,13 @@ __global__ void __launch_bounds__(kBlock) k_sizes(ItemArgs A) {
     if (threadIdx.x < (med ? 2u : 3u)) A.tile[(med ? 0 : 2) * A.tile_stride + threadIdx.x * A.tile_stride + tile] = s_sum[threadIdx.x];
 }
 
-// One workgroup: the tiles' sums to exclusive prefixes, the totals to the host.
+// One workgroup: the tiles' sums to exclusive prefixes, the totals and the most items of a tile to the host.
 constexpr unsigned kTileBlock = 1024;
 __global__ void __launch_bounds__(kTileBlock) k_tile_sums(ItemArgs A, unsigned long long *__restrict__ host) {
     __shared__ unsigned long long s_wave[kTileBlock / 64];
+    __shared__ unsigned long long s_most;
+    if (threadIdx.x == 0) s_most = 0;
+    unsigned long long most = 0;
     for (int x = 0; x < kSeqs; ++x) {
         unsigned long long *t = A.tile + (uint64_t)x * A.tile_stride;
         const unsigned n = x < 2 ? A.tiles_m : A.tiles_h;
@@ -678,6 +684,7 @@ __global__ void __launch_bounds__(kTileBlock) k_tile_sums(ItemArgs A, unsigned l
         for (unsigned b = 0; b < n; b += kTileBlock) {
             const unsigned i = b + threadIdx.x;
             const unsigned long long v = i < n ? t[i] : 0ull;
+            if (x != 2 && v > most) most = v;   // (the slots have no items)
             unsigned long long total;
             const unsigned long long at = block_scan(v, s_wave, total);
             if (i < n) t[i] = run + at;
@@ -685,6 +692,9 @@ __global__ void __launch_bounds__(kTileBlock) k_tile_sums(ItemArgs A, unsigned l
         }
         if (threadIdx.x == 0) host[x] = run;
     }
+    if (most) atomicMax(&s_most, most);
+    __syncthreads();
+    if (threadIdx.x == 0) host[kSeqs] = s_most;
 }
 
 // the tile's item p of s_pre (kItemTile + 1 prefixes): its entry
@@ -719,14 +729,15 @@ __global__ void __launch_bounds__(kBlock) k_expand(ItemArgs A) {
         for (unsigned j = 0; j < kItemPer; ++j) {
             const uint64_t i = t0 + kItemPer * threadIdx.x + j;
             s_pre[kItemPer * threadIdx.x + j] = at;
-            if (i <= n) A.base[x][i] = base + at;
+            if (i <= n && blockIdx.y == 0) A.base[x][i] = base + at;
             at += v[j];
         }
         if (x == 2) continue;   // (the slots have no items)
         if (threadIdx.x == 0) s_pre[kItemTile] = total;
         __syncthreads();
         uint2 *out = reinterpret_cast<uint2 *>(x == 0 ? A.mitems : (x == 1 ? A.mitems_w : (x == 3 ? A.chunks : A.pchunks)));
-        for (unsigned long long p = threadIdx.x; p < total; p += kBlock) {
+        const uint64_t step = (uint64_t)gridDim.y * kBlock;
+        for (unsigned long long p = (uint64_t)blockIdx.y * kBlock + threadIdx.x; p < total; p += step) {
             const unsigned e = item_entry(s_pre, p);
             uint32_t j = (uint32_t)(p - s_pre[e]);
             if (x == 3) {
@@ -965,6 +976,7 @@ int try_schedule(dt_graph *g, DevMem &tri, bool with_units, bool last, bool lean
         DT_TRY(unit_sort());
         DT_HIP(hipStreamSynchronize(st));
         if (hs[0] != hs[1]) return fail(DT_EDEVICE, "medium work items of the two orders differ");
+        const uint64_t most_items = hs[kSeqs];
         S.n_mitems = hs[0];
         S.n_slots = hs[2];
         S.n_chunks = hs[3];
@@ -981,7 +993,10 @@ int try_schedule(dt_graph *g, DevMem &tri, bool with_units, bool last, bool lean
         A.mitems_w = S.mitems_w.as<uint32_t>();
         A.chunks = S.chunks.as<uint32_t>();
         A.pchunks = S.pchunks.as<uint32_t>();
-        k_expand<<<A.tiles_m + A.tiles_h, kBlock, 0, st>>>(A);
+        // workgroups a tile: about kItemsPerBlock items each, while these are no more than the chip takes
+        const unsigned tiles_all = A.tiles_m + A.tiles_h, room = (unsigned)ctx->num_cus * 16;
+        const unsigned share = (unsigned)std::min<uint64_t>(most_items / kItemsPerBlock, room / tiles_all);
+        k_expand<<<dim3(tiles_all, std::max(share, 1u)), kBlock, 0, st>>>(A);
         DT_HIP(hipGetLastError());
         k_tables<<<1, kBlock, 0, st>>>(S.n_light, na, A, ctr, hs);
         DT_HIP(hipGetLastError());
