@@ -493,6 +493,7 @@ int dt_count_sweep(dt_graph *g, uint64_t k, const dt_query *queries, int64_t *ou
         if (queries[j].t_lo != queries[0].t_lo || queries[j].t_hi != queries[0].t_hi)
             return fail(DT_EINVAL, "the queries of a sweep share one window (query %llu differs)",
                         (unsigned long long)j);
+    DevMem heavy;   // scratch of this call's passes: back to the cache once the stream is done with them
     for (uint64_t b = 0; b < k; b += kSweepMax) {
         const uint32_t kk = (uint32_t)std::min<uint64_t>(kSweepMax, k - b);
         DQuery dq[kSweepMax];
@@ -504,7 +505,12 @@ int dt_count_sweep(dt_graph *g, uint64_t k, const dt_query *queries, int64_t *ou
         }
         dt_ctx *ctx = g->ctx;
         DeviceGuard dg(ctx->device);
-        DT_TRY(count_sweep_enqueue(g, dq, kk, ctx->pinned_out, ctx->stream, ctx->scratch));
+        const int rc = count_sweep_enqueue(g, dq, kk, ctx->pinned_out, ctx->stream, ctx->scratch, heavy);
+        if (rc != DT_OK) {   // (what was launched may still use the scratch)
+            for (hipStream_t s : {ctx->side[0], ctx->side[1], ctx->stream})
+                if (s) (void)hipStreamSynchronize(s);
+            return rc;
+        }
         DT_HIP(hipStreamSynchronize(ctx->stream));
         memcpy(out + 8 * b, ctx->pinned_out, 8 * kk * sizeof(int64_t));
     }

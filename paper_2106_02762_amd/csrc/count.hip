@@ -831,7 +831,8 @@ void count_reduce(uint64_t n_part, const int64_t *part, int64_t *out8_dev, hipSt
 // close pairs once (for the largest d13); only the delta-dependent searches repeat.  The rare heavy
 // triangles are counted for every query in one set of launches (61M edges, eight triples: 1.3 ms of 1.9
 // when each query took its own, one after the other).
-int count_sweep_enqueue(dt_graph *g, const DQuery *qs, uint32_t k, int64_t *out_dev, hipStream_t s, Scratch &sc) {
+int count_sweep_enqueue(dt_graph *g, const DQuery *qs, uint32_t k, int64_t *out_dev, hipStream_t s, Scratch &sc,
+                        DevMem &heavy) {
     dt_ctx *ctx = g->ctx;
     Schedule &S = g->sched;
     if (k == 0 || k > kSweepMax) return fail(DT_EINVAL, "a sweep pass takes 1..%u queries", kSweepMax);
@@ -873,18 +874,25 @@ int count_sweep_enqueue(dt_graph *g, const DQuery *qs, uint32_t k, int64_t *out_
     DT_TRY(ensure(ctx, sc.sweep_partials, (n_slot + hg + 1) * k * 8 * sizeof(int64_t)));
     int64_t *part = sc.sweep_partials.as<int64_t>(), *hpart = part + 8 * n_slot * k;
     // the heavy triangles of all k queries in one set of launches, when their scratch may be had: a
-    // query's prefix arrays each, at most kSweepHeavyBytes of them at a time, else one query after the
-    // other
+    // query's prefix arrays each, at most kSweepHeavyBytes (and half a budget) of them at a time, else one
+    // query after the other
     uint32_t hk = 0;
+    uint8_t *hscratch = nullptr;
     if (hg) {
-        hk = (uint32_t)std::min<uint64_t>(k, std::max<uint64_t>(1, kSweepHeavyBytes / hr.scratch_bytes));
-        int rc = ensure(ctx, sc.heavy_vals, hk * hr.scratch_bytes);
-        if (rc == DT_ENOMEM && hk > 1) {
-            clear_error();
-            hk = 1;
-            rc = ensure(ctx, sc.heavy_vals, hr.scratch_bytes);
+        const uint64_t most = ctx->budget ? std::min<uint64_t>(kSweepHeavyBytes, ctx->budget / 2) : kSweepHeavyBytes;
+        hk = (uint32_t)std::min<uint64_t>(k, std::max<uint64_t>(1, most / hr.scratch_bytes));
+        const size_t bytes = hk * hr.scratch_bytes;
+        if (hk > 1 && heavy.bytes < bytes) {
+            heavy.reset();
+            const int rc = pool_room(ctx, bytes) ? dev_alloc(ctx, heavy, bytes) : DT_ENOMEM;
+            if (rc != DT_OK && rc != DT_ENOMEM) return rc;
+            if (rc == DT_ENOMEM) {
+                clear_error();
+                hk = 1;
+            }
         }
-        DT_TRY(rc);
+        if (hk == 1) DT_TRY(ensure(ctx, sc.heavy_vals, hr.scratch_bytes));
+        hscratch = (hk > 1 ? heavy : sc.heavy_vals).as<uint8_t>();
     }
     // the light (then heavy) and medium passes run on the side streams, beside the unit pass (as in a
     // count)
@@ -916,7 +924,7 @@ int count_sweep_enqueue(dt_graph *g, const DQuery *qs, uint32_t k, int64_t *out_
     }
     for (uint32_t j = 0; hg && j < k; j += hk) {
         const uint32_t kk = std::min(hk, k - j);
-        DT_TRY(launch_heavy<Acc<false>>(g, qs + j, kk, hr, hg, sc.heavy_vals.as<uint8_t>(), hpart + 8ull * hg * j, sl,
+        DT_TRY(launch_heavy<Acc<false>>(g, qs + j, kk, hr, hg, hscratch, hpart + 8ull * hg * j, sl,
                                         nullptr, nullptr));
     }
     if (mg) {

@@ -113,6 +113,7 @@ namespace dt {
 // DT_ENOMEM on budget or HIP failure; see DevMem for when `pooled` is allowed
 int dev_alloc(dt_ctx *ctx, DevMem &m, size_t bytes, bool pooled = true);
 void pool_trim(dt_ctx *ctx, uint64_t keep_bytes);   // free cached blocks down to keep_bytes
+bool pool_room(dt_ctx *ctx, size_t bytes);   // whether the budget has room for bytes, with the cached blocks given up
 
 // profiling marks around one kernel launch (no-ops unless profiling is on)
 enum ProfSlot { kProfPeel = 0, kProfRelayout, kProfTriCount, kProfTriFill, kProfLight,
@@ -381,8 +382,11 @@ void count_reduce(uint64_t n_part, const int64_t *part, int64_t *out8_dev, hipSt
 // delta triples counted in one pass of a sweep
 constexpr uint32_t kSweepMax = 8;
 // Enqueue the counts of k <= kSweepMax queries that share one window (and so one set of list
-// ranges) in one pass over the triangles: out_dev[8 j + i] = type i + 1 of query j.
-int count_sweep_enqueue(dt_graph *g, const DQuery *qs, uint32_t k, int64_t *out_dev, hipStream_t s, Scratch &sc);
+// ranges) in one pass over the triangles: out_dev[8 j + i] = type i + 1 of query j.  heavy: the prefix
+// arrays of several queries at once, where they may be had; pooled memory that the caller gives back once
+// the pass is done, so that no more than one query's (in sc) stays with the context.
+int count_sweep_enqueue(dt_graph *g, const DQuery *qs, uint32_t k, int64_t *out_dev, hipStream_t s, Scratch &sc,
+                        DevMem &heavy);
 void destroy_batch_runner(BatchRunner *r);
 int make_batch_runner(dt_ctx *ctx, BatchRunner **out);
 // plan the item table of k queries and enqueue it on the runner's stream (asynchronous)

@@ -58,6 +58,11 @@ void pool_trim(dt_ctx *ctx, uint64_t keep_bytes) {
     }
 }
 
+bool pool_room(dt_ctx *ctx, size_t bytes) {
+    std::lock_guard<std::mutex> lk(ctx->pool_mu);
+    return !ctx->budget || ctx->used.load() - ctx->pool_bytes + bytes + 256 <= ctx->budget;
+}
+
 void DevMem::reset() {
     if (ptr) {
         if (pooled && ctx) {
