@@ -175,6 +175,9 @@ int dt_graph_load_device(dt_ctx *ctx, uint32_t n, uint64_t m, const uint32_t *sr
  * enumeration in G_prec (Section 5, and the proof of Theorem 1), and the count schedule.  The
  * triangle list stays resident for every later count.  May be called again to rebuild. */
 int dt_graph_build(dt_graph *g);
+/* Tuning of a graph (above).  On a built graph the triangles are split again at once; where that fails
+ * for want of memory once the schedule at hand was dropped, counts return DT_ENOTBUILT until the graph is
+ * built again. */
 int dt_graph_set_tuning(dt_graph *g, const dt_tuning *tuning);
 int dt_graph_stats(const dt_graph *g, dt_stats *out);
 

@@ -321,8 +321,12 @@ int dt_graph_set_tuning(dt_graph *g, const dt_tuning *tu) {
     DT_TRY(enumerate_triangles(g, tri, &ntri, &cand, &nlist));
     if (ntri != g->n_tri) return fail(DT_EDEVICE, "triangle enumeration changed between passes");
     g->n_tri_list = nlist;
+    // (the schedule at hand is dropped for the new one: without it the graph is not built)
+    g->built = false;
     DT_TRY(resolve_split(g, g->tuning.autotune == 2 ? &tri : nullptr));
-    return make_schedule(g, tri, true);
+    DT_TRY(make_schedule(g, tri, true));
+    g->built = true;
+    return DT_OK;
 }
 
 int dt_graph_stats(const dt_graph *g, dt_stats *out) {
