@@ -264,6 +264,8 @@ int dt_graph_free(dt_graph *g);
  *   ms[7] final reduction, ms[8] medium count, ms[9] unit-triangle count, ms[10] the peel's
  *   local adjacency of its last vertices, ms[11] the peel's finish, ms[12] core
  *   numbers and shell rounds (order_method 1; ms[0], ms[10] and ms[11] belong to method 0).
+ * A count small enough to take its light, medium and unit triangles in one launch takes them in three
+ * while profiling is on.
  * dt_ctx_last_profile waits for those events and reports their elapsed times (0 if not run). */
 #define DT_PROFILE_SLOTS 13
 int dt_ctx_set_profiling(dt_ctx *ctx, int enable);

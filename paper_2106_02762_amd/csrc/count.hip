@@ -704,9 +704,7 @@ int launch_paths(dt_graph *g, const DQuery &q, const CountPlan &p, const Scratch
         if (small) {
             SmallCount C{p.lr, p.mr, p.light, p.medium, p.mitems, eoff, p.mlev, key, S.unit.as<uint4>(), p.ub, p.ue, q,
                          unit_query(q), mg, lg, ug};
-            prof_begin(ctx, kProfMedium, s);
             k_small<ACC, 256><<<mg + lg + ug, 256, 0, s>>>(C, mp);
-            prof_end(ctx, kProfMedium, s);
             DT_HIP(hipGetLastError());
             if (p.hr.n) DT_TRY(launch_heavy<ACC>(g, &q, 1, p.hr, hg, sv.heavy, hp, sl, nullptr, nullptr));
             return DT_OK;
@@ -765,8 +763,9 @@ int count_launch(dt_graph *g, const DQuery &q, const CountPlan &p, int64_t *out8
     // the light and then the heavy kernels run on the context's first side stream and the medium
     // kernel on the second, forked from s here and joined back before the reduction, beside the
     // unit kernel on s, so that their latency-bound tails overlap.  A small count takes the light,
-    // medium and unit blocks in one launch on s, and only the heavy kernels beside it.
-    const bool small = !cells && !visits && (lg || mg || ug) && (uint64_t)lg + mg + ug <= (uint64_t)ctx->num_cus * kSmallPerCu;
+    // medium and unit blocks in one launch on s, and only the heavy kernels beside it (not while it is
+    // profiled, so that each path has its time).
+    const bool small = !cells && !visits && !ctx->prof && (lg || mg || ug) && (uint64_t)lg + mg + ug <= (uint64_t)ctx->num_cus * kSmallPerCu;
     hipStream_t sl = s, sm = s;
     const bool fork = ctx->side[0] && (small ? hg != 0 : ((lg || hg ? 1 : 0) + (mg ? 1 : 0) + (ug ? 1 : 0)) >= 2);
     const bool fork_l = fork && (hg || (!small && lg)), fork_m = fork && !small && mg;
