@@ -130,7 +130,8 @@ typedef struct {
                                       (diagnostics and tests)                                     */
     uint32_t peel_tail;            /* the level peel hands the last peel_tail vertices to a finish that
                                       takes their core numbers from falling bounds, and their order
-                                      from when these settled (default 65536, or 32768 from 2^28 pairs on; a value set
+                                      from when these settled, or to the levels of one workgroup
+                                      where the bounds fall too slowly (default 65536; a value set
                                       here is at most 16320; 1 keeps every level on the whole grid);
                                       read by the next dt_graph_build                             */
     uint32_t order_method;         /* 0: the level-by-level core peel (default); 1: core numbers

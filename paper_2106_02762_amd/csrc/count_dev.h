@@ -46,20 +46,12 @@ template <> struct Acc<false> {
     int64_t t[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     int64_t *cells = nullptr;
     uint64_t visits = 0;
-    template <class CA, class CB> __device__ __forceinline__ void add2(bool first, int64_t v) {
-        t[CA::type] += first ? v : 0;
-        t[CB::type] += first ? 0 : v;
-    }
     template <class C> __device__ __forceinline__ void add(int64_t v) { t[C::type] += v; }
 };
 template <> struct Acc<true> {
     int64_t t[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     int64_t *cells = nullptr;
     uint64_t visits = 0;
-    template <class CA, class CB> __device__ __forceinline__ void add2(bool first, int64_t v) {
-        if (v) atomicAdd((unsigned long long *)(cells + (first ? CA::cell : CB::cell)),
-                         (unsigned long long)v);
-    }
     template <class C> __device__ __forceinline__ void add(int64_t v) {
         if (v) atomicAdd((unsigned long long *)(cells + C::cell), (unsigned long long)v);
     }
@@ -71,10 +63,6 @@ struct AccW {
     unsigned __int128 t[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     int64_t *cells = nullptr;
     uint64_t visits = 0;
-    template <class CA, class CB> __device__ __forceinline__ void add2(bool first, int64_t v) {
-        t[CA::type] += first ? (unsigned __int128)(uint64_t)v : 0;
-        t[CB::type] += first ? 0 : (unsigned __int128)(uint64_t)v;
-    }
     template <class C> __device__ __forceinline__ void add(int64_t v) { t[C::type] += (uint64_t)v; }
 };
 

@@ -308,9 +308,9 @@ constexpr uint32_t kNoEdge = 0xffffffffu;
 // every static triangle as (e_uv, e_uw, e_vw) DAG edge ids, in a list of *nlist entries of which
 // *ntri are triangles and the others empty; *cand: candidates tested
 int enumerate_triangles(const dt_graph *g, DevMem &tri, uint64_t *ntri, uint64_t *cand, uint64_t *nlist);
+void unit_keys(dt_graph *g, hipStream_t st);   // g->ukey (allocated) from the store
 // the schedule of g's count from its triangle list tri (g->n_tri_list entries, g->n_tri triangles);
 // last: tri is not read again and may be given back; with_units false: it holds no unit triangle
-void unit_keys(dt_graph *g, hipStream_t st);   // g->ukey (allocated) from the store
 int make_schedule(dt_graph *g, DevMem &tri, bool last, bool with_units = true);
 // orders the context's stream after a re-layout that orient(g, true) left running on side[0]
 // (no-op otherwise) and releases its temporaries; to be called before anything reads g->key

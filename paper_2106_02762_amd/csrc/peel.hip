@@ -1339,10 +1339,7 @@ int peel(dt_graph *g) {
     DT_TRY(dev_alloc(ctx, ctlm, kCtlBytes + 2 * kBarBytes));
     // the finish: at most tail_cap vertices, their adjacency within 2 m_static entries and below
     // tail_cap (tail_cap - 1) as well
-    // (twice a core number and one more fit 16 bits: of 32768 vertices always, of more while the pairs
-    // are too few for a core number of 2^15)
-    const uint32_t tail_max = g->m_s < (1ull << 28) ? kTail : kTail / 2;
-    const uint32_t tail_cap = std::min<uint32_t>(g->tuning.peel_tail ? g->tuning.peel_tail : tail_max, tail_max);
+    const uint32_t tail_cap = g->tuning.peel_tail ? g->tuning.peel_tail : kTail;
     const uint64_t lcol_cap = std::min<uint64_t>(2ull * g->m_s, (uint64_t)tail_cap * (tail_cap - 1));
     DT_TRY(dev_alloc(ctx, loc, (uint64_t)n * 4));
     DT_TRY(dev_alloc(ctx, rlist, (uint64_t)tail_cap * 4));

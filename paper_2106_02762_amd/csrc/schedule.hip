@@ -562,8 +562,6 @@ k_place(uint64_t n_l, uint64_t n_a, uint64_t n_c, unsigned tiles_l, unsigned til
         }
 }
 
-// bucket starts from the sorted bucket keys: start[x] for every x in (key[j - 1], key[j]] is j;
-// j = nu closes the array at nbk
 // first position of every bucket 0..nbk in the nu sorted bucket keys (a binary search per bucket;
 // nu for nbk and for buckets past the last key)
 __global__ void k_unit_starts(uint64_t nu, uint32_t nbk, const uint16_t *__restrict__ bkt,
@@ -901,7 +899,8 @@ int try_schedule(dt_graph *g, DevMem &tri, bool with_units, bool last, bool lean
             if (s != main) (void)hipStreamSynchronize(s);
         }
     } join{us, st};
-    // (both are launched with the context's stream idle, after the classes were read)
+    // (its blocks come from the cache, whose released blocks the context's stream may still use: it was idle
+    // when the classes were read, and nothing is released between that and this)
     auto unit_sort = [&]() -> int {
         if (!nu) return DT_OK;
         DT_TRY(dev_alloc(ctx, ubkt2, nu * 2));
