@@ -17,7 +17,9 @@ struct FinishRoom {
     static constexpr uint64_t kWhen = kCur + kCells;     // uint32[kTail]: phase of each vertex
     static constexpr uint64_t kPos = kWhen + kTail;      // uint32[kTail]: its place in its cell
     static constexpr uint64_t kVal = kPos + kTail;       // uint16[2 * kTail]: two buffers of bounds
-    static constexpr uint64_t kWords = kVal + kTail;
+    static constexpr uint32_t kBlocks = 1024;            // blocks at most
+    static constexpr uint64_t kFalls = kVal + kTail;     // uint32[2 * kBlocks]: two phases' falls, by block
+    static constexpr uint64_t kWords = kFalls + 2 * kBlocks;
     // cells that a finish of R vertices uses at most
     static constexpr uint32_t cells(uint32_t R) {
         return R < (kCells - 1024) / 32 ? 32 * R + 1024 : kCells;

@@ -71,7 +71,6 @@ struct PeelCtl {
     unsigned int error;      // a barrier gave up waiting, or a consistency check failed
     unsigned int rounds;     // removal rounds
     unsigned int kappa;      // largest level that removed a vertex
-    unsigned int fin[3];     // finish, per phase mod 3: bounds that fell (or kManyFell and more)
     unsigned int left;       // the finish left its vertices to the level peel
     unsigned long long lres; // hand-over: local ids (low word) and adjacency entries (high word) given out
     unsigned int ho;         // 1: the grid handed its last vertices over (the state below is set)
@@ -223,15 +222,15 @@ constexpr uint32_t kRegPieces = 8;   // pieces of a row held in registers
 constexpr uint32_t kRegRow = kPiece * kRegPieces;
 constexpr uint32_t kFinSmall = 1024; // up to this many vertices one block finishes alone
 // When the finish leaves its vertices to the levels: after phase kSlowPhase if more than a quarter as many
-// bounds still fall as in the first, after kFewPhases phases in a row of at most kFewFell falls, and after
-// kPhaseMost phases.  Where degrees are spread, falls are a fifteenth of the first ones by then (61M edges;
-// random graphs, preferential attachment, small worlds, points in a plane: 1/9 to 1/1700), few for at most
-// 18 phases before the end, and the phases at most 65; on a chain or a lattice they go on as they began (a
-// path of 60,000 vertices: 2 a phase for 30,000 phases, 373 ms by them all, 42 ms left to the levels; a
-// 1,000-vertex path beside a 40,000-vertex power law: 15.4 and 4.3 ms; a lattice of 250 x 250: 4.2 and
-// 1.9), so that the phases tried cost little beside the levels.
-constexpr uint32_t kSlowPhase = 8, kFewFell = 64, kFewPhases = 24, kPhaseMost = 128;
-constexpr uint32_t kManyFell = 1u << 24;
+// bounds still fall as in the first; after kFewPhases phases in a row of at most kFewFell falls that do not
+// grow to twice the first of them; and after kPhaseMost phases.  Where degrees are spread, falls are a
+// fifteenth of the first ones by phase 8 (61M edges; random graphs, preferential attachment, small worlds,
+// points in a plane: 1/9 to 1/1700), then few and growing until they burst again and again (seven 61M-edge
+// graphs: such rows of at most 16 phases, small worlds 21), and the phases at most 75.  On a chain or a
+// lattice they go on as they began (a path of 60,000 vertices: 2 a phase for 30,000 phases, 373 ms by them
+// all, 42 ms left to the levels; a 1,000-vertex path beside a 40,000-vertex power law: 15.4 and 4.8 ms; a
+// lattice of 250 x 250: 4.2 and 1.9), so that the phases tried cost little beside the levels.
+constexpr uint32_t kSlowPhase = 8, kFewFell = 64, kFewPhases = 48, kPhaseMost = 192;
 constexpr uint32_t kSharedRows = 16; // rows at most that a block's wavefronts walk together
 constexpr uint32_t kSlots = 2048;    // places a block takes together
 
@@ -244,22 +243,17 @@ struct FinArgs {
     uint32_t *when;       // the last phase in which each vertex's bound fell, and one; 0: in none
     uint32_t *pos;        // position of each vertex among those of its (core, phase)
     uint32_t *level, *queue;
+    uint32_t *falls;      // bounds that fell in a phase, by block: two buffers
     unsigned *bar;        // barrier counters (kBarWords)
     PeelCtl *ctl;
 };
 
-// Barrier of the finish's nblk blocks.  With `flag`, its value and the error state come back in s_flag,
-// read once every block has arrived.
-__device__ void fin_barrier(const FinArgs &A, unsigned nblk, BarTurn &turn, const unsigned *flag = nullptr,
-                            unsigned *s_flag = nullptr) {
+// Barrier of the finish's nblk blocks; the error state comes back in *s_err, read once every block has
+// arrived.
+__device__ void fin_barrier(const FinArgs &A, unsigned nblk, BarTurn &turn, unsigned *s_err) {
     group_barrier(A.bar, &A.ctl->error, nblk, turn);
-    if (flag) {
-        if (threadIdx.x == 0) {
-            s_flag[0] = ld_relaxed(flag);
-            s_flag[1] = ld_relaxed(&A.ctl->error);
-        }
-        __syncthreads();
-    }
+    if (threadIdx.x == 0) *s_err = ld_relaxed(&A.ctl->error);
+    __syncthreads();
 }
 
 // f(I) for every piece I that begins before entry d: nested, so that one jump skips the rest
@@ -475,7 +469,7 @@ __global__ void __launch_bounds__(kBlock)
 k_peel_finish(FinArgs A) {
     __shared__ __attribute__((aligned(16))) uint16_t s_v[kTail];
     __shared__ uint32_t s_key[kSlots], s_cnt[kSlots];
-    __shared__ unsigned s_any, s_more[2], s_scan[kBlock / 64];
+    __shared__ unsigned s_any, s_more, s_err, s_scan[kBlock / 64];
     __shared__ uint32_t s_row[kSharedRows], s_rows, s_ge[kSharedRows], s_at[3][8];
     PeelCtl *ctl = A.ctl;
     if (!ctl->ho || ctl->error) return;
@@ -519,7 +513,7 @@ k_peel_finish(FinArgs A) {
         A.when[v] = 0;
     }
     for (uint32_t c = gtid; c < cell_cap; c += gsize) A.cur[c] = 0;
-    fin_barrier(A, nblk, turn);
+    fin_barrier(A, nblk, turn, &s_err);
     auto load_values = [&](const uint16_t *from) {
         const uint4 *src = reinterpret_cast<const uint4 *>(from);
         uint4 *dst = reinterpret_cast<uint4 *>(s_v);
@@ -596,23 +590,29 @@ k_peel_finish(FinArgs A) {
         }
         return tid / 64 ? 0u : fell;
     };
-    // every block learns how many bounds fell in phase ph (kManyFell and more: many); s_more[1]: an error
-    auto any_left = [&](uint32_t fell, uint32_t ph) {
+    // every block learns how many bounds fell in phase ph: each leaves its own and adds up all of them (an
+    // atomic on one counter by each would take as long as the barrier)
+    auto all_fell = [&](uint32_t fell, uint32_t ph) {
         if (fell && lane == 0) atomicAdd(&s_any, fell);
         __syncthreads();
-        if (tid == 0 && s_any) {
-            if (s_any <= kFewFell / 4 || ph == 0 || ph == kSlowPhase) atomicAdd(&ctl->fin[ph % 3], s_any);
-            else __hip_atomic_store(&ctl->fin[ph % 3], kManyFell, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        uint32_t *falls = A.falls + (ph & 1) * FinishRoom::kBlocks;
+        if (tid == 0) {
+            __hip_atomic_store(&falls[blockIdx.x], s_any, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            s_more = 0;
         }
-        fin_barrier(A, nblk, turn, &ctl->fin[ph % 3], s_more);
-        const unsigned more = s_more[0];
-        // read by every block before the next barrier: cleared for the phase after next
-        if (gtid == 0)
-            __hip_atomic_store(&ctl->fin[(ph + 2) % 3], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        return more;
+        group_barrier(A.bar, &ctl->error, nblk, turn);
+        uint32_t n = tid < nblk ? ld_relaxed(&falls[tid]) : 0u;
+        if (tid / 64 * 64 < nblk) {
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) n += __shfl_xor(n, o, 64);
+            if (lane == 0 && n) atomicAdd(&s_more, n);
+        }
+        if (tid == 0) s_err = ld_relaxed(&ctl->error);
+        __syncthreads();
+        return s_more;
     };
     // core numbers
-    uint32_t ph = 0, first_fell = 0, few = 0;
+    uint32_t ph = 0, first_fell = 0, few = 0, few_first = 0;
     for (;; ++ph) {
         load_values(A.val + (ph & 1 ? kTail : 0));
         __syncthreads();
@@ -633,11 +633,13 @@ k_peel_finish(FinArgs A) {
             __syncthreads();   // (the wavefronts' own bounds written)
             fell += shared_rows(out, ph);
         }
-        const uint32_t more = any_left(fell, ph);
-        if (s_more[1]) return;
+        const uint32_t more = all_fell(fell, ph);
+        if (s_err) return;
         if (!more) break;
         if (ph == 0) first_fell = more;
-        few = more <= kFewFell ? few + 1 : 0;
+        if (more > kFewFell || more > 2 * few_first) few = 0;
+        if (few == 0) few_first = more;
+        few += more <= kFewFell ? 1 : 0;
         if ((ph == kSlowPhase && 4 * more > first_fell) || few >= kFewPhases || ph + 1 >= kPhaseMost) {
             if (gtid == 0) ctl->left = 1;   // (every block sees the same counts, and leaves)
             return;
@@ -687,8 +689,8 @@ k_peel_finish(FinArgs A) {
             if (in) A.pos[v] = held ? s_cnt[slot] + at : at;
             __syncthreads();
         }
-        fin_barrier(A, nblk, turn, &ctl->fin[0], s_more);
-        if (s_more[1]) return;
+        fin_barrier(A, nblk, turn, &s_err);
+        if (s_err) return;
     }
     // first position of every cell: every block writes the same ones, and reads its own back
     uint32_t run = 0;
@@ -1406,12 +1408,13 @@ int peel(dt_graph *g) {
     fa.when = fin.as<uint32_t>() + FinishRoom::kWhen;
     fa.pos = fin.as<uint32_t>() + FinishRoom::kPos;
     fa.val = reinterpret_cast<uint16_t *>(fin.as<uint32_t>() + FinishRoom::kVal);
+    fa.falls = fin.as<uint32_t>() + FinishRoom::kFalls;
     fa.level = level;
     fa.queue = queue;
     fa.bar = lbar + kBarWords;
     fa.ctl = ctl;
     // as many blocks as the most vertices it can get fill (co-resident: one per CU)
-    const unsigned fgrid = std::min<unsigned>(std::min<unsigned>((unsigned)ctx->num_cus, 1024u),
+    const unsigned fgrid = std::min<unsigned>(std::min<unsigned>((unsigned)ctx->num_cus, FinishRoom::kBlocks),
                                               grid_for(std::min(n, tail_cap), kPerWave * (kBlock / 64)));
     void *fargs[] = {&fa};
     DT_HIP(hipLaunchCooperativeKernel((const void *)k_peel_finish, dim3(fgrid), dim3(kBlock), fargs, 0, st));
