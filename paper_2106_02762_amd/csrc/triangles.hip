@@ -251,6 +251,12 @@ struct TriSink {
         return true;
     }
 
+    // k buffered triangles to the positions from `at` on
+    __device__ __forceinline__ void copy_out(unsigned long long at, const uint32_t *from, uint32_t k, unsigned lane) const {
+        for (uint32_t x = lane; x < 3 * k; x += 64)
+            if (at + x / 3 < cap) tri[3 * at + x] = from[x];
+    }
+
     __device__ __forceinline__ void flush(unsigned lane) {
         if (n == 0) return;
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
@@ -286,23 +292,19 @@ struct TriSink {
         } else {
             found += n;
             // the first `here` triangles to the stretch at hand, the others to a new one
-            const unsigned long long base = cb;
-            unsigned long long next = 0;
             const uint32_t here = ce - cb < n ? (uint32_t)(ce - cb) : n;
+            copy_out(cb, buf, here, lane);
             cb += here;
             if (here < n) {
                 const uint32_t more = n - here;
                 const uint32_t size = ce < stretch.until ? stretch.size : (ce < cap ? 0u : kChunkTri);
                 const unsigned long long want = size > more ? size : more;
+                unsigned long long next = 0;
                 if (lane == 0) next = atomicAdd(total, want);
                 next = __shfl(next, 0, 64);
+                copy_out(next, buf + 3 * here, more, lane);
                 cb = next + more;
                 ce = next + want;
-            }
-            for (uint32_t x = lane; x < 3 * n; x += 64) {
-                const uint32_t t = x / 3;
-                const unsigned long long at = t < here ? base + t : next + (t - here);
-                if (at < cap) tri[3 * at + (x - 3 * t)] = buf[x];
             }
         }
         __builtin_amdgcn_wave_barrier();
