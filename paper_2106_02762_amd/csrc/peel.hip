@@ -71,6 +71,7 @@ struct PeelCtl {
     unsigned int error;      // a barrier gave up waiting, or a consistency check failed
     unsigned int rounds;     // removal rounds
     unsigned int kappa;      // largest level that removed a vertex
+    unsigned int fin[3];     // finish, per phase mod 3: a bound fell
     unsigned int left;       // the finish left its vertices to the level peel
     unsigned long long lres; // hand-over: local ids (low word) and adjacency entries (high word) given out
     unsigned int ho;         // 1: the grid handed its last vertices over (the state below is set)
@@ -202,7 +203,10 @@ __device__ __forceinline__ void remove_edges(uint32_t v, uint32_t first, uint32_
 // shell: when v's bound fell to core(v), at most core(v) of its neighbours had larger ones, and those of
 // v's shell that fell to their core numbers in the same phase or later, like all of larger cores, were
 // among them.  Vertices ordered by (core, phase) are therefore in degeneracy order, and no vertex need be
-// removed from the others' counts.  65 phases for the 61M-edge graph's last 65,536 vertices where levels
+// removed from the others' counts.  Those of one shell and phase come by classes of their degree over the core
+// number, hubs last, as the levels would remove them: a hub before its shell's other vertices is the source of
+// all their triangles, with its long edge lists (40,000 vertices of a power law whose hubs share pairs: prefix
+// arrays of 2.3M to 3.7M slots in any order, 1.6M to 2.0M so, 1.8M by levels).  65 phases for the 61M-edge graph's last 65,536 vertices where levels
 // took 410 and 2,000 rounds (its peel then 13.9 ms, now 6.7, 2.2 of them here; 2.8 with a second part of
 // 50 phases that removed the shells' vertices in rounds, at 1.3M edges 0.36 against 0.26 ms).  A finish whose
 // falls do not die down leaves its vertices to the levels (kSlowPhase below).  65,536 is
@@ -222,15 +226,16 @@ constexpr uint32_t kRegPieces = 8;   // pieces of a row held in registers
 constexpr uint32_t kRegRow = kPiece * kRegPieces;
 constexpr uint32_t kFinSmall = 1024; // up to this many vertices one block finishes alone
 // When the finish leaves its vertices to the levels: after phase kSlowPhase if more than a quarter as many
-// bounds still fall as in the first; after kFewPhases phases in a row of at most kFewFell falls that do not
-// grow to twice the first of them; and after kPhaseMost phases.  Where degrees are spread, falls are a
+// bounds still fall as in the first; when kFewPhases phases, seen every kTellPhases, had at most kFewFell
+// falls each and no twice as many as the first of them; and after kPhaseMost phases.  Where degrees are spread, falls are a
 // fifteenth of the first ones by phase 8 (61M edges; random graphs, preferential attachment, small worlds,
 // points in a plane: 1/9 to 1/1700), then few and growing until they burst again and again (seven 61M-edge
 // graphs: such rows of at most 16 phases, small worlds 21), and the phases at most 75.  On a chain or a
 // lattice they go on as they began (a path of 60,000 vertices: 2 a phase for 30,000 phases, 373 ms by them
-// all, 42 ms left to the levels; a 1,000-vertex path beside a 40,000-vertex power law: 15.4 and 4.8 ms; a
+// all, 42 ms left to the levels; a 1,000-vertex path beside a 40,000-vertex power law: 15.4 and 4.5 ms; a
 // lattice of 250 x 250: 4.2 and 1.9), so that the phases tried cost little beside the levels.
-constexpr uint32_t kSlowPhase = 8, kFewFell = 64, kFewPhases = 48, kPhaseMost = 192;
+constexpr uint32_t kTellPhases = 8, kSlowPhase = 8, kFewFell = 64, kFewPhases = 48, kPhaseMost = 192;
+static_assert(kSlowPhase % kTellPhases == 0 && kFewPhases % kTellPhases == 0, "falls are told then");
 constexpr uint32_t kSharedRows = 16; // rows at most that a block's wavefronts walk together
 constexpr uint32_t kSlots = 2048;    // places a block takes together
 
@@ -502,7 +507,7 @@ k_peel_finish(FinArgs A) {
     if (tid == 0) s_rows = 0;
     if (tid < 24) s_at[tid / 8][tid % 8] = 0;
     __syncthreads();
-    for (uint32_t v = va + lane; v < vb; v += 64)
+    for (uint32_t v = va + lane; R > shared && v < vb; v += 64)
         if (A.lrow[v + 1] - A.lrow[v] >= shared) {
             const uint32_t x = atomicAdd(&s_rows, 1u);
             if (x < kSharedRows) s_row[x] = v;
@@ -590,26 +595,39 @@ k_peel_finish(FinArgs A) {
         }
         return tid / 64 ? 0u : fell;
     };
-    // every block learns how many bounds fell in phase ph: each leaves its own and adds up all of them (an
-    // atomic on one counter by each would take as long as the barrier)
+    // Every block learns whether a bound fell in phase ph, and every kTellPhases phases how many did: then
+    // each block leaves its falls in a slot and adds up all slots (an atomic on one counter by each would take
+    // as long as the barrier; adding up the slots in every phase made the finish of 61M edges 2% longer).
     auto all_fell = [&](uint32_t fell, uint32_t ph) {
         if (fell && lane == 0) atomicAdd(&s_any, fell);
         __syncthreads();
-        uint32_t *falls = A.falls + (ph & 1) * FinishRoom::kBlocks;
+        const bool tell = ph % kTellPhases == 0;
+        uint32_t *falls = A.falls + (ph / kTellPhases & 1) * FinishRoom::kBlocks;
         if (tid == 0) {
-            __hip_atomic_store(&falls[blockIdx.x], s_any, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (tell)
+                __hip_atomic_store(&falls[blockIdx.x], s_any, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            else if (s_any)
+                __hip_atomic_store(&ctl->fin[ph % 3], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             s_more = 0;
         }
         group_barrier(A.bar, &ctl->error, nblk, turn);
-        uint32_t n = tid < nblk ? ld_relaxed(&falls[tid]) : 0u;
-        if (tid / 64 * 64 < nblk) {
+        if (tid == kBlock - 1) s_err = ld_relaxed(&ctl->error);   // (beside the first wavefront's load)
+        if (tell) {
+            uint32_t n = tid < nblk ? ld_relaxed(&falls[tid]) : 0u;
+            if (tid / 64 * 64 < nblk) {
 #pragma unroll
-            for (int o = 32; o > 0; o >>= 1) n += __shfl_xor(n, o, 64);
-            if (lane == 0 && n) atomicAdd(&s_more, n);
+                for (int o = 32; o > 0; o >>= 1) n += __shfl_xor(n, o, 64);
+                if (lane == 0 && n) atomicAdd(&s_more, n);
+            }
+        } else if (tid == 0) {
+            s_more = ld_relaxed(&ctl->fin[ph % 3]);
         }
-        if (tid == 0) s_err = ld_relaxed(&ctl->error);
         __syncthreads();
-        return s_more;
+        const uint32_t more = s_more;
+        // read by every block before the next barrier: cleared for the phase after next
+        if (gtid == 0)
+            __hip_atomic_store(&ctl->fin[(ph + 2) % 3], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return more;
     };
     // core numbers
     uint32_t ph = 0, first_fell = 0, few = 0, few_first = 0;
@@ -636,11 +654,15 @@ k_peel_finish(FinArgs A) {
         const uint32_t more = all_fell(fell, ph);
         if (s_err) return;
         if (!more) break;
-        if (ph == 0) first_fell = more;
-        if (more > kFewFell || more > 2 * few_first) few = 0;
-        if (few == 0) few_first = more;
-        few += more <= kFewFell ? 1 : 0;
-        if ((ph == kSlowPhase && 4 * more > first_fell) || few >= kFewPhases || ph + 1 >= kPhaseMost) {
+        bool leave = ph + 1 >= kPhaseMost;
+        if (ph % kTellPhases == 0) {
+            if (ph == 0) first_fell = more;
+            if (more > kFewFell || more > 2 * few_first) few = 0;
+            if (few == 0) few_first = more;
+            few += more <= kFewFell ? 1 : 0;
+            leave |= (ph == kSlowPhase && 4 * more > first_fell) || few > kFewPhases / kTellPhases;
+        }
+        if (leave) {
             if (gtid == 0) ctl->left = 1;   // (every block sees the same counts, and leaves)
             return;
         }
@@ -654,8 +676,9 @@ k_peel_finish(FinArgs A) {
     __syncthreads();
     const uint32_t kmax = s_any;
     const uint32_t T = ph + 1, shells = kmax >= k0 ? kmax - k0 + 1 : 1;
-    const bool wide = (uint64_t)shells * T > cell_cap;   // (core, phase) pairs beyond the room for them
-    const uint32_t cells = wide ? (shells < cell_cap ? shells : cell_cap) : shells * T;
+    constexpr uint32_t kCls = FinishRoom::kClasses;
+    const bool wide = (uint64_t)shells * T * kCls > cell_cap;   // cells beyond the room for them
+    const uint32_t cells = wide ? (shells < cell_cap ? shells : cell_cap) : shells * T * kCls;
     // this block's vertices, one a thread and chunk: their places among those of their cell, taken with
     // one atomic a block, chunk and cell where the cell's slot in LDS is free for it.  Beyond the room the
     // cells are the shells, and the phases take their places one after the other.
@@ -663,7 +686,7 @@ k_peel_finish(FinArgs A) {
     const uint32_t last = ba + 1 < nblk ? split_vertex(A.lrow, R, work * ((ba + 1) * kBW) / W, lane) : R;
     auto cell_of = [&](uint32_t v) {
         const uint32_t c = s_v[v] > k0 ? s_v[v] - k0 : 0u;
-        return wide ? c : c * T + A.when[v];
+        return wide ? c : (c * T + A.when[v]) * kCls + FinishRoom::deg_class(A.lrow[v + 1] - A.lrow[v], s_v[v]);
     };
     for (uint32_t t = 0; t < (wide ? T : 1u); ++t) {
         for (uint32_t v0 = first; v0 < last; v0 += kBlock) {
@@ -675,6 +698,7 @@ k_peel_finish(FinArgs A) {
             const uint32_t v = v0 + tid;
             const bool in = v < last && (!wide || A.when[v] == t);
             const uint32_t cell = in ? cell_of(v) : 0u, slot = cell % kSlots;
+            if (in && !wide) A.when[v] = cell;   // (this thread's own from here on)
             uint32_t at = 0;
             bool held = false;
             if (in) {
@@ -692,13 +716,15 @@ k_peel_finish(FinArgs A) {
         fin_barrier(A, nblk, turn, &s_err);
         if (s_err) return;
     }
-    // first position of every cell: every block writes the same ones, and reads its own back
+    // first position of every cell that holds a vertex: every block writes the same ones, and reads its own
+    // back
+    constexpr uint32_t kPer = 8;   // cells a thread
     uint32_t run = 0;
-    for (uint32_t c0 = 0; c0 < cells && run < R; c0 += 4 * kBlock) {
-        const uint32_t c = c0 + 4 * tid;
-        uint32_t n[4], mine = 0;
+    for (uint32_t c0 = 0; c0 < cells && run < R; c0 += kPer * kBlock) {
+        const uint32_t c = c0 + kPer * tid;
+        uint32_t n[kPer], mine = 0;
 #pragma unroll
-        for (uint32_t j = 0; j < 4; ++j) {
+        for (uint32_t j = 0; j < kPer; ++j) {
             n[j] = c + j < cells ? A.cur[c + j] : 0u;
             mine += n[j];
         }
@@ -717,8 +743,8 @@ k_peel_finish(FinArgs A) {
         }
         uint32_t at = run + before + x - mine;
 #pragma unroll
-        for (uint32_t j = 0; j < 4; ++j) {
-            if (c + j < cells) A.base[c + j] = at;
+        for (uint32_t j = 0; j < kPer; ++j) {
+            if (n[j]) A.base[c + j] = at;
             at += n[j];
         }
         run += total;
@@ -728,7 +754,7 @@ k_peel_finish(FinArgs A) {
     for (uint32_t v0 = first; v0 < last; v0 += kBlock) {
         const uint32_t v = v0 + tid;
         if (v < last) {
-            const uint32_t p = qbase + A.base[cell_of(v)] + A.pos[v], x = A.rlist[v];
+            const uint32_t p = qbase + A.base[wide ? cell_of(v) : A.when[v]] + A.pos[v], x = A.rlist[v];
             if (p < qbase + R) A.queue[p] = x;
             else atomicOr(&ctl->error, 16u);
             A.level[x] = s_v[v];

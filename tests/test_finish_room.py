@@ -1,4 +1,4 @@
-"""The (core, phase) cells of the level peel's finish, on the CPU: for every number of vertices they stay
+"""The (core, phase, degree class) cells of the level peel's finish, on the CPU: for every number of vertices they stay
 within the arrays that hold them, and for graphs whose cells come near the room -- a part of one high core
 number, a path of many phases, isolated vertices -- so does the cell of every vertex.  The phases are
 those of the finish: every bound replaced at once by the largest t such that t neighbours have bounds of
@@ -17,7 +17,7 @@ PROGRAM = r"""
 #include "finish_room.h"
 using dt::FinishRoom;
 int main() {
-    std::printf("%u %llu %llu %llu %llu %llu %llu\n", dt::kTail, (unsigned long long)FinishRoom::kBase,
+    std::printf("%u %u %llu %llu %llu %llu %llu %llu\n", dt::kTail, FinishRoom::kClasses, (unsigned long long)FinishRoom::kBase,
                 (unsigned long long)FinishRoom::kCur, (unsigned long long)FinishRoom::kWhen,
                 (unsigned long long)FinishRoom::kPos, (unsigned long long)FinishRoom::kVal,
                 (unsigned long long)FinishRoom::kWords);
@@ -36,7 +36,7 @@ def room(tmp_path_factory):
 
 
 def test_arrays_hold_every_count_of_cells(room):
-    (tail, base, cur, when, pos, val, words), cells = room
+    (tail, _, base, cur, when, pos, val, words), cells = room
     assert len(cells) == tail + 1
     for R in range(1, tail + 1):
         assert R <= cells[R] <= min(cur - base, when - cur), R
@@ -63,13 +63,14 @@ def _path_phases(k):
 
 
 @pytest.mark.parametrize("R", [8160, 8161, 8175, 8190, 8191, 8192, 8193])
-@pytest.mark.parametrize("core,path", [(2629, 200), (2621, 200), (1314, 400), (1310, 400), (2032, 258), (130, 4000)])
+@pytest.mark.parametrize("core,path", [(2629, 200), (2621, 200), (1314, 400), (1310, 400), (2032, 258), (130, 4000),
+                                       (657, 200), (655, 200), (654, 200), (650, 200), (327, 400), (326, 400), (64, 2000)])
 def test_cells_of_a_high_core_beside_a_path(room, R, core, path):
-    (_, base, cur, when_at, _, _, _), cells = room
+    (_, classes, base, cur, when_at, _, _, _), cells = room
     when, T = _path_phases(path)
     shells = core + 1                                # isolated vertices are the lowest shell
-    if shells * T > cells[R]:                        # the finish counts shells only
+    if shells * T * classes > cells[R]:                        # the finish counts shells only
         assert min(shells, cells[R]) <= min(cur - base, when_at - cur)
         return
-    top = max(core * T, T + int(when.max()))
-    assert top < min(cur - base, when_at - cur), (top, shells * T, cells[R])
+    top = max(core * T, T + int(when.max())) * classes + classes - 1
+    assert top < min(cur - base, when_at - cur), (top, shells * T * classes, cells[R])

@@ -1,4 +1,4 @@
-"""The level peel's finish where its (core, phase) cells come near the room for them: 8,160 to 8,192
+"""The level peel's finish where its (core, phase, degree class) cells come near the room for them: 8,160 to 8,192
 vertices of a complete bipartite part (one high core number, no triangles), a path of many phases and
 isolated vertices.  Core numbers equal the construction's, the ordering is a permutation, and no vertex
 has more than core(v) neighbours after it."""
@@ -22,6 +22,7 @@ def ctx():
 @pytest.mark.parametrize("n,side,path", [
     (8160, 1314, 400), (8161, 1314, 400), (8175, 1314, 400), (8191, 1314, 400), (8192, 1314, 400),
     (8161, 2621, 200), (8191, 2629, 200),
+    (8160, 654, 200), (8161, 655, 200), (8191, 655, 200), (8191, 656, 200), (8191, 657, 200), (8192, 655, 200),
 ])
 def test_cells_near_their_room(ctx, n, side, path):
     rng = np.random.default_rng([n, side])
