@@ -203,15 +203,17 @@ __device__ __forceinline__ void remove_edges(uint32_t v, uint32_t first, uint32_
 // shell: when v's bound fell to core(v), at most core(v) of its neighbours had larger ones, and those of
 // v's shell that fell to their core numbers in the same phase or later, like all of larger cores, were
 // among them.  Vertices ordered by (core, phase) are therefore in degeneracy order, and no vertex need be
-// removed from the others' counts.  Those of one shell and phase come by classes of their degree over the core
-// number, hubs last, as the levels would remove them: a hub before its shell's other vertices is the source of
-// all their triangles, with its long edge lists (40,000 vertices of a power law whose hubs share pairs: prefix
-// arrays of 2.3M to 3.7M slots in any order, 1.6M to 2.0M so, 1.8M by levels).  65 phases for the 61M-edge graph's last 65,536 vertices where levels
-// took 410 and 2,000 rounds (its peel then 13.9 ms, now 6.7, 2.2 of them here; 2.8 with a second part of
-// 50 phases that removed the shells' vertices in rounds, at 1.3M edges 0.36 against 0.26 ms).  A finish whose
-// falls do not die down leaves its vertices to the levels (kSlowPhase below).  65,536 is
-// what 16-bit ids and one workgroup's LDS hold; above it the level peel is the faster one (a level of many
-// vertices there costs less than their share of 65 phases).
+// removed from the others' counts.  Those of one shell and phase come by classes of their degree over the
+// core number, hubs last, as the levels would remove them: a hub before its shell's other vertices is the
+// source of all their triangles, with its long edge lists (40,000 vertices of a power law whose hubs share
+// pairs: prefix arrays of 2.3M to 3.7M slots in any order, 1.6M to 2.0M so, 1.8M by levels).
+//
+// 57 to 77 phases for the last 65,536 vertices of 61M-edge graphs, where levels took 410 and 2,000 rounds
+// (one's peel then 13.9 ms, now 6.7, 2.3 of them here; 2.8 with a second part of 50 phases that removed the
+// shells' vertices in rounds, at 1.3M edges 0.36 against 0.26 ms).  A finish whose falls do not die down
+// leaves its vertices to the levels (kSlowPhase below).  65,536 is what 16-bit ids and one workgroup's LDS
+// hold; above it the level peel is the faster one (a level of many vertices there costs less than their
+// share of those phases).
 //
 // A wavefront owns consecutive local ids holding an even share of the entries.  Every phase each block
 // copies all bounds (128 KB at most) into LDS, where the gathers along the rows go; rows stream from
@@ -227,13 +229,14 @@ constexpr uint32_t kRegRow = kPiece * kRegPieces;
 constexpr uint32_t kFinSmall = 1024; // up to this many vertices one block finishes alone
 // When the finish leaves its vertices to the levels: after phase kSlowPhase if more than a quarter as many
 // bounds still fall as in the first; when kFewPhases phases, seen every kTellPhases, had at most kFewFell
-// falls each and no twice as many as the first of them; and after kPhaseMost phases.  Where degrees are spread, falls are a
-// fifteenth of the first ones by phase 8 (61M edges; random graphs, preferential attachment, small worlds,
-// points in a plane: 1/9 to 1/1700), then few and growing until they burst again and again (seven 61M-edge
-// graphs: such rows of at most 16 phases, small worlds 21), and the phases at most 75.  On a chain or a
-// lattice they go on as they began (a path of 60,000 vertices: 2 a phase for 30,000 phases, 373 ms by them
-// all, 42 ms left to the levels; a 1,000-vertex path beside a 40,000-vertex power law: 15.4 and 4.5 ms; a
-// lattice of 250 x 250: 4.2 and 1.9), so that the phases tried cost little beside the levels.
+// falls each and none twice as many as the first of them; and after kPhaseMost phases.  Where degrees are
+// spread, falls are a fifteenth of the first ones by phase 8 (61M edges; random graphs, preferential
+// attachment, small worlds, points in a plane: 1/9 to 1/1700), then few and growing until they burst again
+// and again (seven 61M-edge graphs: such rows of at most 16 phases, small worlds 21), and the phases at most
+// 77.  On a chain or a lattice they go on as they began (a path of 60,000 vertices: 2 a phase for 30,000
+// phases, 373 ms by them all, 42 ms left to the levels; a 1,000-vertex path beside a 40,000-vertex power law:
+// 15.4 and 4.5 ms; a lattice of 250 x 250: 4.2 and 1.9), so that the phases tried cost little beside the
+// levels.
 constexpr uint32_t kTellPhases = 8, kSlowPhase = 8, kFewFell = 64, kFewPhases = 48, kPhaseMost = 192;
 static_assert(kSlowPhase % kTellPhases == 0 && kFewPhases % kTellPhases == 0, "falls are told then");
 constexpr uint32_t kSharedRows = 16; // rows at most that a block's wavefronts walk together
@@ -243,10 +246,10 @@ struct FinArgs {
     const uint32_t *rlist, *lrow;
     const uint16_t *lcol;
     uint16_t *val;        // two buffers of R bounds
-    uint32_t *base;       // first position of each (core, phase)
+    uint32_t *base;       // first position of each cell: core, phase and class of degree
     uint32_t *cur;        // positions taken in each
-    uint32_t *when;       // the last phase in which each vertex's bound fell, and one; 0: in none
-    uint32_t *pos;        // position of each vertex among those of its (core, phase)
+    uint32_t *when;       // the last phase in which each vertex's bound fell, and one (0: in none), then its cell
+    uint32_t *pos;        // position of each vertex among those of its cell
     uint32_t *level, *queue;
     uint32_t *falls;      // bounds that fell in a phase, by block: two buffers
     unsigned *bar;        // barrier counters (kBarWords)
