@@ -36,8 +36,8 @@ def log(*a):
 # the source files each kernel is compiled from (its .hip file and the library headers it includes);
 # a counter record holds the sha256 of their concatenation in this order
 _HDR = ["internal.h", "count_dev.h"]
-KERNEL_SOURCE = {"peel": ["peel.hip", "internal.h"], "peel_adj": ["peel.hip", "internal.h"],
-                 "peel_tail": ["peel.hip", "internal.h"], "core": ["core.hip", "internal.h"],
+_PEEL = ["peel.hip", "internal.h", "finish_room.h"]
+KERNEL_SOURCE = {"peel": _PEEL, "peel_adj": _PEEL, "peel_tail": _PEEL, "core": ["core.hip", "internal.h"],
                  "relayout": ["orient.hip", "internal.h"], "tri_count": ["triangles.hip"] + _HDR,
                  "tri_fill": ["triangles.hip"] + _HDR, "light": ["count.hip"] + _HDR,
                  "medium": ["count.hip"] + _HDR, "unit": ["count.hip"] + _HDR,

@@ -229,7 +229,7 @@ constexpr uint32_t kRegRow = kPiece * kRegPieces;
 constexpr uint32_t kFinSmall = 1024; // up to this many vertices one block finishes alone
 // When the finish leaves its vertices to the levels: after phase kSlowPhase if more than a quarter as many
 // bounds still fall as in the first; when kFewPhases phases, seen every kTellPhases, had at most kFewFell
-// falls each and none twice as many as the first of them; and after kPhaseMost phases.  Where degrees are
+// falls each and none more than twice those of the first; and after kPhaseMost phases.  Where degrees are
 // spread, falls are a fifteenth of the first ones by phase 8 (61M edges; random graphs, preferential
 // attachment, small worlds, points in a plane: 1/9 to 1/1700), then few and growing until they burst again
 // and again (seven 61M-edge graphs: such rows of at most 16 phases, small worlds 21), and the phases at most
