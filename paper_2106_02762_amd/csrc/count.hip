@@ -765,7 +765,8 @@ int count_launch(dt_graph *g, const DQuery &q, const CountPlan &p, int64_t *out8
     // unit kernel on s, so that their latency-bound tails overlap.  A small count takes the light,
     // medium and unit blocks in one launch on s, and only the heavy kernels beside it (not while it is
     // profiled, so that each path has its time).
-    const bool small = !cells && !visits && !ctx->prof && (lg || mg || ug) && (uint64_t)lg + mg + ug <= (uint64_t)ctx->num_cus * kSmallPerCu;
+    const bool small = !cells && !visits && !ctx->prof && (lg || mg || ug) &&
+                       (uint64_t)lg + mg + ug <= (uint64_t)ctx->num_cus * kSmallPerCu;
     hipStream_t sl = s, sm = s;
     const bool fork = ctx->side[0] && (small ? hg != 0 : ((lg || hg ? 1 : 0) + (mg ? 1 : 0) + (ug ? 1 : 0)) >= 2);
     const bool fork_l = fork && (hg || (!small && lg)), fork_m = fork && !small && mg;
