@@ -17,10 +17,10 @@
 //
 // Waves take source vertices from the highest rank down, so the heaviest (the dense core, last in
 // the ordering) start first.  One pass writes the list: each wavefront buffers its triangles in
-// LDS and appends them with one atomic per buffer, so triangles sharing a source vertex stay
-// mostly adjacent (as do their edge lists in the temporal store); the list's order is otherwise
-// unspecified.  The list is sized at four triangles per static pair and the pass runs again at
-// the counted size when a graph has more.  A vertex whose N+(u) exceeds the LDS slice takes the
+// LDS and copies full buffers into stretches of positions that it takes from one counter, so
+// triangles sharing a source vertex stay mostly adjacent (as do their edge lists in the temporal
+// store); the list's order is otherwise unspecified.  The list is sized at four triangles per static
+// pair and the pass runs again at the counted size when a graph has more.  A vertex whose N+(u) exceeds the LDS slice takes the
 // same steps on global memory (degeneracy above the slice, as in the densest inputs of Table 1).
 #include <algorithm>
 

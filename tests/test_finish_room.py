@@ -1,6 +1,6 @@
-"""The (core, phase, degree class) cells of the level peel's finish, on the CPU: for every number of vertices they stay
-within the arrays that hold them, and for graphs whose cells come near the room -- a part of one high core
-number, a path of many phases, isolated vertices -- so does the cell of every vertex.  The phases are
+"""The (core, phase, degree class) cells of the level peel's finish, on the CPU: for every number of
+vertices they stay within the arrays that hold them, and for graphs whose cells come near the room -- a
+part of one high core number, a path of many phases, isolated vertices -- so does the cell of every vertex.  The phases are
 those of the finish: every bound replaced at once by the largest t such that t neighbours have bounds of
 at least t, until none falls."""
 import functools

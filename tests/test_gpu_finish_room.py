@@ -1,5 +1,5 @@
-"""The level peel's finish where its (core, phase, degree class) cells come near the room for them: 8,160 to 8,192
-vertices of a complete bipartite part (one high core number, no triangles), a path of many phases and
+"""The level peel's finish where its (core, phase, degree class) cells come near the room for them: 8,160
+to 8,192 vertices of a complete bipartite part (one high core number, no triangles), a path of many phases and
 isolated vertices.  Core numbers equal the construction's, the ordering is a permutation, and no vertex
 has more than core(v) neighbours after it."""
 import numpy as np
